@@ -37,10 +37,35 @@ struct SubDev {
 struct TileDev {
     int32_t sub, tile, kstart, ncols;
     int64_t x_off;
-    int32_t start_block[4];   // first factor block each 16-column stripe works on
-    int64_t visit_off;        // blocks the tile visits: visit[visit_off .. + nvisit),
-    int32_t nvisit, pad;      // increasing indices relative to the subdomain's first block
+    int64_t visit_off;        // blocks the tile visits: visits[visit_off .. + nvisit),
+    int32_t nvisit, pad;      // increasing
 };
+
+// One factor block a TRSM tile visits, as the kernel walks it (offsets
+// relative to the subdomain's factor values and row array).
+struct VisitDev {
+    uint64_t on;              // bit i: row row0 + i is in the slab and on the tile's paths
+    int64_t linv_off;         // inverse of the diagonal block
+    int64_t aoff;             // pruned rows as MFMA A tiles
+    int64_t pair_aoff;        // second block of a pair: the first block's A tiles of the same rows
+    int64_t rows_off;
+    int32_t row0, w;
+    int32_t urows;            // rows the visit's update covers
+    int32_t pair_nks;         // k-slices of those A tiles
+    int32_t flags;            // bits 0-1: role in a merged pair (0 alone, 1 first block: updates only
+                              // the next block's rows, 2 second block: also applies the first's
+                              // update); kVisitNextEarly; kVisitActShift + v: stripe v has started
+    int32_t pad;
+};
+// the last chunk of the visit's update holds no row of the next visit's block
+constexpr int kVisitNextEarly = 4;
+constexpr int kVisitActShift = 4;
+// Pruned row tiles per TRSM chunk: 16 KB of A tiles, two FP64 or four FP32
+// row tiles of 16 k-slices.
+template <class TA>
+constexpr int kPruneTiles = sizeof(TA) == 8 ? 2 : 4;
+// X slabs from this size on are out of the 32-bit offsets of a buffer resource
+constexpr int64_t kTrsmSlabBytes = 0xFFFFFF00ll;
 
 // SYRK work item.  Subdomains with n <= kSyrkBlockMaxN (FP64; FP32:
 // kSyrkBlockMaxNMixed): a 64 x 64 block of F
@@ -66,7 +91,7 @@ constexpr int kStepRowMask = (1 << kStepSlabShift) - 1;   // rows below 2^27 (ch
 
 struct BlockDev {
     int32_t row0, w, nbelow;
-    int32_t flags;       // bit 0: merged with the next block in the TRSM's updates below
+    int32_t pad;
     int64_t lval_off;    // diagonal block (w x w, column-major), relative to the subdomain's lval_off
     int64_t rows_off;    // relative to the subdomain's rows_off
     int64_t aoff;        // pruned rows as MFMA A tiles, relative to the subdomain's lval_off

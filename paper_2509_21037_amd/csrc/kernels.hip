@@ -56,22 +56,38 @@ __device__ __forceinline__ v4f mfma_f32(float a, float b, v4f c) {
 //   2. the pruned rows below the block, 32 at a time (64 in mixed precision):
 //      X[R_b] -= L[R_b, b] X[b] (MFMA, rows gathered and scattered).
 // The factor flows through the workgroup as a stream of chunks (the inverse
-// of a diagonal block, up to 20 KB, or 16 KB of pruned-row tiles): while
-// chunk c is used from LDS, chunks c+1 and c+2 are in registers (loaded two
-// steps ahead: one step of latency hiding was measured 23% slower); c+1 is
-// written to the other half of a double buffer at the end of the step; one
-// barrier per chunk, on LDS only (X columns of a stripe are private to its
-// wavefront, so no barrier waits on global memory).  Rows of the next chunk
-// of the same block are gathered before the current chunk's MFMAs (the
-// chunks of one block update disjoint rows); a wavefront reads rows it wrote
-// itself in program order.
+// of a diagonal block, up to 20 KB, or 16 KB of pruned-row tiles), one per
+// step.  At the start of a step the next chunk, whose loads have had the
+// whole last step to arrive, goes from registers to the other half of a
+// double buffer in LDS, and the loads of the chunk after it are issued into
+// the same registers; one barrier per chunk, on LDS only (X columns of a
+// stripe are private to its wavefront, so no barrier waits on global
+// memory).  Rows of the next chunk of the same block are gathered before the
+// current chunk's MFMAs (the chunks of one block update disjoint rows), and
+// the rows of the next block before those of the last chunk where it does
+// not update them (VisitDev); a wavefront reads rows it wrote itself in
+// program order.
+// What bounds it is the latency of the X rows, so no load or store waits for
+// another: global memory operations complete in issue order, and the wait
+// for one of them can leave younger ones in flight only where the compiler
+// knows how many there are.  Rows that are not there (past a row list, off
+// the paths) are therefore out-of-range offsets of a buffer resource (read
+// as zero, not written) instead of branches, and no register holding a load
+// in flight is copied.  Before (branches, and a two-chunk prefetch whose
+// register rotation waited for every operation in flight at each step) / now:
+// 16 x 20^3 elasticity 23.3 / 19.8 ms FP64 (now 98 GB of memory traffic at 4.95
+// TB/s, the rate of a copy), 17.1 / 10.3 ms mixed; 512 x 12^3 heat 3.33 / 3.08
+// and 2.94 / 1.92 ms; 128 2D triangle meshes of 129^2 nodes 1.11 / 1.02 ms.
 // Mixed precision: the same with FP32 X and FP32 A tiles / MFMA for step 2;
-// step 1 stays FP64 (the block rows are widened, solved, rounded back).
+// step 1 stays FP64 (the block rows are widened, solved, rounded back).  The
+// FP32 A tiles are read with their rows permuted (4a + b -> 4b + a), which
+// gives the FP32 accumulator the row layout of the FP64 one.
 // Merged pairs: two consecutive blocks b, b + 1 that a tile visits one after
 // the other and whose rows below nest, R_b = rows(b + 1) followed by R_{b+1}
-// (BlockDev::flags, set by the host: two panels of one supernode, or a child
+// (planner's merge_pairs: two panels of one supernode, or a child
 // block with its parent's structure).  Block b then
-// updates only the rows of b + 1; its solved rows -X[b] wait in LDS (one 64 x
+// updates only the rows of b + 1, which stay in registers for the solve of
+// b + 1; its solved rows -X[b] wait in LDS (one 64 x
 // 16 slot per wavefront); block b + 1 updates R_{b+1} once with both:
 // X[R] -= L[R, b] X[b] + L[R, b + 1] X[b + 1], two chunk steps per row group
 // (the A tiles of b, then those of b + 1), one gather and one scatter.  The
@@ -92,143 +108,115 @@ __device__ __forceinline__ void lds_barrier() {
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
-struct ChunkSrc {
-    const char* p;       // always a valid address (the subdomain's factor when bytes == 0)
-    int bytes;
-    bool has_idx;        // the chunk carries the row indices at ip
-    const int32_t* ip;   // row indices of the pruned chunk gathered next (64 are read);
-                         // always a valid address (the row array is padded by 64 entries)
-};
+typedef uint32_t v2u __attribute__((ext_vector_type(2)));
+typedef uint32_t v4u __attribute__((ext_vector_type(4)));
 
-// Register prefetch of one chunk: five 16-byte pieces per thread, loaded
-// unconditionally (pieces past the chunk re-read its first bytes), plus the
-// 32 row indices (threads 0..7 keep them).  Separate registers, not a struct:
-// the prefetch must stay out of scratch memory.
-__device__ __forceinline__ void chunk_load(uint4& v0, uint4& v1, uint4& v2, uint4& v3, uint4& v4, uint4& vi,
-                                           const ChunkSrc& s) {
-    const int e = threadIdx.x * 16;
-    v0 = *reinterpret_cast<const uint4*>(s.p + (e < s.bytes ? e : 0));
-    v1 = *reinterpret_cast<const uint4*>(s.p + (e + 4096 < s.bytes ? e + 4096 : 0));
-    v2 = *reinterpret_cast<const uint4*>(s.p + (e + 8192 < s.bytes ? e + 8192 : 0));
-    v3 = *reinterpret_cast<const uint4*>(s.p + (e + 12288 < s.bytes ? e + 12288 : 0));
-    v4 = *reinterpret_cast<const uint4*>(s.p + (e + 16384 < s.bytes ? e + 16384 : 0));
-    vi = *reinterpret_cast<const uint4*>(s.ip + 4 * (threadIdx.x & 15));
+// Raw buffer resource over `bytes` bytes at p (wave-uniform): loads past them
+// return zero, stores past them are dropped.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void* p, uint32_t bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, bytes, 0x00027000);
 }
 
-__device__ __forceinline__ void chunk_store(const uint4& v0, const uint4& v1, const uint4& v2, const uint4& v3,
-                                            const uint4& v4, const uint4& vi, char* __restrict__ dst,
-                                            const ChunkSrc& s) {
-    const int e = threadIdx.x * 16;
-    if (e < s.bytes) *reinterpret_cast<uint4*>(dst + e) = v0;
-    if (e + 4096 < s.bytes) *reinterpret_cast<uint4*>(dst + e + 4096) = v1;
-    if (e + 8192 < s.bytes) *reinterpret_cast<uint4*>(dst + e + 8192) = v2;
-    if (e + 12288 < s.bytes) *reinterpret_cast<uint4*>(dst + e + 12288) = v3;
-    if (e + 16384 < s.bytes) *reinterpret_cast<uint4*>(dst + e + 16384) = v4;
-    if (s.has_idx && threadIdx.x < 16) *reinterpret_cast<uint4*>(dst + kChunkBytes + 16 * threadIdx.x) = vi;
-}
-
-// Scalar copy of the block descriptor fields the TRSM uses.
-struct BlockLite {
-    int w, nb;
-    int64_t aoff, linv_off, rows_off;
-};
-
-__device__ __forceinline__ BlockLite block_lite(const BlockDev* __restrict__ B, int b) {
-    return {B[b].w, B[b].nbelow, B[b].aoff, B[b].linv_off, B[b].rows_off};
-}
-
-// Pruned row tiles per chunk: 16 KB of A tiles, two FP64 or four FP32 row
-// tiles of 16 k-slices.
-template <class TA>
-constexpr int kPruneTiles = sizeof(TA) == 8 ? 2 : 4;
-
-// Role of a visit in a merged pair (see above): 0 = alone, 1 = first block
-// (updates only the rows of the next block), 2 = second block (its update of
-// the rows below also applies the first block's).
-__device__ __forceinline__ int visit_role(const BlockDev* __restrict__ B, const int32_t* __restrict__ V, int k,
-                                          int nv, int prev_role) {
-    if (prev_role == 1) return 2;
-    return (k + 1 < nv && B[V[k]].flags != 0 && V[k + 1] == V[k] + 1) ? 1 : 0;
-}
-
-// Rows the update of a visit covers: the rows of the next block (role 1,
-// whole 16-row tiles), else the block's pruned rows.
-__device__ __forceinline__ int update_rows(const BlockDev* __restrict__ B, const int32_t* __restrict__ V, int k,
-                                           int role, int nb) {
-    return role == 1 ? B[V[k] + 1].w : nb;
-}
-
-// Chunk c of a visit (block bd, role, `urows` rows in its update; prev = the
-// first block of the pair for role 2): c = 0 is the inverse of the diagonal
-// block (its lower tiles), the rest groups of kPruneTiles pruned row tiles
-// (TA = precision of the update's A tiles); role 2 alternates the first
-// block's A tiles of a row group (its pruned rows from the second block's
-// width on) with the second block's.  The diagonal chunk carries the row
-// indices of the first row group, the (second) chunk of row group p those of
-// group p + 1: they are gathered while the chunk is in use.
-template <class TA>
-__device__ __forceinline__ ChunkSrc chunk_src(const BlockLite& bd, int prev_w, int64_t prev_aoff, int role, int urows,
-                                              int c, const double* __restrict__ L, const TA* __restrict__ LA,
-                                              const int32_t* __restrict__ R) {
-    const int nks = (bd.w + 3) >> 2;
-    const int nrt_d = (bd.w + 15) >> 4;
-    constexpr int PT = kPruneTiles<TA>;
-    const int nrt = (urows + 15) >> 4;
-    const int np = (nrt + PT - 1) / PT;
-    if (c == 0)
-        return {reinterpret_cast<const char*>(L + bd.linv_off), (2 * (nrt_d - 1) * nrt_d + nks) * 64 * 8, np > 0,
-                R + bd.rows_off};
-    const int p = role == 2 ? (c - 1) >> 1 : c - 1;
-    const int nt = min(PT, nrt - PT * p);
-    if (role == 2 && ((c - 1) & 1) == 0) {
-        const int nks1 = (prev_w + 3) >> 2;
-        return {reinterpret_cast<const char*>(LA + prev_aoff + (int64_t)((bd.w >> 4) + PT * p) * nks1 * 64),
-                nt * nks1 * 64 * (int)sizeof(TA), false, R};
+// Access to the rows of one X slab by element offset.  LARGE = false: 32-bit
+// byte offsets of a buffer resource, kNone an offset past any slab.  LARGE =
+// true (slabs of kTrsmSlabBytes and more, which those offsets cannot span):
+// element indices and plain accesses under a branch.
+template <class TX, bool LARGE>
+struct SlabRows {
+    static constexpr int kNone = LARGE ? -1 : -16;
+    TX* p;
+    __amdgpu_buffer_rsrc_t r;
+    __device__ __forceinline__ SlabRows(TX* x, int64_t elems)
+        : p(x), r(buffer_of(x, LARGE ? 0u : (uint32_t)(elems * (int64_t)sizeof(TX)))) {}
+    __device__ __forceinline__ static int at(int row, int col) {
+        return LARGE ? row * kTile + col : (int)((uint32_t)(row * kTile + col) * (uint32_t)sizeof(TX));
     }
-    return {reinterpret_cast<const char*>(LA + bd.aoff + (int64_t)PT * p * nks * 64),
-            nt * nks * 64 * (int)sizeof(TA), p + 1 < np, R + bd.rows_off + 16 * PT * min(p + 1, np - 1)};
-}
+    __device__ __forceinline__ TX load(int off) const {
+        if constexpr (LARGE) return off >= 0 ? p[off] : TX(0);
+        else if constexpr (sizeof(TX) == 8) return __builtin_bit_cast(TX, __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0));
+        else return __builtin_bit_cast(TX, __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0));
+    }
+    __device__ __forceinline__ void store(int off, TX v) const {
+        if constexpr (LARGE) {
+            if (off >= 0) p[off] = v;
+        } else if constexpr (sizeof(TX) == 8) {
+            __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(v2u, v), r, off, 0, 0);
+        } else {
+            __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v), r, off, 0, 0);
+        }
+    }
+};
 
 // LDS slot of the first block's solved rows: 16 values per lane and wavefront.
 template <class TX>
 constexpr int kSlotBytes = 4 * 16 * 64 * (int)sizeof(TX);
 
-template <bool MIXED, bool MERGE>
+// acc[u] += A row tile u x B over nks k-slices (up to 16), NT row tiles of a
+// chunk at sA (this lane's values); B(t, s) = k-slice 4 t + s, zero past nks
+// (the A values met there are those of the next row tile or the zeros a chunk
+// ends in).  Four slices of every row tile are read ahead of the four in use.
+template <bool MIXED, int NT, class TX, class VX, class FB>
+__device__ __forceinline__ void mma_group(const TX* __restrict__ sA, int nks, const FB& B, VX* acc) {
+    TX a[2][NT][4];
+#pragma unroll
+    for (int u = 0; u < NT; ++u)
+#pragma unroll
+        for (int s = 0; s < 4; ++s) a[0][u][s] = sA[(u * nks + s) * 64];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+        if (4 * t >= nks) break;
+        TX b[4];
+#pragma unroll
+        for (int s = 0; s < 4; ++s) b[s] = B(t, s);
+        if (t < 3) {
+#pragma unroll
+            for (int u = 0; u < NT; ++u)
+#pragma unroll
+                for (int s = 0; s < 4; ++s)
+                    a[(t + 1) & 1][u][s] = sA[(u * nks + 4 * (t + 1) + s) * 64];
+        }
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+#pragma unroll
+            for (int u = 0; u < NT; ++u) {
+                if constexpr (MIXED) acc[u] = mfma_f32(a[t & 1][u][s], b[s], acc[u]);
+                else acc[u] = mfma_f64(a[t & 1][u][s], b[s], acc[u]);
+            }
+    }
+}
+
+template <bool MIXED, bool MERGE, bool LARGE>
 __device__ __forceinline__ void trsm_tile(
-    const SubDev* __restrict__ subs, const TileDev* __restrict__ tiles,
-    const BlockDev* __restrict__ blocks, const int32_t* __restrict__ rows,
-    const int32_t* __restrict__ visit, const uint64_t* __restrict__ vrows,
-    const double* __restrict__ lval, const float* __restrict__ lval32,
+    const SubDev* __restrict__ subs, const TileDev* __restrict__ tiles, const int32_t* __restrict__ rows,
+    const VisitDev* __restrict__ visits, const double* __restrict__ lval, const float* __restrict__ lval32,
     const int32_t* __restrict__ piv, const int8_t* __restrict__ sgn,
     typename std::conditional<MIXED, float, double>::type* __restrict__ X, int ti, char* __restrict__ smem)
 {
     using TX = typename std::conditional<MIXED, float, double>::type;
     using VX = typename std::conditional<MIXED, v4f, v4d>::type;
+    using Rows = SlabRows<TX, LARGE>;
     constexpr int PT = kPruneTiles<TX>;          // pruned row tiles per chunk
     const int lane = threadIdx.x & 63;
-    const int wv = threadIdx.x >> 6;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int g = lane >> 4;
     const int j = lane & 15;
+    const int la = MIXED ? 4 * (j & 3) + (j >> 2) + 16 * g : lane;   // A tile position this lane reads
     const TileDev T = tiles[ti];
     const SubDev S = subs[T.sub];
     const int kstart = T.kstart;
     TX* __restrict__ Xs = X + T.x_off;
+    const Rows xr_(Xs, (int64_t)(S.n - kstart) * kTile);
     const int col = wv * kStripe + j;
     const int64_t cbase = S.col_off + (int64_t)T.tile * kTile;
-    const BlockDev* __restrict__ B = blocks + S.blk_off;
     const int32_t* __restrict__ R = rows + S.rows_off;
     const double* __restrict__ L = lval + S.lval_off;
     const TX* __restrict__ LA;
     if constexpr (MIXED) LA = lval32 + S.lval_off;
     else LA = lval + S.lval_off;
-    const int my_start = tiles[ti].start_block[wv];
     // the blocks this tile visits, increasing: those holding rows on the
     // elimination-tree paths of its pivots (all other rows of X are zero)
     const int nv = T.nvisit;
-    const int32_t* __restrict__ V = visit + T.visit_off;
-    // per visit, the rows of the block on the paths: the others are zero
-    // before and after its diagonal solve and are neither read nor written
-    const uint64_t* __restrict__ VR = vrows + T.visit_off;
+    const VisitDev* __restrict__ V = visits + T.visit_off;
 
     // right-hand side P B^T: sign at the pivot row, zero elsewhere.  Only the
     // 16-row steps of visited blocks that hold a row on the paths are cleared:
@@ -237,9 +225,9 @@ __device__ __forceinline__ void trsm_tile(
     // reads nor writes them, and the SYRK reads only the steps of a slab that
     // hold a row on its paths
     for (int k = 0; k < nv; ++k) {
-        const int r0 = B[V[k]].row0;
-        const int r1 = r0 + B[V[k]].w;
-        const uint64_t on = VR[k];
+        const int r0 = V[k].row0;
+        const int r1 = r0 + V[k].w;
+        const uint64_t on = V[k].on;
         for (int q = 0; q < 4; ++q) {
             if (((on >> (16 * q)) & 0xFFFFull) == 0) continue;
             const int qe = min(r0 + 16 * (q + 1), r1);
@@ -249,210 +237,226 @@ __device__ __forceinline__ void trsm_tile(
     __threadfence_block();
     if (g == 0 && col < T.ncols) Xs[(int64_t)(piv[cbase + col] - kstart) * kTile + col] = (TX)sgn[cbase + col];
     if (nv <= 0) return;
+    __threadfence_block();
 
-    BlockLite bd = block_lite(B, V[0]);
-    TX* __restrict__ slot = reinterpret_cast<TX*>(smem + kTrsmSmem) + wv * 16 * 64;
-    // prefetch cursor over the flattened chunk stream: chunk s+2 is loaded
-    // into registers at the start of step s, chunk s+1 goes to LDS at its end
+    TX* __restrict__ slot = reinterpret_cast<TX*>(smem + kTrsmSmem) + wv * 16 * 64 + lane;
+
+    // ---- the chunk stream: chunk c of visit record p.  c = 0 is the inverse
+    // of the diagonal block (its lower tiles), the rest groups of PT pruned
+    // row tiles; the second block of a pair alternates the first block's A
+    // tiles of a row group with its own.  The diagonal chunk carries the row
+    // indices of the first row group, the (second) chunk of row group q those
+    // of group q + 1: they are gathered while the chunk is in use.
     int pk = 0, pc = 0;
-    BlockLite pbd = bd;
-    int pprev_w = 0;
-    int64_t pprev_aoff = 0;
-    int prole = MERGE ? visit_role(B, V, 0, nv, 0) : 0;
-    int purows = update_rows(B, V, 0, prole, pbd.nb);
-    auto nchunks = [](int role, int urows) {
-        const int np = (((urows + 15) >> 4) + PT - 1) / PT;
-        return 1 + (role == 2 ? 2 * np : np);
-    };
-    int pnch = nchunks(prole, purows);
-    auto take = [&]() {
-        ChunkSrc c{reinterpret_cast<const char*>(L), 0, false, R};
+    VisitDev p = V[0];
+    v4u c0, c1, c2, c3, c4, ci;                  // the chunk after the one(s) in LDS
+    auto load_chunk = [&]() {
+        const char* src = reinterpret_cast<const char*>(L);
+        const int32_t* ip = R;
+        uint32_t bytes = 0, ibytes = 0;
         if (pk < nv) {
-            c = chunk_src(pbd, pprev_w, pprev_aoff, prole, purows, pc, L, LA, R);
-            if (++pc >= pnch) {
+            const int prole = MERGE ? p.flags & 3 : 0;
+            const int nks = (p.w + 3) >> 2;
+            const int nrt = (p.urows + 15) >> 4;
+            const int np = (nrt + PT - 1) / PT;
+            if (pc == 0) {
+                const int nrt_d = (p.w + 15) >> 4;
+                src = reinterpret_cast<const char*>(L + p.linv_off);
+                bytes = (2 * (nrt_d - 1) * nrt_d + nks) * 64 * 8;
+                ip = R + p.rows_off;
+                ibytes = np > 0 ? kIdxBytes : 0;
+            } else {
+                const int q = prole == 2 ? (pc - 1) >> 1 : pc - 1;
+                const int nt = min(PT, nrt - PT * q);
+                const bool first = prole == 2 && ((pc - 1) & 1) == 0;
+                const int ks = first ? p.pair_nks : nks;
+                src = reinterpret_cast<const char*>(LA + (first ? p.pair_aoff : p.aoff) + (int64_t)PT * q * ks * 64);
+                bytes = nt * ks * 64 * (int)sizeof(TX);
+                ip = R + p.rows_off + 16 * PT * (q + 1);
+                ibytes = !first && q + 1 < np ? kIdxBytes : 0;
+            }
+            if (++pc > (prole == 2 ? 2 * np : np)) {
                 ++pk;
                 pc = 0;
-                if (pk < nv) {
-                    pprev_w = pbd.w;
-                    pprev_aoff = pbd.aoff;
-                    pbd = block_lite(B, V[pk]);
-                    prole = MERGE ? visit_role(B, V, pk, nv, prole) : 0;
-                    purows = update_rows(B, V, pk, prole, pbd.nb);
-                    pnch = nchunks(prole, purows);
-                }
+                if (pk < nv) p = V[pk];
             }
         }
-        return c;
+        const __amdgpu_buffer_rsrc_t rc = buffer_of(src, bytes), ri = buffer_of(ip, ibytes);
+        const int e = threadIdx.x * 16;
+        c0 = __builtin_amdgcn_raw_buffer_load_b128(rc, e, 0, 0);
+        c1 = __builtin_amdgcn_raw_buffer_load_b128(rc, e, 4096, 0);
+        c2 = __builtin_amdgcn_raw_buffer_load_b128(rc, e, 8192, 0);
+        c3 = __builtin_amdgcn_raw_buffer_load_b128(rc, e, 12288, 0);
+        c4 = __builtin_amdgcn_raw_buffer_load_b128(rc, e, 16384, 0);
+        ci = __builtin_amdgcn_raw_buffer_load_b128(ri, e & 255, 0, 0);
     };
-    // a*: chunk s+1 (stored to LDS at the end of step s), b*: chunk s+2;
-    // sa_* / sb_* describe them
-    uint4 a0, a1, a2, a3, a4, ai, b0, b1, b2, b3, b4, bi;
-    {
-        const ChunkSrc c0 = take();
-        chunk_load(a0, a1, a2, a3, a4, ai, c0);
-        chunk_store(a0, a1, a2, a3, a4, ai, smem, c0);
-    }
-    const char* sa_p; int sa_bytes; bool sa_idx; const int32_t* sa_ip;
-    const char* sb_p = reinterpret_cast<const char*>(L); int sb_bytes = 0; bool sb_idx = false; const int32_t* sb_ip = R;
-    {
-        const ChunkSrc c1 = take();
-        chunk_load(a0, a1, a2, a3, a4, ai, c1);
-        sa_p = c1.p; sa_bytes = c1.bytes; sa_idx = c1.has_idx; sa_ip = c1.ip;
-    }
-    lds_barrier();
+    auto put_chunk = [&](char* dst) {
+        const int e = threadIdx.x * 16;
+        *reinterpret_cast<v4u*>(dst + e) = c0;
+        *reinterpret_cast<v4u*>(dst + e + 4096) = c1;
+        *reinterpret_cast<v4u*>(dst + e + 8192) = c2;
+        *reinterpret_cast<v4u*>(dst + e + 12288) = c3;
+        *reinterpret_cast<v4u*>(dst + e + 16384) = c4;
+        if (threadIdx.x < kIdxBytes / 16) *reinterpret_cast<v4u*>(dst + kChunkBytes + e) = ci;
+    };
     int buf = 0;
-
     auto step_begin = [&]() {
-        const ChunkSrc cb = take();
-        chunk_load(b0, b1, b2, b3, b4, bi, cb);
-        sb_p = cb.p; sb_bytes = cb.bytes; sb_idx = cb.has_idx; sb_ip = cb.ip;
+        put_chunk(smem + (buf ^ 1) * kBufBytes);
+        load_chunk();
     };
     auto step_end = [&]() {
-        if (sa_bytes > 0) {
-            const ChunkSrc ca{sa_p, sa_bytes, sa_idx, sa_ip};
-            chunk_store(a0, a1, a2, a3, a4, ai, smem + (buf ^ 1) * kBufBytes, ca);
-            lds_barrier();
-            buf ^= 1;
-        }
-        a0 = b0; a1 = b1; a2 = b2; a3 = b3; a4 = b4; ai = bi;
-        sa_p = sb_p; sa_bytes = sb_bytes; sa_idx = sb_idx; sa_ip = sb_ip;
+        lds_barrier();
+        buf ^= 1;
     };
-    int role = 0;
-    int nks_prev = 0;                            // k-slices of the pair's first block (role 2)
+    load_chunk();
+    put_chunk(smem);
+    load_chunk();
+    lds_barrier();
+
+    TX xin[4][4];                                // X rows of the next block, accumulator layout
+    auto load_block = [&](const VisitDev& v, uint64_t on, bool act) {
+        const uint64_t onl = act ? on >> g : 0;
+        const int b0 = Rows::at(v.row0 + g - kstart, col);
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+                xin[t][r] = xr_.load(((onl >> (16 * t + 4 * r)) & 1) ? b0 + Rows::at(16 * t + 4 * r, 0) : Rows::kNone);
+    };
+
+    VisitDev v = V[0];
+    load_block(v, v.on, (v.flags >> (kVisitActShift + wv)) & 1);
+    int pair_nks = 0;
     for (int k = 0; k < nv; ++k) {
-        const int b = V[k];
-        const uint64_t on = VR[k] >> g;          // bit 16t + 4r: row 16t + 4r + g of the block
-        const int w = bd.w;
-        const int row0 = B[b].row0;
-        role = MERGE ? visit_role(B, V, k, nv, role) : 0;
-        const int nb = update_rows(B, V, k, role, bd.nb);   // rows this visit's update covers
-        const int nks = (w + 3) >> 2;
-        const int nrt_d = (w + 15) >> 4;
-        const int nrt = (nb + 15) >> 4;
+        const VisitDev nx = V[min(k + 1, nv - 1)];
+        const uint64_t nx_on = k + 1 < nv ? nx.on : 0;
+        const bool nx_act = (nx.flags >> (kVisitActShift + wv)) & 1;
+        const bool act = (v.flags >> (kVisitActShift + wv)) & 1;
+        const int role = MERGE ? v.flags & 3 : 0;
+        const bool early = (v.flags & kVisitNextEarly) != 0;
+        const int urows = v.urows;
+        const int nks = (v.w + 3) >> 2;
+        const int nrt_d = (v.w + 15) >> 4;
+        const int nrt = (urows + 15) >> 4;
         const int np = (nrt + PT - 1) / PT;
-        const bool act = b >= my_start;
-        const BlockLite bn = block_lite(B, V[k + 1 < nv ? k + 1 : k]);
+        // the first block of a pair hands the next block's rows on in
+        // registers: they are read for the stripes active there
+        const bool gact = role == 1 ? nx_act : act;
 
         VX accn[PT];                             // rows of the next pruned chunk
         int offn[PT][4];
-        auto gather = [&](int p) {               // row indices from the chunk in LDS
+        auto gather = [&](int q) {               // row indices from the chunk in LDS
             const int32_t* __restrict__ sidx = reinterpret_cast<const int32_t*>(smem + buf * kBufBytes + kChunkBytes);
+            const int left = gact ? urows - 16 * PT * q : 0;
 #pragma unroll
             for (int u = 0; u < PT; ++u)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    const int k = 16 * u + (MIXED ? 4 * g + r : 4 * r + g);
-                    offn[u][r] = 16 * PT * p + k < nb ? (sidx[k] - kstart) * kTile + col : -1;
-                    accn[u][r] = offn[u][r] >= 0 ? Xs[offn[u][r]] : TX(0);
+                    const int i = 16 * u + 4 * r + g;
+                    offn[u][r] = i < left ? Rows::at(sidx[i] - kstart, col) : Rows::kNone;
                 }
+#pragma unroll
+            for (int u = 0; u < PT; ++u)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) accn[u][r] = xr_.load(offn[u][r]);
         };
 
         // ---- 1. X[b] <- L_bb^{-1} X[b]
         TX xb[4][4];                             // -X[b]: B operands of step 2
+        step_begin();
+        if (np > 0) gather(0);
+        __builtin_amdgcn_sched_barrier(0);
         {
-            v4d xr[4];
-            if (act) {
+            v4d xr[4], tmp[4];
 #pragma unroll
-                for (int t = 0; t < 4; ++t)
+            for (int t = 0; t < 4; ++t)
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const int i = 16 * t + 4 * r + g;
-                        const int row = row0 + i;
-                        xr[t][r] = (((on >> (16 * t + 4 * r)) & 1) && row >= kstart)
-                                       ? (double)Xs[(int64_t)(row - kstart) * kTile + col] : 0.0;
-                    }
-                if (np > 0) gather(0);
-            }
-            step_begin();
-            if (act) {
-                // lower tiles only: row tile u needs k-slices of row tiles t <= u
-                const double* __restrict__ sA = reinterpret_cast<const double*>(smem + buf * kBufBytes);
-                v4d tmp[4];
+                for (int r = 0; r < 4; ++r) xr[t][r] = (double)xin[t][r];
+            // lower tiles only: row tile u needs k-slices of row tiles t <= u
+            const double* __restrict__ sA = reinterpret_cast<const double*>(smem + buf * kBufBytes) + lane;
 #pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    tmp[u] = v4d{0.0, 0.0, 0.0, 0.0};
-                    if (u < nrt_d) {
+            for (int u = 0; u < 4; ++u) {
+                tmp[u] = v4d{0.0, 0.0, 0.0, 0.0};
+                if (u < nrt_d) {
 #pragma unroll
-                        for (int t = 0; t <= u; ++t)
+                    for (int t = 0; t <= u; ++t)
 #pragma unroll
-                            for (int s = 0; s < 4; ++s) {
-                                const int ks = 4 * t + s;
-                                if (ks < nks) tmp[u] = mfma_f64(sA[(2 * u * (u + 1) + ks) * 64 + lane], xr[t][s], tmp[u]);
-                            }
-                    }
+                        for (int s = 0; s < 4; ++s)
+                            tmp[u] = mfma_f64(sA[(2 * u * (u + 1) + 4 * t + s) * 64], xr[t][s], tmp[u]);
                 }
-#pragma unroll
-                for (int u = 0; u < 4; ++u)
-                    if (u < nrt_d) xr[u] = tmp[u];
             }
-            step_end();
-            if (act) {
+            const uint64_t onl = act ? v.on >> g : 0;
+            const int b0 = Rows::at(v.row0 + g - kstart, col);
 #pragma unroll
-                for (int t = 0; t < 4; ++t)
+            for (int t = 0; t < 4; ++t)
 #pragma unroll
-                    for (int r = 0; r < 4; ++r) {
-                        const int i = 16 * t + 4 * r + g;
-                        const int row = row0 + i;
-                        const TX v = (TX)xr[t][r];
-                        if (((on >> (16 * t + 4 * r)) & 1) && row >= kstart)
-                            Xs[(int64_t)(row - kstart) * kTile + col] = v;
-                        xb[t][r] = -v;
-                    }
-            }
-            // the first block of a pair keeps its solved rows for the second
-            // (zero for a wavefront that starts at the second)
-            if (role == 1) {
-#pragma unroll
-                for (int t = 0; t < 4; ++t)
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) slot[(4 * t + r) * 64 + lane] = act ? xb[t][r] : TX(0);
-            }
+                for (int r = 0; r < 4; ++r) {
+                    const TX x = (TX)tmp[t][r];
+                    xr_.store(((onl >> (16 * t + 4 * r)) & 1) ? b0 + Rows::at(16 * t + 4 * r, 0) : Rows::kNone, x);
+                    xb[t][r] = -x;
+                }
         }
+        // the first block of a pair keeps its solved rows for the second
+        // (zero for a wavefront that starts at the second)
+        if (role == 1) {
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) slot[(4 * t + r) * 64] = xb[t][r];
+        }
+        step_end();
 
-        // ---- 2. X[R_b] -= L[R_b, b] X[b], pruned row tiles PT p .. PT p + PT - 1
-        // (role 2: first the pair's first block's A tiles with its solved
-        // rows from LDS, then this block's, one gather and one scatter)
+        // ---- 2. X[R_b] -= L[R_b, b] X[b], pruned row tiles PT q .. PT q + PT - 1
         VX acc[PT];
-        int off[PT][4];
-        for (int p = 0; p < np; ++p) {
-            if (role == 2) {
-                if constexpr (MIXED) step_begin();
-                if (act) {
+        auto own = [&](int t, int s) { return xb[t][s]; };
+        auto kept = [&](int t, int s) { return slot[(4 * t + s) * 64]; };
+        auto update = [&](int nk, const auto& B, int nt) {
+            const TX* __restrict__ sA = reinterpret_cast<const TX*>(smem + buf * kBufBytes) + la;
+            if (!act && role != 2) return;
+            if (nt > PT / 2) mma_group<MIXED, PT>(sA, nk, B, acc);
+            else mma_group<MIXED, PT / 2>(sA, nk, B, acc);
+        };
+        if (MERGE && role == 1) {
+            // the rows of the next block: kept in registers, zero off the paths
+            const uint64_t onl = nx_on >> g;
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) xin[t][r] = TX(0);
+#pragma unroll
+            for (int q = 0; q < 4 / PT; ++q)
+                if (q < np) {
+                    step_begin();
+#pragma unroll
+                    for (int u = 0; u < PT; ++u) acc[u] = accn[u];
+                    if (q + 1 < np) gather(q + 1);
+                    __builtin_amdgcn_sched_barrier(0);
+                    update(nks, own, min(PT, nrt - PT * q));
+#pragma unroll
+                    for (int u = 0; u < PT; ++u)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r)
+                            xin[PT * q + u][r] = ((onl >> (16 * (PT * q + u) + 4 * r)) & 1) ? acc[u][r] : TX(0);
+                    step_end();
+                }
+            pair_nks = nks;
+        } else {
+            int off[PT][4];
+            for (int q = 0; q < np; ++q) {
+                const int nt = min(PT, nrt - PT * q);
+                if (MERGE && role == 2) {
+                    step_begin();
 #pragma unroll
                     for (int u = 0; u < PT; ++u) {
                         acc[u] = accn[u];
 #pragma unroll
                         for (int r = 0; r < 4; ++r) off[u][r] = offn[u][r];
                     }
+                    __builtin_amdgcn_sched_barrier(0);
+                    update(pair_nks, kept, nt);
+                    step_end();
                 }
-                if constexpr (!MIXED) step_begin();
-                if (act) {
-                    const TX* __restrict__ sA = reinterpret_cast<const TX*>(smem + buf * kBufBytes);
-                    const int nt = min(PT, nrt - PT * p);
-#pragma unroll
-                    for (int u = 0; u < PT; ++u) {
-                        if (u < nt) {
-#pragma unroll
-                            for (int t = 0; t < 4; ++t)
-#pragma unroll
-                                for (int s = 0; s < 4; ++s) {
-                                    const int ks = 4 * t + s;
-                                    if (ks < nks_prev) {
-                                        const TX xv = slot[ks * 64 + lane];
-                                        if constexpr (MIXED) acc[u] = mfma_f32(sA[(u * nks_prev + ks) * 64 + lane], xv, acc[u]);
-                                        else acc[u] = mfma_f64(sA[(u * nks_prev + ks) * 64 + lane], xv, acc[u]);
-                                    }
-                                }
-                        }
-                    }
-                }
-                step_end();
-            }
-            // FP64: the next gather is issued before the next chunk's loads, so
-            // that waiting for it a step later does not wait for them as well
-            // (the mixed kernel has no registers left for that order)
-            if constexpr (MIXED) step_begin();
-            if (act) {
+                step_begin();
                 if (role != 2) {
 #pragma unroll
                     for (int u = 0; u < PT; ++u) {
@@ -461,67 +465,49 @@ __device__ __forceinline__ void trsm_tile(
                         for (int r = 0; r < 4; ++r) off[u][r] = offn[u][r];
                     }
                 }
-                if (p + 1 < np) gather(p + 1);
-            }
-            if constexpr (!MIXED) step_begin();
-            if (act) {
-                const TX* __restrict__ sA = reinterpret_cast<const TX*>(smem + buf * kBufBytes);
-                const int nt = min(PT, nrt - PT * p);
-#pragma unroll
-                for (int u = 0; u < PT; ++u) {
-                    if (u < nt) {
-#pragma unroll
-                        for (int t = 0; t < 4; ++t)
-#pragma unroll
-                            for (int s = 0; s < 4; ++s) {
-                                const int ks = 4 * t + s;
-                                if (ks < nks) {
-                                    if constexpr (MIXED) acc[u] = mfma_f32(sA[(u * nks + ks) * 64 + lane], xb[t][s], acc[u]);
-                                    else acc[u] = mfma_f64(sA[(u * nks + ks) * 64 + lane], xb[t][s], acc[u]);
-                                }
-                            }
-                    }
-                }
+                if (q + 1 < np) gather(q + 1);
+                else if (early) load_block(nx, nx_on, nx_act);
+                __builtin_amdgcn_sched_barrier(0);
+                update(nks, own, nt);
 #pragma unroll
                 for (int u = 0; u < PT; ++u)
 #pragma unroll
-                    for (int r = 0; r < 4; ++r)
-                        if (off[u][r] >= 0) Xs[off[u][r]] = acc[u][r];
+                    for (int r = 0; r < 4; ++r) xr_.store(off[u][r], acc[u][r]);
+                if (q + 1 == np && !early) load_block(nx, nx_on, nx_act);
+                step_end();
             }
-            step_end();
+            if (np == 0) load_block(nx, nx_on, nx_act);
         }
-        nks_prev = nks;
-        bd = bn;
+        v = nx;
     }
 }
 
-// MERGE: with the merged pairs (BlockDev::flags); without, the flags are
-// ignored and the merged code paths compile away.
-template <bool MERGE>
+// MERGE: with the merged pairs (the visits' roles); without, every visit is
+// alone and the merged code paths compile away.  LARGE: some X slab holds
+// kTrsmSlabBytes or more.
+template <bool MERGE, bool LARGE>
 __global__ __launch_bounds__(256, 2) void trsm_stair_f64(
-    const SubDev* __restrict__ subs, const TileDev* __restrict__ tiles,
-    const BlockDev* __restrict__ blocks, const int32_t* __restrict__ rows, const int32_t* __restrict__ visit,
-    const uint64_t* __restrict__ vrows, const double* __restrict__ lval, const int32_t* __restrict__ piv,
+    const SubDev* __restrict__ subs, const TileDev* __restrict__ tiles, const int32_t* __restrict__ rows,
+    const VisitDev* __restrict__ visits, const double* __restrict__ lval, const int32_t* __restrict__ piv,
     const int8_t* __restrict__ sgn, const int32_t* __restrict__ order, double* __restrict__ X)
 {
     __shared__ __align__(16) char smem[kTrsmSmem + (MERGE ? kSlotBytes<double> : 0)];
     const int ti = order[blockIdx.x];
     if (ti < 0) return;
-    trsm_tile<false, MERGE>(subs, tiles, blocks, rows, visit, vrows, lval, nullptr, piv, sgn, X, ti, smem);
+    trsm_tile<false, MERGE, LARGE>(subs, tiles, rows, visits, lval, nullptr, piv, sgn, X, ti, smem);
 }
 
-template <bool MERGE>
+template <bool MERGE, bool LARGE>
 __global__ __launch_bounds__(256, 2) void trsm_stair_mixed(
-    const SubDev* __restrict__ subs, const TileDev* __restrict__ tiles,
-    const BlockDev* __restrict__ blocks, const int32_t* __restrict__ rows, const int32_t* __restrict__ visit,
-    const uint64_t* __restrict__ vrows, const double* __restrict__ lval, const float* __restrict__ lval32,
-    const int32_t* __restrict__ piv,
-    const int8_t* __restrict__ sgn, const int32_t* __restrict__ order, float* __restrict__ X)
+    const SubDev* __restrict__ subs, const TileDev* __restrict__ tiles, const int32_t* __restrict__ rows,
+    const VisitDev* __restrict__ visits, const double* __restrict__ lval, const float* __restrict__ lval32,
+    const int32_t* __restrict__ piv, const int8_t* __restrict__ sgn, const int32_t* __restrict__ order,
+    float* __restrict__ X)
 {
     __shared__ __align__(16) char smem[kTrsmSmem + (MERGE ? kSlotBytes<float> : 0)];
     const int ti = order[blockIdx.x];
     if (ti < 0) return;
-    trsm_tile<true, MERGE>(subs, tiles, blocks, rows, visit, vrows, lval, lval32, piv, sgn, X, ti, smem);
+    trsm_tile<true, MERGE, LARGE>(subs, tiles, rows, visits, lval, lval32, piv, sgn, X, ti, smem);
 }
 
 // ---------------------------------------------------------------------------
@@ -949,23 +935,20 @@ __global__ __launch_bounds__(256) void syrk_tile_f32(
 }
 
 // ---------------------------------------------------------------------------
+template <bool MERGE, bool LARGE>
+static void trsm_launch(const DevTables& t, const int32_t* order, int64_t count, hipStream_t stream) {
+    if (t.X32)
+        hipLaunchKernelGGL((trsm_stair_mixed<MERGE, LARGE>), dim3((unsigned)count), dim3(256), 0, stream, t.subs,
+                           t.tiles, t.rows, t.visits, t.lval, t.lval32, t.piv, t.sgn, order, t.X32);
+    else
+        hipLaunchKernelGGL((trsm_stair_f64<MERGE, LARGE>), dim3((unsigned)count), dim3(256), 0, stream, t.subs,
+                           t.tiles, t.rows, t.visits, t.lval, t.piv, t.sgn, order, t.X);
+}
+
 hipError_t launch_trsm(const DevTables& t, const int32_t* order, int64_t count, hipStream_t stream) {
     if (count <= 0) return hipSuccess;
-    if (t.X32) {
-        if (t.trsm_merge)
-            hipLaunchKernelGGL(trsm_stair_mixed<true>, dim3((unsigned)count), dim3(256), 0, stream, t.subs, t.tiles,
-                               t.blocks, t.rows, t.visit, t.vrows, t.lval, t.lval32, t.piv, t.sgn, order, t.X32);
-        else
-            hipLaunchKernelGGL(trsm_stair_mixed<false>, dim3((unsigned)count), dim3(256), 0, stream, t.subs, t.tiles,
-                               t.blocks, t.rows, t.visit, t.vrows, t.lval, t.lval32, t.piv, t.sgn, order, t.X32);
-    } else {
-        if (t.trsm_merge)
-            hipLaunchKernelGGL(trsm_stair_f64<true>, dim3((unsigned)count), dim3(256), 0, stream, t.subs, t.tiles,
-                               t.blocks, t.rows, t.visit, t.vrows, t.lval, t.piv, t.sgn, order, t.X);
-        else
-            hipLaunchKernelGGL(trsm_stair_f64<false>, dim3((unsigned)count), dim3(256), 0, stream, t.subs, t.tiles,
-                               t.blocks, t.rows, t.visit, t.vrows, t.lval, t.piv, t.sgn, order, t.X);
-    }
+    if (t.trsm_large) t.trsm_merge ? trsm_launch<true, true>(t, order, count, stream) : trsm_launch<false, true>(t, order, count, stream);
+    else t.trsm_merge ? trsm_launch<true, false>(t, order, count, stream) : trsm_launch<false, false>(t, order, count, stream);
     return hipGetLastError();
 }
 

@@ -16,9 +16,8 @@ struct DevTables {
     const TileDev* tiles = nullptr;
     const BlockDev* blocks = nullptr;
     const int32_t* rows = nullptr;
-    const int32_t* visit = nullptr;        // blocks visited per TRSM tile (TileDev::visit_off)
+    const VisitDev* visits = nullptr;      // blocks visited per TRSM tile (TileDev::visit_off)
     const int32_t* ksteps = nullptr;       // SYRK k-steps per item (SyrkItem::step_off)
-    const uint64_t* vrows = nullptr;       // per visit: rows of the block on the tile's paths
     const double* lval = nullptr;
     const float* lval32 = nullptr;
     const int32_t* piv = nullptr;
@@ -34,7 +33,8 @@ struct DevTables {
     const int2* frows = nullptr;           // (subdomain, 128-row block): symmetric apply pass 2
     double* part = nullptr;                // 256 partial sums per stored F tile
     int64_t ntiles = 0;          // TRSM workgroups (length of tile_order)
-    bool trsm_merge = false;     // TRSM with the merged pairs of BlockDev::flags
+    bool trsm_merge = false;     // TRSM with the merged pairs (VisitDev::flags)
+    bool trsm_large = false;     // some X slab holds kTrsmSlabBytes or more
     int64_t nsyrk = 0;           // SYRK workgroups (items with sub < 0 are idle)
     int64_t nsyrk_tile = 0;      // the first nsyrk_tile of them are 128 x 128 tiles, the rest 64 x 64 blocks
     int64_t nftiles = 0;

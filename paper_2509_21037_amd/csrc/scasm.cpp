@@ -167,6 +167,57 @@ Prediction predict(const SubPlan& sp, bool mixed, const sc_options_t& o) {
     return q;
 }
 
+// Visit records of tile t of a subdomain (VisitDev), in visit order: the
+// rows on the paths that the slab holds, the roles in merged pairs (`pair`:
+// merge_pairs flags, null = every visit alone), the stripes that have started
+// (a stripe's columns begin at the block of its first pivot) and whether the
+// last chunk of the update (`pt` row tiles) leaves the next block's rows alone.
+void append_visits(const SubPlan& sp, int32_t t, int32_t kstart, bool staircase, const std::vector<int32_t>* pair,
+                   int pt, std::vector<VisitDev>& out) {
+    const int64_t v0 = sp.visit_ptr[t], v1 = sp.visit_ptr[t + 1];
+    int32_t start[4];
+    for (int w = 0; w < 4; ++w) {
+        const int32_t c = t * kTile + w * kStripe;
+        start[w] = c >= sp.m ? (int32_t)sp.blocks.size() : staircase ? sp.block_of_row[sp.piv[c]] : 0;
+    }
+    int prev = 0;
+    for (int64_t k = v0; k < v1; ++k) {
+        const int32_t b = sp.visit[k];
+        const BlockDesc& d = sp.blocks[b];
+        const int32_t nextb = k + 1 < v1 ? sp.visit[k + 1] : -1;
+        VisitDev v{};
+        v.on = sp.visit_rows[k];
+        if (kstart > d.row0) v.on = kstart - d.row0 >= 64 ? 0 : v.on & (~0ull << (kstart - d.row0));
+        v.linv_off = d.linv_off;
+        v.aoff = d.aoff;
+        v.rows_off = d.rows_off;
+        v.row0 = d.row0;
+        v.w = d.w;
+        const int role = prev == 1 ? 2 : pair && (*pair)[b] && nextb == b + 1 ? 1 : 0;
+        v.urows = role == 1 ? sp.blocks[b + 1].w : d.nbelow;
+        if (role == 2) {
+            const BlockDesc& f = sp.blocks[b - 1];
+            v.pair_nks = (f.w + 3) / 4;
+            v.pair_aoff = f.aoff + (int64_t)(d.w / 16) * v.pair_nks * 64;
+        }
+        v.flags = role;
+        for (int w = 0; w < 4; ++w)
+            if (b >= start[w]) v.flags |= 1 << (kVisitActShift + w);
+        if (nextb >= 0 && v.urows > 0) {
+            const int32_t r0 = sp.blocks[nextb].row0, r1 = r0 + sp.blocks[nextb].w;
+            const int32_t last = (v.urows - 1) / (16 * pt) * (16 * pt);
+            bool clear = true;
+            for (int32_t q = last; q < v.urows; ++q) {
+                const int32_t r = sp.brows[d.rows_off + q];
+                clear = clear && (r < r0 || r >= r1);
+            }
+            if (clear) v.flags |= kVisitNextEarly;
+        }
+        out.push_back(v);
+        prev = role;
+    }
+}
+
 #define HIP_TRY(expr)                                                                        \
     do {                                                                                     \
         hipError_t e_ = (expr);                                                              \
@@ -204,8 +255,7 @@ struct sc_plan_s {
     std::vector<SubDev> h_subs;
     std::vector<TileDev> h_tiles;
     std::vector<BlockDev> h_blocks;
-    std::vector<int32_t> h_visit;               // TRSM visit lists of all tiles
-    std::vector<uint64_t> h_vrows;              // per visit: the block's rows on the paths
+    std::vector<VisitDev> h_visits;             // TRSM visit lists of all tiles
     std::vector<int32_t> h_ksteps;              // SYRK k-step lists of all items
     std::vector<SyrkItem> h_syrk;               // interleaved over XCDs, idle items sub = -1
     std::vector<int32_t> h_tile_order;          // TRSM workgroup -> tile (-1 idle)
@@ -244,8 +294,8 @@ struct sc_plan_s {
     double* scratch = nullptr;
     hipError_t scratch_err = hipSuccess;
     int32_t noalloc_too_big = -1;
-    DevBuf<int32_t> d_rows, d_piv, d_pi, d_visit, d_ksteps;
-    DevBuf<uint64_t> d_vrows;
+    DevBuf<int32_t> d_rows, d_piv, d_pi, d_ksteps;
+    DevBuf<VisitDev> d_visits;
     DevBuf<int8_t> d_sgn;
     DevBuf<double> d_lval, d_X, d_F;
     DevBuf<float> d_lval32, d_X32, d_F32;
@@ -272,6 +322,7 @@ struct sc_plan_s {
     // kMergeMinShare of the batch's pruned-row updates (below that, the
     // merge-capable kernel's extra scalar state costs more than it saves)
     bool trsm_merge = false;
+    bool trsm_large = false;                    // some X slab holds kTrsmSlabBytes or more
     // select_iters: per subdomain applied with the factor (not assembled),
     // and the prediction behind the choice
     std::vector<uint8_t> implicit_sub;
@@ -381,7 +432,8 @@ struct sc_plan_s {
                          d_ftiles.count * sizeof(SyrkItem) + d_frows.count * sizeof(int2) +
                          d_part.count * 8 + d_tile_order.count * 4 +
                          d_tile_order_g.count * 4 + d_syrk_g.count * sizeof(SyrkItem) +
-                         (d_rows.count + d_piv.count + d_pi.count + d_visit.count + d_ksteps.count) * 4 + d_vrows.count * 8 + d_sgn.count +
+                         (d_rows.count + d_piv.count + d_pi.count + d_ksteps.count) * 4 + d_visits.count * sizeof(VisitDev) +
+                         d_sgn.count +
                          (d_lval.count + d_X.count + d_F.count) * 8 +
                          (d_lval32.count + d_X32.count + d_F32.count) * 4 +
                          (d_xwork.count + d_ywork.count + d_xoff.count) * 8 + (d_ifw.count + d_ibw.count) * sizeof(int2) +
@@ -392,7 +444,7 @@ struct sc_plan_s {
         d_subs.release(); d_tiles.release(); d_blocks.release(); d_syrk.release();
         d_ftiles.release(); d_frows.release(); d_part.release();
         d_tile_order.release(); d_tile_order_g.release(); d_syrk_g.release();
-        d_rows.release(); d_piv.release(); d_pi.release(); d_visit.release(); d_ksteps.release(); d_vrows.release(); d_sgn.release();
+        d_rows.release(); d_piv.release(); d_pi.release(); d_ksteps.release(); d_visits.release(); d_sgn.release();
         d_lval.release(); d_X.release(); d_F.release();
         d_lval32.release(); d_X32.release(); d_F32.release();
         d_xwork.release(); d_ywork.release(); d_xoff.release();
@@ -415,9 +467,8 @@ struct sc_plan_s {
     }
     DevTables tables() const {
         DevTables t;
-        t.subs = d_subs.p; t.tiles = d_tiles.p; t.blocks = d_blocks.p; t.rows = d_rows.p; t.visit = d_visit.p;
+        t.subs = d_subs.p; t.tiles = d_tiles.p; t.blocks = d_blocks.p; t.rows = d_rows.p; t.visits = d_visits.p;
         t.ksteps = d_ksteps.p;
-        t.vrows = d_vrows.p;
         t.lval = d_lval.p; t.piv = d_piv.p; t.pi = d_pi.p; t.sgn = d_sgn.p; t.syrk = d_syrk.p;
         t.X = d_X.p; t.F = d_F.p;
         t.lval32 = d_lval32.p; t.X32 = d_X32.p; t.F32 = d_F32.p;
@@ -426,6 +477,7 @@ struct sc_plan_s {
         t.part = d_part.p;
         t.tile_order = d_tile_order.p;
         t.trsm_merge = trsm_merge;
+        t.trsm_large = trsm_large;
         t.ntiles = (int64_t)h_tile_order.size();
         t.nsyrk = (int64_t)h_syrk.size();
         t.nsyrk_tile = nsyrk_tile;
@@ -545,6 +597,7 @@ sc_status_t sc_plan_create(const sc_subdomain_desc_t* sd, int32_t nsub, const sc
     std::vector<std::vector<SyrkItem>> sub_tiles(nsub), sub_blocks(nsub);
     std::vector<int64_t> x_elems(nsub, 0);      // X slab elements of each subdomain
     int64_t blk = 0, rows = 0, lv = 0, colo = 0, xo = 0, fo = 0, dual = 0;
+    std::vector<std::vector<int32_t>> pairs(nsub);   // merge_pairs flags per block
     int64_t upd_rows = 0, merged_rows = 0;      // TRSM pruned-row updates, and those the merged pairs save
     P->implicit_sub.assign(nsub, 0);
     P->pred.resize(nsub);
@@ -573,12 +626,12 @@ sc_status_t sc_plan_create(const sc_subdomain_desc_t* sd, int32_t nsub, const sc
         {
             // merged pairs of the TRSM's updates below (unless disabled), and
             // the pruned-row updates of the tiles' visits they save
-            const std::vector<int32_t> pair =
-                P->opt.disable_pair_merge ? std::vector<int32_t>(sp.blocks.size(), 0) : merge_pairs(sp);
+            std::vector<int32_t>& pair = pairs[i];
+            pair = P->opt.disable_pair_merge ? std::vector<int32_t>(sp.blocks.size(), 0) : merge_pairs(sp);
             for (size_t k = 0; k < sp.blocks.size(); ++k) {
                 const BlockDesc& b = sp.blocks[k];
                 P->h_blocks.push_back(
-                    BlockDev{b.row0, b.w, b.nbelow, pair[k], b.lval_off, b.rows_off, b.aoff, b.linv_off});
+                    BlockDev{b.row0, b.w, b.nbelow, 0, b.lval_off, b.rows_off, b.aoff, b.linv_off});
             }
             if (!impl)
                 for (int32_t t = 0; t + 1 < (int32_t)sp.visit_ptr.size(); ++t)
@@ -598,16 +651,8 @@ sc_status_t sc_plan_create(const sc_subdomain_desc_t* sd, int32_t nsub, const sc
             T.x_off = xo;
             xo += (int64_t)(sp.n - T.kstart) * kTile;
             x_elems[i] += (int64_t)(sp.n - T.kstart) * kTile;
-            for (int w = 0; w < 4; ++w) {
-                const int c = t * kTile + w * kStripe;
-                if (w * kStripe >= T.ncols) T.start_block[w] = s.nblocks;
-                else T.start_block[w] = po.staircase ? sp.block_of_row[sp.piv[c]] : 0;
-            }
-            T.visit_off = (int64_t)P->h_visit.size();
+            if ((int64_t)(sp.n - T.kstart) * kTile * (P->mixed ? 4 : 8) >= kTrsmSlabBytes) P->trsm_large = true;
             T.nvisit = (int32_t)(sp.visit_ptr[t + 1] - sp.visit_ptr[t]);
-            P->h_visit.insert(P->h_visit.end(), sp.visit.begin() + sp.visit_ptr[t], sp.visit.begin() + sp.visit_ptr[t + 1]);
-            P->h_vrows.insert(P->h_vrows.end(), sp.visit_rows.begin() + sp.visit_ptr[t],
-                              sp.visit_rows.begin() + sp.visit_ptr[t + 1]);
             P->h_tiles.push_back(T);
         }
         const int32_t nst = (sp.m + kSyrkTile - 1) / kSyrkTile;
@@ -844,6 +889,13 @@ sc_status_t sc_plan_create(const sc_subdomain_desc_t* sd, int32_t nsub, const sc
     }
     P->nval_total = lv;
     P->trsm_merge = merged_rows > 0 && (double)merged_rows >= kMergeMinShare * (double)upd_rows;
+    for (int32_t i = 0; i < nsub; ++i)
+        for (int32_t t = 0; t < P->h_subs[i].ntiles; ++t) {
+            TileDev& T = P->h_tiles[P->h_subs[i].tile_off + t];
+            T.visit_off = (int64_t)P->h_visits.size();
+            append_visits(P->plans[i], t, T.kstart, po.staircase != 0, P->trsm_merge ? &pairs[i] : nullptr,
+                          P->mixed ? kPruneTiles<float> : kPruneTiles<double>, P->h_visits);
+        }
     rows += 64;                            // the TRSM reads whole 64-entry groups of a row list
     P->nrows_total = rows;
     P->ncol_total = colo;
@@ -893,9 +945,8 @@ sc_status_t sc_plan_create(const sc_subdomain_desc_t* sd, int32_t nsub, const sc
     ALLOC(p->d_tile_order_g, p->h_tile_order_g.size());
     ALLOC(p->d_syrk_g, p->h_syrk_g.size());
     ALLOC(p->d_rows, (size_t)rows);
-    ALLOC(p->d_visit, std::max<size_t>(1, p->h_visit.size()));
+    ALLOC(p->d_visits, std::max<size_t>(1, p->h_visits.size()));
     ALLOC(p->d_ksteps, std::max<size_t>(1, p->h_ksteps.size()));
-    ALLOC(p->d_vrows, std::max<size_t>(1, p->h_vrows.size()));
     ALLOC(p->d_piv, (size_t)colo);
     ALLOC(p->d_pi, (size_t)colo);
     ALLOC(p->d_sgn, (size_t)colo);
@@ -941,9 +992,8 @@ sc_status_t sc_plan_create(const sc_subdomain_desc_t* sd, int32_t nsub, const sc
     if (e == hipSuccess) e = up(p->d_syrk_g.p, p->h_syrk_g.data(), p->h_syrk_g.size() * sizeof(SyrkItem));
     if (e == hipSuccess && p->overlapped()) e = p->prepare_overlap();
     if (e == hipSuccess) e = up(p->d_rows.p, h_rows.data(), h_rows.size() * 4);
-    if (e == hipSuccess) e = up(p->d_visit.p, p->h_visit.data(), p->h_visit.size() * 4);
+    if (e == hipSuccess) e = up(p->d_visits.p, p->h_visits.data(), p->h_visits.size() * sizeof(VisitDev));
     if (e == hipSuccess) e = up(p->d_ksteps.p, p->h_ksteps.data(), p->h_ksteps.size() * 4);
-    if (e == hipSuccess) e = up(p->d_vrows.p, p->h_vrows.data(), p->h_vrows.size() * 8);
     // F is cleared once: the SYRK never writes its structurally zero blocks
     // nor the columns past m of the last tiles
     if (e == hipSuccess && fo > 0)
