@@ -122,6 +122,10 @@ hipError_t launch_apply_implicit(const DevTables& t, const ImplicitLevels& lv, c
 // passes over the packed sorted F; optional events ev[0] before, ev[1] after.
 hipError_t launch_apply(const DevTables& t, const double* p, double* q, hipStream_t stream, hipEvent_t* ev);
 
+// F of subdomain `sub` (m multipliers, assembled) as a dense FP64 matrix in
+// multiplier order, column-major with leading dimension ld >= m.
+hipError_t launch_expand_F(const DevTables& t, int32_t sub, int32_t m, double* out, int64_t ld, hipStream_t stream);
+
 // Allocation-free explicit apply.  Its partial sums live in a fixed device
 // array of kApplyScratchTiles stored tiles (256 doubles each: 32 MiB), one per
 // GPU for the life of the process.

@@ -1569,6 +1569,11 @@ sc_status_t sc_get_F(sc_plan_t P, int32_t sub, double* out, int32_t ld, int32_t 
     HIP_TRY(hipSetDevice(P->device));
     hipStream_t st = (hipStream_t)stream;
     // packed lower tiles in sorted column order -> dense, original order
+    if (on_device) {
+        HIP_TRY(launch_expand_F(P->tables(), sub, s.m, out, ld, st));
+        HIP_TRY(hipStreamSynchronize(st));
+        return SC_OK;
+    }
     const int64_t m = s.m;
     const int64_t nt = (m + kSyrkTile - 1) / kSyrkTile;
     const size_t cnt = (size_t)(nt * (nt + 1) / 2) * kFTileElems;
@@ -1592,13 +1597,7 @@ sc_status_t sc_get_F(sc_plan_t P, int32_t sub, double* out, int32_t ld, int32_t 
             dense[(size_t)pi[b] * m + pi[a]] =
                 tiles[(size_t)(I * (I + 1) / 2 + J) * kFTileElems + (hi % kSyrkTile) * kSyrkTile + lo % kSyrkTile];
         }
-    if (on_device) {
-        HIP_TRY(hipMemcpy2DAsync(out, (size_t)ld * sizeof(double), dense.data(), (size_t)m * sizeof(double),
-                                 (size_t)m * sizeof(double), (size_t)m, hipMemcpyHostToDevice, st));
-        HIP_TRY(hipStreamSynchronize(st));
-    } else {
-        for (int64_t c = 0; c < m; ++c) std::copy(dense.begin() + c * m, dense.begin() + (c + 1) * m, out + c * ld);
-    }
+    for (int64_t c = 0; c < m; ++c) std::copy(dense.begin() + c * m, dense.begin() + (c + 1) * m, out + c * ld);
     return SC_OK;
 }
 

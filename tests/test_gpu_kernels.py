@@ -1,0 +1,44 @@
+"""Kernels at the sizes where their tiling can go wrong, on the GPU."""
+import numpy as np
+import pytest
+
+import oracle
+import scgen
+from scgen.rng import signs_from_seed
+
+P = pytest.importorskip("paper_2509_21037_amd")
+pytestmark = pytest.mark.gpu
+
+
+def _plan(subs, **kw):
+    import torch
+    assert torch.cuda.is_available()
+    torch.cuda.init()
+    plan = P.Plan(subs, **kw)
+    plan.factor()
+    plan.assemble()
+    return plan
+
+
+def _columns(s, m, seed):
+    """s with m multipliers on random DOFs, some of them repeated, in no order."""
+    dof = np.random.default_rng(seed).choice(s.n, size=m, replace=True).astype(np.int32)
+    return s.with_columns(dof, signs_from_seed(seed, m))
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+def test_dense_F_on_device_at_tile_edges(precision):
+    """sc_get_F on the device at the edges of its 64-row quadrants and of the
+    stored 128 x 128 tiles, columns in random order: the host copy's values
+    bit for bit, nothing else written."""
+    import torch
+    box = scgen.box_subdomain("heat", (20, 14), 1.0 / 20, seed=3)
+    subs = [_columns(box, m, 40 + m) for m in (1, 63, 64, 65, 127, 128, 129, 193, 260)]
+    plan = _plan(subs, precision=precision)
+    for i, s in enumerate(subs):
+        ld = s.m + i % 3
+        out = torch.full((ld * s.m + 5,), -3.0, dtype=torch.float64, device="cuda")
+        F = plan.get_F_device(i, out=out, ld=ld)
+        assert np.array_equal(F.cpu().numpy(), plan.get_F(i)), s.m
+        assert bool((out[:ld * s.m].view(s.m, ld)[:, s.m:] == -3.0).all()) and bool((out[ld * s.m:] == -3.0).all())
+    plan.destroy()
