@@ -38,13 +38,16 @@ struct TileDev {
     int32_t sub, tile, kstart, ncols;
     int64_t x_off;
     int64_t visit_off;        // blocks the tile visits: visits[visit_off .. + nvisit),
-    int32_t nvisit, pad;      // increasing
+    int64_t fresh_off;        // increasing; their VisitDev::fresh masks from here on
+    int64_t clear_off;        // rows cleared before the sweep: clear[clear_off .. + nclear)
+    int32_t nvisit, nclear;
 };
 
 // One factor block a TRSM tile visits, as the kernel walks it (offsets
 // relative to the subdomain's factor values and row array).
 struct VisitDev {
     uint64_t on;              // bit i: row row0 + i is in the slab and on the tile's paths
+    uint64_t held;            // ... and was written before this visit (pivots, earlier updates)
     int64_t linv_off;         // inverse of the diagonal block
     int64_t aoff;             // pruned rows as MFMA A tiles
     int64_t pair_aoff;        // second block of a pair: the first block's A tiles of the same rows
@@ -52,6 +55,8 @@ struct VisitDev {
     int32_t row0, w;
     int32_t urows;            // rows the visit's update covers
     int32_t pair_nks;         // k-slices of those A tiles
+    int32_t fresh;            // masks of the update's chunks at TileDev::fresh_off + fresh: bit i =
+                              // row i of the chunk was never written before
     int32_t flags;            // bits 0-1: role in a merged pair (0 alone, 1 first block: updates only
                               // the next block's rows, 2 second block: also applies the first's
                               // update); kVisitNextEarly; kVisitActShift + v: stripe v has started

@@ -26,13 +26,6 @@ __device__ __forceinline__ v4d mfma_f64(double a, double b, v4d c) {
     return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
 }
 
-// Orders this wavefront's LDS and global accesses across lanes.
-__device__ __forceinline__ void wave_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 typedef float v4f __attribute__((ext_vector_type(4)));
 
 // v_mfma_f32_16x16x4f32 takes A and B in the same lane layout as the FP64
@@ -57,27 +50,31 @@ __device__ __forceinline__ v4f mfma_f32(float a, float b, v4f c) {
 //      X[R_b] -= L[R_b, b] X[b] (MFMA, rows gathered and scattered).
 // The factor flows through the workgroup as a stream of chunks (the inverse
 // of a diagonal block, up to 20 KB, or 16 KB of pruned-row tiles), one per
-// step.  At the start of a step the next chunk, whose loads have had the
-// whole last step to arrive, goes from registers to the other half of a
-// double buffer in LDS, and the loads of the chunk after it are issued into
-// the same registers; one barrier per chunk, on LDS only (X columns of a
-// stripe are private to its wavefront, so no barrier waits on global
-// memory).  Rows of the next chunk of the same block are gathered before the
+// step.  The loads of the next chunk are issued at the start of a step and go
+// from registers to the other half of a double buffer in LDS at its end; one
+// barrier per chunk, on LDS only (X columns of a stripe are private to its
+// wavefront, so no barrier waits on global memory).  Rows of the next chunk of the same block are gathered before the
 // current chunk's MFMAs (the chunks of one block update disjoint rows), and
 // the rows of the next block before those of the last chunk where it does
 // not update them (VisitDev); a wavefront reads rows it wrote itself in
 // program order.
-// What bounds it is the latency of the X rows, so no load or store waits for
-// another: global memory operations complete in issue order, and the wait
-// for one of them can leave younger ones in flight only where the compiler
-// knows how many there are.  Rows that are not there (past a row list, off
-// the paths) are therefore out-of-range offsets of a buffer resource (read
-// as zero, not written) instead of branches, and no register holding a load
-// in flight is copied.  Before (branches, and a two-chunk prefetch whose
+// What bounds it is the traffic and the latency of the X rows.  Traffic: a
+// row is read only if the tile wrote it before (VisitDev::held and the fresh
+// masks; it counts as zero until then), so X is not cleared and a first
+// update only writes.  Latency: no load or store waits for another: global
+// memory operations complete in issue order, and the wait for one of them can
+// leave younger ones in flight only where the compiler knows how many there
+// are.  Rows that are not there (past a row list, off the paths, not written
+// yet) are therefore out-of-range offsets of a buffer resource (read as zero,
+// not written) instead of branches, a load is waited for in the code path
+// that issued it, and no register holding a load in flight is copied (the
+// last chunk of a block, which loads the next block's rows, is a step of its
+// own).  Before (branches, a cleared X, and a two-chunk prefetch whose
 // register rotation waited for every operation in flight at each step) / now:
-// 16 x 20^3 elasticity 23.3 / 19.8 ms FP64 (now 98 GB of memory traffic at 4.95
-// TB/s, the rate of a copy), 17.1 / 10.3 ms mixed; 512 x 12^3 heat 3.33 / 3.08
-// and 2.94 / 1.92 ms; 128 2D triangle meshes of 129^2 nodes 1.11 / 1.02 ms.
+// 16 x 20^3 elasticity 23.3 / 18.4 ms FP64, 17.1 / 9.6 ms mixed; 64 uneven
+// elasticity boxes 4.61 / 3.36 ms; 512 x 12^3 heat 3.33 / 2.64 and 2.94 / 1.57
+// ms; 128 2D triangle meshes of 129^2 nodes 1.11 / 0.86 ms (3 workgroups per
+// CU without merged pairs; 0.93 with 2).
 // Mixed precision: the same with FP32 X and FP32 A tiles / MFMA for step 2;
 // step 1 stays FP64 (the block rows are widened, solved, rounded back).  The
 // FP32 A tiles are read with their rows permuted (4a + b -> 4b + a), which
@@ -98,7 +95,8 @@ __device__ __forceinline__ v4f mfma_f32(float a, float b, v4f c) {
 // a chunk: the 40 lower tiles of a 64 x 64 diagonal inverse (20 KB), or 16 KB
 // of pruned-row tiles
 constexpr int kChunkBytes = 40 * 64 * 8;
-constexpr int kIdxBytes = 64 * 4;                // row indices carried by a chunk (up to 64)
+constexpr int kRowsBytes = 64 * 4;               // row indices carried by a chunk (up to 64)
+constexpr int kIdxBytes = kRowsBytes + 16;       // ... and the mask of those never written before
 constexpr int kBufBytes = kChunkBytes + kIdxBytes;
 constexpr int kTrsmSmem = 2 * kBufBytes;
 
@@ -131,6 +129,8 @@ struct SlabRows {
     __device__ __forceinline__ static int at(int row, int col) {
         return LARGE ? row * kTile + col : (int)((uint32_t)(row * kTile + col) * (uint32_t)sizeof(TX));
     }
+    // or-ed to an offset: kNone where c holds
+    __device__ __forceinline__ static int none_if(bool c) { return c ? kNone : 0; }
     __device__ __forceinline__ TX load(int off) const {
         if constexpr (LARGE) return off >= 0 ? p[off] : TX(0);
         else if constexpr (sizeof(TX) == 8) return __builtin_bit_cast(TX, __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0));
@@ -188,8 +188,9 @@ __device__ __forceinline__ void mma_group(const TX* __restrict__ sA, int nks, co
 template <bool MIXED, bool MERGE, bool LARGE>
 __device__ __forceinline__ void trsm_tile(
     const SubDev* __restrict__ subs, const TileDev* __restrict__ tiles, const int32_t* __restrict__ rows,
-    const VisitDev* __restrict__ visits, const double* __restrict__ lval, const float* __restrict__ lval32,
-    const int32_t* __restrict__ piv, const int8_t* __restrict__ sgn,
+    const VisitDev* __restrict__ visits, const uint64_t* __restrict__ fresh, const int32_t* __restrict__ clear,
+    const double* __restrict__ lval,
+    const float* __restrict__ lval32, const int32_t* __restrict__ piv, const int8_t* __restrict__ sgn,
     typename std::conditional<MIXED, float, double>::type* __restrict__ X, int ti, char* __restrict__ smem)
 {
     using TX = typename std::conditional<MIXED, float, double>::type;
@@ -217,23 +218,14 @@ __device__ __forceinline__ void trsm_tile(
     // elimination-tree paths of its pivots (all other rows of X are zero)
     const int nv = T.nvisit;
     const VisitDev* __restrict__ V = visits + T.visit_off;
+    const uint64_t* __restrict__ FR = fresh + T.fresh_off;
 
     // right-hand side P B^T: sign at the pivot row, zero elsewhere.  Only the
-    // 16-row steps of visited blocks that hold a row on the paths are cleared:
-    // the other rows are off every path, the sweep writes them at most with
-    // exact-zero updates of whatever they held, the diagonal step neither
-    // reads nor writes them, and the SYRK reads only the steps of a slab that
-    // hold a row on its paths
-    for (int k = 0; k < nv; ++k) {
-        const int r0 = V[k].row0;
-        const int r1 = r0 + V[k].w;
-        const uint64_t on = V[k].on;
-        for (int q = 0; q < 4; ++q) {
-            if (((on >> (16 * q)) & 0xFFFFull) == 0) continue;
-            const int qe = min(r0 + 16 * (q + 1), r1);
-            for (int r = max(r0 + 16 * q, kstart) + g; r < qe; r += 4) Xs[(int64_t)(r - kstart) * kTile + col] = TX(0);
-        }
-    }
+    // pivot rows are set in memory, and the rows off the paths that the SYRK
+    // reads (in its 16-row steps with a row on them) cleared: every other row
+    // counts as zero until the sweep first writes it
+    const int32_t* __restrict__ CL = clear + T.clear_off;
+    for (int i = g; i < T.nclear; i += 4) Xs[(int64_t)(CL[i] - kstart) * kTile + col] = TX(0);
     __threadfence_block();
     if (g == 0 && col < T.ncols) Xs[(int64_t)(piv[cbase + col] - kstart) * kTile + col] = (TX)sgn[cbase + col];
     if (nv <= 0) return;
@@ -245,15 +237,17 @@ __device__ __forceinline__ void trsm_tile(
     // of the diagonal block (its lower tiles), the rest groups of PT pruned
     // row tiles; the second block of a pair alternates the first block's A
     // tiles of a row group with its own.  The diagonal chunk carries the row
-    // indices of the first row group, the (second) chunk of row group q those
-    // of group q + 1: they are gathered while the chunk is in use.
+    // indices (and the mask of those never written before) of the first row
+    // group, the (second) chunk of row group q those of group q + 1: they are
+    // gathered while the chunk is in use.
     int pk = 0, pc = 0;
     VisitDev p = V[0];
-    v4u c0, c1, c2, c3, c4, ci;                  // the chunk after the one(s) in LDS
+    v4u c0, c1, c2, c3, c4, ci;                  // the chunk after the one in LDS
     auto load_chunk = [&]() {
         const char* src = reinterpret_cast<const char*>(L);
         const int32_t* ip = R;
-        uint32_t bytes = 0, ibytes = 0;
+        const uint64_t* fp = FR;
+        uint32_t bytes = 0;
         if (pk < nv) {
             const int prole = MERGE ? p.flags & 3 : 0;
             const int nks = (p.w + 3) >> 2;
@@ -264,7 +258,7 @@ __device__ __forceinline__ void trsm_tile(
                 src = reinterpret_cast<const char*>(L + p.linv_off);
                 bytes = (2 * (nrt_d - 1) * nrt_d + nks) * 64 * 8;
                 ip = R + p.rows_off;
-                ibytes = np > 0 ? kIdxBytes : 0;
+                fp = FR + p.fresh;
             } else {
                 const int q = prole == 2 ? (pc - 1) >> 1 : pc - 1;
                 const int nt = min(PT, nrt - PT * q);
@@ -272,8 +266,8 @@ __device__ __forceinline__ void trsm_tile(
                 const int ks = first ? p.pair_nks : nks;
                 src = reinterpret_cast<const char*>(LA + (first ? p.pair_aoff : p.aoff) + (int64_t)PT * q * ks * 64);
                 bytes = nt * ks * 64 * (int)sizeof(TX);
-                ip = R + p.rows_off + 16 * PT * (q + 1);
-                ibytes = !first && q + 1 < np ? kIdxBytes : 0;
+                ip = R + p.rows_off + 16 * PT * min(q + 1, np - 1);
+                fp = FR + p.fresh + min(q + 1, np - 1);
             }
             if (++pc > (prole == 2 ? 2 * np : np)) {
                 ++pk;
@@ -281,14 +275,15 @@ __device__ __forceinline__ void trsm_tile(
                 if (pk < nv) p = V[pk];
             }
         }
-        const __amdgpu_buffer_rsrc_t rc = buffer_of(src, bytes), ri = buffer_of(ip, ibytes);
+        const __amdgpu_buffer_rsrc_t rc = buffer_of(src, bytes);
         const int e = threadIdx.x * 16;
         c0 = __builtin_amdgcn_raw_buffer_load_b128(rc, e, 0, 0);
         c1 = __builtin_amdgcn_raw_buffer_load_b128(rc, e, 4096, 0);
         c2 = __builtin_amdgcn_raw_buffer_load_b128(rc, e, 8192, 0);
         c3 = __builtin_amdgcn_raw_buffer_load_b128(rc, e, 12288, 0);
         c4 = __builtin_amdgcn_raw_buffer_load_b128(rc, e, 16384, 0);
-        ci = __builtin_amdgcn_raw_buffer_load_b128(ri, e & 255, 0, 0);
+        ci = *reinterpret_cast<const v4u*>(lane < kRowsBytes / 16 ? reinterpret_cast<const char*>(ip) + 16 * lane
+                                                                   : reinterpret_cast<const char*>(fp));
     };
     auto put_chunk = [&](char* dst) {
         const int e = threadIdx.x * 16;
@@ -297,25 +292,22 @@ __device__ __forceinline__ void trsm_tile(
         *reinterpret_cast<v4u*>(dst + e + 8192) = c2;
         *reinterpret_cast<v4u*>(dst + e + 12288) = c3;
         *reinterpret_cast<v4u*>(dst + e + 16384) = c4;
-        if (threadIdx.x < kIdxBytes / 16) *reinterpret_cast<v4u*>(dst + kChunkBytes + e) = ci;
+        if (threadIdx.x <= kRowsBytes / 16) *reinterpret_cast<v4u*>(dst + kChunkBytes + e) = ci;
     };
     int buf = 0;
-    auto step_begin = [&]() {
-        put_chunk(smem + (buf ^ 1) * kBufBytes);
-        load_chunk();
-    };
+    auto step_begin = [&]() { load_chunk(); };
     auto step_end = [&]() {
+        put_chunk(smem + (buf ^ 1) * kBufBytes);
         lds_barrier();
         buf ^= 1;
     };
     load_chunk();
     put_chunk(smem);
-    load_chunk();
     lds_barrier();
 
     TX xin[4][4];                                // X rows of the next block, accumulator layout
-    auto load_block = [&](const VisitDev& v, uint64_t on, bool act) {
-        const uint64_t onl = act ? on >> g : 0;
+    auto load_block = [&](const VisitDev& v, uint64_t held, bool act) {
+        const uint64_t onl = act ? held >> g : 0;
         const int b0 = Rows::at(v.row0 + g - kstart, col);
 #pragma unroll
         for (int t = 0; t < 4; ++t)
@@ -325,11 +317,11 @@ __device__ __forceinline__ void trsm_tile(
     };
 
     VisitDev v = V[0];
-    load_block(v, v.on, (v.flags >> (kVisitActShift + wv)) & 1);
+    load_block(v, v.held, (v.flags >> (kVisitActShift + wv)) & 1);
     int pair_nks = 0;
     for (int k = 0; k < nv; ++k) {
         const VisitDev nx = V[min(k + 1, nv - 1)];
-        const uint64_t nx_on = k + 1 < nv ? nx.on : 0;
+        const uint64_t nx_held = k + 1 < nv ? nx.held : 0;
         const bool nx_act = (nx.flags >> (kVisitActShift + wv)) & 1;
         const bool act = (v.flags >> (kVisitActShift + wv)) & 1;
         const int role = MERGE ? v.flags & 3 : 0;
@@ -344,21 +336,39 @@ __device__ __forceinline__ void trsm_tile(
         const bool gact = role == 1 ? nx_act : act;
 
         VX accn[PT];                             // rows of the next pruned chunk
-        int offn[PT][4];
-        auto gather = [&](int q) {               // row indices from the chunk in LDS
+        int offn[PT][4];                         // where they are written
+        auto gather = [&](int q) {               // row indices and mask from the chunk in LDS
             const int32_t* __restrict__ sidx = reinterpret_cast<const int32_t*>(smem + buf * kBufBytes + kChunkBytes);
-            const int left = gact ? urows - 16 * PT * q : 0;
+            const int left = urows - 16 * PT * q;
+            // rows never written before are zero: not read
+            uint64_t fr = *reinterpret_cast<const uint64_t*>(sidx + kRowsBytes / 4) >> g;
+            int offl[PT][4];
 #pragma unroll
             for (int u = 0; u < PT; ++u)
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int i = 16 * u + 4 * r + g;
-                    offn[u][r] = i < left ? Rows::at(sidx[i] - kstart, col) : Rows::kNone;
-                }
+                for (int r = 0; r < 4; ++r) offn[u][r] = Rows::at(sidx[16 * u + 4 * r + g] - kstart, col);
+            if (left < 16 * PT) {
+#pragma unroll
+                for (int u = 0; u < PT; ++u)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) offn[u][r] |= Rows::none_if(16 * u + 4 * r + g >= left);
+            }
+            if (!gact) fr = ~0ull;
 #pragma unroll
             for (int u = 0; u < PT; ++u)
 #pragma unroll
-                for (int r = 0; r < 4; ++r) accn[u][r] = xr_.load(offn[u][r]);
+                for (int r = 0; r < 4; ++r) offl[u][r] = offn[u][r] | Rows::none_if((fr >> (16 * u + 4 * r)) & 1);
+            if (!act) {                          // a stripe not started writes its zeros once
+                fr = *reinterpret_cast<const uint64_t*>(sidx + kRowsBytes / 4) >> g;
+#pragma unroll
+                for (int u = 0; u < PT; ++u)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) offn[u][r] |= Rows::none_if(!((fr >> (16 * u + 4 * r)) & 1));
+            }
+#pragma unroll
+            for (int u = 0; u < PT; ++u)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) accn[u][r] = xr_.load(offl[u][r]);
         };
 
         // ---- 1. X[b] <- L_bb^{-1} X[b]
@@ -384,8 +394,9 @@ __device__ __forceinline__ void trsm_tile(
                         for (int s = 0; s < 4; ++s)
                             tmp[u] = mfma_f64(sA[(2 * u * (u + 1) + 4 * t + s) * 64], xr[t][s], tmp[u]);
                 }
+                __builtin_amdgcn_sched_barrier(0);
             }
-            const uint64_t onl = act ? v.on >> g : 0;
+            const uint64_t onl = (act ? v.on : v.on & ~v.held) >> g;
             const int b0 = Rows::at(v.row0 + g - kstart, col);
 #pragma unroll
             for (int t = 0; t < 4; ++t)
@@ -418,7 +429,7 @@ __device__ __forceinline__ void trsm_tile(
         };
         if (MERGE && role == 1) {
             // the rows of the next block: kept in registers, zero off the paths
-            const uint64_t onl = nx_on >> g;
+            const uint64_t onl = nx.on >> g;
 #pragma unroll
             for (int t = 0; t < 4; ++t)
 #pragma unroll
@@ -440,43 +451,75 @@ __device__ __forceinline__ void trsm_tile(
                     step_end();
                 }
             pair_nks = nks;
-        } else {
+        } else if (np > 0) {
             int off[PT][4];
-            for (int q = 0; q < np; ++q) {
-                const int nt = min(PT, nrt - PT * q);
-                if (MERGE && role == 2) {
-                    step_begin();
+            auto take_rows = [&]() {
 #pragma unroll
-                    for (int u = 0; u < PT; ++u) {
-                        acc[u] = accn[u];
+                for (int u = 0; u < PT; ++u) {
+                    acc[u] = accn[u];
 #pragma unroll
-                        for (int r = 0; r < 4; ++r) off[u][r] = offn[u][r];
-                    }
-                    __builtin_amdgcn_sched_barrier(0);
-                    update(pair_nks, kept, nt);
-                    step_end();
+                    for (int r = 0; r < 4; ++r) off[u][r] = offn[u][r];
                 }
-                step_begin();
-                if (role != 2) {
-#pragma unroll
-                    for (int u = 0; u < PT; ++u) {
-                        acc[u] = accn[u];
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) off[u][r] = offn[u][r];
-                    }
-                }
-                if (q + 1 < np) gather(q + 1);
-                else if (early) load_block(nx, nx_on, nx_act);
-                __builtin_amdgcn_sched_barrier(0);
-                update(nks, own, nt);
+            };
+            auto scatter = [&]() {
 #pragma unroll
                 for (int u = 0; u < PT; ++u)
 #pragma unroll
                     for (int r = 0; r < 4; ++r) xr_.store(off[u][r], acc[u][r]);
-                if (q + 1 == np && !early) load_block(nx, nx_on, nx_act);
+            };
+            // the last chunk: the rows of the next block are loaded with it,
+            // before its products unless it updates them
+            auto last = [&]() {
+                if (early) {
+                    load_block(nx, nx_held, nx_act);
+                    __builtin_amdgcn_sched_barrier(0);
+                    update(nks, own, nrt - PT * (np - 1));
+                    scatter();
+                } else {
+                    __builtin_amdgcn_sched_barrier(0);
+                    update(nks, own, nrt - PT * (np - 1));
+                    scatter();
+                    load_block(nx, nx_held, nx_act);
+                }
                 step_end();
+            };
+            if (MERGE && role == 2) {
+                for (int q = 0; q + 1 < np; ++q) {
+                    step_begin();
+                    take_rows();
+                    __builtin_amdgcn_sched_barrier(0);
+                    update(pair_nks, kept, PT);
+                    step_end();
+                    step_begin();
+                    gather(q + 1);
+                    __builtin_amdgcn_sched_barrier(0);
+                    update(nks, own, PT);
+                    scatter();
+                    step_end();
+                }
+                step_begin();
+                take_rows();
+                __builtin_amdgcn_sched_barrier(0);
+                update(pair_nks, kept, nrt - PT * (np - 1));
+                step_end();
+                step_begin();
+                last();
+            } else {
+                for (int q = 0; q + 1 < np; ++q) {
+                    step_begin();
+                    take_rows();
+                    gather(q + 1);
+                    __builtin_amdgcn_sched_barrier(0);
+                    update(nks, own, PT);
+                    scatter();
+                    step_end();
+                }
+                step_begin();
+                take_rows();
+                last();
             }
-            if (np == 0) load_block(nx, nx_on, nx_act);
+        } else {
+            load_block(nx, nx_held, nx_act);
         }
         v = nx;
     }
@@ -486,28 +529,30 @@ __device__ __forceinline__ void trsm_tile(
 // alone and the merged code paths compile away.  LARGE: some X slab holds
 // kTrsmSlabBytes or more.
 template <bool MERGE, bool LARGE>
-__global__ __launch_bounds__(256, 2) void trsm_stair_f64(
+__global__ __launch_bounds__(256, MERGE ? 2 : 3) void trsm_stair_f64(
     const SubDev* __restrict__ subs, const TileDev* __restrict__ tiles, const int32_t* __restrict__ rows,
-    const VisitDev* __restrict__ visits, const double* __restrict__ lval, const int32_t* __restrict__ piv,
-    const int8_t* __restrict__ sgn, const int32_t* __restrict__ order, double* __restrict__ X)
+    const VisitDev* __restrict__ visits, const uint64_t* __restrict__ fresh, const int32_t* __restrict__ clear,
+    const double* __restrict__ lval,
+    const int32_t* __restrict__ piv, const int8_t* __restrict__ sgn, const int32_t* __restrict__ order, double* __restrict__ X)
 {
     __shared__ __align__(16) char smem[kTrsmSmem + (MERGE ? kSlotBytes<double> : 0)];
     const int ti = order[blockIdx.x];
     if (ti < 0) return;
-    trsm_tile<false, MERGE, LARGE>(subs, tiles, rows, visits, lval, nullptr, piv, sgn, X, ti, smem);
+    trsm_tile<false, MERGE, LARGE>(subs, tiles, rows, visits, fresh, clear, lval, nullptr, piv, sgn, X, ti, smem);
 }
 
 template <bool MERGE, bool LARGE>
-__global__ __launch_bounds__(256, 2) void trsm_stair_mixed(
+__global__ __launch_bounds__(256, MERGE ? 2 : 3) void trsm_stair_mixed(
     const SubDev* __restrict__ subs, const TileDev* __restrict__ tiles, const int32_t* __restrict__ rows,
-    const VisitDev* __restrict__ visits, const double* __restrict__ lval, const float* __restrict__ lval32,
-    const int32_t* __restrict__ piv, const int8_t* __restrict__ sgn, const int32_t* __restrict__ order,
-    float* __restrict__ X)
+    const VisitDev* __restrict__ visits, const uint64_t* __restrict__ fresh, const int32_t* __restrict__ clear,
+    const double* __restrict__ lval,
+    const float* __restrict__ lval32, const int32_t* __restrict__ piv, const int8_t* __restrict__ sgn,
+    const int32_t* __restrict__ order, float* __restrict__ X)
 {
     __shared__ __align__(16) char smem[kTrsmSmem + (MERGE ? kSlotBytes<float> : 0)];
     const int ti = order[blockIdx.x];
     if (ti < 0) return;
-    trsm_tile<true, MERGE, LARGE>(subs, tiles, rows, visits, lval, lval32, piv, sgn, X, ti, smem);
+    trsm_tile<true, MERGE, LARGE>(subs, tiles, rows, visits, fresh, clear, lval, lval32, piv, sgn, X, ti, smem);
 }
 
 // ---------------------------------------------------------------------------
@@ -939,10 +984,10 @@ template <bool MERGE, bool LARGE>
 static void trsm_launch(const DevTables& t, const int32_t* order, int64_t count, hipStream_t stream) {
     if (t.X32)
         hipLaunchKernelGGL((trsm_stair_mixed<MERGE, LARGE>), dim3((unsigned)count), dim3(256), 0, stream, t.subs,
-                           t.tiles, t.rows, t.visits, t.lval, t.lval32, t.piv, t.sgn, order, t.X32);
+                           t.tiles, t.rows, t.visits, t.fresh, t.clear, t.lval, t.lval32, t.piv, t.sgn, order, t.X32);
     else
         hipLaunchKernelGGL((trsm_stair_f64<MERGE, LARGE>), dim3((unsigned)count), dim3(256), 0, stream, t.subs,
-                           t.tiles, t.rows, t.visits, t.lval, t.piv, t.sgn, order, t.X);
+                           t.tiles, t.rows, t.visits, t.fresh, t.clear, t.lval, t.piv, t.sgn, order, t.X);
 }
 
 hipError_t launch_trsm(const DevTables& t, const int32_t* order, int64_t count, hipStream_t stream) {

@@ -17,6 +17,8 @@ struct DevTables {
     const BlockDev* blocks = nullptr;
     const int32_t* rows = nullptr;
     const VisitDev* visits = nullptr;      // blocks visited per TRSM tile (TileDev::visit_off)
+    const uint64_t* fresh = nullptr;       // rows first written by an update (TileDev::fresh_off)
+    const int32_t* clear = nullptr;        // rows a TRSM tile clears (TileDev::clear_off)
     const int32_t* ksteps = nullptr;       // SYRK k-steps per item (SyrkItem::step_off)
     const double* lval = nullptr;
     const float* lval32 = nullptr;

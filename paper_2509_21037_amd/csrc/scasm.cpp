@@ -143,10 +143,12 @@ constexpr double kSelectExplGBps = 5800.0;
 constexpr double kSelectImplGBps = 3190.0;
 
 // Share of a batch's TRSM pruned-row updates the merged pairs must save for
-// the merge-capable TRSM kernel to be launched (the 12^3 heat batch saves 5%
-// and ran 2% slower with it, the uneven elasticity batch 4% faster, the 20^3
-// batch, 36% saved, 12% faster).
-constexpr double kMergeMinShare = 0.10;
+// the merge-capable TRSM kernel to be launched.  That kernel holds a slot of
+// solved rows in LDS (2 workgroups per CU instead of 3) and steps twice per
+// row group.  Measured, merged / separate: FP64 12^3 heat (22% saved) 2.64 /
+// 2.68 ms, uneven elasticity (30%) 3.36 / 3.77, 20^3 (43%) 18.4 / 23.5; mixed
+// heat 1.74 / 1.57 ms, uneven elasticity 1.96 / 2.06, 20^3 9.6 / 11.8.
+constexpr double kMergeMinShare = 0.10, kMergeMinShareMixed = 0.25;
 
 struct Prediction {
     double t_asm_ms = 0, t_expl_ms = 0, t_impl_ms = 0, n_star = 0;
@@ -167,55 +169,107 @@ Prediction predict(const SubPlan& sp, bool mixed, const sc_options_t& o) {
     return q;
 }
 
-// Visit records of tile t of a subdomain (VisitDev), in visit order: the
-// rows on the paths that the slab holds, the roles in merged pairs (`pair`:
-// merge_pairs flags, null = every visit alone), the stripes that have started
-// (a stripe's columns begin at the block of its first pivot) and whether the
-// last chunk of the update (`pt` row tiles) leaves the next block's rows alone.
-void append_visits(const SubPlan& sp, int32_t t, int32_t kstart, bool staircase, const std::vector<int32_t>* pair,
-                   int pt, std::vector<VisitDev>& out) {
-    const int64_t v0 = sp.visit_ptr[t], v1 = sp.visit_ptr[t + 1];
-    int32_t start[4];
-    for (int w = 0; w < 4; ++w) {
-        const int32_t c = t * kTile + w * kStripe;
-        start[w] = c >= sp.m ? (int32_t)sp.blocks.size() : staircase ? sp.block_of_row[sp.piv[c]] : 0;
-    }
-    int prev = 0;
-    for (int64_t k = v0; k < v1; ++k) {
-        const int32_t b = sp.visit[k];
-        const BlockDesc& d = sp.blocks[b];
-        const int32_t nextb = k + 1 < v1 ? sp.visit[k + 1] : -1;
-        VisitDev v{};
-        v.on = sp.visit_rows[k];
-        if (kstart > d.row0) v.on = kstart - d.row0 >= 64 ? 0 : v.on & (~0ull << (kstart - d.row0));
-        v.linv_off = d.linv_off;
-        v.aoff = d.aoff;
-        v.rows_off = d.rows_off;
-        v.row0 = d.row0;
-        v.w = d.w;
-        const int role = prev == 1 ? 2 : pair && (*pair)[b] && nextb == b + 1 ? 1 : 0;
-        v.urows = role == 1 ? sp.blocks[b + 1].w : d.nbelow;
-        if (role == 2) {
-            const BlockDesc& f = sp.blocks[b - 1];
-            v.pair_nks = (f.w + 3) / 4;
-            v.pair_aoff = f.aoff + (int64_t)(d.w / 16) * v.pair_nks * 64;
+// Visit records of one subdomain's tiles, tile after tile, in visit order
+// (VisitDev): the rows on the paths that the slab holds (of tile t from
+// kstart[t] on), the roles in merged pairs (`pair`: merge_pairs flags, null =
+// every visit alone), the stripes that have started (a stripe's columns begin
+// at the block of its first pivot), whether the last chunk of the update (`pt`
+// row tiles) leaves the next block's rows alone, and which rows the sweep
+// meets for the first time: it reads only rows written before.
+struct TileVisits {
+    std::vector<VisitDev> visits;
+    std::vector<uint64_t> fresh;
+    std::vector<int32_t> clear;                      // rows set or cleared before the sweep
+    std::vector<int64_t> fresh_ptr, clear_ptr;       // each tile's first mask and row
+};
+
+void build_visits(const SubPlan& sp, bool staircase, const std::vector<int32_t>* pair, int pt, TileVisits& out) {
+    const int32_t ntiles = (sp.m + kTile - 1) / kTile;
+    std::vector<int32_t> written(sp.n, -1), on_path(sp.n, -1);   // last tile that wrote the row, with it on its paths
+    for (int32_t t = 0; t < ntiles; ++t) {
+        const int64_t v0 = sp.visit_ptr[t], v1 = sp.visit_ptr[t + 1];
+        const int32_t c1 = std::min(sp.m, (t + 1) * kTile);
+        const int32_t kstart = staircase ? sp.piv[(size_t)t * kTile] : 0;
+        const size_t first = out.visits.size();
+        out.fresh_ptr.push_back((int64_t)out.fresh.size());
+        out.clear_ptr.push_back((int64_t)out.clear.size());
+        auto clear_row = [&](int32_t r) {
+            if (written[r] == t) return;
+            written[r] = t;
+            out.clear.push_back(r);
+        };
+        for (int32_t c = t * kTile; c < c1; ++c) clear_row(sp.piv[c]);
+        for (int64_t k = v0; k < v1; ++k) {
+            const BlockDesc& d = sp.blocks[sp.visit[k]];
+            VisitDev v{};
+            v.on = sp.visit_rows[k];
+            if (kstart > d.row0) v.on = kstart - d.row0 >= 64 ? 0 : v.on & (~0ull << (kstart - d.row0));
+            for (int32_t i = 0; i < d.w; ++i)
+                if ((v.on >> i) & 1) on_path[d.row0 + i] = t;
+            out.visits.push_back(v);
         }
-        v.flags = role;
-        for (int w = 0; w < 4; ++w)
-            if (b >= start[w]) v.flags |= 1 << (kVisitActShift + w);
-        if (nextb >= 0 && v.urows > 0) {
-            const int32_t r0 = sp.blocks[nextb].row0, r1 = r0 + sp.blocks[nextb].w;
-            const int32_t last = (v.urows - 1) / (16 * pt) * (16 * pt);
-            bool clear = true;
-            for (int32_t q = last; q < v.urows; ++q) {
-                const int32_t r = sp.brows[d.rows_off + q];
-                clear = clear && (r < r0 || r >= r1);
+        // rows off the paths, in this or another block, in a step read as a whole
+        for (int32_t q = 0; q < sp.mask_words; ++q)
+            for (uint64_t m = sp.step_mask[(size_t)t * sp.mask_words + q]; m; m &= m - 1) {
+                const int32_t r0 = 16 * (64 * q + __builtin_ctzll(m));
+                for (int32_t r = std::max(r0, kstart); r < std::min(r0 + 16, sp.n); ++r)
+                    if (on_path[r] != t) clear_row(r);
             }
-            if (clear) v.flags |= kVisitNextEarly;
+        int32_t start[4];
+        for (int w = 0; w < 4; ++w) {
+            const int32_t c = t * kTile + w * kStripe;
+            start[w] = c >= sp.m ? (int32_t)sp.blocks.size() : staircase ? sp.block_of_row[sp.piv[c]] : 0;
         }
-        out.push_back(v);
-        prev = role;
+        int prev = 0;
+        for (int64_t k = v0; k < v1; ++k) {
+            const int32_t b = sp.visit[k];
+            const BlockDesc& d = sp.blocks[b];
+            const int32_t nextb = k + 1 < v1 ? sp.visit[k + 1] : -1;
+            VisitDev& v = out.visits[first + (size_t)(k - v0)];
+            v.linv_off = d.linv_off;
+            v.aoff = d.aoff;
+            v.rows_off = d.rows_off;
+            v.row0 = d.row0;
+            v.w = d.w;
+            const int role = prev == 1 ? 2 : pair && (*pair)[b] && nextb == b + 1 ? 1 : 0;
+            v.urows = role == 1 ? sp.blocks[b + 1].w : d.nbelow;
+            if (role == 2) {
+                const BlockDesc& f = sp.blocks[b - 1];
+                v.pair_nks = (f.w + 3) / 4;
+                v.pair_aoff = f.aoff + (int64_t)(d.w / 16) * v.pair_nks * 64;
+            }
+            v.flags = role;
+            for (int w = 0; w < 4; ++w)
+                if (b >= start[w]) v.flags |= 1 << (kVisitActShift + w);
+            for (int32_t i = 0; i < d.w; ++i)
+                if ((v.on >> i) & 1) {
+                    if (written[d.row0 + i] == t) v.held |= 1ull << i;
+                    written[d.row0 + i] = t;
+                }
+            const int32_t r0 = nextb >= 0 ? sp.blocks[nextb].row0 : 0, r1 = nextb >= 0 ? r0 + sp.blocks[nextb].w : 0;
+            const int32_t last = v.urows > 0 ? (v.urows - 1) / (16 * pt) * (16 * pt) : 0;
+            bool clear = true;
+            v.fresh = (int32_t)((int64_t)out.fresh.size() - out.fresh_ptr.back());
+            uint64_t m = 0;
+            for (int32_t q = 0; q < v.urows; ++q) {
+                const int32_t r = sp.brows[d.rows_off + q];
+                const int32_t i = q % (16 * pt);
+                if (q > 0 && i == 0) {
+                    out.fresh.push_back(m);
+                    m = 0;
+                }
+                if (written[r] != t) m |= 1ull << i;
+                // the first block of a pair hands its rows on in registers
+                if (role != 1) written[r] = t;
+                if (q >= last) clear = clear && (r < r0 || r >= r1);
+            }
+            out.fresh.push_back(m);
+            if (clear && v.urows > 0) v.flags |= kVisitNextEarly;
+            prev = role;
+        }
     }
+    out.fresh_ptr.push_back((int64_t)out.fresh.size());
+    out.clear_ptr.push_back((int64_t)out.clear.size());
 }
 
 #define HIP_TRY(expr)                                                                        \
@@ -256,6 +310,8 @@ struct sc_plan_s {
     std::vector<TileDev> h_tiles;
     std::vector<BlockDev> h_blocks;
     std::vector<VisitDev> h_visits;             // TRSM visit lists of all tiles
+    std::vector<uint64_t> h_fresh;              // VisitDev::fresh masks of all tiles
+    std::vector<int32_t> h_clear;               // rows the tiles clear
     std::vector<int32_t> h_ksteps;              // SYRK k-step lists of all items
     std::vector<SyrkItem> h_syrk;               // interleaved over XCDs, idle items sub = -1
     std::vector<int32_t> h_tile_order;          // TRSM workgroup -> tile (-1 idle)
@@ -294,8 +350,9 @@ struct sc_plan_s {
     double* scratch = nullptr;
     hipError_t scratch_err = hipSuccess;
     int32_t noalloc_too_big = -1;
-    DevBuf<int32_t> d_rows, d_piv, d_pi, d_ksteps;
+    DevBuf<int32_t> d_rows, d_piv, d_pi, d_ksteps, d_clear;
     DevBuf<VisitDev> d_visits;
+    DevBuf<uint64_t> d_fresh;
     DevBuf<int8_t> d_sgn;
     DevBuf<double> d_lval, d_X, d_F;
     DevBuf<float> d_lval32, d_X32, d_F32;
@@ -319,8 +376,7 @@ struct sc_plan_s {
     int64_t arena_elems = 0;
     std::vector<int32_t> syrk_kind;             // per subdomain: 0 by size, 1 blocks, 2 tiles
     // the TRSM kernel with the merged pairs: when they save at least
-    // kMergeMinShare of the batch's pruned-row updates (below that, the
-    // merge-capable kernel's extra scalar state costs more than it saves)
+    // kMergeMinShare of the batch's pruned-row updates
     bool trsm_merge = false;
     bool trsm_large = false;                    // some X slab holds kTrsmSlabBytes or more
     // select_iters: per subdomain applied with the factor (not assembled),
@@ -432,8 +488,8 @@ struct sc_plan_s {
                          d_ftiles.count * sizeof(SyrkItem) + d_frows.count * sizeof(int2) +
                          d_part.count * 8 + d_tile_order.count * 4 +
                          d_tile_order_g.count * 4 + d_syrk_g.count * sizeof(SyrkItem) +
-                         (d_rows.count + d_piv.count + d_pi.count + d_ksteps.count) * 4 + d_visits.count * sizeof(VisitDev) +
-                         d_sgn.count +
+                         (d_rows.count + d_piv.count + d_pi.count + d_ksteps.count + d_clear.count) * 4 + d_visits.count * sizeof(VisitDev) +
+                         d_fresh.count * 8 + d_sgn.count +
                          (d_lval.count + d_X.count + d_F.count) * 8 +
                          (d_lval32.count + d_X32.count + d_F32.count) * 4 +
                          (d_xwork.count + d_ywork.count + d_xoff.count) * 8 + (d_ifw.count + d_ibw.count) * sizeof(int2) +
@@ -444,7 +500,7 @@ struct sc_plan_s {
         d_subs.release(); d_tiles.release(); d_blocks.release(); d_syrk.release();
         d_ftiles.release(); d_frows.release(); d_part.release();
         d_tile_order.release(); d_tile_order_g.release(); d_syrk_g.release();
-        d_rows.release(); d_piv.release(); d_pi.release(); d_ksteps.release(); d_visits.release(); d_sgn.release();
+        d_rows.release(); d_piv.release(); d_pi.release(); d_ksteps.release(); d_clear.release(); d_visits.release(); d_fresh.release(); d_sgn.release();
         d_lval.release(); d_X.release(); d_F.release();
         d_lval32.release(); d_X32.release(); d_F32.release();
         d_xwork.release(); d_ywork.release(); d_xoff.release();
@@ -467,7 +523,8 @@ struct sc_plan_s {
     }
     DevTables tables() const {
         DevTables t;
-        t.subs = d_subs.p; t.tiles = d_tiles.p; t.blocks = d_blocks.p; t.rows = d_rows.p; t.visits = d_visits.p;
+        t.subs = d_subs.p; t.tiles = d_tiles.p; t.blocks = d_blocks.p; t.rows = d_rows.p; t.visits = d_visits.p; t.fresh = d_fresh.p;
+        t.clear = d_clear.p;
         t.ksteps = d_ksteps.p;
         t.lval = d_lval.p; t.piv = d_piv.p; t.pi = d_pi.p; t.sgn = d_sgn.p; t.syrk = d_syrk.p;
         t.X = d_X.p; t.F = d_F.p;
@@ -888,14 +945,39 @@ sc_status_t sc_plan_create(const sc_subdomain_desc_t* sd, int32_t nsub, const sc
         syrk_list(xsub, P->h_syrk, P->nsyrk_tile, nb);
     }
     P->nval_total = lv;
-    P->trsm_merge = merged_rows > 0 && (double)merged_rows >= kMergeMinShare * (double)upd_rows;
-    for (int32_t i = 0; i < nsub; ++i)
-        for (int32_t t = 0; t < P->h_subs[i].ntiles; ++t) {
-            TileDev& T = P->h_tiles[P->h_subs[i].tile_off + t];
-            T.visit_off = (int64_t)P->h_visits.size();
-            append_visits(P->plans[i], t, T.kstart, po.staircase != 0, P->trsm_merge ? &pairs[i] : nullptr,
-                          P->mixed ? kPruneTiles<float> : kPruneTiles<double>, P->h_visits);
+    P->trsm_merge = merged_rows > 0 &&
+                    (double)merged_rows >= (P->mixed ? kMergeMinShareMixed : kMergeMinShare) * (double)upd_rows;
+    {
+        std::vector<TileVisits> tv(nsub);
+        bool oom = false;
+#pragma omp parallel for schedule(dynamic, 1) num_threads(nthr)
+        for (int32_t i = 0; i < nsub; ++i) {
+            try {
+                build_visits(P->plans[i], po.staircase != 0, P->trsm_merge ? &pairs[i] : nullptr,
+                             P->mixed ? kPruneTiles<float> : kPruneTiles<double>, tv[i]);
+            } catch (const std::bad_alloc&) {
+#pragma omp atomic write
+                oom = true;
+            }
         }
+        if (oom) return fail(SC_ERR_OOM, "host allocation failed");
+        for (int32_t i = 0; i < nsub; ++i) {
+            int64_t k = 0;
+            for (int32_t t = 0; t < P->h_subs[i].ntiles; ++t) {
+                TileDev& T = P->h_tiles[P->h_subs[i].tile_off + t];
+                T.visit_off = (int64_t)P->h_visits.size() + k;
+                T.fresh_off = (int64_t)P->h_fresh.size() + tv[i].fresh_ptr[t];
+                T.clear_off = (int64_t)P->h_clear.size() + tv[i].clear_ptr[t];
+                T.nclear = (int32_t)(tv[i].clear_ptr[t + 1] - tv[i].clear_ptr[t]);
+                k += T.nvisit;
+            }
+            P->h_visits.insert(P->h_visits.end(), tv[i].visits.begin(), tv[i].visits.end());
+            P->h_fresh.insert(P->h_fresh.end(), tv[i].fresh.begin(), tv[i].fresh.end());
+            P->h_clear.insert(P->h_clear.end(), tv[i].clear.begin(), tv[i].clear.end());
+            tv[i] = TileVisits();
+        }
+        P->h_fresh.resize(P->h_fresh.size() + 2, 0);      // read 16 bytes at a time
+    }
     rows += 64;                            // the TRSM reads whole 64-entry groups of a row list
     P->nrows_total = rows;
     P->ncol_total = colo;
@@ -946,6 +1028,8 @@ sc_status_t sc_plan_create(const sc_subdomain_desc_t* sd, int32_t nsub, const sc
     ALLOC(p->d_syrk_g, p->h_syrk_g.size());
     ALLOC(p->d_rows, (size_t)rows);
     ALLOC(p->d_visits, std::max<size_t>(1, p->h_visits.size()));
+    ALLOC(p->d_fresh, std::max<size_t>(1, p->h_fresh.size()));
+    ALLOC(p->d_clear, std::max<size_t>(1, p->h_clear.size()));
     ALLOC(p->d_ksteps, std::max<size_t>(1, p->h_ksteps.size()));
     ALLOC(p->d_piv, (size_t)colo);
     ALLOC(p->d_pi, (size_t)colo);
@@ -993,6 +1077,8 @@ sc_status_t sc_plan_create(const sc_subdomain_desc_t* sd, int32_t nsub, const sc
     if (e == hipSuccess && p->overlapped()) e = p->prepare_overlap();
     if (e == hipSuccess) e = up(p->d_rows.p, h_rows.data(), h_rows.size() * 4);
     if (e == hipSuccess) e = up(p->d_visits.p, p->h_visits.data(), p->h_visits.size() * sizeof(VisitDev));
+    if (e == hipSuccess) e = up(p->d_fresh.p, p->h_fresh.data(), p->h_fresh.size() * 8);
+    if (e == hipSuccess) e = up(p->d_clear.p, p->h_clear.data(), p->h_clear.size() * 4);
     if (e == hipSuccess) e = up(p->d_ksteps.p, p->h_ksteps.data(), p->h_ksteps.size() * 4);
     // F is cleared once: the SYRK never writes its structurally zero blocks
     // nor the columns past m of the last tiles

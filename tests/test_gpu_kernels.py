@@ -42,3 +42,29 @@ def test_dense_F_on_device_at_tile_edges(precision):
         assert np.array_equal(F.cpu().numpy(), plan.get_F(i)), s.m
         assert bool((out[:ld * s.m].view(s.m, ld)[:, s.m:] == -3.0).all()) and bool((out[ld * s.m:] == -3.0).all())
     plan.destroy()
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("split", ["uniform", "etree"])
+def test_trsm_reads_only_rows_it_wrote(precision, split):
+    """The X buffer full of another batch's values (temporary-memory waves
+    that reuse it, subdomains of several sizes, stripes that start late): the
+    same F bit for bit as with an X of its own, and as the oracle's."""
+    subs = [scgen.box_subdomain("elasticity", e, 1.0 / 8, 60 + i)
+            for i, e in enumerate([(8, 7, 6), (5, 5, 5), (7, 3, 8), (6, 6, 4)])]
+    subs += [scgen.box_subdomain("heat", (12, 11, 9), 1.0 / 12, 70), scgen.simplex_subdomain(2, 40, 71)]
+    subs += [_columns(scgen.box_subdomain("heat", (12, 12, 12), 1.0 / 12, 72), 300, 73)]
+    kw = dict(precision=precision, block_split=split, panel_width=48)
+    ref = _plan(subs, **kw)
+    size = 8 if precision == "fp64" else 4
+    cap = max(s.n * ((s.m + 63) // 64) * 64 * size for s in subs)
+    wav = _plan(subs, arena_cap_bytes=cap, **kw)
+    wav.assemble()
+    tol = 1e-12 if precision == "fp64" else 1e-5
+    for i, s in enumerate(subs):
+        F = wav.get_F(i)
+        assert np.array_equal(F, ref.get_F(i)), i
+        sel = np.sort(np.random.default_rng(i).choice(s.m, size=min(64, s.m), replace=False))
+        assert oracle.relF(F[np.ix_(sel, sel)], oracle.schur(s, sel=sel)) <= tol, i
+    wav.destroy()
+    ref.destroy()
