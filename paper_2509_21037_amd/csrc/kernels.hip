@@ -578,19 +578,17 @@ __global__ __launch_bounds__(256, MERGE ? 2 : 3) void trsm_stair_mixed(
 constexpr int kSyrkKC = 16;                  // X rows per step
 constexpr int kSyrkLd = kTile + 4;           // LDS row stride (elements)
 
-template <class TX>
-constexpr int kSyrkSmem = 4 * kSyrkKC * kSyrkLd * (int)sizeof(TX);
+constexpr int kSyrkSmem = 4 * kSyrkKC * kSyrkLd * 8;
 
-template <bool MIXED>
 __device__ __forceinline__ void syrk_block(
     const SubDev* __restrict__ subs, const TileDev* __restrict__ tiles, const SyrkItem it,
-    const int32_t* __restrict__ ksteps, const typename std::conditional<MIXED, float, double>::type* __restrict__ X,
-    typename std::conditional<MIXED, float, double>::type* __restrict__ F, char* __restrict__ smem)
+    const int32_t* __restrict__ ksteps, const double* __restrict__ X, double* __restrict__ F,
+    char* __restrict__ smem)
 {
-    using TX = typename std::conditional<MIXED, float, double>::type;
-    using VX = typename std::conditional<MIXED, v4f, v4d>::type;
-    using LV = typename std::conditional<MIXED, float4, double2>::type;
-    constexpr int kVec = sizeof(LV) / sizeof(TX);                // elements per load
+    using TX = double;
+    using VX = v4d;
+    using LV = double2;
+    constexpr int kVec = 2;                                      // elements per load
     constexpr int kPer = kSyrkKC * kTile / kVec / 256;           // loads per thread and slab
     TX (*sA)[kSyrkKC * kSyrkLd] = reinterpret_cast<TX (*)[kSyrkKC * kSyrkLd]>(smem);
     TX (*sB)[kSyrkKC * kSyrkLd] = sA + 2;
@@ -658,8 +656,7 @@ __device__ __forceinline__ void syrk_block(
             for (int t = 0; t < 4; ++t) b[t] = pb[4 * s * kSyrkLd + 16 * t];
 #pragma unroll
             for (int t = 0; t < 4; ++t) {
-                if constexpr (MIXED) acc[t] = mfma_f32(a, b[t], acc[t]);
-                else acc[t] = mfma_f64(a, b[t], acc[t]);
+                acc[t] = mfma_f64(a, b[t], acc[t]);
             }
         }
         if (st + 1 < nsteps) store_step(buf ^ 1);
@@ -674,7 +671,7 @@ __device__ __forceinline__ void syrk_block(
     for (int t = 0; t < 4; ++t)
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            const int row = r0 + (MIXED ? 4 * g + r : 4 * r + g);
+            const int row = r0 + 4 * r + g;
             const int col = c0 + 16 * t + j;
             Ft[row * kSyrkTile + col] = acc[t][r];
             if (mirror) Ft[col * kSyrkTile + row] = acc[t][r];
@@ -686,10 +683,10 @@ __global__ __launch_bounds__(256) void syrk_block_f64(
     const SyrkItem* __restrict__ items, const int32_t* __restrict__ ksteps, const double* __restrict__ X,
     double* __restrict__ F)
 {
-    __shared__ __align__(16) char smem[kSyrkSmem<double>];
+    __shared__ __align__(16) char smem[kSyrkSmem];
     const SyrkItem it = items[blockIdx.x];
     if (it.sub < 0) return;
-    syrk_block<false>(subs, tiles, it, ksteps, X, F, smem);
+    syrk_block(subs, tiles, it, ksteps, X, F, smem);
 }
 
 // ---------------------------------------------------------------------------
@@ -830,8 +827,8 @@ __global__ __launch_bounds__(256) void syrk_tile_f64(
 }
 
 // ---------------------------------------------------------------------------
-// Mixed precision (FP64 diagonal solves; FP32 X, off-diagonal updates and
-// SYRK with FP32 MFMA and FP32 accumulation).
+// Mixed precision (FP64 diagonal solves; FP32 X and off-diagonal updates with
+// FP32 MFMA; SYRK with FP32 sums of exact bf16 products).
 // ---------------------------------------------------------------------------
 
 // FP64 factor values -> FP32 copy (round to nearest even).
@@ -840,143 +837,202 @@ __global__ __launch_bounds__(256) void convert_f64_f32(const double* __restrict_
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) b[i] = (float)a[i];
 }
-// FP32 SYRK over 64 x 64 blocks: as syrk_block_f64 with FP32 X, FP32 MFMA and
-// FP32 accumulation; F stored FP32.
-__global__ __launch_bounds__(256) void syrk_block_f32(
+// ---------------------------------------------------------------------------
+// SYRK of the FP32 X, F stored FP32: as the FP64 kernels above over 64 x 64
+// blocks (EDGE = 64) or 128 x 128 tiles (EDGE = 128) of F, on the bf16 matrix
+// units.  An FP32 value is exactly the sum of three bf16 values (24 = 3 x 8
+// significant bits, each the rounded remainder of the last), so x y is a sum
+// of nine exact bf16 products; the six down to 2^-16 of x y are formed, the
+// others are below 2^-25 of it, half an FP32 rounding.  Sums stay FP32:
+// v_mfma_f32_32x32x16_bf16 adds the products of a whole 16-row step at once,
+// where the FP32 instruction takes four of its rows, and the five smaller
+// products have their own accumulator, so that the main one is rounded once a
+// step.  The bf16 units do 16 times the FP32 rate: six products take 3/8 of
+// the time.  Mixed F against the FP64 F, FP32 units before / now (relative
+// Frobenius; largest element error over sqrt(F_ii F_jj)): 16 x 16 heat square
+// 8.2e-8 / 7.1e-8; 3.6e-7 / 2.6e-7, 12^3 heat 1.10e-7 / 1.08e-7; 1.0e-6 /
+// 5.6e-7, 20^3 elasticity 4.38e-7 / 4.28e-7; 5.5e-6 / 3.7e-6, 129^2 triangles
+// 1.72e-7 / 1.22e-7; 1.1e-6 / 5.2e-7 (one accumulator for all six: 8.4e-8,
+// 1.08e-7, 4.31e-7, 1.52e-7, and up to 1.3 times the old element error).
+// Per step a thread loads 8 rows of one column (a wavefront: 8 rows of 256
+// bytes), splits them and writes three 16-byte pieces, [plane][row half]
+// [column], the operand layout of the instruction (lane l: column l % 32, rows
+// 8 (l / 32) .. + 7): LDS reads and writes of 16 consecutive bytes a lane.
+// The loads of two steps are in flight, in two register sets (the loop takes
+// two steps: no copies between them).  Wavefront (wi, wj) computes the
+// (EDGE / 2)^2 quadrant.  The two sides of a tile on the diagonal would be
+// summed in different orders: the lower one is written to both.
+// Between the matrix units (4.5 of its 9.9 ms), the split and the LDS:
+// 16 x 20^3 elasticity 15.0 ms on the FP32 units / 9.9 now, 512 x 12^3 heat
+// 1.22 / 0.84, 64 uneven elasticity boxes 2.45 / 1.54.
+// ---------------------------------------------------------------------------
+typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
+typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
+typedef float v2f __attribute__((ext_vector_type(2)));
+typedef float v16f __attribute__((ext_vector_type(16)));
+
+// x[0..8) as three bf16 planes, h + m + l = x
+__device__ __forceinline__ void split_bf16(const float (&x)[8], v4u& h, v4u& m, v4u& l) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        v2f r = {x[2 * i], x[2 * i + 1]};
+        h[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector(r, v2bf));
+        r[0] -= __builtin_bit_cast(float, h[i] << 16);
+        r[1] -= __builtin_bit_cast(float, h[i] & 0xFFFF0000u);
+        m[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector(r, v2bf));
+        r[0] -= __builtin_bit_cast(float, m[i] << 16);
+        r[1] -= __builtin_bit_cast(float, m[i] & 0xFFFF0000u);
+        l[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector(r, v2bf));
+    }
+}
+
+template <int EDGE>
+__global__ __launch_bounds__(256, EDGE == 128 ? 2 : 4) void syrk_split_f32(
     const SubDev* __restrict__ subs, const TileDev* __restrict__ tiles,
     const SyrkItem* __restrict__ items, const int32_t* __restrict__ ksteps, const float* __restrict__ X,
     float* __restrict__ F)
 {
-    __shared__ __align__(16) char smem[kSyrkSmem<float>];
+    constexpr int NS = EDGE / 64;                // 64-column slabs per side, sub-tiles per wavefront and side
+    constexpr int kPlane = EDGE * 2;             // 16-byte pieces of one plane of one side
+    __shared__ v4u lds[2][2][3 * kPlane];        // [buffer][side]
     const SyrkItem it = items[blockIdx.x];
     if (it.sub < 0) return;
-    syrk_block<true>(subs, tiles, it, ksteps, X, F, smem);
-}
-
-// FP32 SYRK over 128 x 128 tiles: as syrk_tile_f64 with FP32 X, FP32 MFMA and
-// FP32 accumulation (33 KB of LDS: 4 workgroups per CU); F stored FP32.
-constexpr int kWideSmemF = 4 * kSyrkKC * kWideLd * 4;
-
-__device__ __forceinline__ void syrk_tile_item_f32(
-    const SubDev* __restrict__ subs, const TileDev* __restrict__ tiles, const SyrkItem it,
-    const int32_t* __restrict__ ksteps, const float* __restrict__ X, float* __restrict__ F,
-    char* __restrict__ smem)
-{
-    float (*sI)[kSyrkKC * kWideLd] = reinterpret_cast<float (*)[kSyrkKC * kWideLd]>(smem);
-    float (*sJ)[kSyrkKC * kWideLd] = sI + 2;
     const SubDev S = subs[it.sub];
     const int lane = threadIdx.x & 63;
-    const int wv = threadIdx.x >> 6;
-    const int g = lane >> 4;
-    const int j = lane & 15;
-    const int wi = wv >> 1;
-    const int wj = wv & 1;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n = S.n;
-
-    const float* xs[4];
-    int ks[4];
+    const bool diag = it.I == it.J;              // one side: J reads I's planes
+    // this wavefront's slab of each side it loads (EDGE = 64: wavefronts 0-1
+    // load side I, 2-3 side J) and the half of the 16 rows
+    const int half = EDGE == 128 ? wv >> 1 : wv & 1;
+    const float* xs[NS];
+    int ks[NS], bit[NS];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const int t64 = 2 * (q < 2 ? it.I : it.J) + (q & 1);
-        if (t64 < S.ntiles) {
-            const TileDev& T = tiles[S.tile_off + t64];
-            xs[q] = X + T.x_off;
-            ks[q] = T.kstart;
-        } else {
-            xs[q] = nullptr;
-            ks[q] = INT_MAX;
-        }
+    for (int q = 0; q < NS; ++q) {
+        const int side = EDGE == 128 ? q : wv >> 1;
+        const int t64 = (side ? it.J : it.I) * NS + (EDGE == 128 ? wv & 1 : 0);
+        const bool have = t64 < S.ntiles && !(side && diag);
+        const TileDev& T = tiles[S.tile_off + (have ? t64 : 0)];
+        xs[q] = X + T.x_off;
+        ks[q] = have ? T.kstart : INT_MAX;
+        bit[q] = EDGE == 128 ? 2 * side + (wv & 1) : 0;
     }
     const int32_t* __restrict__ KS = ksteps + it.step_off;
-    // a diagonal tile reads one slab pair (sJ aliases sI)
-    const bool diag = it.I == it.J;
-
-    v4f acc[4][4];
-#pragma unroll
-    for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int b = 0; b < 4; ++b) acc[a][b] = (v4f){0.f, 0.f, 0.f, 0.f};
-
-    // thread -> (row, 4 columns) of a 16 x 128 step, 2 per operand
-    float4 rI[kSyrkKC / 8], rJ[kSyrkKC / 8];
-    auto load_step = [&](int ent) {
-        const int kb = ent & kStepRowMask;
-#pragma unroll
-        for (int e = 0; e < kSyrkKC / 8; ++e) {
-            const int idx = threadIdx.x + 256 * e;
-            const int rr = idx >> 5;
-            const int cc = 4 * (idx & 31);
-            const int half = cc >> 6;
-            const int c = cc & 63;
-            const int k = kb + rr;
-            const int qi = half, qj = 2 + half;
-            const bool li = ((ent >> (kStepSlabShift + qi)) & 1) && k < n && k >= ks[qi];
-            const bool lj = !diag && ((ent >> (kStepSlabShift + qj)) & 1) && k < n && k >= ks[qj];
-            rI[e] = li ? *reinterpret_cast<const float4*>(xs[qi] + (int64_t)(k - ks[qi]) * kTile + c)
-                       : make_float4(0.f, 0.f, 0.f, 0.f);
-            rJ[e] = lj ? *reinterpret_cast<const float4*>(xs[qj] + (int64_t)(k - ks[qj]) * kTile + c)
-                       : make_float4(0.f, 0.f, 0.f, 0.f);
-        }
-    };
-    auto store_step = [&](int buf) {
-#pragma unroll
-        for (int e = 0; e < kSyrkKC / 8; ++e) {
-            const int idx = threadIdx.x + 256 * e;
-            const int rr = idx >> 5;
-            const int cc = 4 * (idx & 31);
-            *reinterpret_cast<float4*>(&sI[buf][rr * kWideLd + cc]) = rI[e];
-            if (!diag) *reinterpret_cast<float4*>(&sJ[buf][rr * kWideLd + cc]) = rJ[e];
-        }
-    };
-
     const int nsteps = it.nsteps;
-    if (nsteps > 0) {
-        load_step(KS[0]);
-        store_step(0);
-    }
-    __syncthreads();
-    for (int st = 0; st < nsteps; ++st) {
-        const int buf = st & 1;
-        if (st + 1 < nsteps) load_step(KS[st + 1]);
-        {
-#pragma unroll
-            for (int s = 0; s < kSyrkKC / 4; ++s) {
-                const float* ai = &sI[buf][(4 * s + g) * kWideLd + 64 * wi + j];
-                const float* bj = &(diag ? sI : sJ)[buf][(4 * s + g) * kWideLd + 64 * wj + j];
-                float a[4], b[4];
-#pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                    a[t] = ai[16 * t];
-                    b[t] = bj[16 * t];
-                }
-#pragma unroll
-                for (int ti = 0; ti < 4; ++ti)
-#pragma unroll
-                    for (int tj = 0; tj < 4; ++tj) acc[ti][tj] = mfma_f32(a[ti], b[tj], acc[ti][tj]);
-            }
-        }
-        if (st + 1 < nsteps) store_step(buf ^ 1);
-        __syncthreads();
-    }
-    float* __restrict__ Ft = F + S.F_off + (int64_t)(it.I * (it.I + 1) / 2 + it.J) * kFTileElems;
-#pragma unroll
-    for (int ti = 0; ti < 4; ++ti)
-#pragma unroll
-        for (int tj = 0; tj < 4; ++tj)
-#pragma unroll
-            for (int r = 0; r < 4; ++r)
-                Ft[(64 * wi + 16 * ti + 4 * g + r) * kSyrkTile + 64 * wj + 16 * tj + j] = acc[ti][tj][r];
-}
 
-__global__ __launch_bounds__(256) void syrk_tile_f32(
-    const SubDev* __restrict__ subs, const TileDev* __restrict__ tiles,
-    const SyrkItem* __restrict__ items, const int32_t* __restrict__ ksteps, const float* __restrict__ X,
-    float* __restrict__ F)
-{
-    __shared__ __align__(16) char smem[kWideSmemF];
-    const SyrkItem it = items[blockIdx.x];
-    if (it.sub < 0) return;
-    syrk_tile_item_f32(subs, tiles, it, ksteps, X, F, smem);
+    auto load_step = [&](float (&v)[NS][8], int ent, bool have) __attribute__((always_inline)) {
+        const int kb = EDGE == 128 ? ent & kStepRowMask : ent;
+#pragma unroll
+        for (int q = 0; q < NS; ++q) {
+            // rows [r0, kb + 16) of the slab, fewer at its ends, none where
+            // the step entry says so: the others read as zero
+            const int r0 = max(kb, ks[q]);
+            const bool on = EDGE == 64 || ((ent >> (kStepSlabShift + bit[q])) & 1);
+            const int rows = on && have ? min(kb + kSyrkKC, n) - r0 : 0;
+            const __amdgpu_buffer_rsrc_t r =
+                buffer_of(xs[q] + (int64_t)(rows > 0 ? r0 - ks[q] : 0) * kTile, rows > 0 ? rows * kTile * 4 : 0);
+            const int skip = rows > 0 ? r0 - kb : 0;       // rows of the step above the slab
+            int o[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) o[e] = lane * 4 + (8 * half + e) * (kTile * 4);
+            if (skip > 0) {
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    o[e] = 8 * half + e >= skip ? o[e] - skip * (kTile * 4) : SlabRows<float, false>::kNone;
+            }
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                v[q][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, o[e], 0, 0));
+        }
+    };
+    auto store_step = [&](const float (&v)[NS][8], int buf) __attribute__((always_inline)) {
+#pragma unroll
+        for (int q = 0; q < NS; ++q) {
+            const int side = EDGE == 128 ? q : wv >> 1;
+            if (side && diag) continue;
+            v4u h, m, l;
+            split_bf16(v[q], h, m, l);
+            v4u* d = &lds[buf][side][half * EDGE + (EDGE == 128 ? 64 * (wv & 1) : 0) + lane];
+            d[0] = h;
+            d[kPlane] = m;
+            d[2 * kPlane] = l;
+        }
+    };
+
+    v16f acc[NS][NS], low[NS][NS];               // h h products; the smaller ones
+#pragma unroll
+    for (int a = 0; a < NS; ++a)
+#pragma unroll
+        for (int b = 0; b < NS; ++b)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[a][b][r] = low[a][b][r] = 0.f;
+    const int wi = wv >> 1, wj = wv & 1;
+    const int frag = (lane & 31) + (lane >> 5) * EDGE;
+    auto entry = [&](int st) { return KS[min(st, nsteps - 1)]; };
+    // step st from LDS buffer `buf`; `v`: the rows of step st + 1, then st + 3
+    auto step = [&](float (&v)[NS][8], int st, int buf) __attribute__((always_inline)) {
+        const int ent = entry(st + 3);
+        const v4u* pa = &lds[buf][0][wi * (EDGE / 2) + frag];
+        const v4u* pb = &lds[buf][diag ? 0 : 1][wj * (EDGE / 2) + frag];
+        v8bf a[NS][3], b[NS][3];
+#pragma unroll
+        for (int k = 0; k < 3; ++k)
+#pragma unroll
+            for (int q = 0; q < NS; ++q) {
+                a[q][k] = __builtin_bit_cast(v8bf, pa[k * kPlane + 32 * q]);
+                b[q][k] = __builtin_bit_cast(v8bf, pb[k * kPlane + 32 * q]);
+            }
+        // smallest products first
+        constexpr int kOrder[6][2] = {{2, 0}, {0, 2}, {1, 1}, {1, 0}, {0, 1}, {0, 0}};
+#pragma unroll
+        for (int k = 0; k < 6; ++k)
+#pragma unroll
+            for (int q = 0; q < NS; ++q)
+#pragma unroll
+                for (int p = 0; p < NS; ++p) {
+                    v16f& c = k == 5 ? acc[q][p] : low[q][p];
+                    c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[q][kOrder[k][0]], b[p][kOrder[k][1]], c, 0, 0, 0);
+                }
+        store_step(v, buf ^ 1);
+        load_step(v, ent, st + 3 < nsteps);
+        lds_barrier();
+    };
+    float v0[NS][8], v1[NS][8];                  // two steps in flight
+    load_step(v0, entry(0), nsteps > 0);
+    load_step(v1, entry(1), nsteps > 1);
+    store_step(v0, 0);
+    load_step(v0, entry(2), nsteps > 2);
+    lds_barrier();
+    int st = 0;
+    for (; st + 1 < nsteps; st += 2) {
+        step(v1, st, 0);
+        step(v0, st + 1, 1);
+    }
+    if (st < nsteps) step(v1, st, 0);
+#pragma unroll
+    for (int a = 0; a < NS; ++a)
+#pragma unroll
+        for (int b = 0; b < NS; ++b)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[a][b][r] += low[a][b][r];
+    // D: lane l, register r holds row 8 (r / 4) + 4 (l / 32) + r % 4, column l % 32
+    const int I2 = EDGE == 128 ? it.I : it.I >> 1, J2 = EDGE == 128 ? it.J : it.J >> 1;
+    float* __restrict__ Ft = F + S.F_off + (int64_t)(I2 * (I2 + 1) / 2 + J2) * kFTileElems;
+    const int r0 = (EDGE == 128 ? 0 : 64 * (it.I & 1)) + wi * (EDGE / 2);
+    const int c0 = (EDGE == 128 ? 0 : 64 * (it.J & 1)) + wj * (EDGE / 2);
+    const bool mirror = I2 == J2;                // a stored tile on the diagonal is kept whole
+#pragma unroll
+    for (int q = 0; q < NS; ++q)
+#pragma unroll
+        for (int p = 0; p < NS; ++p)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int row = r0 + 32 * q + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
+                const int col = c0 + 32 * p + (lane & 31);
+                if (mirror && row < col) continue;
+                Ft[row * kSyrkTile + col] = acc[q][p][r];
+                if (mirror && row > col) Ft[col * kSyrkTile + row] = acc[q][p][r];
+            }
 }
 
 // ---------------------------------------------------------------------------
@@ -1001,7 +1057,7 @@ hipError_t launch_syrk(const DevTables& t, const SyrkItem* items, int64_t ntile,
                        hipStream_t stream) {
     if (ntile > 0) {
         if (t.X32)
-            hipLaunchKernelGGL(syrk_tile_f32, dim3((unsigned)ntile), dim3(256), 0, stream, t.subs, t.tiles, items,
+            hipLaunchKernelGGL(syrk_split_f32<128>, dim3((unsigned)ntile), dim3(256), 0, stream, t.subs, t.tiles, items,
                                t.ksteps, t.X32, t.F32);
         else
             hipLaunchKernelGGL(syrk_tile_f64, dim3((unsigned)ntile), dim3(256), 0, stream, t.subs, t.tiles, items,
@@ -1011,7 +1067,7 @@ hipError_t launch_syrk(const DevTables& t, const SyrkItem* items, int64_t ntile,
     }
     if (nblock > 0) {
         if (t.X32)
-            hipLaunchKernelGGL(syrk_block_f32, dim3((unsigned)nblock), dim3(256), 0, stream, t.subs, t.tiles,
+            hipLaunchKernelGGL(syrk_split_f32<64>, dim3((unsigned)nblock), dim3(256), 0, stream, t.subs, t.tiles,
                                items + ntile, t.ksteps, t.X32, t.F32);
         else
             hipLaunchKernelGGL(syrk_block_f64, dim3((unsigned)nblock), dim3(256), 0, stream, t.subs, t.tiles,
