@@ -557,273 +557,175 @@ __global__ __launch_bounds__(256, MERGE ? 2 : 3) void trsm_stair_mixed(
 
 // ---------------------------------------------------------------------------
 // Staircase SYRK, F = X^T X (Sec. 3.3, output splitting): one workgroup per
-// 64 x 64 block (I >= J, in units of 64-column X tiles) of the lower triangle
-// of the column-sorted F; wavefront w computes its rows 16w .. 16w + 15
-// (1 x 4 MFMA tiles).  The k-range is the block's list of 16-row steps: those
-// where both X tiles hold rows on the elimination-tree paths of their pivots
-// (every other step adds zero products; the staircase bound, rows below the
-// first pivot of tile I, is the outer limit of that set).  Blocks with an
-// empty list are structurally zero and are not launched: the plan clears F
-// once when it is created.  Used for subdomains up to kSyrkBlockMaxN rows
-// (FP32: kSyrkBlockMaxNMixed), whose X slabs largely stay in L2 while their
-// blocks re-read them.  X rows are staged through double-buffered LDS, 16
-// rows per step, the next step prefetched into registers.  F stays in the
-// sorted column order (the permutation back to the multiplier order is
-// applied to the vectors of the apply and by sc_get_F), stored as the lower
-// triangle of 128 x 128 tiles, tile (I, J) at I(I+1)/2 + J, each row-major,
-// diagonal tiles whole: block (2T+1, 2T) also writes its transpose, the upper
-// quadrant of diagonal tile T.  Columns past m are never written and stay
-// zero.
+// 64 x 64 block (EDGE = 64; I >= J, in units of 64-column X tiles) or 128 x
+// 128 tile (EDGE = 128; units of kSyrkTile) of the lower triangle of the
+// column-sorted F, wavefront (wi, wj) its (EDGE / 2)^2 quadrant (2 x 2 or 4 x
+// 4 MFMA tiles).  The k-range is the item's list of 16-row steps: those where
+// both sides hold rows on the elimination-tree paths of their pivots (every
+// other step adds zero products; the staircase bound, rows below the first
+// pivot of tile I, is the outer limit of that set).  A tile's step entry
+// marks which of its four 64-column slabs hold such rows (bits at
+// kStepSlabShift); the others read as zero, as do rows above the first pivot
+// of a slab.  Items with an empty list are structurally zero and are not
+// launched: the plan clears F once when it is created.  The blocks execute
+// fewer steps, the tiles read half as much of X per product; both sum in the
+// same order, so F is the same bit for bit.  F stays in the sorted column
+// order (the permutation back to the multiplier order is applied to the
+// vectors of the apply and by sc_get_F), stored as the lower triangle of 128 x
+// 128 tiles, tile (I, J) at I(I+1)/2 + J, each row-major, diagonal tiles
+// whole: block (2T+1, 2T) also writes its transpose, the upper quadrant of
+// diagonal tile T.  Columns past m are never written and stay zero.
+// Bound by the FP64 matrix units.  X rows go through double-buffered LDS, 16
+// per step; the loads of two further steps are in flight in two register sets
+// (the loop takes two steps, so that no load in flight is copied), through
+// buffer resources whose range ends at the rows that exist (no branches), and
+// a step's rows are written to LDS before the last quarter of its products.
+// Before (one step in flight, loads under branches, step entries loaded when
+// used) / now: 16 x 20^3 elasticity 29.9 / 27.2 ms, 64 uneven elasticity boxes
+// 4.32 / 3.87, 512 x 12^3 heat 2.26 / 1.99, 32 tetrahedral meshes of 21^3
+// nodes 2.16 / 1.84 ms; with one step in flight 27.6, 3.97, 2.10 and 1.94.
 // ---------------------------------------------------------------------------
 constexpr int kSyrkKC = 16;                  // X rows per step
-constexpr int kSyrkLd = kTile + 4;           // LDS row stride (elements)
 
-constexpr int kSyrkSmem = 4 * kSyrkKC * kSyrkLd * 8;
-
-__device__ __forceinline__ void syrk_block(
-    const SubDev* __restrict__ subs, const TileDev* __restrict__ tiles, const SyrkItem it,
-    const int32_t* __restrict__ ksteps, const double* __restrict__ X, double* __restrict__ F,
-    char* __restrict__ smem)
+template <int EDGE>
+__global__ __launch_bounds__(256, EDGE == 128 ? 2 : 4) void syrk_f64(
+    const SubDev* __restrict__ subs, const TileDev* __restrict__ tiles,
+    const SyrkItem* __restrict__ items, const int32_t* __restrict__ ksteps, const double* __restrict__ X,
+    double* __restrict__ F)
 {
-    using TX = double;
-    using VX = v4d;
-    using LV = double2;
-    constexpr int kVec = 2;                                      // elements per load
-    constexpr int kPer = kSyrkKC * kTile / kVec / 256;           // loads per thread and slab
-    TX (*sA)[kSyrkKC * kSyrkLd] = reinterpret_cast<TX (*)[kSyrkKC * kSyrkLd]>(smem);
-    TX (*sB)[kSyrkKC * kSyrkLd] = sA + 2;
+    constexpr int NS = EDGE / 64;                // 64-column slabs per side
+    constexpr int MT = EDGE / 32;                // 16-column MFMA tiles per side of a wavefront's quadrant
+    constexpr int kLd = EDGE + 4;                // LDS row stride (elements)
+    __shared__ __align__(16) double lds[2][2][kSyrkKC * kLd];    // [buffer][side]
+    const SyrkItem it = items[blockIdx.x];
+    if (it.sub < 0) return;
     const SubDev S = subs[it.sub];
     const int lane = threadIdx.x & 63;
-    const int wv = threadIdx.x >> 6;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int g = lane >> 4;
     const int j = lane & 15;
     const int n = S.n;
-    const bool diag = it.I == it.J;          // one slab: sB aliases sA
-    const TileDev& TI = tiles[S.tile_off + it.I];
-    const TileDev& TJ = tiles[S.tile_off + it.J];
-    const TX* __restrict__ xi = X + TI.x_off;
-    const TX* __restrict__ xj = X + TJ.x_off;
-    const int ki = TI.kstart, kj = TJ.kstart;
+    const bool diag = it.I == it.J;              // one side: J reads I's rows
+    // this wavefront's slab of each side it loads (EDGE = 64: wavefronts 0-1
+    // load side I, 2-3 side J) and the half of the 16 rows; a lane loads two
+    // columns of every second row
+    const int half = EDGE == 128 ? wv >> 1 : wv & 1;
+    const double* xs[NS];
+    int ks[NS], bit[NS];
+#pragma unroll
+    for (int q = 0; q < NS; ++q) {
+        const int side = EDGE == 128 ? q : wv >> 1;
+        const int t64 = (side ? it.J : it.I) * NS + (EDGE == 128 ? wv & 1 : 0);
+        const bool have = t64 < S.ntiles && !(side && diag);
+        const TileDev& T = tiles[S.tile_off + (have ? t64 : 0)];
+        xs[q] = X + T.x_off;
+        ks[q] = have ? T.kstart : INT_MAX;
+        bit[q] = EDGE == 128 ? 2 * side + (wv & 1) : 0;
+    }
     const int32_t* __restrict__ KS = ksteps + it.step_off;
     const int nsteps = it.nsteps;
+    const int lrow = 8 * half + (lane >> 5), lcol = 2 * (lane & 31);
 
-    VX acc[4];
+    // rows lrow + 2 e of a step (zeros for a step past the last)
+    auto load_step = [&](v4u (&v)[NS][4], int ent, bool have) __attribute__((always_inline)) {
+        const int kb = EDGE == 128 ? ent & kStepRowMask : ent;
 #pragma unroll
-    for (int t = 0; t < 4; ++t)
+        for (int q = 0; q < NS; ++q) {
+            // rows [r0, kb + 16) of the slab, fewer at its ends, none where
+            // the step entry says so (they may never have been written): the
+            // others read as zero
+            const int r0 = max(kb, ks[q]);
+            const bool on = EDGE == 64 || ((ent >> (kStepSlabShift + bit[q])) & 1);
+            const int rows = on && have ? min(kb + kSyrkKC, n) - r0 : 0;
+            const __amdgpu_buffer_rsrc_t r =
+                buffer_of(xs[q] + (int64_t)(rows > 0 ? r0 - ks[q] : 0) * kTile, rows > 0 ? rows * kTile * 8 : 0);
+            const int skip = rows > 0 ? r0 - kb : 0;       // rows of the step above the slab
+            int o[4];
 #pragma unroll
-        for (int r = 0; r < 4; ++r) acc[t][r] = TX(0);
-
-    LV rA[kPer], rB[kPer];
-    auto load_step = [&](int kb) {
+            for (int e = 0; e < 4; ++e) o[e] = ((lrow + 2 * e) * kTile + lcol) * 8;
+            if (skip > 0) {
 #pragma unroll
-        for (int e = 0; e < kPer; ++e) {
-            const int idx = threadIdx.x + 256 * e;
-            const int rr = idx / (kTile / kVec);
-            const int cc = kVec * (idx % (kTile / kVec));
-            const int k = kb + rr;
-            if (k < n && k >= ki) rA[e] = *reinterpret_cast<const LV*>(xi + (int64_t)(k - ki) * kTile + cc);
-            else rA[e] = LV{};
-            if (!diag && k < n && k >= kj) rB[e] = *reinterpret_cast<const LV*>(xj + (int64_t)(k - kj) * kTile + cc);
-            else rB[e] = LV{};
+                for (int e = 0; e < 4; ++e)
+                    o[e] = lrow + 2 * e >= skip ? o[e] - skip * (kTile * 8) : SlabRows<double, false>::kNone;
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[q][e] = __builtin_amdgcn_raw_buffer_load_b128(r, o[e], 0, 0);
         }
     };
-    auto store_step = [&](int buf) {
+    auto store_step = [&](const v4u (&v)[NS][4], int buf) __attribute__((always_inline)) {
 #pragma unroll
-        for (int e = 0; e < kPer; ++e) {
-            const int idx = threadIdx.x + 256 * e;
-            const int rr = idx / (kTile / kVec);
-            const int cc = kVec * (idx % (kTile / kVec));
-            *reinterpret_cast<LV*>(&sA[buf][rr * kSyrkLd + cc]) = rA[e];
-            if (!diag) *reinterpret_cast<LV*>(&sB[buf][rr * kSyrkLd + cc]) = rB[e];
+        for (int q = 0; q < NS; ++q) {
+            const int side = EDGE == 128 ? q : wv >> 1;
+            if (side && diag) continue;
+            double* d = &lds[buf][side][lrow * kLd + (EDGE == 128 ? 64 * (wv & 1) : 0) + lcol];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) *reinterpret_cast<v4u*>(d + 2 * e * kLd) = v[q][e];
         }
     };
 
-    if (nsteps > 0) {
-        load_step(KS[0]);
-        store_step(0);
-    }
-    __syncthreads();
-    for (int st = 0; st < nsteps; ++st) {
-        const int buf = st & 1;
-        if (st + 1 < nsteps) load_step(KS[st + 1]);
-        const TX* __restrict__ pa = &sA[buf][g * kSyrkLd + 16 * wv + j];
-        const TX* __restrict__ pb = &(diag ? sA : sB)[buf][g * kSyrkLd + j];
+    const int wi = wv >> 1, wj = wv & 1;
+    v4d acc[MT][MT];
+#pragma unroll
+    for (int a = 0; a < MT; ++a)
+#pragma unroll
+        for (int b = 0; b < MT; ++b) acc[a][b] = v4d{0.0, 0.0, 0.0, 0.0};
+    auto entry = [&](int st) { return KS[min(st, nsteps - 1)]; };
+    // step st from LDS buffer `buf`; v: the rows of step st + 1, then st + 3
+    auto step = [&](v4u (&v)[NS][4], int st, int buf) __attribute__((always_inline)) {
+        const int ent = entry(st + 3);
+        const double* pa = &lds[buf][0][g * kLd + wi * (EDGE / 2) + j];
+        const double* pb = &lds[buf][diag ? 0 : 1][g * kLd + wj * (EDGE / 2) + j];
 #pragma unroll
         for (int s = 0; s < kSyrkKC / 4; ++s) {
-            const TX a = pa[4 * s * kSyrkLd];
-            TX b[4];
+            double a[MT], b[MT];
 #pragma unroll
-            for (int t = 0; t < 4; ++t) b[t] = pb[4 * s * kSyrkLd + 16 * t];
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                acc[t] = mfma_f64(a, b[t], acc[t]);
+            for (int t = 0; t < MT; ++t) {
+                a[t] = pa[4 * s * kLd + 16 * t];
+                b[t] = pb[4 * s * kLd + 16 * t];
             }
-        }
-        if (st + 1 < nsteps) store_step(buf ^ 1);
-        __syncthreads();
-    }
-    const int I2 = it.I >> 1, J2 = it.J >> 1;
-    TX* __restrict__ Ft = F + S.F_off + (int64_t)(I2 * (I2 + 1) / 2 + J2) * kFTileElems;
-    const bool mirror = I2 == J2 && !diag;
-    const int r0 = 64 * (it.I & 1) + 16 * wv;
-    const int c0 = 64 * (it.J & 1);
-#pragma unroll
-    for (int t = 0; t < 4; ++t)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int row = r0 + 4 * r + g;
-            const int col = c0 + 16 * t + j;
-            Ft[row * kSyrkTile + col] = acc[t][r];
-            if (mirror) Ft[col * kSyrkTile + row] = acc[t][r];
-        }
-}
-
-__global__ __launch_bounds__(256) void syrk_block_f64(
-    const SubDev* __restrict__ subs, const TileDev* __restrict__ tiles,
-    const SyrkItem* __restrict__ items, const int32_t* __restrict__ ksteps, const double* __restrict__ X,
-    double* __restrict__ F)
-{
-    __shared__ __align__(16) char smem[kSyrkSmem];
-    const SyrkItem it = items[blockIdx.x];
-    if (it.sub < 0) return;
-    syrk_block(subs, tiles, it, ksteps, X, F, smem);
-}
-
-// ---------------------------------------------------------------------------
-// The same SYRK over 128 x 128 tiles (I >= J in units of kSyrkTile), each
-// wavefront a 64 x 64 quadrant (4 x 4 MFMA tiles): twice the MFMA work per
-// byte of X of the 64 x 64 blocks, used for the subdomains whose X slabs are
-// too large to be re-read from L2 (n above kSyrkBlockMaxN, FP32 above
-// kSyrkBlockMaxNMixed).  The k-range is the
-// tile's list of 16-row steps where both column halves can hold nonzero rows;
-// each entry marks which of the four 64-column slabs have nonzero rows in
-// the step (bits at kStepSlabShift), the others read as zero (their rows may
-// never have been written).  Diagonal tiles are computed whole.
-// ---------------------------------------------------------------------------
-constexpr int kWideLd = kSyrkTile + 4;
-constexpr int kWideSmem = 4 * kSyrkKC * kWideLd * 8;
-
-__device__ __forceinline__ void syrk_tile_item_f64(
-    const SubDev* __restrict__ subs, const TileDev* __restrict__ tiles, const SyrkItem it,
-    const int32_t* __restrict__ ksteps, const double* __restrict__ X, double* __restrict__ F,
-    char* __restrict__ smem)
-{
-    double (*sI)[kSyrkKC * kWideLd] = reinterpret_cast<double (*)[kSyrkKC * kWideLd]>(smem);
-    double (*sJ)[kSyrkKC * kWideLd] = sI + 2;
-    const SubDev S = subs[it.sub];
-    const int lane = threadIdx.x & 63;
-    const int wv = threadIdx.x >> 6;
-    const int g = lane >> 4;
-    const int j = lane & 15;
-    const int wi = wv >> 1;
-    const int wj = wv & 1;
-    const int n = S.n;
-
-    // the two 64-column slabs of each 128-column tile (the second may not exist)
-    const double* xs[4];
-    int ks[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const int t64 = 2 * (q < 2 ? it.I : it.J) + (q & 1);
-        if (t64 < S.ntiles) {
-            const TileDev& T = tiles[S.tile_off + t64];
-            xs[q] = X + T.x_off;
-            ks[q] = T.kstart;
-        } else {
-            xs[q] = nullptr;
-            ks[q] = INT_MAX;
-        }
-    }
-    const int32_t* __restrict__ KS = ksteps + it.step_off;
-
-    v4d acc[4][4];
-#pragma unroll
-    for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int b = 0; b < 4; ++b) acc[a][b] = (v4d){0.0, 0.0, 0.0, 0.0};
-
-    // thread -> (row, column pair) of a 16 x 128 step, 4 pairs per operand;
-    // a slab whose bit is clear in the step entry holds no nonzero row there
-    // (its rows may never have been written) and reads as zero
-    double2 rI[4], rJ[4];
-    auto load_step = [&](int ent) {
-        const int kb = ent & kStepRowMask;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int idx = threadIdx.x + 256 * e;
-            const int rr = idx >> 6;
-            const int cc = 2 * (idx & 63);
-            const int half = cc >> 6;
-            const int c = cc & 63;
-            const int k = kb + rr;
-            const int qi = half, qj = 2 + half;
-            const bool li = ((ent >> (kStepSlabShift + qi)) & 1) && k < n && k >= ks[qi];
-            const bool lj = ((ent >> (kStepSlabShift + qj)) & 1) && k < n && k >= ks[qj];
-            rI[e] = li ? *reinterpret_cast<const double2*>(xs[qi] + (int64_t)(k - ks[qi]) * kTile + c)
-                       : make_double2(0.0, 0.0);
-            rJ[e] = lj ? *reinterpret_cast<const double2*>(xs[qj] + (int64_t)(k - ks[qj]) * kTile + c)
-                       : make_double2(0.0, 0.0);
-        }
-    };
-    auto store_step = [&](int buf) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int idx = threadIdx.x + 256 * e;
-            const int rr = idx >> 6;
-            const int cc = 2 * (idx & 63);
-            *reinterpret_cast<double2*>(&sI[buf][rr * kWideLd + cc]) = rI[e];
-            *reinterpret_cast<double2*>(&sJ[buf][rr * kWideLd + cc]) = rJ[e];
-        }
-    };
-
-    const int nsteps = it.nsteps;
-    if (nsteps > 0) {
-        load_step(KS[0]);
-        store_step(0);
-    }
-    __syncthreads();
-    for (int st = 0; st < nsteps; ++st) {
-        const int buf = st & 1;
-        if (st + 1 < nsteps) load_step(KS[st + 1]);
-        {
-#pragma unroll
-            for (int s = 0; s < kSyrkKC / 4; ++s) {
-                const double* ai = &sI[buf][(4 * s + g) * kWideLd + 64 * wi + j];
-                const double* bj = &sJ[buf][(4 * s + g) * kWideLd + 64 * wj + j];
-                double a[4], b[4];
-#pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                    a[t] = ai[16 * t];
-                    b[t] = bj[16 * t];
-                }
-#pragma unroll
-                for (int ti = 0; ti < 4; ++ti)
-#pragma unroll
-                    for (int tj = 0; tj < 4; ++tj) acc[ti][tj] = mfma_f64(a[ti], b[tj], acc[ti][tj]);
+            // the next step goes to LDS before the last products, so that
+            // those cover the write
+            if (s == kSyrkKC / 4 - 1) {
+                __builtin_amdgcn_sched_barrier(0);
+                store_step(v, buf ^ 1);
+                load_step(v, ent, st + 3 < nsteps);
+                __builtin_amdgcn_sched_barrier(0);
             }
+#pragma unroll
+            for (int ta = 0; ta < MT; ++ta)
+#pragma unroll
+                for (int tb = 0; tb < MT; ++tb) acc[ta][tb] = mfma_f64(a[ta], b[tb], acc[ta][tb]);
         }
-        if (st + 1 < nsteps) store_step(buf ^ 1);
-        __syncthreads();
+        lds_barrier();
+    };
+    v4u v0[NS][4], v1[NS][4];                    // two steps in flight
+    load_step(v0, entry(0), nsteps > 0);
+    load_step(v1, entry(1), nsteps > 1);
+    store_step(v0, 0);
+    load_step(v0, entry(2), nsteps > 2);
+    lds_barrier();
+    int st = 0;
+    for (; st + 1 < nsteps; st += 2) {
+        step(v1, st, 0);
+        step(v0, st + 1, 1);
     }
-    double* __restrict__ Ft = F + S.F_off + (int64_t)(it.I * (it.I + 1) / 2 + it.J) * kFTileElems;
+    if (st < nsteps) step(v1, st, 0);
+    const int I2 = EDGE == 128 ? it.I : it.I >> 1, J2 = EDGE == 128 ? it.J : it.J >> 1;
+    double* __restrict__ Ft = F + S.F_off + (int64_t)(I2 * (I2 + 1) / 2 + J2) * kFTileElems;
+    const int r0 = (EDGE == 128 ? 0 : 64 * (it.I & 1)) + wi * (EDGE / 2);
+    const int c0 = (EDGE == 128 ? 0 : 64 * (it.J & 1)) + wj * (EDGE / 2);
+    const bool mirror = EDGE == 64 && I2 == J2 && !diag;
 #pragma unroll
-    for (int ti = 0; ti < 4; ++ti)
+    for (int ta = 0; ta < MT; ++ta)
 #pragma unroll
-        for (int tj = 0; tj < 4; ++tj)
+        for (int tb = 0; tb < MT; ++tb)
 #pragma unroll
-            for (int r = 0; r < 4; ++r)
-                Ft[(64 * wi + 16 * ti + 4 * r + g) * kSyrkTile + 64 * wj + 16 * tj + j] = acc[ti][tj][r];
-}
-
-__global__ __launch_bounds__(256) void syrk_tile_f64(
-    const SubDev* __restrict__ subs, const TileDev* __restrict__ tiles,
-    const SyrkItem* __restrict__ items, const int32_t* __restrict__ ksteps, const double* __restrict__ X,
-    double* __restrict__ F)
-{
-    __shared__ __align__(16) char smem[kWideSmem];
-    const SyrkItem it = items[blockIdx.x];
-    if (it.sub < 0) return;
-    syrk_tile_item_f64(subs, tiles, it, ksteps, X, F, smem);
+            for (int r = 0; r < 4; ++r) {
+                const int row = r0 + 16 * ta + 4 * r + g;
+                const int col = c0 + 16 * tb + j;
+                Ft[row * kSyrkTile + col] = acc[ta][tb][r];
+                if (mirror) Ft[col * kSyrkTile + row] = acc[ta][tb][r];
+            }
 }
 
 // ---------------------------------------------------------------------------
@@ -1060,7 +962,7 @@ hipError_t launch_syrk(const DevTables& t, const SyrkItem* items, int64_t ntile,
             hipLaunchKernelGGL(syrk_split_f32<128>, dim3((unsigned)ntile), dim3(256), 0, stream, t.subs, t.tiles, items,
                                t.ksteps, t.X32, t.F32);
         else
-            hipLaunchKernelGGL(syrk_tile_f64, dim3((unsigned)ntile), dim3(256), 0, stream, t.subs, t.tiles, items,
+            hipLaunchKernelGGL(syrk_f64<128>, dim3((unsigned)ntile), dim3(256), 0, stream, t.subs, t.tiles, items,
                                t.ksteps, t.X, t.F);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
@@ -1070,7 +972,7 @@ hipError_t launch_syrk(const DevTables& t, const SyrkItem* items, int64_t ntile,
             hipLaunchKernelGGL(syrk_split_f32<64>, dim3((unsigned)nblock), dim3(256), 0, stream, t.subs, t.tiles,
                                items + ntile, t.ksteps, t.X32, t.F32);
         else
-            hipLaunchKernelGGL(syrk_block_f64, dim3((unsigned)nblock), dim3(256), 0, stream, t.subs, t.tiles,
+            hipLaunchKernelGGL(syrk_f64<64>, dim3((unsigned)nblock), dim3(256), 0, stream, t.subs, t.tiles,
                                items + ntile, t.ksteps, t.X, t.F);
         return hipGetLastError();
     }

@@ -70,22 +70,23 @@ def test_trsm_reads_only_rows_it_wrote(precision, split):
     ref.destroy()
 
 
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
 @pytest.mark.parametrize("kind", [1, 2])
-def test_mixed_syrk_at_tile_edges(kind):
-    """The mixed SYRK (64 x 64 blocks, 128 x 128 tiles) with first pivots at
+def test_syrk_at_tile_edges(kind, precision):
+    """The SYRK (64 x 64 blocks, 128 x 128 tiles) with first pivots at
     every offset of its 16-row steps, last columns and rows at every remainder
-    and one to three column tiles: F within 1e-5 of the oracle, exactly
+    and one to three column tiles: F within the bar of the oracle, exactly
     symmetric, the two kinds the same bit for bit."""
     subs = []
     for i, (e, m) in enumerate([((3, 2), 1), ((9, 7), 17), ((16, 9), 63), ((15, 13), 65), ((11, 18), 127),
                                 ((14, 17), 129), ((20, 11), 192), ((19, 19), 193)]):
         subs.append(_columns(scgen.box_subdomain("heat", e, 1.0 / 16, i), m, 80 + i))
     subs += [_columns(scgen.box_subdomain("elasticity", (4, 3, 5), 0.2, 5), 140, 90)]
-    plan = _plan(subs, precision="mixed", syrk_kind=kind, block_split="etree", panel_width=48)
-    other = _plan(subs, precision="mixed", syrk_kind=3 - kind, block_split="etree", panel_width=48)
+    plan = _plan(subs, precision=precision, syrk_kind=kind, block_split="etree", panel_width=48)
+    other = _plan(subs, precision=precision, syrk_kind=3 - kind, block_split="etree", panel_width=48)
     for i, s in enumerate(subs):
         F = plan.get_F(i)
         assert np.array_equal(F, F.T) and np.array_equal(F, other.get_F(i)), i
-        assert oracle.relF(F, oracle.schur(s)) <= 1e-5, i
+        assert oracle.relF(F, oracle.schur(s)) <= (1e-12 if precision == "fp64" else 1e-5), i
     plan.destroy()
     other.destroy()
