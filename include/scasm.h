@@ -159,9 +159,10 @@ typedef struct {
  *                    value arrays of sc_factor / sc_preprocess follow that
  *                    pattern
  *   syrk_kind        SYRK work items for every subdomain a tune class does
- *                    not cover: 0 (default) = by size (64 x 64 blocks up to
- *                    16384 rows FP64 / 6144 mixed, 128 x 128 tiles above),
- *                    1 = 64 x 64 blocks, 2 = 128 x 128 tiles
+ *                    not cover: 0 (default) = 128 x 128 tiles where they execute
+ *                    at most 5% (FP64) or 12% (mixed) more products than
+ *                    64 x 64 blocks, else the blocks; 1 = 64 x 64 blocks,
+ *                    2 = 128 x 128 tiles (the same F bit for bit)
  *   disable_pair_merge  0 (default) = the TRSM updates the rows below two
  *                    consecutive factor blocks once for both where the
  *                    first's rows below are the second's rows followed by
@@ -206,9 +207,8 @@ typedef struct {
  * only); a subdomain outside every class takes the plan-wide options.
  *   panel_width   GPU factor block width, 16..64 (0 = plan option)
  *   block_split   0 uniform, 1 elimination-tree ranges, -1 = plan option
- *   syrk_kind     SYRK work items: 0 = by size (64 x 64 blocks up to 16384
- *                 rows FP64 / 6144 mixed, 128 x 128 tiles above), 1 = 64 x
- *                 64 blocks, 2 = 128 x 128 tiles
+ *   syrk_kind     SYRK work items: 0 = by their products (see sc_options_t),
+ *                 1 = 64 x 64 blocks, 2 = 128 x 128 tiles
  *   ms_per_sub    measured assembly time per subdomain of the class sample
  *                 with these settings (output; informational)
  */

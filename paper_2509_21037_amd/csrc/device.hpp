@@ -72,25 +72,29 @@ constexpr int kPruneTiles = sizeof(TA) == 8 ? 2 : 4;
 // X slabs from this size on are out of the 32-bit offsets of a buffer resource
 constexpr int64_t kTrsmSlabBytes = 0xFFFFFF00ll;
 
-// SYRK work item.  Subdomains with n <= kSyrkBlockMaxN (FP64; FP32:
-// kSyrkBlockMaxNMixed): a 64 x 64 block of F
-// (I >= J in units of 64-column X tiles), its k-range a list of 16-row steps
-// (first rows at ksteps[step_off .. step_off + nsteps)) where both X tiles can
-// hold a nonzero row.  Larger subdomains: a 128 x 128 tile of F (I >= J in
-// units of kSyrkTile), each step entry = first row | slab bits <<
-// kStepSlabShift, bit q set when 64-column slab q (2I, 2I+1, 2J, 2J+1) has a
-// nonzero row in the step.  Every other step adds zero products.  Also used,
-// in units of kSyrkTile and without steps, for the stored F tiles of the apply.
+// SYRK work item: a 64 x 64 block of F (I >= J in units of 64-column X
+// tiles), its k-range a list of 16-row steps (first rows at
+// ksteps[step_off .. step_off + nsteps)) where both X tiles can hold a nonzero
+// row; or a 128 x 128 tile of F (I >= J in units of kSyrkTile), each step entry
+// = first row | slab bits << kStepSlabShift, bit q set when 64-column slab q
+// (2I, 2I+1, 2J, 2J+1) has a nonzero row in the step.  Every other step adds
+// zero products.  Also used, in units of kSyrkTile and without steps, for the
+// stored F tiles of the apply.
 struct SyrkItem {
     int32_t sub;
     int32_t I, J;
     int32_t nsteps;
     int64_t step_off;
 };
-// measured on the elasticity batches: the FP64 blocks beat the tiles up to
-// n = 14739 and lose at 27783; the FP32 tiles win above ~6000
-constexpr int kSyrkBlockMaxN = 16384;
-constexpr int kSyrkBlockMaxNMixed = 6144;
+// Blocks or tiles, per subdomain: the tiles where the products they execute
+// (zero columns of a slab included) are at most this multiple of the blocks'.
+// A tile reads half as much X per product, a block skips more zeros: 2.2 times
+// fewer products on a 2D mesh of 129^2 nodes (m = 512), 1.04 times on a 20^3
+// elasticity box.  Measured, blocks / tiles at products tiles : blocks: FP64
+// 0.39 / 0.89 ms at 2.25, 7.04 / 7.24 at 1.064, 8.19 / 8.22 at 1.054, 14.1 /
+// 13.5 at 1.051, 13.7 / 12.5 at 1.036; mixed 0.134 / 0.258 at 2.25, 1.14 / 1.18
+// at 1.143, 1.46 / 1.44 at 1.112, 2.73 / 2.51 at 1.054.
+constexpr double kSyrkTileCost = 1.053, kSyrkTileCostMixed = 1.12;
 constexpr int kStepSlabShift = 27;
 constexpr int kStepRowMask = (1 << kStepSlabShift) - 1;   // rows below 2^27 (checked at plan creation)
 

@@ -374,7 +374,7 @@ struct sc_plan_s {
     // temporary-memory waves (arena_cap_bytes > 0): X elements the cap holds;
     // the groups are then waves that reuse one X buffer one after the other
     int64_t arena_elems = 0;
-    std::vector<int32_t> syrk_kind;             // per subdomain: 0 by size, 1 blocks, 2 tiles
+    std::vector<int32_t> syrk_kind;             // per subdomain: 0 by their products, 1 blocks, 2 tiles
     // the TRSM kernel with the merged pairs: when they save at least
     // kMergeMinShare of the batch's pruned-row updates
     bool trsm_merge = false;
@@ -726,8 +726,19 @@ sc_status_t sc_plan_create(const sc_subdomain_desc_t* sd, int32_t nsub, const sc
             auto mask = [&](int32_t t64, int32_t q) -> uint64_t {
                 return t64 < s.ntiles ? sp.step_mask[(size_t)t64 * nw + q] : 0;
             };
-            const bool blocks = P->syrk_kind[i] == 1 ||
-                                (P->syrk_kind[i] == 0 && sp.n <= (P->mixed ? kSyrkBlockMaxNMixed : kSyrkBlockMaxN));
+            bool blocks = P->syrk_kind[i] == 1;
+            if (P->syrk_kind[i] == 0) {                // fewer products, or fewer X reads
+                int64_t nblock = 0, ntile = 0;         // steps
+                for (int32_t I = 0; I < s.ntiles && !impl; ++I)
+                    for (int32_t J = 0; J <= I; ++J)
+                        for (int32_t q = 0; q < nw; ++q) nblock += __builtin_popcountll(mask(I, q) & mask(J, q));
+                for (int32_t I = 0; I < nst && !impl; ++I)
+                    for (int32_t J = 0; J <= I; ++J)
+                        for (int32_t q = 0; q < nw; ++q)
+                            ntile += __builtin_popcountll((mask(2 * I, q) | mask(2 * I + 1, q)) &
+                                                          (mask(2 * J, q) | mask(2 * J + 1, q)));
+                blocks = 4.0 * (double)ntile > (P->mixed ? kSyrkTileCostMixed : kSyrkTileCost) * (double)nblock;
+            }
             if (blocks) {
                 for (int32_t I = 0; I < s.ntiles; ++I)
                     for (int32_t J = 0; J <= I; ++J) {
@@ -2018,29 +2029,27 @@ sc_status_t sc_autotune_classes(const sc_subdomain_desc_t* sd, int32_t nsub, con
                 o.ntune_classes = 1;
                 return time_candidate(sub.data(), ns, o, vals.data(), reps, stream, e0, e1, ms);
             };
-            // SYRK kind the size rule gives this class's largest sample member
-            const int32_t nmax = sub[ns - 1].n;
-            const int32_t by_size = nmax <= (o0.precision == SC_PREC_MIXED ? kSyrkBlockMaxNMixed : kSyrkBlockMaxN) ? 1 : 2;
+            const int32_t first_kind = 1;              // SYRK kind while the others are searched
             double best = 0.0, t = 0.0;
-            status = run(64, 0, by_size, &best);
+            status = run(64, 0, first_kind, &best);
             out.panel_width = 64;
             out.block_split = 0;
-            out.syrk_kind = by_size;
-            if (status == SC_OK && (status = run(64, 1, by_size, &t)) == SC_OK && t < best) {
+            out.syrk_kind = first_kind;
+            if (status == SC_OK && (status = run(64, 1, first_kind, &t)) == SC_OK && t < best) {
                 best = t;
                 out.block_split = 1;
             }
             for (int32_t pw : {32, 48}) {
                 if (status != SC_OK) break;
-                if ((status = run(pw, out.block_split, by_size, &t)) == SC_OK && t < best) {
+                if ((status = run(pw, out.block_split, first_kind, &t)) == SC_OK && t < best) {
                     best = t;
                     out.panel_width = pw;
                 }
             }
-            if (status == SC_OK && (status = run(out.panel_width, out.block_split, 3 - by_size, &t)) == SC_OK &&
+            if (status == SC_OK && (status = run(out.panel_width, out.block_split, 3 - first_kind, &t)) == SC_OK &&
                 t < best) {
                 best = t;
-                out.syrk_kind = 3 - by_size;
+                out.syrk_kind = 3 - first_kind;
             }
             out.ms_per_sub = (float)(best / ns);
             char line[512];
