@@ -21,7 +21,7 @@ namespace scasm {
 // through pi; diagonal tiles are stored whole, v unused); pass 2, one
 // workgroup per 128-row block K of a subdomain, sums u of (K, J <= K) and v
 // of (I > K, K) in a fixed order and scatters the result to q in multiplier
-// order.  Deterministic; reads F once, about half of the dense m x m.
+// order (a subdomain of one tile, m <= 128, has no pass 2: pass 1 writes q).  Deterministic; reads F once, about half of the dense m x m.
 // The partial sums of stored tile k live at part[(k - part_base) * 256]: the
 // plan-owned buffer holds every tile (part_base 0); the fixed scratch array of
 // the allocation-free apply holds one chunk of subdomains at a time.
@@ -50,7 +50,8 @@ __device__ __forceinline__ void load8(const T* __restrict__ src, double (&t)[8])
 template <class T>
 __global__ __launch_bounds__(256) void symv_tiles(
     const SubDev* __restrict__ subs, const SyrkItem* __restrict__ ftiles, const T* __restrict__ F,
-    const int32_t* __restrict__ pi, const double* __restrict__ p, double* __restrict__ part, int64_t part_base)
+    const int32_t* __restrict__ pi, const double* __restrict__ p, double* __restrict__ part, int64_t part_base,
+    double* __restrict__ q)
 {
     __shared__ double sp[2][kSyrkTile];                 // p_s of the tile's columns (J) and rows (I)
     __shared__ double su[kSyrkTile][17];                // row sums per group of 8 columns
@@ -102,22 +103,42 @@ __global__ __launch_bounds__(256) void symv_tiles(
 #pragma unroll
         for (int g = 0; g < 16; ++g) acc += sv[k][g];
     }
+    if (S.m <= kSyrkTile) {                             // the only tile: u is the result
+        if (tid < S.m) q[S.dual_off + pi[S.col_off + tid]] = acc;
+        return;
+    }
     part[((S.ftile_off + tile - part_base) << 8) + tid] = acc;
 }
 
-__global__ __launch_bounds__(128) void symv_rows(
+// 128 rows x kRowParts threads, each a share of the row block's partial sums
+// (four loads in flight), combined in LDS.  16 x 20^3 elasticity (62 tiles per
+// row block): 34 us with one thread per row, now 14.7;
+// 64 uneven boxes (37 tiles) 19.2 / 8.2 us.
+constexpr int kRowParts = 4;
+
+__global__ __launch_bounds__(128 * kRowParts) void symv_rows(
     const SubDev* __restrict__ subs, const int2* __restrict__ frows, const int32_t* __restrict__ pi,
     const double* __restrict__ part, int64_t part_base, double* __restrict__ q)
 {
+    __shared__ double sum[kRowParts][kSyrkTile];
     const int2 it = frows[blockIdx.x];                  // (subdomain, row block K)
     const SubDev S = subs[it.x];
     const int K = it.y;
-    const int r = threadIdx.x;
+    const int r = threadIdx.x & (kSyrkTile - 1);
+    const int pt = threadIdx.x / kSyrkTile;
     const int nt = (S.m + kSyrkTile - 1) / kSyrkTile;
     const double* __restrict__ P = part + ((S.ftile_off - part_base) << 8);
     double y = 0.0;
-    for (int J = 0; J <= K; ++J) y += P[(((int64_t)K * (K + 1) / 2 + J) << 8) + r];
-    for (int I = K + 1; I < nt; ++I) y += P[(((int64_t)I * (I + 1) / 2 + K) << 8) + 128 + r];
+#pragma unroll 4
+    for (int T = pt; T < nt; T += kRowParts) {          // u of tile (K, T), or v of tile (T, K)
+        const int64_t hi = max(K, T), lo = min(K, T);
+        y += P[((hi * (hi + 1) / 2 + lo) << 8) + (T > K ? 128 : 0) + r];
+    }
+    sum[pt][r] = y;
+    __syncthreads();
+    if (pt) return;
+#pragma unroll
+    for (int k = 1; k < kRowParts; ++k) y += sum[k][r];
     const int a = K * kSyrkTile + r;
     if (a < S.m) q[S.dual_off + pi[S.col_off + a]] = y;
 }
@@ -129,13 +150,13 @@ static hipError_t apply_range(const DevTables& t, const double* p, double* q, do
     if (t1 <= t0) return hipSuccess;
     if (t.F32)
         hipLaunchKernelGGL(symv_tiles<float>, dim3((unsigned)(t1 - t0)), dim3(256), 0, stream, t.subs,
-                           t.ftiles + t0, (const float*)t.F32, t.pi, p, part, t0);
+                           t.ftiles + t0, (const float*)t.F32, t.pi, p, part, t0, q);
     else
         hipLaunchKernelGGL(symv_tiles<double>, dim3((unsigned)(t1 - t0)), dim3(256), 0, stream, t.subs,
-                           t.ftiles + t0, (const double*)t.F, t.pi, p, part, t0);
+                           t.ftiles + t0, (const double*)t.F, t.pi, p, part, t0, q);
     hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(symv_rows, dim3((unsigned)(r1 - r0)), dim3(128), 0, stream, t.subs, t.frows + r0, t.pi,
+    if (e != hipSuccess || r1 <= r0) return e;
+    hipLaunchKernelGGL(symv_rows, dim3((unsigned)(r1 - r0)), dim3(128 * kRowParts), 0, stream, t.subs, t.frows + r0, t.pi,
                        (const double*)part, t0, q);
     return hipGetLastError();
 }
@@ -261,7 +282,7 @@ hipError_t launch_apply_chunked(const DevTables& t, const ApplyChunk* chunks, in
 // ---------------------------------------------------------------------------
 // Projected conjugate gradients on each subdomain's dual problem (Sec. 2.1,
 // eq. (7), with e = 0 and the identity preconditioner), FP64 vectors; the
-// per-subdomain scalars stay on the device.  One workgroup per subdomain.
+// per-subdomain scalars stay on the device.
 //   lambda_0 = 0, r_0 = d, w_0 = P r_0, p_0 = w_0,  P = I - G (G^T G)^{-1} G^T
 //   q = F p;  alpha = (w.w)/(p.q);  lambda += alpha p;  r -= alpha q
 //   w' = P r;  beta = (w'.w')/(w.w);  p = w' + beta p
@@ -282,99 +303,143 @@ struct PcpgDev {
     int32_t nsub;
 };
 
-__device__ double block_sum(double v, double* red) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
-    __syncthreads();
-    double t = 0.0;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) t += red[i];
-    return t;
-}
+// One workgroup of NT threads per subdomain; thread i owns the rows i, i + NT,
+// ... of every vector, so only the sums need barriers.  Bound by latency (the
+// vectors are a few tens of KB): three reductions per step, the kernel
+// dimension's dot products in one of them.  64 uneven elasticity boxes (m up
+// to 4614, k = 6): 84 us per step with 256 threads and one reduction per dot
+// product, now 38.
+template <int NT>
+struct BlockSums {
+    double part[kMaxKer][NT / 64];
+};
 
-// w = r - G (G^T G)^{-1} G^T r over one subdomain; returns w.w
-__device__ double project(const SubDev& S, const PcpgDev& D, int sub, const double* r, double* w, double* red,
-                          double* su) {
-    const int m = S.m;
-    const int k = D.kdim[sub];
-    const double* G = D.G + D.g_off[sub];
-    for (int c = 0; c < k; ++c) {
+// sums of v[0 .. k) over the workgroup, to all threads, in a fixed order
+template <int NT>
+__device__ __forceinline__ void block_sums(double (&v)[kMaxKer], int k, BlockSums<NT>& red) {
+#pragma unroll
+    for (int c = 0; c < kMaxKer; ++c) {
+        if (c >= k) break;
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) v[c] += __shfl_xor(v[c], off, 64);
+    }
+    __syncthreads();                             // the last sums have been read
+    if ((threadIdx.x & 63) == 0)
+        for (int c = 0; c < k; ++c) red.part[c][threadIdx.x >> 6] = v[c];
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < kMaxKer; ++c) {
+        if (c >= k) break;
         double t = 0.0;
-        for (int i = threadIdx.x; i < m; i += 256) t += G[(int64_t)c * m + i] * r[i];
-        t = block_sum(t, red);
-        if (threadIdx.x == 0) su[c] = t;
+#pragma unroll
+        for (int i = 0; i < NT / 64; ++i) t += red.part[c][i];
+        v[c] = t;
     }
-    __syncthreads();
-    if ((int)threadIdx.x < k) {
-        double u = 0.0;
-        for (int c = 0; c < k; ++c) u += D.GtGinv[64 * sub + threadIdx.x * k + c] * su[c];
-        su[kMaxKer + threadIdx.x] = u;
-    }
-    __syncthreads();
-    double ww = 0.0;
-    for (int i = threadIdx.x; i < m; i += 256) {
-        double v = r[i];
-        for (int c = 0; c < k; ++c) v -= G[(int64_t)c * m + i] * su[kMaxKer + c];
-        w[i] = v;
-        ww += v * v;
-    }
-    return block_sum(ww, red);
 }
 
-__global__ __launch_bounds__(256) void pcpg_init(const SubDev* __restrict__ subs, PcpgDev D,
-                                                 const double* __restrict__ d, double* __restrict__ lambda) {
-    __shared__ double red[4];
-    __shared__ double su[2 * kMaxKer];
-    const int sub = blockIdx.x;
-    const SubDev S = subs[sub];
-    const int64_t o = S.dual_off;
-    for (int i = threadIdx.x; i < S.m; i += 256) {
-        lambda[o + i] = 0.0;
-        D.r[o + i] = d[o + i];
+// w = r - G (G^T G)^{-1} G^T r over one subdomain, gr = G^T r; returns w.w
+template <int NT>
+__device__ __forceinline__ double project(int m, const PcpgDev& D, int sub, double (&gr)[kMaxKer], const double* r,
+                                          double* w, BlockSums<NT>& red) {
+    const int k = D.kdim[sub];
+    const double* __restrict__ G = D.G + D.g_off[sub];
+    block_sums<NT>(gr, k, red);
+    double u[kMaxKer];
+#pragma unroll
+    for (int a = 0; a < kMaxKer; ++a) {
+        u[a] = 0.0;
+        if (a < k)
+#pragma unroll
+            for (int c = 0; c < kMaxKer; ++c)
+                if (c < k) u[a] += D.GtGinv[64 * sub + a * k + c] * gr[c];
     }
-    __syncthreads();
-    const double ww = project(S, D, sub, D.r + o, D.w + o, red, su);
-    for (int i = threadIdx.x; i < S.m; i += 256) D.pvec[o + i] = D.w[o + i];
+    double ww[kMaxKer];
+    ww[0] = 0.0;
+#pragma unroll 2
+    for (int i = threadIdx.x; i < m; i += NT) {
+        double v = r[i];
+#pragma unroll
+        for (int c = 0; c < kMaxKer; ++c)
+            if (c < k) v -= G[(int64_t)c * m + i] * u[c];
+        w[i] = v;
+        ww[0] += v * v;
+    }
+    block_sums<NT>(ww, 1, red);
+    return ww[0];
+}
+
+template <int NT>
+__global__ __launch_bounds__(NT) void pcpg_init(const SubDev* __restrict__ subs, PcpgDev D,
+                                                const double* __restrict__ d, double* __restrict__ lambda) {
+    __shared__ BlockSums<NT> red;
+    const int sub = blockIdx.x;
+    const int m = subs[sub].m;
+    const int64_t o = subs[sub].dual_off;
+    const int k = D.kdim[sub];
+    const double* __restrict__ G = D.G + D.g_off[sub];
+    double gr[kMaxKer] = {};
+    for (int i = threadIdx.x; i < m; i += NT) {
+        const double v = d[o + i];
+        lambda[o + i] = 0.0;
+        D.r[o + i] = v;
+#pragma unroll
+        for (int c = 0; c < kMaxKer; ++c)
+            if (c < k) gr[c] += G[(int64_t)c * m + i] * v;
+    }
+    const double ww = project<NT>(m, D, sub, gr, D.r + o, D.w + o, red);
+    for (int i = threadIdx.x; i < m; i += NT) D.pvec[o + i] = D.w[o + i];
     if (threadIdx.x == 0) {
         D.ww[sub] = ww;
         if (D.hist) D.hist[sub] = sqrt(ww);
     }
 }
 
-__global__ __launch_bounds__(256) void pcpg_step(const SubDev* __restrict__ subs, PcpgDev D,
-                                                 double* __restrict__ lambda, int iter) {
-    __shared__ double red[4];
-    __shared__ double su[2 * kMaxKer];
+template <int NT>
+__global__ __launch_bounds__(NT) void pcpg_step(const SubDev* __restrict__ subs, PcpgDev D,
+                                                double* __restrict__ lambda, int iter) {
+    __shared__ BlockSums<NT> red;
     const int sub = blockIdx.x;
-    const SubDev S = subs[sub];
-    const int64_t o = S.dual_off;
-    const int m = S.m;
+    const int m = subs[sub].m;
+    const int64_t o = subs[sub].dual_off;
+    const int k = D.kdim[sub];
+    const double* __restrict__ G = D.G + D.g_off[sub];
     double* r = D.r + o;
     double* w = D.w + o;
     double* pv = D.pvec + o;
     const double* q = D.q + o;
     const double ww = D.ww[sub];
-    double pq = 0.0;
-    for (int i = threadIdx.x; i < m; i += 256) pq += pv[i] * q[i];
-    pq = block_sum(pq, red);
-    const bool go = pq > 0.0 && ww > 0.0;       // converged (or breakdown): keep the iterate
-    const double alpha = go ? ww / pq : 0.0;
-    for (int i = threadIdx.x; i < m; i += 256) {
+    double pq[kMaxKer];
+    pq[0] = 0.0;
+#pragma unroll 4
+    for (int i = threadIdx.x; i < m; i += NT) pq[0] += pv[i] * q[i];
+    block_sums<NT>(pq, 1, red);
+    const bool go = pq[0] > 0.0 && ww > 0.0;    // converged (or breakdown): keep the iterate
+    const double alpha = go ? ww / pq[0] : 0.0;
+    double gr[kMaxKer] = {};
+#pragma unroll 2
+    for (int i = threadIdx.x; i < m; i += NT) {
         lambda[o + i] += alpha * pv[i];
-        r[i] -= alpha * q[i];
+        const double v = r[i] - alpha * q[i];
+        r[i] = v;
+#pragma unroll
+        for (int c = 0; c < kMaxKer; ++c)
+            if (c < k) gr[c] += G[(int64_t)c * m + i] * v;
     }
-    __syncthreads();
-    const double ww2 = go ? project(S, D, sub, r, w, red, su) : ww;
+    const double ww2 = go ? project<NT>(m, D, sub, gr, r, w, red) : ww;
     const double beta = go ? ww2 / ww : 0.0;
     if (go)
-        for (int i = threadIdx.x; i < m; i += 256) pv[i] = w[i] + beta * pv[i];
+#pragma unroll 4
+        for (int i = threadIdx.x; i < m; i += NT) pv[i] = w[i] + beta * pv[i];
     if (threadIdx.x == 0) {
         D.ww[sub] = ww2;
         if (D.hist) D.hist[(int64_t)(iter + 1) * D.nsub + sub] = sqrt(ww2);
     }
 }
+
+// Threads per subdomain: 1024 from this mean number of multipliers on (5 rows
+// a thread at m = 4614); below, 256 threads cover them in as few rounds and
+// more subdomains share a CU.
+constexpr int64_t kPcpgWideFrom = 768;
 
 hipError_t launch_pcpg(const DevTables& t, const PcpgArgs& a, hipStream_t stream, const ImplicitLevels* lvh,
                        const int64_t* xoff, double* xwork, int32_t nimpl) {
@@ -382,14 +447,18 @@ hipError_t launch_pcpg(const DevTables& t, const PcpgArgs& a, hipStream_t stream
     D.G = a.G; D.g_off = a.g_off; D.kdim = a.kdim; D.GtGinv = a.GtGinv;
     D.r = a.r; D.w = a.w; D.pvec = a.p; D.q = a.q; D.ww = a.ww; D.hist = a.hist; D.nsub = a.nsub;
     if (a.nsub <= 0) return hipSuccess;
-    hipLaunchKernelGGL(pcpg_init, dim3((unsigned)a.nsub), dim3(256), 0, stream, t.subs, D, a.d, a.lambda);
+    const bool wide = a.dual_total >= kPcpgWideFrom * a.nsub;
+    const dim3 grid((unsigned)a.nsub);
+    if (wide) hipLaunchKernelGGL(pcpg_init<1024>, grid, dim3(1024), 0, stream, t.subs, D, a.d, a.lambda);
+    else hipLaunchKernelGGL(pcpg_init<256>, grid, dim3(256), 0, stream, t.subs, D, a.d, a.lambda);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     for (int it = 0; it < a.iters; ++it) {
         if ((e = launch_apply(t, a.p, a.q, stream, nullptr)) != hipSuccess) return e;
         if (lvh && (e = launch_apply_implicit(t, *lvh, xoff, xwork, a.p, a.q, nimpl, stream, nullptr)) != hipSuccess)
             return e;
-        hipLaunchKernelGGL(pcpg_step, dim3((unsigned)a.nsub), dim3(256), 0, stream, t.subs, D, a.lambda, it);
+        if (wide) hipLaunchKernelGGL(pcpg_step<1024>, grid, dim3(1024), 0, stream, t.subs, D, a.lambda, it);
+        else hipLaunchKernelGGL(pcpg_step<256>, grid, dim3(256), 0, stream, t.subs, D, a.lambda, it);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     return hipSuccess;

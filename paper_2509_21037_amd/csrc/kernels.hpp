@@ -71,6 +71,7 @@ struct PcpgArgs {
     double* hist;           // [(iters + 1) * nsub] or null
     int32_t nsub;
     int32_t iters;
+    int64_t dual_total;     // multipliers of all subdomains
 };
 
 struct ImplicitLevels;

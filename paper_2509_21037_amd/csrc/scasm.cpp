@@ -715,7 +715,7 @@ sc_status_t sc_plan_create(const sc_subdomain_desc_t* sd, int32_t nsub, const sc
         const int32_t nst = (sp.m + kSyrkTile - 1) / kSyrkTile;
         s.ftile_off = (int64_t)P->h_ftiles.size();
         for (int32_t I = 0; I < nst && !impl; ++I) {     // implicit subdomains: no F
-            P->h_frows.push_back(make_int2(i, I));
+            if (nst > 1) P->h_frows.push_back(make_int2(i, I));   // one tile: pass 1 alone
             for (int32_t J = 0; J <= I; ++J) P->h_ftiles.push_back(SyrkItem{i, I, J, 0, 0});
         }
         {
@@ -1008,7 +1008,7 @@ sc_status_t sc_plan_create(const sc_subdomain_desc_t* sd, int32_t nsub, const sc
                 cur = ApplyChunk{cur.t1, cur.t1, cur.r1, cur.r1};
             }
             cur.t1 += nt;
-            cur.r1 += nst;
+            cur.r1 += nst > 1 ? nst : 0;
         }
         if (cur.t1 > cur.t0) P->h_chunks.push_back(cur);
     }
@@ -1431,6 +1431,7 @@ sc_status_t sc_pcpg(sc_plan_t P, const double* const* R_host, const int32_t* k_h
         a.d = d_dev; a.lambda = lambda_dev;
         a.r = dwork.p; a.w = dwork.p + nd; a.p = dwork.p + 2 * nd; a.q = dwork.p + 3 * nd;
         a.ww = dww.p; a.hist = dhist.p; a.nsub = P->nsub; a.iters = iters;
+        a.dual_total = P->dual_total;
         e = launch_pcpg(P->tables(), a, st, P->n_implicit > 0 ? &P->ilv_h : nullptr, P->d_xoff.p, P->d_xwork.p,
                         P->n_implicit);
     }

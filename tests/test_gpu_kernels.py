@@ -90,3 +90,43 @@ def test_syrk_at_tile_edges(kind, precision):
         assert oracle.relF(F, oracle.schur(s)) <= (1e-12 if precision == "fp64" else 1e-5), i
     plan.destroy()
     other.destroy()
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+def test_apply_and_pcpg_at_tile_edges(precision):
+    """q = F p through both explicit applies, and one projected CG step count
+    of each workgroup width, at m around the stored 128 x 128 tiles: against
+    the dense product of the assembled F (FP64 sums of at most 400 terms: 1e-13
+    of their size) and against the oracle's CG on that F."""
+    import torch
+    box = scgen.box_subdomain("heat", (20, 14), 1.0 / 20, seed=3)
+    wide = scgen.box_subdomain("elasticity", (6, 7, 8), 1.0 / 8, seed=4)
+    for subs in ([_columns(box, m, 140 + m) for m in (1, 127, 128, 129, 256, 257, 400)],
+                 [wide, _columns(box, 100, 7)]):
+        plan = _plan(subs, precision=precision)
+        rng = np.random.default_rng(9)
+        p = torch.from_numpy(rng.uniform(-1, 1, plan.dual_total)).cuda()
+        q, q2 = torch.zeros_like(p), torch.zeros_like(p)
+        plan.apply(p, q)
+        plan.apply_noalloc(p, q2)
+        assert torch.equal(q, q2)
+        for i, s in enumerate(subs):
+            o, F = plan.query(i)["dual_offset"], plan.get_F(i)
+            x = p[o:o + s.m].cpu().numpy()
+            bound = 1e-13 * (np.abs(F) @ np.abs(x))
+            assert np.all(np.abs(q[o:o + s.m].cpu().numpy() - F @ x) <= bound), s.m
+        plan.destroy()
+    subs = [scgen.box_subdomain("elasticity", e, 1.0 / 8, 20 + i) for i, e in enumerate([(6, 7, 8), (7, 7, 7)])]
+    for batch in (subs, [scgen.box_subdomain("elasticity", (2, 3, 2), 0.5, 30)]):
+        plan = _plan(batch, precision=precision)
+        d = torch.from_numpy(np.random.default_rng(8).uniform(-1, 1, plan.dual_total)).cuda()
+        lam = torch.zeros_like(d)
+        plan.pcpg(d, lam, 4)
+        for i, s in enumerate(batch):
+            o = plan.query(i)["dual_offset"]
+            G = s.sign[:, None] * s.R[s.dof]
+            ref = oracle.pcpg(plan.get_F(i), G, d[o:o + s.m].cpu().numpy(), 4)
+            ref = ref[0] if isinstance(ref, tuple) else ref
+            got = lam[o:o + s.m].cpu().numpy()
+            assert np.linalg.norm(got - ref) <= 1e-9 * np.linalg.norm(ref), i
+        plan.destroy()
