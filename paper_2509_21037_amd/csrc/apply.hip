@@ -475,8 +475,8 @@ hipError_t launch_pcpg(const DevTables& t, const PcpgArgs& a, hipStream_t stream
 //   forward, block b:   y_b = L_bb^{-1} (x_b - sum of the update entries of
 //                       its rows), then u_b = L[R_b, b] y_b into the update
 //                       buffer (parallel to the pruned-row lists); a row's
-//                       entries are summed by its own thread in a fixed order
-//                       (planner lists), no atomics
+//                       entries are summed in a fixed order (planner lists),
+//                       no atomics
 //   backward, block b:  z_b = L_bb^{-T} (y_b - L[R_b, b]^T z[R_b])
 // The diagonal inverses are the ones the TRSM uses.  Repeated DOFs (several
 // multipliers on one DOF) are summed by one thread per run of equal pivots.
@@ -492,37 +492,46 @@ __device__ __forceinline__ double linv_at(const double* __restrict__ Lv, int r, 
     return Lv[(2 * rt * (rt + 1) + (k >> 2)) * 64 + (r & 15) + 16 * (k & 3)];
 }
 
-// one 1024-thread workgroup per subdomain (x has n_i entries: ~30k on the
-// 20^3 subdomains)
+// x = P B^T p and q = B P^T x: 1024-thread workgroups, on small batches up to
+// kInitSplit per subdomain, each a share of the rows (it walks all multipliers
+// and keeps those whose pivot is in its share) or of the multipliers.
+// 16 x 20^3 elasticity (27783 rows, 7938 multipliers): 30 + 10 us with one per
+// subdomain, now 11 + 5.
 constexpr int kInitThreads = 1024;
+constexpr int kInitSplit = 8;
+static inline int init_split(int64_t subdomains) {
+    return (int)std::max<int64_t>(1, std::min<int64_t>(kInitSplit, 256 / subdomains));
+}
 
 __global__ __launch_bounds__(kInitThreads) void implicit_init(
     const SubDev* __restrict__ subs, const int32_t* __restrict__ piv, const int32_t* __restrict__ pi,
     const int8_t* __restrict__ sgn, const int64_t* __restrict__ xoff, const double* __restrict__ p,
-    double* __restrict__ xwork, const int32_t* __restrict__ sub_list)
+    double* __restrict__ xwork, const int32_t* __restrict__ sub_list, int C)
 {
-    const int sub = sub_list ? sub_list[blockIdx.x] : (int)blockIdx.x;
+    const int at = (int)blockIdx.x / C, c = (int)blockIdx.x % C;
+    const int sub = sub_list ? sub_list[at] : at;
     const SubDev S = subs[sub];
     double* __restrict__ x = xwork + xoff[sub];
     const int32_t* __restrict__ pv = piv + S.col_off;
     const int32_t* __restrict__ pis = pi + S.col_off;
     const int8_t* __restrict__ sg = sgn + S.col_off;
     const double* __restrict__ ps = p + S.dual_off;
-    for (int i = threadIdx.x; i < S.n; i += kInitThreads) x[i] = 0.0;
+    const int r0 = (int)((int64_t)S.n * c / C), r1 = (int)((int64_t)S.n * (c + 1) / C);
+    for (int i = r0 + threadIdx.x; i < r1; i += kInitThreads) x[i] = 0.0;
     __syncthreads();
     for (int a = threadIdx.x; a < S.m; a += kInitThreads) {
-        if (a > 0 && pv[a - 1] == pv[a]) continue;
+        const int row = pv[a];
+        if (row < r0 || row >= r1 || (a > 0 && pv[a - 1] == row)) continue;
         double v = 0.0;
-        for (int b = a; b < S.m && pv[b] == pv[a]; ++b) v += (double)sg[b] * ps[pis[b]];
-        x[pv[a]] = v;
+        for (int b = a; b < S.m && pv[b] == row; ++b) v += (double)sg[b] * ps[pis[b]];
+        x[row] = v;
     }
 }
 
-// One block step per workgroup of kImplThreads threads: thread (part, r) =
-// (tid / 64, tid % 64) works on row / column r and a 1/kImplParts share of
-// each sum; partial sums meet in LDS in a fixed order.  The blocks of a level
-// are few (the chain of one subdomain each), so each step spreads its short
-// dependent sums over many threads.
+// One block step per workgroup of kImplThreads threads (16 wavefronts): the
+// blocks of a level are few (the chain of one subdomain each), so each step
+// spreads its short dependent sums over many threads; partial sums meet in
+// LDS in a fixed order.
 constexpr int kImplThreads = 1024;
 constexpr int kImplParts = kImplThreads / 64;
 // factor tiles each wavefront has in flight in the off-diagonal products:
@@ -530,8 +539,22 @@ constexpr int kImplParts = kImplThreads / 64;
 // latency is the level's time), 8 on wide levels (two workgroups per CU
 // share the memory system)
 constexpr int kImplBatchNarrow = 16, kImplBatchWide = 8;
+// Levels of fewer blocks than this split each block over up to kImplSplit
+// workgroups, as many as fill the chip twice.  Forward, each repeats the
+// update sums and the diagonal product and takes its share of the row tiles
+// (at least one per wavefront).  Backward, a first launch sums shares of the
+// rows, a second adds them and does the diagonal product: from
+// kImplBwdSplitRows rows on in a block of the level (the second launch costs 4
+// us, a row tile in one workgroup about 0.15 us).  16 x 20^3 elasticity,
+// levels of 16-32 blocks of up to 1600 rows: forward 15.8 us with 4 shares and
+// a load at a time in the update sums, now 13.7; backward 19.1 us in one
+// launch, now 10.6 + 4.2 in two (7.3 in one for blocks below 512 rows).
 constexpr int64_t kImplNarrowBelow = 256;
-constexpr int kImplSplit = 4;
+constexpr int kImplSplit = 8;
+constexpr int kImplBwdSplitRows = 512;
+static inline int impl_split(int64_t blocks, int tiles) {
+    return (int)std::max<int64_t>(1, std::min<int64_t>({kImplSplit, 512 / blocks, tiles}));
+}
 
 __device__ __forceinline__ double sum_parts(const double (*sp)[64], int r) {
     double v = 0.0;
@@ -540,47 +563,75 @@ __device__ __forceinline__ double sum_parts(const double (*sp)[64], int r) {
     return v;
 }
 
-// forward step of block bd of subdomain S: x_b <- L_bb^{-1}(x_b - updates),
-// then its updates L[R_b, b] x_b into its entries of ubuf
-template <int NB>
+// forward step of block b: x_b <- L_bb^{-1}(x_b - updates), then its updates
+// L[R_b, b] x_b into its entries of ubuf; share g of G of the row tiles.
+// EARLY (narrow levels): the loads of the diagonal inverse and of the first
+// factor tiles are in flight during the update sums.
+template <int NB, bool EARLY>
 __device__ __forceinline__ void implicit_fwd_block(
-    const SubDev& S, const BlockDev& bd, const double* __restrict__ lval, const int32_t* __restrict__ rp,
+    const ImplBlock& b, const double* __restrict__ lval, const int32_t* __restrict__ rptr,
     const int32_t* __restrict__ rpos, const double* __restrict__ x, double* __restrict__ yo,
-    double* __restrict__ ubuf, double (*sp)[64], double* sx, int g = 0, int G = 1)
+    double* ubuf, double (*sp)[64], double* sx, int g = 0, int G = 1)
 {
-    const double* __restrict__ L = lval + S.lval_off;
     const int tid = threadIdx.x;
     const int r = tid & 63;
     const int part = tid >> 6;
-    const int w = bd.w;
-    // x_b minus the update entries of its rows
-    double v = 0.0;
-    if (r < w) {
-        const int row = bd.row0 + r;
-        for (int e = rp[row] + part; e < rp[row + 1]; e += kImplParts) v -= ubuf[rpos[e]];
-        if (part == 0) v += x[row];
+    const int w = b.w;
+    const int nks = (w + 3) >> 2;
+    const int nrt = (b.nbelow + 15) >> 4;
+    const double* __restrict__ At = lval + b.aoff + r;
+    double* u = ubuf + b.rows;
+    // L_bb^{-1}: k split in kImplParts ranges of 4
+    const double* __restrict__ Lv = lval + b.linv;
+    double li[4];
+    auto load_inverse = [&]() {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) li[i] = r < w && 4 * part + i <= r ? linv_at(Lv, r, 4 * part + i) : 0.0;
+    };
+    int t = part + kImplParts * g;
+    double a[NB];
+    auto load_tile = [&](int s0) {
+#pragma unroll
+        for (int i = 0; i < NB; ++i) a[i] = s0 + i < nks ? At[((int64_t)t * nks + s0 + i) * 64] : 0.0;
+    };
+    if (EARLY) {
+        load_inverse();
+        if (t < nrt) load_tile(0);
     }
-    sp[part][r] = v;
+    // x_b minus the update entries of its rows: wavefront `part` rows 4 part
+    // .. 4 part + 3, 16 lanes each, four loads a lane in flight
+    {
+        const int q = 4 * part + (r >> 4);
+        double v = 0.0;
+        if (q < w) {
+            const int32_t* __restrict__ rp = rptr + b.rptr + b.row0 + q;
+            const int e1 = rp[1];
+            for (int e = rp[0] + (r & 15); e < e1; e += 64) {
+                double c[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) c[i] = ubuf[rpos[min(e + 16 * i, e1 - 1)]];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) v -= e + 16 * i < e1 ? c[i] : 0.0;
+            }
+            if ((r & 15) == 0) v += x[b.x + b.row0 + q];
+        }
+        v += __shfl_xor(v, 1, 64);
+        v += __shfl_xor(v, 2, 64);
+        v += __shfl_xor(v, 4, 64);
+        v += __shfl_xor(v, 8, 64);
+        if ((r & 15) == 0) sx[q] = v;
+    }
+    if (!EARLY) load_inverse();
     __syncthreads();
-    if (tid < 64) sx[tid] = sum_parts(sp, tid);
-    __syncthreads();
-    // y_b = L_bb^{-1} x_b: k split in kImplParts ranges of 4
-    const double* __restrict__ Lv = L + bd.linv_off;
     double y = 0.0;
-    if (r < w) {
-        double a[4];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) a[i] = 4 * part + i <= r ? linv_at(Lv, r, 4 * part + i) : 0.0;
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-            if (4 * part + i <= r) y += a[i] * sx[4 * part + i];
-    }
+    for (int i = 0; i < 4; ++i) y += li[i] * sx[4 * part + i];
     sp[part][r] = y;
     __syncthreads();
     if (tid < 64) {
         const double yb = sum_parts(sp, tid);
         sx[tid] = tid < w ? yb : 0.0;
-        if (g == 0 && tid < w) yo[bd.row0 + tid] = yb;   // one writer of the G copies
+        if (g == 0 && tid < w) yo[b.x + b.row0 + tid] = yb;   // one writer of the G copies
     }
     __syncthreads();
     // u_b = L[R_b, b] y_b: wavefront `part` takes row tiles part, part +
@@ -588,122 +639,181 @@ __device__ __forceinline__ void implicit_fwd_block(
     // y[4 s + l / 16] over the k-slices s of row tile t, each wavefront load
     // one whole 512-byte A tile, NB in flight at a time; then the four
     // lanes of a row combine (y is zero past w, the tiles' padding is zero)
-    const double* __restrict__ At = L + bd.aoff;
-    const int nks = (w + 3) >> 2;
-    const int nrt = (bd.nbelow + 15) >> 4;
-    double* __restrict__ u = ubuf + S.rows_off + bd.rows_off;
-    for (int t = part + kImplParts * g; t < nrt; t += kImplParts * G) {
-        const double* __restrict__ Tt = At + (int64_t)t * nks * 64 + r;
+    if (!EARLY && t < nrt) load_tile(0);
+    while (t < nrt) {
+        const int row = 16 * t + r;
         double acc = 0.0;
-        for (int s0 = 0; s0 < nks; s0 += NB) {
-            double a[NB];
-#pragma unroll
-            for (int i = 0; i < NB; ++i) a[i] = s0 + i < nks ? Tt[(s0 + i) * 64] : 0.0;
+        for (int s0 = 0;;) {
 #pragma unroll
             for (int i = 0; i < NB; ++i)
                 if (s0 + i < nks) acc += a[i] * sx[4 * (s0 + i) + (r >> 4)];
+            s0 += NB;
+            if (s0 >= nks) break;
+            load_tile(s0);
         }
+        t += kImplParts * G;
+        if (t < nrt) load_tile(0);
         acc += __shfl_xor(acc, 16, 64);
         acc += __shfl_xor(acc, 32, 64);
-        if (r < 16 && 16 * t + r < bd.nbelow) u[16 * t + r] = acc;
+        if (r < 16 && row < b.nbelow) u[row] = acc;
     }
 }
 
 template <int NB>
 __global__ __launch_bounds__(kImplThreads) void implicit_fwd(
-    const SubDev* __restrict__ subs, const BlockDev* __restrict__ blocks, const double* __restrict__ lval,
-    const int64_t* __restrict__ rptr_off, const int32_t* __restrict__ rptr, const int32_t* __restrict__ rpos,
-    const int2* __restrict__ items, const int64_t* __restrict__ xoff, double* __restrict__ xwork,
-    double* __restrict__ ywork, double* __restrict__ ubuf, int G)
+    const ImplBlock* __restrict__ items, const double* __restrict__ lval, const int32_t* __restrict__ rptr,
+    const int32_t* __restrict__ rpos, double* __restrict__ xwork, double* __restrict__ ywork, double* ubuf, int G)
 {
     __shared__ double sp[kImplParts][64];
     __shared__ double sx[64];
-    const int2 it = items[blockIdx.x / G];
-    const SubDev S = subs[it.x];
-    const BlockDev bd = blocks[S.blk_off + it.y];
-    implicit_fwd_block<NB>(S, bd, lval, rptr + rptr_off[it.x], rpos, xwork + xoff[it.x], ywork + xoff[it.x], ubuf,
-                           sp, sx, (int)(blockIdx.x % G), G);
+    const ImplBlock b = items[blockIdx.x / G];
+    const int g = (int)(blockIdx.x % G);
+    if (g > 0 && 16 * kImplParts * g >= b.nbelow) return;        // no row tile left for this share
+    implicit_fwd_block<NB, NB == kImplBatchNarrow>(b, lval, rptr, rpos, xwork, ywork, ubuf, sp, sx, g, G);
 }
 
-// backward step of block bd: z_b <- L_bb^{-T}(y_b - L[R_b, b]^T z[R_b])
-template <int NB>
-__device__ __forceinline__ void implicit_bwd_block(
-    const SubDev& S, const BlockDev& bd, const int32_t* __restrict__ rows, const double* __restrict__ lval,
-    const double* __restrict__ yi, double* __restrict__ x, double (*sp)[64], double* sz, double* sv)
+// L[R_b, b]^T z[R_b] over the pruned row tiles [t0, t1): column 4 part + l / 16
+// in the lanes l of wavefront `part`.  Rows in groups of kImplThreads;
+// wavefront `part` takes k-slice `part` (columns 4 part .. 4 part + 3), lane l
+// the products L[16 t + l % 16, 4 part + l / 16] z[16 t + l % 16] over the row
+// tiles t: each wavefront load is one whole 512-byte A tile, NB in flight at
+// a time (EARLY: the first ones while z is gathered).  Rows past nb read the
+// tiles' zero padding against zero z entries.
+template <int NB, bool EARLY>
+__device__ __forceinline__ double implicit_bwd_sum(
+    const ImplBlock& b, const int32_t* __restrict__ rows, const double* __restrict__ lval, const double* x, int t0,
+    int t1, double* sz)
 {
-    const double* __restrict__ L = lval + S.lval_off;
-    const int32_t* __restrict__ rw = rows + S.rows_off + bd.rows_off;
+    const int32_t* __restrict__ rw = rows + b.rows;
     const int tid = threadIdx.x;
     const int r = tid & 63;
     const int part = tid >> 6;
-    const int w = bd.w, nb = bd.nbelow, nks = (w + 3) >> 2;
-    const double* __restrict__ At = L + bd.aoff;
-    // y_b - L[R_b, b]^T z[R_b]: pruned rows in groups of kImplThreads;
-    // wavefront `part` takes k-slice `part` (columns 4 part .. 4 part + 3),
-    // lane l the products L[16 t + l % 16, 4 part + l / 16] z[16 t + l % 16]
-    // over the row tiles t: each wavefront load is one whole 512-byte A tile,
-    // NB in flight at a time.  Rows past nb read the tiles' zero padding
-    // against zero z entries.
+    const int nks = (b.w + 3) >> 2;
+    const int nb = min(b.nbelow, 16 * t1);
+    const double* __restrict__ At = lval + b.aoff;
     double acc = 0.0;
-    for (int c0 = 0; c0 < nb; c0 += kImplThreads) {
-        __syncthreads();
-        sz[tid] = c0 + tid < nb ? x[rw[c0 + tid]] : 0.0;   // z of the pruned rows: final
-        __syncthreads();
-        if (part < nks) {
-            const int nrt = (min(kImplThreads, nb - c0) + 15) >> 4;
-            const double* __restrict__ Ts = At + ((int64_t)(c0 >> 4) * nks + part) * 64 + r;
-            for (int t0 = 0; t0 < nrt; t0 += NB) {
-                double a[NB];
+    for (int c0 = 16 * t0; c0 < nb; c0 += kImplThreads) {
+        const int nrt = part < nks ? (min(kImplThreads, nb - c0) + 15) >> 4 : 0;
+        const double* __restrict__ Ts = At + ((int64_t)(c0 >> 4) * nks + part) * 64 + r;
+        double a[NB];
+        auto load_tiles = [&](int u0) {
 #pragma unroll
-                for (int i = 0; i < NB; ++i) a[i] = t0 + i < nrt ? Ts[(int64_t)(t0 + i) * nks * 64] : 0.0;
+            for (int i = 0; i < NB; ++i) a[i] = u0 + i < nrt ? Ts[(int64_t)(u0 + i) * nks * 64] : 0.0;
+        };
+        if (EARLY) load_tiles(0);
+        const double z = c0 + tid < nb ? x[b.x + rw[c0 + tid]] : 0.0;   // z of the pruned rows: final
+        __syncthreads();
+        sz[tid] = z;
+        __syncthreads();
+        for (int u0 = 0; u0 < nrt; u0 += NB) {
+            if (!EARLY || u0 > 0) load_tiles(u0);
 #pragma unroll
-                for (int i = 0; i < NB; ++i)
-                    if (t0 + i < nrt) acc += a[i] * sz[16 * (t0 + i) + (r & 15)];
-            }
+            for (int i = 0; i < NB; ++i)
+                if (u0 + i < nrt) acc += a[i] * sz[16 * (u0 + i) + (r & 15)];
         }
     }
-    // column 4 part + l / 16: the sum over its 16 lanes
     acc += __shfl_xor(acc, 1, 64);
     acc += __shfl_xor(acc, 2, 64);
     acc += __shfl_xor(acc, 4, 64);
     acc += __shfl_xor(acc, 8, 64);
-    if (part < nks && (r & 15) == 0 && 4 * part + (r >> 4) < w)
-        sv[4 * part + (r >> 4)] = yi[bd.row0 + 4 * part + (r >> 4)] - acc;
-    __syncthreads();
-    // z_b = L_bb^{-T} v: k split in kImplParts ranges of 4
-    const double* __restrict__ Lv = L + bd.linv_off;
-    double z = 0.0;
-    if (r < w) {
-        double a[4];
+    return acc;
+}
+
+// z_b = L_bb^{-T} v (v in sv): k split in kImplParts ranges of 4; li: this
+// thread's values of the inverse (linv_col)
+__device__ __forceinline__ void linv_col(const ImplBlock& b, const double* __restrict__ lval, double (&li)[4]) {
+    const double* __restrict__ Lv = lval + b.linv;
+    const int r = threadIdx.x & 63, part = threadIdx.x >> 6;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int k = 4 * part + i;
-            a[i] = k >= r && k < w ? linv_at(Lv, k, r) : 0.0;
-        }
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int k = 4 * part + i;
-            if (k >= r && k < w) z += a[i] * sv[k];
-        }
+    for (int i = 0; i < 4; ++i) {
+        const int k = 4 * part + i;
+        li[i] = k >= r && k < b.w ? linv_at(Lv, k, r) : 0.0;
     }
+}
+
+__device__ __forceinline__ void implicit_bwd_finish(const ImplBlock& b, const double (&li)[4], double* x,
+                                                    double (*sp)[64], const double* sv) {
+    const int r = threadIdx.x & 63, part = threadIdx.x >> 6;
+    double z = 0.0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) z += li[i] * sv[4 * part + i];
     sp[part][r] = z;
     __syncthreads();
-    if (tid < w) x[bd.row0 + tid] = sum_parts(sp, tid);
+    if ((int)threadIdx.x < b.w) x[b.x + b.row0 + threadIdx.x] = sum_parts(sp, threadIdx.x);
+}
+
+// backward step of block b: z_b <- L_bb^{-T}(y_b - L[R_b, b]^T z[R_b])
+template <int NB, bool EARLY>
+__device__ __forceinline__ void implicit_bwd_block(
+    const ImplBlock& b, const int32_t* __restrict__ rows, const double* __restrict__ lval,
+    const double* __restrict__ yi, double* x, double (*sp)[64], double* sz, double* sv)
+{
+    const int r = threadIdx.x & 63, part = threadIdx.x >> 6;
+    const int c = 4 * part + (r >> 4);
+    double li[4];
+    if (EARLY) linv_col(b, lval, li);
+    const double acc = implicit_bwd_sum<NB, EARLY>(b, rows, lval, x, 0, (b.nbelow + 15) >> 4, sz);
+    if (!EARLY) linv_col(b, lval, li);
+    if ((r & 15) == 0) sv[c] = c < b.w ? yi[b.x + b.row0 + c] - acc : 0.0;
+    __syncthreads();
+    implicit_bwd_finish(b, li, x, sp, sv);
 }
 
 template <int NB>
 __global__ __launch_bounds__(kImplThreads) void implicit_bwd(
-    const SubDev* __restrict__ subs, const BlockDev* __restrict__ blocks, const int32_t* __restrict__ rows,
-    const double* __restrict__ lval, const int2* __restrict__ items, const int64_t* __restrict__ xoff,
-    const double* __restrict__ ywork, double* __restrict__ xwork)
+    const ImplBlock* __restrict__ items, const int32_t* __restrict__ rows, const double* __restrict__ lval,
+    const double* __restrict__ ywork, double* xwork)
 {
     __shared__ double sp[kImplParts][64];
     __shared__ double sz[kImplThreads];
     __shared__ double sv[64];
-    const int2 it = items[blockIdx.x];
-    const SubDev S = subs[it.x];
-    const BlockDev bd = blocks[S.blk_off + it.y];
-    implicit_bwd_block<NB>(S, bd, rows, lval, ywork + xoff[it.x], xwork + xoff[it.x], sp, sz, sv);
+    const ImplBlock b = items[blockIdx.x];
+    implicit_bwd_block<NB, NB == kImplBatchNarrow>(b, rows, lval, ywork, xwork, sp, sz, sv);
+}
+
+// The same step in two launches: share g of G of the row sums into bpart
+// [block of the level][share][64] (row tiles in shares of ceil(tiles / G)),
+// then their sum and the diagonal product.
+template <int NB>
+__global__ __launch_bounds__(kImplThreads) void implicit_bwd_part(
+    const ImplBlock* __restrict__ items, const int32_t* __restrict__ rows, const double* __restrict__ lval,
+    const double* __restrict__ xwork, double* __restrict__ bpart, int G)
+{
+    __shared__ double sz[kImplThreads];
+    const ImplBlock b = items[blockIdx.x / G];
+    const int g = (int)(blockIdx.x % G);
+    const int nrt = (b.nbelow + 15) >> 4;
+    const int per = (nrt + G - 1) / G;
+    if (g * per >= nrt) return;
+    const double acc = implicit_bwd_sum<NB, true>(b, rows, lval, xwork, g * per, min(nrt, (g + 1) * per), sz);
+    const int r = threadIdx.x & 63, part = threadIdx.x >> 6;
+    if ((r & 15) == 0) bpart[(int64_t)blockIdx.x * 64 + 4 * part + (r >> 4)] = acc;
+}
+
+__global__ __launch_bounds__(kImplThreads) void implicit_bwd_last(
+    const ImplBlock* __restrict__ items, const double* __restrict__ lval, const double* __restrict__ ywork,
+    double* __restrict__ xwork, const double* __restrict__ bpart, int G)
+{
+    __shared__ double sp[kImplParts][64];
+    __shared__ double sv[64];
+    const ImplBlock b = items[blockIdx.x];
+    double li[4];
+    linv_col(b, lval, li);
+    if (threadIdx.x < 64) {
+        const int c = threadIdx.x;
+        const int nrt = (b.nbelow + 15) >> 4;
+        const int per = (nrt + G - 1) / G;
+        double v = c < b.w ? ywork[b.x + b.row0 + c] : 0.0;
+        double s[kImplSplit];
+#pragma unroll
+        for (int g = 0; g < kImplSplit; ++g)
+            s[g] = g < G && g * per < nrt ? bpart[((int64_t)blockIdx.x * G + g) * 64 + c] : 0.0;
+#pragma unroll
+        for (int g = 0; g < kImplSplit; ++g) v -= s[g];
+        sv[c] = c < b.w ? v : 0.0;
+    }
+    __syncthreads();
+    implicit_bwd_finish(b, li, xwork, sp, sv);
 }
 
 // Both sweeps of one subdomain in one workgroup: its blocks in increasing
@@ -713,25 +823,26 @@ __global__ __launch_bounds__(kImplThreads) void implicit_bwd(
 __global__ __launch_bounds__(kImplThreads) void implicit_sweeps(
     const SubDev* __restrict__ subs, const BlockDev* __restrict__ blocks, const int32_t* __restrict__ rows,
     const double* __restrict__ lval, const int64_t* __restrict__ rptr_off, const int32_t* __restrict__ rptr,
-    const int32_t* __restrict__ rpos, const int64_t* __restrict__ xoff, double* __restrict__ xwork,
-    double* __restrict__ ywork, double* __restrict__ ubuf, const int32_t* __restrict__ sub_list)
+    const int32_t* __restrict__ rpos, const int64_t* __restrict__ xoff, double* xwork, double* ywork, double* ubuf,
+    const int32_t* __restrict__ sub_list)
 {
     __shared__ double sp[kImplParts][64];
     __shared__ double sx[64];
     __shared__ double sz[kImplThreads];
     const int sub = sub_list ? sub_list[blockIdx.x] : (int)blockIdx.x;
     const SubDev S = subs[sub];
-    double* __restrict__ x = xwork + xoff[sub];
-    double* __restrict__ y = ywork + xoff[sub];
-    const int32_t* __restrict__ rp = rptr + rptr_off[sub];
-    for (int b = 0; b < S.nblocks; ++b) {
-        const BlockDev bd = blocks[S.blk_off + b];
-        implicit_fwd_block<kImplBatchNarrow>(S, bd, lval, rp, rpos, x, y, ubuf, sp, sx);
+    const int64_t xo = xoff[sub], ro = rptr_off[sub];
+    auto block = [&](int k) {
+        const BlockDev d = blocks[S.blk_off + k];
+        return ImplBlock{S.lval_off + d.linv_off, S.lval_off + d.aoff, S.rows_off + d.rows_off, xo, ro,
+                         d.row0, d.w, d.nbelow, 0};
+    };
+    for (int k = 0; k < S.nblocks; ++k) {
+        implicit_fwd_block<kImplBatchWide, true>(block(k), lval, rptr, rpos, xwork, ywork, ubuf, sp, sx);
         __syncthreads();
     }
-    for (int b = S.nblocks - 1; b >= 0; --b) {
-        const BlockDev bd = blocks[S.blk_off + b];
-        implicit_bwd_block<kImplBatchNarrow>(S, bd, rows, lval, y, x, sp, sz, sx);
+    for (int k = S.nblocks - 1; k >= 0; --k) {
+        implicit_bwd_block<kImplBatchWide, true>(block(k), rows, lval, ywork, xwork, sp, sz, sx);
         __syncthreads();
     }
 }
@@ -739,20 +850,22 @@ __global__ __launch_bounds__(kImplThreads) void implicit_sweeps(
 __global__ __launch_bounds__(kInitThreads) void implicit_gather(
     const SubDev* __restrict__ subs, const int32_t* __restrict__ piv, const int32_t* __restrict__ pi,
     const int8_t* __restrict__ sgn, const int64_t* __restrict__ xoff, const double* __restrict__ xwork,
-    double* __restrict__ q, const int32_t* __restrict__ sub_list)
+    double* __restrict__ q, const int32_t* __restrict__ sub_list, int C)
 {
-    const int sub = sub_list ? sub_list[blockIdx.x] : (int)blockIdx.x;
+    const int at = (int)blockIdx.x / C, c = (int)blockIdx.x % C;
+    const int sub = sub_list ? sub_list[at] : at;
     const SubDev S = subs[sub];
     const double* __restrict__ x = xwork + xoff[sub];
-    for (int a = threadIdx.x; a < S.m; a += kInitThreads)
+    for (int a = c * kInitThreads + threadIdx.x; a < S.m; a += C * kInitThreads)
         q[S.dual_off + pi[S.col_off + a]] = (double)sgn[S.col_off + a] * x[piv[S.col_off + a]];
 }
 
 hipError_t launch_implicit_init(const DevTables& t, const int64_t* xoff, double* xwork, const double* p,
                                 const int32_t* sub_list, int32_t count, hipStream_t stream) {
     if (count <= 0) return hipSuccess;
-    hipLaunchKernelGGL(implicit_init, dim3((unsigned)count), dim3(kInitThreads), 0, stream, t.subs, t.piv, t.pi, t.sgn,
-                       xoff, p, xwork, sub_list);
+    const int C = init_split(count);
+    hipLaunchKernelGGL(implicit_init, dim3((unsigned)(count * C)), dim3(kInitThreads), 0, stream, t.subs, t.piv, t.pi,
+                       t.sgn, xoff, p, xwork, sub_list, C);
     return hipGetLastError();
 }
 
@@ -760,8 +873,9 @@ hipError_t launch_implicit_sweeps(const DevTables& t, const ImplicitLevels& lv, 
                                   int32_t count, hipStream_t stream) {
     if (count <= 0) return hipSuccess;
     // every table and workspace the sweeps dereference must be in place
-    if (!xoff || !xwork || !lv.ywork || !lv.ubuf || !lv.rptr_off || !lv.rptr || !lv.rpos) return hipErrorInvalidValue;
-    if (!lv.per_subdomain && ((lv.fw_off.size() > 1 && !lv.fw_items) || (lv.bw_off.size() > 1 && !lv.bw_items)))
+    if (!xoff || !xwork || !lv.ywork || !lv.ubuf || !lv.bpart || !lv.rptr_off || !lv.rptr || !lv.rpos) return hipErrorInvalidValue;
+    if (!lv.per_subdomain && ((lv.fw_off.size() > 1 && !lv.fw_items) || (lv.bw_off.size() > 1 && !lv.bw_items) ||
+                              lv.fw_rows.size() + 1 < lv.fw_off.size() || lv.bw_rows.size() + 1 < lv.bw_off.size()))
         return hipErrorInvalidValue;
     hipError_t e = hipSuccess;
     if (lv.per_subdomain) {
@@ -772,30 +886,32 @@ hipError_t launch_implicit_sweeps(const DevTables& t, const ImplicitLevels& lv, 
     for (size_t l = 0; l + 1 < lv.fw_off.size(); ++l) {
         const int64_t cnt = lv.fw_off[l + 1] - lv.fw_off[l];
         if (cnt <= 0) continue;
-        // narrow levels: kImplSplit workgroups per block, each repeating the
-        // update sums and the diagonal product and taking every kImplSplit-th
-        // group of row tiles of the product below
+        const int G = impl_split(cnt, (lv.fw_rows[l] + 16 * kImplParts - 1) / (16 * kImplParts));
         if (cnt < kImplNarrowBelow)
-            hipLaunchKernelGGL(implicit_fwd<kImplBatchNarrow>, dim3((unsigned)(cnt * kImplSplit)), dim3(kImplThreads),
-                               0, stream, t.subs, t.blocks, t.lval, lv.rptr_off, lv.rptr, lv.rpos,
-                               lv.fw_items + lv.fw_off[l], xoff, xwork, lv.ywork, lv.ubuf, kImplSplit);
+            hipLaunchKernelGGL(implicit_fwd<kImplBatchNarrow>, dim3((unsigned)(cnt * G)), dim3(kImplThreads),
+                               0, stream, lv.fw_items + lv.fw_off[l], t.lval, lv.rptr, lv.rpos, xwork, lv.ywork, lv.ubuf,
+                               G);
         else
             hipLaunchKernelGGL(implicit_fwd<kImplBatchWide>, dim3((unsigned)cnt), dim3(kImplThreads), 0, stream,
-                               t.subs, t.blocks, t.lval, lv.rptr_off, lv.rptr, lv.rpos, lv.fw_items + lv.fw_off[l],
-                               xoff, xwork, lv.ywork, lv.ubuf, 1);
+                               lv.fw_items + lv.fw_off[l], t.lval, lv.rptr, lv.rpos, xwork, lv.ywork, lv.ubuf, 1);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     for (size_t l = 0; l + 1 < lv.bw_off.size(); ++l) {
         const int64_t cnt = lv.bw_off[l + 1] - lv.bw_off[l];
         if (cnt <= 0) continue;
-        if (cnt < kImplNarrowBelow)
+        if (cnt < kImplNarrowBelow && lv.bw_rows[l] >= kImplBwdSplitRows) {
+            const int G = impl_split(cnt, kImplSplit);
+            hipLaunchKernelGGL(implicit_bwd_part<kImplBatchNarrow>, dim3((unsigned)(cnt * G)), dim3(kImplThreads), 0,
+                               stream, lv.bw_items + lv.bw_off[l], t.rows, t.lval, xwork, lv.bpart, G);
+            if ((e = hipGetLastError()) != hipSuccess) return e;
+            hipLaunchKernelGGL(implicit_bwd_last, dim3((unsigned)cnt), dim3(kImplThreads), 0, stream,
+                               lv.bw_items + lv.bw_off[l], t.lval, lv.ywork, xwork, lv.bpart, G);
+        } else if (cnt < kImplNarrowBelow)
             hipLaunchKernelGGL(implicit_bwd<kImplBatchNarrow>, dim3((unsigned)cnt), dim3(kImplThreads), 0, stream,
-                               t.subs, t.blocks, t.rows, t.lval, lv.bw_items + lv.bw_off[l], xoff, lv.ywork,
-                               xwork);
+                               lv.bw_items + lv.bw_off[l], t.rows, t.lval, lv.ywork, xwork);
         else
             hipLaunchKernelGGL(implicit_bwd<kImplBatchWide>, dim3((unsigned)cnt), dim3(kImplThreads), 0, stream,
-                               t.subs, t.blocks, t.rows, t.lval, lv.bw_items + lv.bw_off[l], xoff, lv.ywork,
-                               xwork);
+                               lv.bw_items + lv.bw_off[l], t.rows, t.lval, lv.ywork, xwork);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     return hipSuccess;
@@ -804,8 +920,9 @@ hipError_t launch_implicit_sweeps(const DevTables& t, const ImplicitLevels& lv, 
 hipError_t launch_implicit_gather(const DevTables& t, const int64_t* xoff, const double* xwork, double* q,
                                   const int32_t* sub_list, int32_t count, hipStream_t stream) {
     if (count <= 0) return hipSuccess;
-    hipLaunchKernelGGL(implicit_gather, dim3((unsigned)count), dim3(kInitThreads), 0, stream, t.subs, t.piv, t.pi,
-                       t.sgn, xoff, xwork, q, sub_list);
+    const int C = init_split(count);
+    hipLaunchKernelGGL(implicit_gather, dim3((unsigned)(count * C)), dim3(kInitThreads), 0, stream, t.subs, t.piv, t.pi,
+                       t.sgn, xoff, xwork, q, sub_list, C);
     return hipGetLastError();
 }
 

@@ -75,20 +75,30 @@ struct PcpgArgs {
 };
 
 struct ImplicitLevels;
+// 64 sums for each workgroup of a split backward level (at most 512)
+constexpr int64_t kImplPartDoubles = 512 * 64;
 // Projected CG on every subdomain, `iters` iterations: F applied explicitly
 // to the assembled subdomains, and, when lvh is given, with the factor to the
 // nimpl subdomains of lvh->subs (workspace xwork at xoff).
 hipError_t launch_pcpg(const DevTables& t, const PcpgArgs& a, hipStream_t stream, const ImplicitLevels* lvh,
                        const int64_t* xoff, double* xwork, int32_t nimpl);
 
+// One factor block as the implicit sweeps walk it: offsets into the factor
+// values, the row array, the work vectors and rptr.
+struct ImplBlock {
+    int64_t linv, aoff, rows, x, rptr;
+    int32_t row0, w, nbelow, pad;
+};
+
 // Level schedule of the blocked triangular solves of the implicit apply:
-// items (subdomain, block) grouped by level (host offsets, levels run in
-// order); per row of a subdomain (rptr at rptr_off[sub], CSR) the positions
-// in the row array where it is a pruned row: its entries in the update
-// buffer ubuf, which runs parallel to the row array.
+// blocks grouped by level (host offsets, levels run in order; fw_rows /
+// bw_rows: the most pruned rows of a block of the level); per row of a
+// subdomain (rptr at rptr_off[sub], CSR) the positions in the row array where
+// it is a pruned row: its entries in the update buffer ubuf, which runs
+// parallel to the row array.
 struct ImplicitLevels {
-    const int2* fw_items = nullptr;
-    const int2* bw_items = nullptr;
+    const ImplBlock* fw_items = nullptr;
+    const ImplBlock* bw_items = nullptr;
     const int64_t* rptr_off = nullptr;
     const int32_t* rptr = nullptr;
     const int32_t* rpos = nullptr;
@@ -97,7 +107,10 @@ struct ImplicitLevels {
     // xwork offsets): kept apart from x so that several workgroups of one
     // forward block step read x while one of them writes y
     double* ywork = nullptr;
+    // shares of the row sums of a backward level (kImplPartDoubles)
+    double* bpart = nullptr;
     std::vector<int64_t> fw_off, bw_off;
+    std::vector<int32_t> fw_rows, bw_rows;
     // true: one workgroup per subdomain runs both sweeps block by block (the
     // block DAGs are near chains); false: one launch per level
     bool per_subdomain = false;

@@ -359,14 +359,14 @@ struct sc_plan_s {
     DevBuf<double> d_xwork, d_ywork;          // implicit apply: n_i doubles per subdomain each
     DevBuf<int64_t> d_xoff;
     // implicit apply level schedule (built with the workspace, on first use)
-    DevBuf<int2> d_ifw, d_ibw;
+    DevBuf<ImplBlock> d_ifw, d_ibw;
     DevBuf<int64_t> d_rptr_off;
     DevBuf<int32_t> d_rptr, d_rpos;
-    DevBuf<double> d_ubuf;
+    DevBuf<double> d_ubuf, d_bpart;
     ImplicitLevels ilv;
     // the same schedule restricted to the subdomains applied implicitly in
     // sc_apply / sc_pcpg (select_iters)
-    DevBuf<int2> d_ifw_h, d_ibw_h;
+    DevBuf<ImplBlock> d_ifw_h, d_ibw_h;
     DevBuf<int32_t> d_impl_list;
     ImplicitLevels ilv_h;
     bool mixed = false;
@@ -492,9 +492,9 @@ struct sc_plan_s {
                          d_fresh.count * 8 + d_sgn.count +
                          (d_lval.count + d_X.count + d_F.count) * 8 +
                          (d_lval32.count + d_X32.count + d_F32.count) * 4 +
-                         (d_xwork.count + d_ywork.count + d_xoff.count) * 8 + (d_ifw.count + d_ibw.count) * sizeof(int2) +
-                         (d_rptr.count + d_rpos.count) * 4 + (d_rptr_off.count + d_ubuf.count) * 8 +
-                         (d_ifw_h.count + d_ibw_h.count) * sizeof(int2) + d_impl_list.count * 4);
+                         (d_xwork.count + d_ywork.count + d_xoff.count) * 8 + (d_ifw.count + d_ibw.count) * sizeof(ImplBlock) +
+                         (d_rptr.count + d_rpos.count) * 4 + (d_rptr_off.count + d_ubuf.count + d_bpart.count) * 8 +
+                         (d_ifw_h.count + d_ibw_h.count) * sizeof(ImplBlock) + d_impl_list.count * 4);
     }
     void release() {
         d_subs.release(); d_tiles.release(); d_blocks.release(); d_syrk.release();
@@ -504,7 +504,7 @@ struct sc_plan_s {
         d_lval.release(); d_X.release(); d_F.release();
         d_lval32.release(); d_X32.release(); d_F32.release();
         d_xwork.release(); d_ywork.release(); d_xoff.release();
-        d_ifw.release(); d_ibw.release(); d_rptr_off.release(); d_rptr.release(); d_rpos.release(); d_ubuf.release();
+        d_ifw.release(); d_ibw.release(); d_rptr_off.release(); d_rptr.release(); d_rpos.release(); d_ubuf.release(); d_bpart.release();
         d_ifw_h.release(); d_ibw_h.release(); d_impl_list.release();
         if (h_lval) (void)hipHostFree(h_lval);
         h_lval = nullptr;
@@ -1531,14 +1531,39 @@ static sc_status_t build_implicit(sc_plan_s* P, hipStream_t st) {
     };
     subset(fw, fwh, lvh.fw_off);
     subset(bw, bwh, lvh.bw_off);
-    DevBuf<double> xwork, ywork, ubuf;
+    auto device_blocks = [&](const std::vector<int2>& items) {
+        std::vector<ImplBlock> out;
+        out.reserve(items.size());
+        for (const int2& it : items) {
+            const SubDev& sd = P->h_subs[it.x];
+            const BlockDesc& d = P->plans[it.x].blocks[it.y];
+            out.push_back(ImplBlock{sd.lval_off + d.linv_off, sd.lval_off + d.aoff, sd.rows_off + d.rows_off, off[it.x],
+                                    rptr_off[it.x], d.row0, d.w, d.nbelow, 0});
+        }
+        return out;
+    };
+    auto level_rows = [](const std::vector<ImplBlock>& items, const std::vector<int64_t>& lo) {
+        std::vector<int32_t> out;
+        for (size_t l = 0; l + 1 < lo.size(); ++l) {
+            out.push_back(0);
+            for (int64_t k = lo[l]; k < lo[l + 1]; ++k) out.back() = std::max(out.back(), items[(size_t)k].nbelow);
+        }
+        return out;
+    };
+    const std::vector<ImplBlock> fwib = device_blocks(fwi), bwib = device_blocks(bwi), fwhb = device_blocks(fwh),
+                                 bwhb = device_blocks(bwh);
+    lv.fw_rows = level_rows(fwib, lv.fw_off);
+    lv.bw_rows = level_rows(bwib, lv.bw_off);
+    lvh.fw_rows = level_rows(fwhb, lvh.fw_off);
+    lvh.bw_rows = level_rows(bwhb, lvh.bw_off);
+    DevBuf<double> xwork, ywork, ubuf, bpart;
     DevBuf<int64_t> xoff, rptr_off_d;
-    DevBuf<int2> ifw, ibw;
+    DevBuf<ImplBlock> ifw, ibw;
     DevBuf<int32_t> rptr_d, rpos_d;
-    DevBuf<int2> ifwh, ibwh;
+    DevBuf<ImplBlock> ifwh, ibwh;
     DevBuf<int32_t> ilist;
     auto release_all = [&]() {
-        xwork.release(); ywork.release(); ubuf.release(); xoff.release(); rptr_off_d.release();
+        xwork.release(); ywork.release(); ubuf.release(); bpart.release(); xoff.release(); rptr_off_d.release();
         ifw.release(); ibw.release(); rptr_d.release(); rpos_d.release();
         ifwh.release(); ibwh.release(); ilist.release();
     };
@@ -1551,6 +1576,7 @@ static sc_status_t build_implicit(sc_plan_s* P, hipStream_t st) {
     if (e == hipSuccess) e = rptr_d.alloc(rptr.size());
     if (e == hipSuccess) e = rpos_d.alloc(std::max<size_t>(1, rpos.size()));
     if (e == hipSuccess) e = ubuf.alloc((size_t)P->nrows_total);
+    if (e == hipSuccess) e = bpart.alloc((size_t)kImplPartDoubles);
     if (e == hipSuccess) e = ifwh.alloc(fwh.size());
     if (e == hipSuccess) e = ibwh.alloc(bwh.size());
     if (e == hipSuccess) e = ilist.alloc(impl_list.size());
@@ -1558,13 +1584,13 @@ static sc_status_t build_implicit(sc_plan_s* P, hipStream_t st) {
         return bytes ? hipMemcpyAsync(d, h, bytes, hipMemcpyHostToDevice, st) : hipSuccess;
     };
     if (e == hipSuccess) e = up(xoff.p, off.data(), off.size() * 8);
-    if (e == hipSuccess) e = up(ifw.p, fwi.data(), fwi.size() * sizeof(int2));
-    if (e == hipSuccess) e = up(ibw.p, bwi.data(), bwi.size() * sizeof(int2));
+    if (e == hipSuccess) e = up(ifw.p, fwib.data(), fwib.size() * sizeof(ImplBlock));
+    if (e == hipSuccess) e = up(ibw.p, bwib.data(), bwib.size() * sizeof(ImplBlock));
     if (e == hipSuccess) e = up(rptr_off_d.p, rptr_off.data(), rptr_off.size() * 8);
     if (e == hipSuccess) e = up(rptr_d.p, rptr.data(), rptr.size() * 4);
     if (e == hipSuccess) e = up(rpos_d.p, rpos.data(), rpos.size() * 4);
-    if (e == hipSuccess) e = up(ifwh.p, fwh.data(), fwh.size() * sizeof(int2));
-    if (e == hipSuccess) e = up(ibwh.p, bwh.data(), bwh.size() * sizeof(int2));
+    if (e == hipSuccess) e = up(ifwh.p, fwhb.data(), fwhb.size() * sizeof(ImplBlock));
+    if (e == hipSuccess) e = up(ibwh.p, bwhb.data(), bwhb.size() * sizeof(ImplBlock));
     if (e == hipSuccess) e = up(ilist.p, impl_list.data(), impl_list.size() * 4);
     if (e == hipSuccess) e = hipStreamSynchronize(st);    // the host tables go out of scope
     if (e != hipSuccess) {
@@ -1579,11 +1605,12 @@ static sc_status_t build_implicit(sc_plan_s* P, hipStream_t st) {
     lv.rpos = rpos_d.p;
     lv.ubuf = ubuf.p;
     lv.ywork = ywork.p;
+    lv.bpart = bpart.p;
     // near-chain block DAGs (fewer than 1.5 blocks per level): a level
     // launch would carry one block per subdomain
     lv.per_subdomain = 2 * nblocks_all < 3 * nlevels_all;
     P->d_xwork = xwork; P->d_ywork = ywork; P->d_xoff = xoff; P->d_ifw = ifw; P->d_ibw = ibw;
-    P->d_rptr_off = rptr_off_d; P->d_rptr = rptr_d; P->d_rpos = rpos_d; P->d_ubuf = ubuf;
+    P->d_rptr_off = rptr_off_d; P->d_rptr = rptr_d; P->d_rpos = rpos_d; P->d_ubuf = ubuf; P->d_bpart = bpart;
     P->ilv = lv;
     lvh.fw_items = ifwh.p;
     lvh.bw_items = ibwh.p;
@@ -1592,6 +1619,7 @@ static sc_status_t build_implicit(sc_plan_s* P, hipStream_t st) {
     lvh.rpos = lv.rpos;
     lvh.ubuf = lv.ubuf;
     lvh.ywork = lv.ywork;
+    lvh.bpart = lv.bpart;
     lvh.subs = ilist.p;
     // per-subdomain sweeps for the subset when its own block DAGs are near
     // chains (the per-subdomain kernel reads the list)

@@ -130,3 +130,25 @@ def test_apply_and_pcpg_at_tile_edges(precision):
             got = lam[o:o + s.m].cpu().numpy()
             assert np.linalg.norm(got - ref) <= 1e-9 * np.linalg.norm(ref), i
         plan.destroy()
+
+
+@pytest.mark.parametrize("split", ["uniform", "etree"])
+@pytest.mark.parametrize("count", [1, 5])
+def test_implicit_apply_split_levels(count, split):
+    """The implicit apply where its levels are split over workgroups (blocks of
+    more than 512 pruned rows, few per level), where they are not, and with
+    repeated DOFs: against the explicit product of the assembled F."""
+    import torch
+    subs = [scgen.box_subdomain("elasticity", (12, 11, 10), 1.0 / 12, 50 + i, gluing="per_face") for i in range(count)]
+    subs += [scgen.box_subdomain("heat", (3, 2), 0.5, 8), _columns(scgen.box_subdomain("heat", (9, 9, 9), 0.1, 9), 70, 3)]
+    plan = _plan(subs, block_split=split)
+    p = torch.from_numpy(np.random.default_rng(2).uniform(-1, 1, plan.dual_total)).cuda()
+    q, ref = torch.zeros_like(p), torch.zeros_like(p)
+    plan.apply(p, ref)
+    for _ in range(2):
+        plan.apply_implicit(p, q)
+        for i, s in enumerate(subs):
+            o = plan.query(i)["dual_offset"]
+            a, b = q[o:o + s.m], ref[o:o + s.m]
+            assert float((a - b).norm()) <= 1e-11 * float(b.norm()), i
+    plan.destroy()
