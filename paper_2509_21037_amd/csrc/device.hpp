@@ -107,4 +107,10 @@ struct BlockDev {
     int64_t linv_off;    // inverse of the diagonal block as MFMA A tiles (same base)
 };
 
+// One diagonal triangle to invert: offsets into the factor values.
+struct InvItem {
+    int64_t diag, linv;
+    int32_t w, pad;
+};
+
 }  // namespace scasm

@@ -45,7 +45,7 @@ __device__ __forceinline__ v4f mfma_f32(float a, float b, v4f c) {
 // downwards); a stripe whose first pivot lies further down joins at its own
 // first block.  Per block b:
 //   1. X[b] <- L_bb^{-1} X[b], FP64 MFMA with the inverse of the diagonal
-//      block computed on the host (its lower 16 x 4 tiles, one chunk);
+//      block (invert_diag; its lower 16 x 4 tiles, one chunk);
 //   2. the pruned rows below the block, 32 at a time (64 in mixed precision):
 //      X[R_b] -= L[R_b, b] X[b] (MFMA, rows gathered and scattered).
 // The factor flows through the workgroup as a stream of chunks (the inverse
@@ -938,6 +938,89 @@ __global__ __launch_bounds__(256, EDGE == 128 ? 2 : 4) void syrk_split_f32(
 }
 
 // ---------------------------------------------------------------------------
+// ---------------------------------------------------------------------------
+// Inverses of the factor blocks' diagonal triangles (lower triangular, w <=
+// 64), written as the lower MFMA A tiles the TRSM and the implicit apply read.
+// One workgroup per block, four lanes per column: forward substitution on the
+// unit vectors, the dot products of a row split over the four lanes.  Sums in
+// double-double (products and their errors by fma, error-free additions, the
+// quotient corrected once), rounded to FP64 at the end: more digits than the
+// 64-bit mantissas of x87, in which the host computed the inverses before (22%
+// of its time on an 11^3 elasticity subdomain, 40% on 12^3 heat).  Bound by
+// FP64 arithmetic and LDS latency, 50 KB of LDS (packed triangles): @@INV@@
+// ---------------------------------------------------------------------------
+__device__ __forceinline__ int tri(int i, int k) { return i * (i + 1) / 2 + k; }
+
+__global__ __launch_bounds__(256) void invert_diag(const InvItem* __restrict__ items, double* lval) {
+#pragma clang fp contract(off)
+    __shared__ double sl[kMaxPanel * (kMaxPanel + 1) / 2];
+    __shared__ double zh[kMaxPanel * (kMaxPanel + 1) / 2], zl[kMaxPanel * (kMaxPanel + 1) / 2];
+    const InvItem it = items[blockIdx.x];
+    const int w = it.w;
+    for (int e = threadIdx.x; e < w * w; e += 256) {
+        const int k = e / w, i = e - k * w;
+        if (i >= k) sl[tri(i, k)] = lval[it.diag + e];
+    }
+    __syncthreads();
+    const int c = threadIdx.x >> 2, part = threadIdx.x & 3;      // column; share of the dot products
+    const int c0 = (threadIdx.x >> 6) * 16;                      // first column of the wavefront
+    for (int i = c0; i < w; ++i) {
+        double hi = 0.0, lo = 0.0;
+        for (int k = c + part; k < i; k += 4) {
+            const double a = sl[tri(i, k)], b = zh[tri(k, c)];
+            const double p = a * b;
+            const double e = __builtin_fma(a, zl[tri(k, c)], __builtin_fma(a, b, -p));
+            const double s = hi - p;
+            const double t = s - hi;
+            lo += ((hi - (s - t)) - (p + t)) - e;
+            hi = s;
+        }
+#pragma unroll
+        for (int off = 1; off < 4; off <<= 1) {
+            const double h2 = __shfl_xor(hi, off, 64), l2 = __shfl_xor(lo, off, 64);
+            const double s = hi + h2;
+            const double t = s - hi;
+            lo = (lo + l2) + ((hi - (s - t)) + (h2 - t));
+            hi = s;
+        }
+        if (i >= c && c < w && part == 0) {
+            if (i == c) {                                        // the sums are empty
+                hi = 1.0;
+                lo = 0.0;
+            }
+            const double d = sl[tri(i, i)];
+            const double s = hi + lo;
+            const double t = s - hi;
+            lo = (hi - (s - t)) + (lo - t);
+            const double q = s / d;
+            const double q2 = (__builtin_fma(-q, d, s) + lo) / d;
+            const double z = q + q2;
+            zh[tri(i, c)] = z;
+            zl[tri(i, c)] = q2 - (z - q);
+        }
+        // the four lanes of a column are one wavefront: its LDS accesses stay
+        // in order
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    }
+    __syncthreads();
+    const int nks = (w + 3) >> 2, nrt = (w + 15) >> 4;
+    const int ntile = 2 * (nrt - 1) * nrt + nks;
+    for (int e = threadIdx.x; e < ntile * 64; e += 256) {
+        const int tile = e >> 6, pos = e & 63;
+        const int rt = (tile >= 4) + (tile >= 12) + (tile >= 24);
+        const int row = 16 * rt + (pos & 15), col = 4 * (tile - 2 * rt * (rt + 1)) + (pos >> 4);
+        lval[it.linv + e] = row < w && col <= row ? zh[tri(row, col)] : 0.0;
+    }
+}
+
+hipError_t launch_invert_diag(const InvItem* items, int64_t count, double* lval, hipStream_t stream) {
+    if (count <= 0) return hipSuccess;
+    hipLaunchKernelGGL(invert_diag, dim3((unsigned)count), dim3(256), 0, stream, items, lval);
+    return hipGetLastError();
+}
+
 template <bool MERGE, bool LARGE>
 static void trsm_launch(const DevTables& t, const int32_t* order, int64_t count, hipStream_t stream) {
     if (t.X32)

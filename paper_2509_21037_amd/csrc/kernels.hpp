@@ -56,6 +56,9 @@ hipError_t launch_syrk(const DevTables& t, const SyrkItem* items, int64_t ntile,
                        hipStream_t stream);
 hipError_t launch_assemble(const DevTables& t, hipStream_t stream, hipEvent_t* ev);
 
+// Inverses of `count` diagonal triangles, in place in the factor values.
+hipError_t launch_invert_diag(const InvItem* items, int64_t count, double* lval, hipStream_t stream);
+
 // FP64 factor -> FP32 copy (mixed precision).
 hipError_t launch_convert_f32(const double* a, float* b, int64_t n, hipStream_t stream);
 

@@ -761,20 +761,6 @@ void repack_blocks(const SubPlan& P, const double* vals, double* bvals) {
                 }
             }
         }
-        // inverse of the diagonal triangle, column by column (forward
-        // substitution on the unit vectors, accumulated in long double)
-        const int32_t w = b.w;
-        double* li = bvals + b.linv_off;
-        std::vector<long double> z(w);
-        for (int32_t c = 0; c < w; ++c) {
-            for (int32_t i = c; i < w; ++i) {
-                long double acc = (i == c) ? 1.0L : 0.0L;
-                for (int32_t k = c; k < i; ++k) acc -= (long double)diag[(size_t)k * w + i] * z[k];
-                z[i] = acc / (long double)diag[(size_t)i * w + i];
-                const int64_t rt = i / 16;
-                li[(2 * rt * (rt + 1) + c / 4) * 64 + (i % 16) + 16 * (c % 4)] = (double)z[i];
-            }
-        }
     }
 }
 

@@ -54,7 +54,8 @@ struct PlanOptions {
 //     tile (rt, ks) holds 64 values at aoff + 64 (rt * nks + ks), value
 //     (row 16 rt + i, column 4 ks + k) at position i + 16 k, nks = ceil(w/4),
 //     zero padded;
-//   * the inverse of the diagonal triangle (lower triangular) at linv_off, in
+//   * room for the inverse of the diagonal triangle (lower triangular, computed
+//     on the device) at linv_off, in
 //     the same tile format, only the tiles on or below the diagonal: row
 //     tile rt holds k-slices ks < min(nks, 4 (rt + 1)), tile (rt, ks) at
 //     linv_off + 64 (2 rt (rt + 1) + ks).

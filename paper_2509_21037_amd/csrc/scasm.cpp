@@ -325,6 +325,9 @@ struct sc_plan_s {
     // which are laid out group after group: [g_lval[g], g_lval[g + 1])
     std::vector<int32_t> g_sub;
     std::vector<int64_t> g_sub_off, g_lval;
+    // diagonal triangles to invert, group after group: [g_inv[g], g_inv[g + 1])
+    std::vector<InvItem> h_inv;
+    std::vector<int64_t> g_inv;
     int64_t nsyrk_tile = 0;                     // h_syrk: 128 x 128 tiles first, then 64 x 64 blocks
     std::vector<SyrkItem> h_ftiles;             // stored F tiles, subdomain order (apply pass 1)
     std::vector<int2> h_frows;                  // (subdomain, 128-row block) (apply pass 2)
@@ -341,6 +344,7 @@ struct sc_plan_s {
     hipStream_t aux = nullptr;                  // second stream of the overlapped assembly
     std::vector<hipEvent_t> ov_events;          // one per group + join
     DevBuf<SyrkItem> d_ftiles;
+    DevBuf<InvItem> d_inv;
     DevBuf<int2> d_frows;
     DevBuf<double> d_part;                      // apply partial sums, 256 per stored F tile
     // allocation-free apply: chunks of whole subdomains whose stored tiles fit
@@ -486,6 +490,7 @@ struct sc_plan_s {
         return (int64_t)(d_subs.count * sizeof(SubDev) + d_tiles.count * sizeof(TileDev) +
                          d_blocks.count * sizeof(BlockDev) + d_syrk.count * sizeof(SyrkItem) +
                          d_ftiles.count * sizeof(SyrkItem) + d_frows.count * sizeof(int2) +
+                         d_inv.count * sizeof(InvItem) +
                          d_part.count * 8 + d_tile_order.count * 4 +
                          d_tile_order_g.count * 4 + d_syrk_g.count * sizeof(SyrkItem) +
                          (d_rows.count + d_piv.count + d_pi.count + d_ksteps.count + d_clear.count) * 4 + d_visits.count * sizeof(VisitDev) +
@@ -498,7 +503,7 @@ struct sc_plan_s {
     }
     void release() {
         d_subs.release(); d_tiles.release(); d_blocks.release(); d_syrk.release();
-        d_ftiles.release(); d_frows.release(); d_part.release();
+        d_ftiles.release(); d_inv.release(); d_frows.release(); d_part.release();
         d_tile_order.release(); d_tile_order_g.release(); d_syrk_g.release();
         d_rows.release(); d_piv.release(); d_pi.release(); d_ksteps.release(); d_clear.release(); d_visits.release(); d_fresh.release(); d_sgn.release();
         d_lval.release(); d_X.release(); d_F.release();
@@ -918,12 +923,16 @@ sc_status_t sc_plan_create(const sc_subdomain_desc_t* sd, int32_t nsub, const sc
             int64_t off = 0;
             for (size_t g = 0; g + 1 < P->g_sub_off.size(); ++g) {
                 P->g_lval.push_back(off);
+                P->g_inv.push_back((int64_t)P->h_inv.size());
                 for (int64_t k = P->g_sub_off[g]; k < P->g_sub_off[g + 1]; ++k) {
                     const int32_t i = P->g_sub[k];
                     P->h_subs[i].lval_off = off;
+                    for (const BlockDesc& b : P->plans[i].blocks)
+                        P->h_inv.push_back(InvItem{off + b.lval_off, off + b.linv_off, b.w, 0});
                     off += P->plans[i].bval;
                 }
             }
+            P->g_inv.push_back((int64_t)P->h_inv.size());
             P->g_lval.push_back(off);
             if (off != lv || (int64_t)P->g_sub.size() != nsub)
                 return fail(SC_ERR_INVALID_ARG, "internal: subdomain groups do not cover the batch");
@@ -1033,6 +1042,7 @@ sc_status_t sc_plan_create(const sc_subdomain_desc_t* sd, int32_t nsub, const sc
     ALLOC(p->d_syrk, p->h_syrk.size());
     ALLOC(p->d_ftiles, p->h_ftiles.size());
     ALLOC(p->d_frows, p->h_frows.size());
+    ALLOC(p->d_inv, p->h_inv.size());
     ALLOC(p->d_part, p->h_ftiles.size() * 256);
     ALLOC(p->d_tile_order, p->h_tile_order.size());
     ALLOC(p->d_tile_order_g, p->h_tile_order_g.size());
@@ -1082,6 +1092,7 @@ sc_status_t sc_plan_create(const sc_subdomain_desc_t* sd, int32_t nsub, const sc
     if (e == hipSuccess) e = up(p->d_syrk.p, p->h_syrk.data(), p->h_syrk.size() * sizeof(SyrkItem));
     if (e == hipSuccess) e = up(p->d_ftiles.p, p->h_ftiles.data(), p->h_ftiles.size() * sizeof(SyrkItem));
     if (e == hipSuccess) e = up(p->d_frows.p, p->h_frows.data(), p->h_frows.size() * sizeof(int2));
+    if (e == hipSuccess) e = up(p->d_inv.p, p->h_inv.data(), p->h_inv.size() * sizeof(InvItem));
     if (e == hipSuccess) e = up(p->d_tile_order.p, p->h_tile_order.data(), p->h_tile_order.size() * 4);
     if (e == hipSuccess) e = up(p->d_tile_order_g.p, p->h_tile_order_g.data(), p->h_tile_order_g.size() * 4);
     if (e == hipSuccess) e = up(p->d_syrk_g.p, p->h_syrk_g.data(), p->h_syrk_g.size() * sizeof(SyrkItem));
@@ -1150,6 +1161,7 @@ sc_status_t sc_factor(sc_plan_t P, const double* const* kreg_vals, void* stream,
     if (P->nval_total > 0)
         HIP_TRY(hipMemcpyAsync(P->d_lval.p, P->h_lval, (size_t)P->nval_total * sizeof(double),
                                hipMemcpyHostToDevice, st));
+    HIP_TRY(launch_invert_diag(P->d_inv.p, (int64_t)P->h_inv.size(), P->d_lval.p, st));
     if (P->mixed) HIP_TRY(launch_convert_f32(P->d_lval.p, P->d_lval32.p, P->nval_total, st));
     P->factored = true;
     return SC_OK;
@@ -1183,8 +1195,9 @@ sc_status_t sc_preprocess(sc_plan_t P, const double* const* kreg_vals, void* str
     hipError_t herr = hipSuccess;
     bool oom = false;
     // launches every consecutive group whose subdomains are all factored, in
-    // group order, on `st`: its factor values (one copy), the FP32 copy in
-    // mixed precision, its TRSM tiles and its SYRK items
+    // group order, on `st`: its factor values (one copy), the inverses of its
+    // diagonal triangles, the FP32 copy in mixed precision, its TRSM tiles and
+    // its SYRK items
     auto launch_ready = [&]() {
         while (!stop && next < ng && left[next] == 0) {
             const int64_t g = next++;
@@ -1193,6 +1206,8 @@ sc_status_t sc_preprocess(sc_plan_t P, const double* const* kreg_vals, void* str
             if (e == hipSuccess && nv > 0)
                 e = hipMemcpyAsync(P->d_lval.p + v0, P->h_lval + v0, (size_t)nv * sizeof(double),
                                    hipMemcpyHostToDevice, st);
+            if (e == hipSuccess)
+                e = launch_invert_diag(P->d_inv.p + P->g_inv[g], P->g_inv[g + 1] - P->g_inv[g], P->d_lval.p, st);
             if (e == hipSuccess && P->mixed && nv > 0) e = launch_convert_f32(P->d_lval.p + v0, P->d_lval32.p + v0, nv, st);
             if (e == hipSuccess) e = launch_trsm(t, P->d_tile_order_g.p + P->g_toff[g], P->g_tcnt[g], st);
             if (e == hipSuccess) e = launch_syrk(t, P->d_syrk_g.p + P->g_soff[g], P->g_stile[g], P->g_sblock[g], st);

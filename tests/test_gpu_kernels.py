@@ -152,3 +152,24 @@ def test_implicit_apply_split_levels(count, split):
             a, b = q[o:o + s.m], ref[o:o + s.m]
             assert float((a - b).norm()) <= 1e-11 * float(b.norm()), i
     plan.destroy()
+
+
+@pytest.mark.parametrize("width", [16, 32, 48, 64])
+def test_diagonal_inverses_at_block_widths(width):
+    """Diagonal blocks of every width up to 64 (chains of 2 .. 140 nodes: the
+    last block is the remainder), well and badly scaled: the explicit F and the
+    implicit apply, both through the inverses, against the oracle."""
+    import torch
+    subs = [scgen.laplace_1d(n, dof=np.arange(0, n + 1, max(1, n // 7)), seed=n) for n in (1, 2, 15, 16, 17, 31, 33, 47, 62, 63,
+                                                                                   64, 65, 79, 127, 139)]
+    plan = _plan(subs, panel_width=width)
+    p = torch.from_numpy(np.random.default_rng(6).uniform(-1, 1, plan.dual_total)).cuda()
+    q = torch.zeros_like(p)
+    plan.apply_implicit(p, q)
+    for i, s in enumerate(subs):
+        ref = oracle.schur(s)
+        assert oracle.relF(plan.get_F(i), ref) <= 1e-12, s.n
+        o = plan.query(i)["dual_offset"]
+        x = ref @ p[o:o + s.m].cpu().numpy()
+        assert np.linalg.norm(q[o:o + s.m].cpu().numpy() - x) <= 1e-12 * np.linalg.norm(x), s.n
+    plan.destroy()
