@@ -41,6 +41,7 @@ struct TileDev {
     int64_t fresh_off;        // increasing; their VisitDev::fresh masks from here on
     int64_t clear_off;        // rows cleared before the sweep: clear[clear_off .. + nclear)
     int32_t nvisit, nclear;
+    int32_t nchunk, pad;      // chunks of the visits (TRSM steps)
 };
 
 // One factor block a TRSM tile visits, as the kernel walks it (offsets

@@ -185,7 +185,120 @@ __device__ __forceinline__ void mma_group(const TX* __restrict__ sA, int nks, co
     }
 }
 
-template <bool MIXED, bool MERGE, bool LARGE>
+// The chunk stream of one tile: chunk c of visit record p.  c = 0 is the
+// inverse of the diagonal block (its lower tiles), the rest groups of PT
+// pruned row tiles; the second block of a pair alternates the first block's A
+// tiles of a row group with its own.  The diagonal chunk carries the row
+// indices (and the mask of those never written before) of the first row
+// group, the (second) chunk of row group q those of group q + 1: they are
+// gathered while the chunk is in use.
+template <class TX, bool MERGE>
+struct ChunkStream {
+    static constexpr int PT = kPruneTiles<TX>;
+    const VisitDev* __restrict__ V;
+    const double* __restrict__ L;
+    const TX* __restrict__ LA;
+    const int32_t* __restrict__ R;
+    const uint64_t* __restrict__ FR;
+    int nv;
+    int pk = 0, pc = 0;
+    VisitDev p;
+    __device__ __forceinline__ ChunkStream(const VisitDev* v, int n, const double* l, const TX* la, const int32_t* r,
+                                           const uint64_t* fr)
+        : V(v), L(l), LA(la), R(r), FR(fr), nv(n), p(v[0]) {}
+    // the next chunk: `bytes` bytes at src (none past the end), its row
+    // indices at ip and their mask at fp (valid addresses in any case)
+    __device__ __forceinline__ void next(const char*& src, uint32_t& bytes, const int32_t*& ip, const uint64_t*& fp) {
+        src = reinterpret_cast<const char*>(L);
+        ip = R;
+        fp = FR;
+        bytes = 0;
+        if (pk >= nv) return;
+        const int prole = MERGE ? p.flags & 3 : 0;
+        const int nks = (p.w + 3) >> 2;
+        const int nrt = (p.urows + 15) >> 4;
+        const int np = (nrt + PT - 1) / PT;
+        if (pc == 0) {
+            const int nrt_d = (p.w + 15) >> 4;
+            src = reinterpret_cast<const char*>(L + p.linv_off);
+            bytes = (2 * (nrt_d - 1) * nrt_d + nks) * 64 * 8;
+            ip = R + p.rows_off;
+            fp = FR + p.fresh;
+        } else {
+            const int q = prole == 2 ? (pc - 1) >> 1 : pc - 1;
+            const int nt = min(PT, nrt - PT * q);
+            const bool first = prole == 2 && ((pc - 1) & 1) == 0;
+            const int ks = first ? p.pair_nks : nks;
+            src = reinterpret_cast<const char*>(LA + (first ? p.pair_aoff : p.aoff) + (int64_t)PT * q * ks * 64);
+            bytes = nt * ks * 64 * (int)sizeof(TX);
+            ip = R + p.rows_off + 16 * PT * min(q + 1, np - 1);
+            fp = FR + p.fresh + min(q + 1, np - 1);
+        }
+        if (++pc > (prole == 2 ? 2 * np : np)) {
+            ++pk;
+            pc = 0;
+            if (pk < nv) p = V[pk];
+        }
+    }
+};
+
+// Launches of at most kLoaderMaxTiles tiles, one workgroup per CU: a fifth
+// wavefront streams the chunks into LDS, two of them in flight in registers of
+// its own, so that a step no longer lasts as long as a chunk takes to arrive.
+// Larger launches hide that behind the other workgroups of the CU, and the
+// fifth wavefront would cost one of them (registers).  Without / with, FP64:
+// one 16 x 16 heat square (1 tile) 30.6 / 26.7 us, one 12^3 heat cube (14) 154
+// / 122, 16 of them (224) 159 / 127, 32 triangle meshes of 129^2 nodes (256)
+// 309 / 247; beyond, 8 uneven elasticity boxes (288) 1020 / 1031.
+constexpr int64_t kLoaderMaxTiles = 256;
+
+template <class TX, bool MERGE>
+__device__ __forceinline__ void trsm_load_wave(ChunkStream<TX, MERGE> stream, int nchunk, char* __restrict__ smem) {
+    constexpr int kPieces = kChunkBytes / 1024;
+    const int lane = threadIdx.x & 63;
+    struct Set {
+        v4u c[kPieces], ci;
+    };
+    auto load = [&](Set& x) __attribute__((always_inline)) {
+        const char* src;
+        const int32_t* ip;
+        const uint64_t* fp;
+        uint32_t bytes;
+        stream.next(src, bytes, ip, fp);
+        const __amdgpu_buffer_rsrc_t rc = buffer_of(src, bytes);
+#pragma unroll
+        for (int e = 0; e < kPieces; ++e) x.c[e] = __builtin_amdgcn_raw_buffer_load_b128(rc, lane * 16, e * 1024, 0);
+        x.ci = *reinterpret_cast<const v4u*>(lane < kRowsBytes / 16 ? reinterpret_cast<const char*>(ip) + 16 * lane
+                                                                    : reinterpret_cast<const char*>(fp));
+    };
+    auto put = [&](const Set& x, int buf) __attribute__((always_inline)) {
+        char* dst = smem + buf * kBufBytes + lane * 16;
+#pragma unroll
+        for (int e = 0; e < kPieces; ++e) *reinterpret_cast<v4u*>(dst + e * 1024) = x.c[e];
+        if (lane <= kRowsBytes / 16) *reinterpret_cast<v4u*>(dst + kChunkBytes) = x.ci;
+    };
+    Set s0, s1;
+    load(s0);
+    load(s1);
+    put(s0, 0);
+    load(s0);
+    lds_barrier();
+    int s = 0;
+    for (; s + 1 < nchunk; s += 2) {
+        put(s1, 1);
+        load(s1);
+        lds_barrier();
+        put(s0, 0);
+        load(s0);
+        lds_barrier();
+    }
+    if (s < nchunk) {
+        put(s1, 1);
+        lds_barrier();
+    }
+}
+
+template <bool MIXED, bool MERGE, bool LARGE, bool LOADER>
 __device__ __forceinline__ void trsm_tile(
     const SubDev* __restrict__ subs, const TileDev* __restrict__ tiles, const int32_t* __restrict__ rows,
     const VisitDev* __restrict__ visits, const uint64_t* __restrict__ fresh, const int32_t* __restrict__ clear,
@@ -219,6 +332,11 @@ __device__ __forceinline__ void trsm_tile(
     const int nv = T.nvisit;
     const VisitDev* __restrict__ V = visits + T.visit_off;
     const uint64_t* __restrict__ FR = fresh + T.fresh_off;
+    if constexpr (LOADER)
+        if (wv == 4) {
+            if (nv > 0) trsm_load_wave<TX, MERGE>(ChunkStream<TX, MERGE>(V, nv, L, LA, R, FR), T.nchunk, smem);
+            return;
+        }
 
     // right-hand side P B^T: sign at the pivot row, zero elsewhere.  Only the
     // pivot rows are set in memory, and the rows off the paths that the SYRK
@@ -233,48 +351,14 @@ __device__ __forceinline__ void trsm_tile(
 
     TX* __restrict__ slot = reinterpret_cast<TX*>(smem + kTrsmSmem) + wv * 16 * 64 + lane;
 
-    // ---- the chunk stream: chunk c of visit record p.  c = 0 is the inverse
-    // of the diagonal block (its lower tiles), the rest groups of PT pruned
-    // row tiles; the second block of a pair alternates the first block's A
-    // tiles of a row group with its own.  The diagonal chunk carries the row
-    // indices (and the mask of those never written before) of the first row
-    // group, the (second) chunk of row group q those of group q + 1: they are
-    // gathered while the chunk is in use.
-    int pk = 0, pc = 0;
-    VisitDev p = V[0];
+    ChunkStream<TX, MERGE> stream(V, nv, L, LA, R, FR);
     v4u c0, c1, c2, c3, c4, ci;                  // the chunk after the one in LDS
     auto load_chunk = [&]() {
-        const char* src = reinterpret_cast<const char*>(L);
-        const int32_t* ip = R;
-        const uint64_t* fp = FR;
-        uint32_t bytes = 0;
-        if (pk < nv) {
-            const int prole = MERGE ? p.flags & 3 : 0;
-            const int nks = (p.w + 3) >> 2;
-            const int nrt = (p.urows + 15) >> 4;
-            const int np = (nrt + PT - 1) / PT;
-            if (pc == 0) {
-                const int nrt_d = (p.w + 15) >> 4;
-                src = reinterpret_cast<const char*>(L + p.linv_off);
-                bytes = (2 * (nrt_d - 1) * nrt_d + nks) * 64 * 8;
-                ip = R + p.rows_off;
-                fp = FR + p.fresh;
-            } else {
-                const int q = prole == 2 ? (pc - 1) >> 1 : pc - 1;
-                const int nt = min(PT, nrt - PT * q);
-                const bool first = prole == 2 && ((pc - 1) & 1) == 0;
-                const int ks = first ? p.pair_nks : nks;
-                src = reinterpret_cast<const char*>(LA + (first ? p.pair_aoff : p.aoff) + (int64_t)PT * q * ks * 64);
-                bytes = nt * ks * 64 * (int)sizeof(TX);
-                ip = R + p.rows_off + 16 * PT * min(q + 1, np - 1);
-                fp = FR + p.fresh + min(q + 1, np - 1);
-            }
-            if (++pc > (prole == 2 ? 2 * np : np)) {
-                ++pk;
-                pc = 0;
-                if (pk < nv) p = V[pk];
-            }
-        }
+        const char* src;
+        const int32_t* ip;
+        const uint64_t* fp;
+        uint32_t bytes;
+        stream.next(src, bytes, ip, fp);
         const __amdgpu_buffer_rsrc_t rc = buffer_of(src, bytes);
         const int e = threadIdx.x * 16;
         c0 = __builtin_amdgcn_raw_buffer_load_b128(rc, e, 0, 0);
@@ -295,14 +379,18 @@ __device__ __forceinline__ void trsm_tile(
         if (threadIdx.x <= kRowsBytes / 16) *reinterpret_cast<v4u*>(dst + kChunkBytes + e) = ci;
     };
     int buf = 0;
-    auto step_begin = [&]() { load_chunk(); };
+    auto step_begin = [&]() {
+        if constexpr (!LOADER) load_chunk();
+    };
     auto step_end = [&]() {
-        put_chunk(smem + (buf ^ 1) * kBufBytes);
+        if constexpr (!LOADER) put_chunk(smem + (buf ^ 1) * kBufBytes);
         lds_barrier();
         buf ^= 1;
     };
-    load_chunk();
-    put_chunk(smem);
+    if constexpr (!LOADER) {
+        load_chunk();
+        put_chunk(smem);
+    }
     lds_barrier();
 
     TX xin[4][4];                                // X rows of the next block, accumulator layout
@@ -527,9 +615,10 @@ __device__ __forceinline__ void trsm_tile(
 
 // MERGE: with the merged pairs (the visits' roles); without, every visit is
 // alone and the merged code paths compile away.  LARGE: some X slab holds
-// kTrsmSlabBytes or more.
-template <bool MERGE, bool LARGE>
-__global__ __launch_bounds__(256, MERGE ? 2 : 3) void trsm_stair_f64(
+// kTrsmSlabBytes or more.  LOADER: a fifth wavefront streams the chunks
+// (launches of at most kLoaderMaxTiles tiles).
+template <bool MERGE, bool LARGE, bool LOADER>
+__global__ __launch_bounds__(LOADER ? 320 : 256, LOADER ? 1 : MERGE ? 2 : 3) void trsm_stair_f64(
     const SubDev* __restrict__ subs, const TileDev* __restrict__ tiles, const int32_t* __restrict__ rows,
     const VisitDev* __restrict__ visits, const uint64_t* __restrict__ fresh, const int32_t* __restrict__ clear,
     const double* __restrict__ lval,
@@ -538,11 +627,11 @@ __global__ __launch_bounds__(256, MERGE ? 2 : 3) void trsm_stair_f64(
     __shared__ __align__(16) char smem[kTrsmSmem + (MERGE ? kSlotBytes<double> : 0)];
     const int ti = order[blockIdx.x];
     if (ti < 0) return;
-    trsm_tile<false, MERGE, LARGE>(subs, tiles, rows, visits, fresh, clear, lval, nullptr, piv, sgn, X, ti, smem);
+    trsm_tile<false, MERGE, LARGE, LOADER>(subs, tiles, rows, visits, fresh, clear, lval, nullptr, piv, sgn, X, ti, smem);
 }
 
-template <bool MERGE, bool LARGE>
-__global__ __launch_bounds__(256, MERGE ? 2 : 3) void trsm_stair_mixed(
+template <bool MERGE, bool LARGE, bool LOADER>
+__global__ __launch_bounds__(LOADER ? 320 : 256, LOADER ? 1 : MERGE ? 2 : 3) void trsm_stair_mixed(
     const SubDev* __restrict__ subs, const TileDev* __restrict__ tiles, const int32_t* __restrict__ rows,
     const VisitDev* __restrict__ visits, const uint64_t* __restrict__ fresh, const int32_t* __restrict__ clear,
     const double* __restrict__ lval,
@@ -552,7 +641,7 @@ __global__ __launch_bounds__(256, MERGE ? 2 : 3) void trsm_stair_mixed(
     __shared__ __align__(16) char smem[kTrsmSmem + (MERGE ? kSlotBytes<float> : 0)];
     const int ti = order[blockIdx.x];
     if (ti < 0) return;
-    trsm_tile<true, MERGE, LARGE>(subs, tiles, rows, visits, fresh, clear, lval, lval32, piv, sgn, X, ti, smem);
+    trsm_tile<true, MERGE, LARGE, LOADER>(subs, tiles, rows, visits, fresh, clear, lval, lval32, piv, sgn, X, ti, smem);
 }
 
 // ---------------------------------------------------------------------------
@@ -947,7 +1036,8 @@ __global__ __launch_bounds__(256, EDGE == 128 ? 2 : 4) void syrk_split_f32(
 // quotient corrected once), rounded to FP64 at the end: more digits than the
 // 64-bit mantissas of x87, in which the host computed the inverses before (22%
 // of its time on an 11^3 elasticity subdomain, 40% on 12^3 heat).  Bound by
-// FP64 arithmetic and LDS latency, 50 KB of LDS (packed triangles): @@INV@@
+// FP64 arithmetic and LDS latency, 50 KB of LDS (packed triangles): 0.12
+// ms for the 700 blocks of 8 uneven elasticity boxes.
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ int tri(int i, int k) { return i * (i + 1) / 2 + k; }
 
@@ -1021,20 +1111,29 @@ hipError_t launch_invert_diag(const InvItem* items, int64_t count, double* lval,
     return hipGetLastError();
 }
 
-template <bool MERGE, bool LARGE>
+template <bool MERGE, bool LARGE, bool LOADER>
 static void trsm_launch(const DevTables& t, const int32_t* order, int64_t count, hipStream_t stream) {
+    const dim3 grid((unsigned)count), block(LOADER ? 320 : 256);
     if (t.X32)
-        hipLaunchKernelGGL((trsm_stair_mixed<MERGE, LARGE>), dim3((unsigned)count), dim3(256), 0, stream, t.subs,
-                           t.tiles, t.rows, t.visits, t.fresh, t.clear, t.lval, t.lval32, t.piv, t.sgn, order, t.X32);
+        hipLaunchKernelGGL((trsm_stair_mixed<MERGE, LARGE, LOADER>), grid, block, 0, stream, t.subs, t.tiles, t.rows,
+                           t.visits, t.fresh, t.clear, t.lval, t.lval32, t.piv, t.sgn, order, t.X32);
     else
-        hipLaunchKernelGGL((trsm_stair_f64<MERGE, LARGE>), dim3((unsigned)count), dim3(256), 0, stream, t.subs,
-                           t.tiles, t.rows, t.visits, t.fresh, t.clear, t.lval, t.piv, t.sgn, order, t.X);
+        hipLaunchKernelGGL((trsm_stair_f64<MERGE, LARGE, LOADER>), grid, block, 0, stream, t.subs, t.tiles, t.rows,
+                           t.visits, t.fresh, t.clear, t.lval, t.piv, t.sgn, order, t.X);
 }
 
 hipError_t launch_trsm(const DevTables& t, const int32_t* order, int64_t count, hipStream_t stream) {
     if (count <= 0) return hipSuccess;
-    if (t.trsm_large) t.trsm_merge ? trsm_launch<true, true>(t, order, count, stream) : trsm_launch<false, true>(t, order, count, stream);
-    else t.trsm_merge ? trsm_launch<true, false>(t, order, count, stream) : trsm_launch<false, false>(t, order, count, stream);
+    if (t.trsm_large) {
+        if (t.trsm_merge) trsm_launch<true, true, false>(t, order, count, stream);
+        else trsm_launch<false, true, false>(t, order, count, stream);
+    } else if (count <= kLoaderMaxTiles) {
+        if (t.trsm_merge) trsm_launch<true, false, true>(t, order, count, stream);
+        else trsm_launch<false, false, true>(t, order, count, stream);
+    } else {
+        if (t.trsm_merge) trsm_launch<true, false, false>(t, order, count, stream);
+        else trsm_launch<false, false, false>(t, order, count, stream);
+    }
     return hipGetLastError();
 }
 

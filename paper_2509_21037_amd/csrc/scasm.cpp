@@ -181,6 +181,7 @@ struct TileVisits {
     std::vector<uint64_t> fresh;
     std::vector<int32_t> clear;                      // rows set or cleared before the sweep
     std::vector<int64_t> fresh_ptr, clear_ptr;       // each tile's first mask and row
+    std::vector<int32_t> nchunk;                     // each tile's chunks
 };
 
 void build_visits(const SubPlan& sp, bool staircase, const std::vector<int32_t>* pair, int pt, TileVisits& out) {
@@ -193,6 +194,7 @@ void build_visits(const SubPlan& sp, bool staircase, const std::vector<int32_t>*
         const size_t first = out.visits.size();
         out.fresh_ptr.push_back((int64_t)out.fresh.size());
         out.clear_ptr.push_back((int64_t)out.clear.size());
+        out.nchunk.push_back(0);
         auto clear_row = [&](int32_t r) {
             if (written[r] == t) return;
             written[r] = t;
@@ -265,6 +267,8 @@ void build_visits(const SubPlan& sp, bool staircase, const std::vector<int32_t>*
             }
             out.fresh.push_back(m);
             if (clear && v.urows > 0) v.flags |= kVisitNextEarly;
+            const int32_t np = (v.urows + 16 * pt - 1) / (16 * pt);
+            out.nchunk.back() += 1 + (role == 2 ? 2 * np : np);
             prev = role;
         }
     }
@@ -989,6 +993,7 @@ sc_status_t sc_plan_create(const sc_subdomain_desc_t* sd, int32_t nsub, const sc
                 T.fresh_off = (int64_t)P->h_fresh.size() + tv[i].fresh_ptr[t];
                 T.clear_off = (int64_t)P->h_clear.size() + tv[i].clear_ptr[t];
                 T.nclear = (int32_t)(tv[i].clear_ptr[t + 1] - tv[i].clear_ptr[t]);
+                T.nchunk = tv[i].nchunk[t];
                 k += T.nvisit;
             }
             P->h_visits.insert(P->h_visits.end(), tv[i].visits.begin(), tv[i].visits.end());

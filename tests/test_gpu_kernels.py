@@ -45,6 +45,29 @@ def test_dense_F_on_device_at_tile_edges(precision):
 
 
 @pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("shape", ["one block", "two blocks", "pairs", "no pairs"])
+def test_trsm_small_launch_matches_large(precision, shape):
+    """One subdomain alone (at most one TRSM workgroup per CU: the chunks come
+    from a fifth wavefront) and among 520 others (each wavefront loads its
+    share): the same sums in the same order, so the same F bit for bit, for a
+    tile of one block (one chunk), of two, of merged pairs and without."""
+    s, merge = {"one block": (scgen.box_subdomain("heat", (4, 4), 0.25, 80), False),
+                "two blocks": (scgen.box_subdomain("heat", (9, 8), 1.0 / 9, 81), False),
+                "pairs": (scgen.box_subdomain("elasticity", (7, 6, 8), 0.125, 82), True),
+                "no pairs": (scgen.box_subdomain("elasticity", (6, 6, 7), 1.0 / 7, 83), False)}[shape]
+    one = scgen.box_subdomain("heat", (5, 3), 0.2, 84)
+    kw = dict(precision=precision, pair_merge=merge, syrk_kind=1)
+    alone = _plan([s], **kw)
+    batch = _plan([s] + [one] * 520, **kw)
+    F = alone.get_F(0)
+    assert np.array_equal(F, batch.get_F(0))
+    sel = np.sort(np.random.default_rng(85).choice(s.m, size=min(64, s.m), replace=False))
+    assert oracle.relF(F[np.ix_(sel, sel)], oracle.schur(s, sel=sel)) <= (1e-12 if precision == "fp64" else 1e-5)
+    alone.destroy()
+    batch.destroy()
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
 @pytest.mark.parametrize("split", ["uniform", "etree"])
 def test_trsm_reads_only_rows_it_wrote(precision, split):
     """The X buffer full of another batch's values (temporary-memory waves
