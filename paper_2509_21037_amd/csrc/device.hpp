@@ -12,8 +12,8 @@ constexpr int kMaxPanel = 64;      // GPU panel width bound the TRSM kernel is b
 constexpr int kSyrkTile = 128;     // edge of an F output tile (two X column tiles)
 constexpr int kFTileElems = kSyrkTile * kSyrkTile;
 // Workgroups are dispatched to the accelerator's XCDs round-robin (workgroup
-// k runs on XCD k mod kNumXcd); work lists are interleaved so that all items
-// of one subdomain share an XCD and its L2.
+// k runs on XCD k mod kNumXcd); work lists are interleaved so that the items
+// of one subdomain share an XCD and its L2, as far as that keeps all XCDs busy.
 constexpr int kNumXcd = 8;
 // Overlapped assembly: the batch is cut into this many groups of subdomains
 // (each XCD's list into consecutive parts); the SYRK of a group runs on a

@@ -276,6 +276,42 @@ void build_visits(const SubPlan& sp, bool staircase, const std::vector<int32_t>*
     out.clear_ptr.push_back((int64_t)out.clear.size());
 }
 
+// Evens out the work lists of the XCDs (items of a subdomain share an XCD and
+// its L2): items move, the cheapest of the last subdomain first, from the most
+// to the least loaded XCD while the two differ by more than the item and
+// kXcdSlack of the mean load.  A moved item reads its factor (or X) into
+// another L2, which costs far less than idle CUs.  Whole subdomains / evened
+// out: 20^3 elasticity, one subdomain 21.1 / 4.2 ms (mixed 8.5 / 2.0), four
+// 20.9 / 12.5, eight (even as they are) 23.0 / 23.3; uneven elasticity boxes,
+// one 1.20 / 0.57, eight 1.92 / 1.32, sixteen 1.98 / 1.72, 64 7.24 / 7.15.
+// With a slack of 0.2: one 20^3 4.5, eight boxes 1.34, sixteen 1.78.
+constexpr double kXcdSlack = 0.05;
+template <class T, class Cost>
+void even_out_xcds(std::vector<std::vector<T>>& xl, const Cost& cost) {
+    std::vector<double> load(kNumXcd, 0.0);
+    double total = 0;
+    for (int x = 0; x < kNumXcd; ++x) {
+        for (const T& it : xl[x]) load[x] += cost(it);
+        total += load[x];
+    }
+    std::vector<std::vector<T>> got(kNumXcd);
+    for (;;) {
+        const int x = (int)(std::max_element(load.begin(), load.end()) - load.begin());
+        const int y = (int)(std::min_element(load.begin(), load.end()) - load.begin());
+        if (xl[x].empty()) break;
+        const double c = cost(xl[x].back());
+        if (load[x] - load[y] <= c + kXcdSlack * total / kNumXcd) break;
+        got[y].push_back(xl[x].back());
+        xl[x].pop_back();
+        load[x] -= c;
+        load[y] += c;
+    }
+    for (int x = 0; x < kNumXcd; ++x) {              // long items first
+        std::stable_sort(got[x].begin(), got[x].end(), [&](const T& a, const T& b) { return cost(a) > cost(b); });
+        xl[x].insert(xl[x].end(), got[x].begin(), got[x].end());
+    }
+}
+
 #define HIP_TRY(expr)                                                                        \
     do {                                                                                     \
         hipError_t e_ = (expr);                                                              \
@@ -662,6 +698,7 @@ sc_status_t sc_plan_create(const sc_subdomain_desc_t* sd, int32_t nsub, const sc
     // blocks
     std::vector<std::vector<SyrkItem>> sub_tiles(nsub), sub_blocks(nsub);
     std::vector<int64_t> x_elems(nsub, 0);      // X slab elements of each subdomain
+    std::vector<int64_t> tile_steps;            // chunk steps of each tile (its cost)
     int64_t blk = 0, rows = 0, lv = 0, colo = 0, xo = 0, fo = 0, dual = 0;
     std::vector<std::vector<int32_t>> pairs(nsub);   // merge_pairs flags per block
     int64_t upd_rows = 0, merged_rows = 0;      // TRSM pruned-row updates, and those the merged pairs save
@@ -720,6 +757,10 @@ sc_status_t sc_plan_create(const sc_subdomain_desc_t* sd, int32_t nsub, const sc
             if ((int64_t)(sp.n - T.kstart) * kTile * (P->mixed ? 4 : 8) >= kTrsmSlabBytes) P->trsm_large = true;
             T.nvisit = (int32_t)(sp.visit_ptr[t + 1] - sp.visit_ptr[t]);
             P->h_tiles.push_back(T);
+            int64_t steps = 0;
+            for (int64_t k = sp.visit_ptr[t]; k < sp.visit_ptr[t + 1]; ++k)
+                steps += 2 + (sp.blocks[sp.visit[k]].nbelow + 31) / 32;
+            tile_steps.push_back(steps);
         }
         const int32_t nst = (sp.m + kSyrkTile - 1) / kSyrkTile;
         s.ftile_off = (int64_t)P->h_ftiles.size();
@@ -804,7 +845,8 @@ sc_status_t sc_plan_create(const sc_subdomain_desc_t* sd, int32_t nsub, const sc
                                             " is below the X slabs of subdomain " + std::to_string(i) + " (" +
                                             std::to_string(x_elems[i] * (P->mixed ? 4 : 8)) + " bytes)");
     // ---- XCD-aware work lists: subdomains go to XCDs by longest-processing-
-    // time on their useful flops; XCD x receives workgroups x, x + 8, ...
+    // time on their useful flops, then each list (of tiles, of SYRK items) is
+    // evened out; XCD x receives workgroups x, x + 8, ...
     {
         std::vector<int32_t> byc(nsub);
         std::iota(byc.begin(), byc.end(), 0);
@@ -827,10 +869,10 @@ sc_status_t sc_plan_create(const sc_subdomain_desc_t* sd, int32_t nsub, const sc
                 const auto& src = part == 0 ? sub_tiles : sub_blocks;
                 std::vector<std::vector<SyrkItem>> xl(kNumXcd);
                 size_t len = 0;
-                for (int x = 0; x < kNumXcd; ++x) {
+                for (int x = 0; x < kNumXcd; ++x)
                     for (int32_t i : subs_of_xcd[x]) xl[x].insert(xl[x].end(), src[i].begin(), src[i].end());
-                    len = std::max(len, xl[x].size());
-                }
+                even_out_xcds(xl, [](const SyrkItem& it) { return (double)it.nsteps; });
+                for (int x = 0; x < kNumXcd; ++x) len = std::max(len, xl[x].size());
                 const size_t base = out.size();
                 out.resize(base + len * kNumXcd, SyrkItem{-1, 0, 0, 0, 0});
                 for (int x = 0; x < kNumXcd; ++x)
@@ -849,6 +891,7 @@ sc_status_t sc_plan_create(const sc_subdomain_desc_t* sd, int32_t nsub, const sc
                 return P->h_tiles[a].nvisit > P->h_tiles[b].nvisit;
             });
         };
+        auto tile_cost = [&](int32_t t) { return (double)tile_steps[t]; };
         auto by_steps = [](const SyrkItem& a, const SyrkItem& b) { return a.nsteps > b.nsteps; };
         for (int32_t i = 0; i < nsub; ++i) {
             std::stable_sort(sub_tiles[i].begin(), sub_tiles[i].end(), by_steps);
@@ -896,10 +939,10 @@ sc_status_t sc_plan_create(const sc_subdomain_desc_t* sd, int32_t nsub, const sc
                 std::vector<std::vector<int32_t>> gt(kNumXcd), gsub(kNumXcd);
                 for (int32_t i : grp) gsub[xcd_of[i]].push_back(i);
                 size_t lt = 0;
-                for (int x = 0; x < kNumXcd; ++x) {
+                for (int x = 0; x < kNumXcd; ++x)
                     for (int32_t i : gsub[x]) push_tiles(gt[x], i);
-                    lt = std::max(lt, gt[x].size());
-                }
+                even_out_xcds(gt, tile_cost);
+                for (int x = 0; x < kNumXcd; ++x) lt = std::max(lt, gt[x].size());
                 P->g_sub_off.push_back((int64_t)P->g_sub.size());
                 {
                     size_t lg = 0;
@@ -959,6 +1002,7 @@ sc_status_t sc_plan_create(const sc_subdomain_desc_t* sd, int32_t nsub, const sc
         }
         for (int x = 0; x < kNumXcd; ++x)
             for (int32_t i : xsub[x]) push_tiles(xt[x], i);
+        even_out_xcds(xt, tile_cost);
         size_t lt = 0;
         for (int x = 0; x < kNumXcd; ++x) lt = std::max(lt, xt[x].size());
         P->h_tile_order.assign(lt * kNumXcd, -1);

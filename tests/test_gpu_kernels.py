@@ -67,6 +67,28 @@ def test_trsm_small_launch_matches_large(precision, shape):
     batch.destroy()
 
 
+@pytest.mark.parametrize("mode", ["two kernels", "overlapped", "waves", "preprocess"])
+@pytest.mark.parametrize("count", [1, 3, 9])
+def test_work_lists_of_few_uneven_subdomains(count, mode):
+    """Fewer subdomains than XCDs, or one more, of very different sizes: their
+    tiles and SYRK items are dealt out over the XCDs, every one of them once
+    in each way to assemble (F bit for bit as each subdomain's alone)."""
+    edges = [(9, 8, 9), (2, 2, 2), (6, 7, 5), (4, 4, 4), (3, 2, 5), (7, 7, 3), (1, 1, 1), (5, 5, 6), (8, 2, 2)]
+    subs = [scgen.box_subdomain("elasticity", e, 0.125, 90 + i) for i, e in enumerate(edges[:count])]
+    kw = {"overlapped": dict(assembly="overlap"),
+          "waves": dict(arena_cap_bytes=2 * max(s.n * ((s.m + 63) // 64) * 512 for s in subs))}.get(mode, {})
+    plan = _plan(subs, syrk_kind=2, **kw)
+    if mode == "preprocess":
+        plan.preprocess([s.val for s in subs])
+    for i, s in enumerate(subs):
+        alone = _plan([s], syrk_kind=2)
+        assert np.array_equal(plan.get_F(i), alone.get_F(0)), i
+        alone.destroy()
+    sel = np.arange(0, subs[0].m, 7)
+    assert oracle.relF(plan.get_F(0)[np.ix_(sel, sel)], oracle.schur(subs[0], sel=sel)) <= 1e-12
+    plan.destroy()
+
+
 @pytest.mark.parametrize("precision", ["fp64", "mixed"])
 @pytest.mark.parametrize("split", ["uniform", "etree"])
 def test_trsm_reads_only_rows_it_wrote(precision, split):
