@@ -637,52 +637,46 @@ std::string build_plan(const SubdomainInput& in, const PlanOptions& opt, SubPlan
 // ---------------------------------------------------------------------------
 // numeric supernodal Cholesky: for each supernode in order, factor its panel
 // (the (w + r) x w block column: Cholesky of the w x w diagonal block and the
-// triangular solve of the r rows below, left-looking over column blocks of
-// kPanelBlock, the update of each block a product with the columns before it),
-// then subtract its outer-product contribution from every later supernode its
-// rows touch (right-looking: one product per target supernode into a dense
-// buffer, scattered into the target's panel).
+// triangular solve of the r rows below, left-looking over blocks of
+// kFactorColumns columns, the update of each block a product with the columns
+// before it), then subtract its outer-product contribution from every later
+// supernode its rows touch (right-looking).  The rows below are packed once
+// per supernode and each 16 x 8 tile of the product goes from registers to the
+// target's columns, whose lines are on their way while it is computed; the
+// rows of a panel are solved in strips that stay in registers.  A dense buffer
+// per target, its own packing and an element-wise scatter before / now, one
+// thread: 11^3 elasticity 28.2 / 19.8 ms, 16 x 15 x 16 149 / 109, 12^3 heat 3.3
+// / 2.7, 129^2 triangles 10.5 / 7.1.
 // ---------------------------------------------------------------------------
-namespace {
-constexpr int32_t kPanelBlock = 32;
-constexpr int64_t kUpdateBlock = 64;
-}
-
 int64_t factor_numeric(const SubPlan& P, const double* kvals, double* vals) {
     std::memset(vals, 0, sizeof(double) * (size_t)P.nval);
     for (size_t e = 0; e < P.kmap.size(); ++e)
         if (P.kmap[e] >= 0) vals[P.kmap[e]] += kvals[e];
     std::vector<int32_t> pos(P.n, -1);
-    std::vector<double> tmp;
+    std::vector<double> pa, pb;
+    std::vector<int32_t> rel, cols;
     for (int32_t s = 0; s < P.nsuper; ++s) {
         const int32_t f = P.sfirst[s];
         const int32_t w = P.sfirst[s + 1] - f;
         const int64_t ld = P.srow_ptr[s + 1] - P.srow_ptr[s];
         double* A = vals + P.spanel_off[s];
         const int32_t* rows = P.srows.data() + P.srow_ptr[s];
-        for (int32_t j0 = 0; j0 < w; j0 += kPanelBlock) {
-            const int32_t j1 = std::min(w, j0 + kPanelBlock);
+        for (int32_t j0 = 0; j0 < w; j0 += kFactorColumns) {
+            const int32_t j1 = std::min(w, j0 + kFactorColumns);
             // columns [j0, j1) minus the contributions of columns [0, j0)
             // (rows j0.. of both; the entries above the diagonal that this
             // also updates are never read)
             gemm_nt(ld - j0, j1 - j0, j0, -1.0, A + j0, ld, A + j0, ld, A + j0 + (size_t)j0 * ld, ld);
-            for (int32_t c = j0; c < j1; ++c) {
-                double* colc = A + (size_t)c * ld;
-                for (int32_t k = j0; k < c; ++k) {
-                    const double* colk = A + (size_t)k * ld;
-                    const double lck = colk[c];
-                    if (lck == 0.0) continue;
-                    for (int64_t i = c; i < ld; ++i) colc[i] -= colk[i] * lck;
-                }
-                const double d = colc[c];
-                if (!(d > 0.0)) return f + c;
-                const double sd = std::sqrt(d);
-                colc[c] = sd;
-                const double inv = 1.0 / sd;
-                for (int64_t i = c + 1; i < ld; ++i) colc[i] *= inv;
-            }
+            const int64_t bad = factor_columns(A, ld, j0, j1);
+            if (bad >= 0) return f + bad;
         }
-        // contributions to later supernodes
+        // contributions to later supernodes: the rows below packed once, then
+        // one product per target, subtracted tile by tile from its columns
+        if (ld > w) {
+            pack_rows(A + w, ld, ld - w, w, pa);
+            rel.resize((size_t)(ld - w));
+            cols.resize((size_t)(ld - w));
+        }
         int64_t q = w;
         while (q < ld) {
             const int32_t t = P.col2super[rows[q]];
@@ -693,22 +687,9 @@ int64_t factor_numeric(const SubPlan& P, const double* kvals, double* vals) {
             const int64_t ldt = P.srow_ptr[t + 1] - P.srow_ptr[t];
             const int32_t* trows = P.srows.data() + P.srow_ptr[t];
             for (int64_t k = 0; k < ldt; ++k) pos[trows[k]] = (int32_t)k;
-            double* T = vals + P.spanel_off[t];
-            const int64_t nr = ld - q, nb = q1 - q;
-            // tmp = L[q:ld, :] L[q:q1, :]^T (nr x nb), on and below the
-            // diagonal of its top nb x nb block: column block [b0, b1) from
-            // row b0 down
-            tmp.resize((size_t)(nr * nb));
-            for (int64_t b0 = 0; b0 < nb; b0 += kUpdateBlock) {
-                const int64_t b1 = std::min(nb, b0 + kUpdateBlock);
-                for (int64_t b = b0; b < b1; ++b) std::fill(tmp.begin() + b * nr + b0, tmp.begin() + (b + 1) * nr, 0.0);
-                gemm_nt(nr - b0, b1 - b0, w, 1.0, A + q + b0, ld, A + q + b0, ld, tmp.data() + b0 * nr + b0, nr);
-            }
-            for (int64_t b = 0; b < nb; ++b) {
-                double* tcol = T + (size_t)(rows[q + b] - tf) * ldt;
-                const double* src = tmp.data() + b * nr;
-                for (int64_t a = b; a < nr; ++a) tcol[pos[rows[q + a]]] -= src[a];
-            }
+            for (int64_t a = q; a < ld; ++a) rel[a - w] = pos[rows[a]];
+            for (int64_t b = q; b < q1; ++b) cols[b - q] = rows[b] - tf;
+            subtract_outer(pa.data(), ld - w, w, q - w, q1 - q, rel.data(), vals + P.spanel_off[t], ldt, cols.data(), pb);
             q = q1;
         }
     }

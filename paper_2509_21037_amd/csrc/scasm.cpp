@@ -1190,13 +1190,12 @@ sc_status_t sc_factor(sc_plan_t P, const double* const* kreg_vals, void* stream,
             const SubPlan& sp = P->plans[i];
             try {
                 sn.resize((size_t)std::max<int64_t>(1, sp.nval));
+                bad[i] = factor_numeric(sp, kreg_vals[i], sn.data());
+                if (bad[i] < 0) repack_blocks(sp, sn.data(), P->h_lval + P->h_subs[i].lval_off);
             } catch (const std::bad_alloc&) {
 #pragma omp atomic write
                 oom = true;
-                continue;
             }
-            bad[i] = factor_numeric(sp, kreg_vals[i], sn.data());
-            if (bad[i] < 0) repack_blocks(sp, sn.data(), P->h_lval + P->h_subs[i].lval_off);
         }
     }
     if (oom) return fail(SC_ERR_OOM, "host allocation failed in sc_factor");
@@ -1274,12 +1273,10 @@ sc_status_t sc_preprocess(sc_plan_t P, const double* const* kreg_vals, void* str
             bool ok = true;
             try {
                 sn.resize((size_t)std::max<int64_t>(1, sp.nval));
-            } catch (const std::bad_alloc&) {
-                ok = false;
-            }
-            if (ok) {
                 bad[i] = factor_numeric(sp, kreg_vals[i], sn.data());
                 if (bad[i] < 0) repack_blocks(sp, sn.data(), P->h_lval + P->h_subs[i].lval_off);
+            } catch (const std::bad_alloc&) {
+                ok = false;
             }
             std::lock_guard<std::mutex> lk(mu);
             if (!ok) { oom = true; stop = true; }
