@@ -492,7 +492,7 @@ __device__ __forceinline__ double linv_at(const double* __restrict__ Lv, int r, 
     return Lv[(2 * rt * (rt + 1) + (k >> 2)) * 64 + (r & 15) + 16 * (k & 3)];
 }
 
-// x = P B^T p and q = B P^T x: 1024-thread workgroups, on small batches up to
+// x = P B^T p (and the chains' counters cleared) and q = B P^T x: 1024-thread workgroups, on small batches up to
 // kInitSplit per subdomain, each a share of the rows (it walks all multipliers
 // and keeps those whose pivot is in its share) or of the multipliers.
 // 16 x 20^3 elasticity (27783 rows, 7938 multipliers): 30 + 10 us with one per
@@ -506,8 +506,12 @@ static inline int init_split(int64_t subdomains) {
 __global__ __launch_bounds__(kInitThreads) void implicit_init(
     const SubDev* __restrict__ subs, const int32_t* __restrict__ piv, const int32_t* __restrict__ pi,
     const int8_t* __restrict__ sgn, const int64_t* __restrict__ xoff, const double* __restrict__ p,
-    double* __restrict__ xwork, const int32_t* __restrict__ sub_list, int C)
+    double* __restrict__ xwork, const int32_t* __restrict__ sub_list, int C, int32_t* __restrict__ counters,
+    int64_t ncounters)
 {
+    for (int64_t i = blockIdx.x * (int64_t)kInitThreads + threadIdx.x; i < ncounters;
+         i += gridDim.x * (int64_t)kInitThreads)
+        counters[i] = 0;
     const int at = (int)blockIdx.x / C, c = (int)blockIdx.x % C;
     const int sub = sub_list ? sub_list[at] : at;
     const SubDev S = subs[sub];
@@ -532,29 +536,9 @@ __global__ __launch_bounds__(kInitThreads) void implicit_init(
 // blocks of a level are few (the chain of one subdomain each), so each step
 // spreads its short dependent sums over many threads; partial sums meet in
 // LDS in a fixed order.
-constexpr int kImplThreads = 1024;
-constexpr int kImplParts = kImplThreads / 64;
-// factor tiles each wavefront has in flight in the off-diagonal products:
-// 16 where a launch has fewer workgroups than compute units (the step's
-// latency is the level's time), 8 on wide levels (two workgroups per CU
-// share the memory system)
-constexpr int kImplBatchNarrow = 16, kImplBatchWide = 8;
-// Levels of fewer blocks than this split each block over up to kImplSplit
-// workgroups, as many as fill the chip twice.  Forward, each repeats the
-// update sums and the diagonal product and takes its share of the row tiles
-// (at least one per wavefront).  Backward, a first launch sums shares of the
-// rows, a second adds them and does the diagonal product: from
-// kImplBwdSplitRows rows on in a block of the level (the second launch costs 4
-// us, a row tile in one workgroup about 0.15 us).  16 x 20^3 elasticity,
-// levels of 16-32 blocks of up to 1600 rows: forward 15.8 us with 4 shares and
-// a load at a time in the update sums, now 13.7; backward 19.1 us in one
-// launch, now 10.6 + 4.2 in two (7.3 in one for blocks below 512 rows).
-constexpr int64_t kImplNarrowBelow = 256;
-constexpr int kImplSplit = 8;
-constexpr int kImplBwdSplitRows = 512;
-static inline int impl_split(int64_t blocks, int tiles) {
-    return (int)std::max<int64_t>(1, std::min<int64_t>({kImplSplit, 512 / blocks, tiles}));
-}
+// factor tiles each wavefront has in flight in the off-diagonal products (16:
+// 100 registers, one workgroup per CU)
+constexpr int kImplBatch = 8;
 
 __device__ __forceinline__ double sum_parts(const double (*sp)[64], int r) {
     double v = 0.0;
@@ -565,13 +549,30 @@ __device__ __forceinline__ double sum_parts(const double (*sp)[64], int r) {
 
 // forward step of block b: x_b <- L_bb^{-1}(x_b - updates), then its updates
 // L[R_b, b] x_b into its entries of ubuf; share g of G of the row tiles.
-// EARLY (narrow levels): the loads of the diagonal inverse and of the first
-// factor tiles are in flight during the update sums.
-template <int NB, bool EARLY>
+// EARLY (where few workgroups hide it): the loads of the diagonal inverse and
+// of the first factor tiles are in flight during the update sums.
+// wait(): before the first read of what other blocks write; kShared: they run
+// in the same launch, and what passes between them goes through memory (loads
+// and stores at agent scope, past the caches of one XCD).
+struct NoWait {
+    static constexpr bool kShared = false;
+    __device__ void operator()() const {}
+};
+template <bool SHARED>
+__device__ __forceinline__ double get(const double* p) {
+    if constexpr (SHARED) return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    else return *p;
+}
+template <bool SHARED>
+__device__ __forceinline__ void put(double* p, double v) {
+    if constexpr (SHARED) __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    else *p = v;
+}
+template <int NB, bool EARLY, class Wait = NoWait>
 __device__ __forceinline__ void implicit_fwd_block(
     const ImplBlock& b, const double* __restrict__ lval, const int32_t* __restrict__ rptr,
     const int32_t* __restrict__ rpos, const double* __restrict__ x, double* __restrict__ yo,
-    double* ubuf, double (*sp)[64], double* sx, int g = 0, int G = 1)
+    double* ubuf, double (*sp)[64], double* sx, int g = 0, int G = 1, const Wait& wait = Wait())
 {
     const int tid = threadIdx.x;
     const int r = tid & 63;
@@ -603,18 +604,31 @@ __device__ __forceinline__ void implicit_fwd_block(
     {
         const int q = 4 * part + (r >> 4);
         double v = 0.0;
+        int e = 0, e1 = 0, at[4] = {};
+        auto load_positions = [&]() {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) at[i] = rpos[min(e + 16 * i, e1 - 1)];
+        };
         if (q < w) {
             const int32_t* __restrict__ rp = rptr + b.rptr + b.row0 + q;
-            const int e1 = rp[1];
-            for (int e = rp[0] + (r & 15); e < e1; e += 64) {
-                double c[4];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) c[i] = ubuf[rpos[min(e + 16 * i, e1 - 1)]];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) v -= e + 16 * i < e1 ? c[i] : 0.0;
-            }
-            if ((r & 15) == 0) v += x[b.x + b.row0 + q];
+            e1 = rp[1];
+            e = rp[0] + (r & 15);
+            if (e < e1) load_positions();
+            if ((r & 15) == 0) v = x[b.x + b.row0 + q];
         }
+        wait();
+        double sum = 0.0;
+        while (e < e1) {
+            double c[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) c[i] = get<Wait::kShared>(ubuf + at[i]);
+            const int e0 = e;
+            e += 64;
+            if (e < e1) load_positions();
+#pragma unroll
+            for (int i = 0; i < 4; ++i) sum -= e0 + 16 * i < e1 ? c[i] : 0.0;
+        }
+        v = sum + v;
         v += __shfl_xor(v, 1, 64);
         v += __shfl_xor(v, 2, 64);
         v += __shfl_xor(v, 4, 64);
@@ -655,21 +669,17 @@ __device__ __forceinline__ void implicit_fwd_block(
         if (t < nrt) load_tile(0);
         acc += __shfl_xor(acc, 16, 64);
         acc += __shfl_xor(acc, 32, 64);
-        if (r < 16 && row < b.nbelow) u[row] = acc;
+        if (r < 16 && row < b.nbelow) put<Wait::kShared>(u + row, acc);
     }
 }
 
-template <int NB>
 __global__ __launch_bounds__(kImplThreads) void implicit_fwd(
     const ImplBlock* __restrict__ items, const double* __restrict__ lval, const int32_t* __restrict__ rptr,
-    const int32_t* __restrict__ rpos, double* __restrict__ xwork, double* __restrict__ ywork, double* ubuf, int G)
+    const int32_t* __restrict__ rpos, double* __restrict__ xwork, double* __restrict__ ywork, double* ubuf)
 {
     __shared__ double sp[kImplParts][64];
     __shared__ double sx[64];
-    const ImplBlock b = items[blockIdx.x / G];
-    const int g = (int)(blockIdx.x % G);
-    if (g > 0 && 16 * kImplParts * g >= b.nbelow) return;        // no row tile left for this share
-    implicit_fwd_block<NB, NB == kImplBatchNarrow>(b, lval, rptr, rpos, xwork, ywork, ubuf, sp, sx, g, G);
+    implicit_fwd_block<kImplBatch, false>(items[blockIdx.x], lval, rptr, rpos, xwork, ywork, ubuf, sp, sx);
 }
 
 // L[R_b, b]^T z[R_b] over the pruned row tiles [t0, t1): column 4 part + l / 16
@@ -679,10 +689,10 @@ __global__ __launch_bounds__(kImplThreads) void implicit_fwd(
 // tiles t: each wavefront load is one whole 512-byte A tile, NB in flight at
 // a time (EARLY: the first ones while z is gathered).  Rows past nb read the
 // tiles' zero padding against zero z entries.
-template <int NB, bool EARLY>
+template <int NB, bool EARLY, class Wait = NoWait>
 __device__ __forceinline__ double implicit_bwd_sum(
     const ImplBlock& b, const int32_t* __restrict__ rows, const double* __restrict__ lval, const double* x, int t0,
-    int t1, double* sz)
+    int t1, double* sz, const Wait& wait = Wait())
 {
     const int32_t* __restrict__ rw = rows + b.rows;
     const int tid = threadIdx.x;
@@ -701,7 +711,9 @@ __device__ __forceinline__ double implicit_bwd_sum(
             for (int i = 0; i < NB; ++i) a[i] = u0 + i < nrt ? Ts[(int64_t)(u0 + i) * nks * 64] : 0.0;
         };
         if (EARLY) load_tiles(0);
-        const double z = c0 + tid < nb ? x[b.x + rw[c0 + tid]] : 0.0;   // z of the pruned rows: final
+        const int row = c0 + tid < nb ? rw[c0 + tid] : -1;
+        if (c0 == 16 * t0) wait();
+        const double z = row >= 0 ? get<Wait::kShared>(x + b.x + row) : 0.0;               // z of the pruned rows: final
         __syncthreads();
         sz[tid] = z;
         __syncthreads();
@@ -731,6 +743,7 @@ __device__ __forceinline__ void linv_col(const ImplBlock& b, const double* __res
     }
 }
 
+template <bool SHARED = false>
 __device__ __forceinline__ void implicit_bwd_finish(const ImplBlock& b, const double (&li)[4], double* x,
                                                     double (*sp)[64], const double* sv) {
     const int r = threadIdx.x & 63, part = threadIdx.x >> 6;
@@ -739,7 +752,7 @@ __device__ __forceinline__ void implicit_bwd_finish(const ImplBlock& b, const do
     for (int i = 0; i < 4; ++i) z += li[i] * sv[4 * part + i];
     sp[part][r] = z;
     __syncthreads();
-    if ((int)threadIdx.x < b.w) x[b.x + b.row0 + threadIdx.x] = sum_parts(sp, threadIdx.x);
+    if ((int)threadIdx.x < b.w) put<SHARED>(x + b.x + b.row0 + threadIdx.x, sum_parts(sp, threadIdx.x));
 }
 
 // backward step of block b: z_b <- L_bb^{-T}(y_b - L[R_b, b]^T z[R_b])
@@ -759,7 +772,6 @@ __device__ __forceinline__ void implicit_bwd_block(
     implicit_bwd_finish(b, li, x, sp, sv);
 }
 
-template <int NB>
 __global__ __launch_bounds__(kImplThreads) void implicit_bwd(
     const ImplBlock* __restrict__ items, const int32_t* __restrict__ rows, const double* __restrict__ lval,
     const double* __restrict__ ywork, double* xwork)
@@ -767,53 +779,120 @@ __global__ __launch_bounds__(kImplThreads) void implicit_bwd(
     __shared__ double sp[kImplParts][64];
     __shared__ double sz[kImplThreads];
     __shared__ double sv[64];
-    const ImplBlock b = items[blockIdx.x];
-    implicit_bwd_block<NB, NB == kImplBatchNarrow>(b, rows, lval, ywork, xwork, sp, sz, sv);
+    implicit_bwd_block<kImplBatch, false>(items[blockIdx.x], rows, lval, ywork, xwork, sp, sz, sv);
 }
 
-// The same step in two launches: share g of G of the row sums into bpart
-// [block of the level][share][64] (row tiles in shares of ceil(tiles / G)),
-// then their sum and the diagonal product.
-template <int NB>
-__global__ __launch_bounds__(kImplThreads) void implicit_bwd_part(
-    const ImplBlock* __restrict__ items, const int32_t* __restrict__ rows, const double* __restrict__ lval,
-    const double* __restrict__ xwork, double* __restrict__ bpart, int G)
-{
-    __shared__ double sz[kImplThreads];
-    const ImplBlock b = items[blockIdx.x / G];
-    const int g = (int)(blockIdx.x % G);
-    const int nrt = (b.nbelow + 15) >> 4;
-    const int per = (nrt + G - 1) / G;
-    if (g * per >= nrt) return;
-    const double acc = implicit_bwd_sum<NB, true>(b, rows, lval, xwork, g * per, min(nrt, (g + 1) * per), sz);
-    const int r = threadIdx.x & 63, part = threadIdx.x >> 6;
-    if ((r & 15) == 0) bpart[(int64_t)blockIdx.x * 64 + 4 * part + (r >> 4)] = acc;
+// A chain of levels in one launch: a workgroup waits for its own subdomain's
+// earlier levels instead of for a launch.  A workgroup takes the next item of
+// the list when it starts and waits only for items before its own, which
+// started workgroups hold: whatever the order of dispatch, the earliest
+// unfinished item waits for none, so every wait ends.  Bound by the latency of
+// a level (a counter and the rows it depends on through memory, two reductions
+// over the workgroup, 8.5 us): the factor tiles, the inverse and all indices
+// are loaded while it waits, several levels ahead of the sweep.  A launch (or
+// two) per level / chains: 16 x 20^3 elasticity 1.80 / 1.32 ms, 64 uneven
+// boxes 1.03 / 0.74, 8 triangle meshes of 129^2 nodes 0.198 / 0.161.  What passes
+// between workgroups is written through to memory and read from there; with
+// the caches written back and invalidated instead (agent-scope fences) a level
+// took 100 us.
+__device__ __forceinline__ int chain_ticket(int32_t* ticket, int* sh) {
+    if (threadIdx.x == 0) *sh = __hip_atomic_fetch_add(ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    return __builtin_amdgcn_readfirstlane(*sh);
 }
-
-__global__ __launch_bounds__(kImplThreads) void implicit_bwd_last(
-    const ImplBlock* __restrict__ items, const double* __restrict__ lval, const double* __restrict__ ywork,
-    double* __restrict__ xwork, const double* __restrict__ bpart, int G)
-{
-    __shared__ double sp[kImplParts][64];
-    __shared__ double sv[64];
-    const ImplBlock b = items[blockIdx.x];
-    double li[4];
-    linv_col(b, lval, li);
-    if (threadIdx.x < 64) {
-        const int c = threadIdx.x;
-        const int nrt = (b.nbelow + 15) >> 4;
-        const int per = (nrt + G - 1) / G;
-        double v = c < b.w ? ywork[b.x + b.row0 + c] : 0.0;
-        double s[kImplSplit];
-#pragma unroll
-        for (int g = 0; g < kImplSplit; ++g)
-            s[g] = g < G && g * per < nrt ? bpart[((int64_t)blockIdx.x * G + g) * 64 + c] : 0.0;
-#pragma unroll
-        for (int g = 0; g < kImplSplit; ++g) v -= s[g];
-        sv[c] = c < b.w ? v : 0.0;
+// Until `need` items have finished; what they wrote is visible afterwards.
+// Calls that overlap on one plan (they may not) share the counters: a wait
+// that they leave without an end gives up after kChainTicks (10 s at 100 MHz)
+// and releases all others of its subdomain.
+constexpr long long kChainTicks = 1000000000;
+__device__ __forceinline__ void chain_wait(int32_t* done, int need) {
+    if (threadIdx.x == 0 && need > 0) {
+        const long long t0 = wall_clock64();
+        while (__hip_atomic_load(done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < need) {
+            __builtin_amdgcn_s_sleep(8);
+            if (wall_clock64() - t0 > kChainTicks)
+                __hip_atomic_store(done, 1 << 30, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
     }
     __syncthreads();
-    implicit_bwd_finish(b, li, xwork, sp, sv);
+}
+struct ChainWait {
+    static constexpr bool kShared = true;
+    int32_t* done;
+    int need;
+    __device__ __forceinline__ void operator()() const { chain_wait(done, need); }
+};
+// counts this workgroup's item, once its stores have reached memory; returns
+// the count before (thread 0)
+__device__ __forceinline__ int chain_done(int32_t* done) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (threadIdx.x == 0) return __hip_atomic_fetch_add(done, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return 0;
+}
+
+__global__ __launch_bounds__(kImplThreads, 8) void implicit_fwd_chain(
+    const ImplChainItem* __restrict__ items, const double* __restrict__ lval, const int32_t* __restrict__ rptr,
+    const int32_t* __restrict__ rpos, const double* __restrict__ xwork, double* __restrict__ ywork, double* ubuf,
+    int32_t* ticket, int32_t* done, int n)
+{
+    __shared__ double sp[kImplParts][64];
+    __shared__ double sx[64];
+    __shared__ int sh;
+    const int at = chain_ticket(ticket, &sh);
+    if (at >= n) return;
+    const ImplChainItem it = items[at];
+    implicit_fwd_block<kImplBatch, true>(it.b, lval, rptr, rpos, xwork, ywork, ubuf, sp, sx, it.g, it.G,
+                                              ChainWait{done + it.sub * kImplCounterStride, it.need});
+    chain_done(done + it.sub * kImplCounterStride);
+}
+
+__global__ __launch_bounds__(kImplThreads, 8) void implicit_bwd_chain(
+    const ImplChainItem* __restrict__ items, const int32_t* __restrict__ rows, const double* __restrict__ lval,
+    const double* __restrict__ ywork, double* xwork, double* cpart, int32_t* ticket, int32_t* done, int32_t* shares,
+    int n)
+{
+    __shared__ double sp[kImplParts][64];
+    __shared__ double sz[kImplThreads];
+    __shared__ double sv[64];
+    __shared__ int sh;
+    const int at = chain_ticket(ticket, &sh);
+    if (at >= n) return;
+    const ImplChainItem it = items[at];
+    const ImplBlock& b = it.b;
+    const int r = threadIdx.x & 63, part = threadIdx.x >> 6;
+    const int c = 4 * part + (r >> 4);
+    const int nrt = (b.nbelow + 15) >> 4;
+    const int per = (nrt + it.G - 1) / it.G;
+    const ChainWait wait{done + it.sub * kImplCounterStride, it.need};
+    double li[4];
+    if (it.G == 1) linv_col(b, lval, li);
+    const double acc = implicit_bwd_sum<kImplBatch, true>(b, rows, lval, xwork, it.g * per,
+                                                               min(nrt, (it.g + 1) * per), sz, wait);
+    if (it.G == 1) {
+        if ((r & 15) == 0) sv[c] = c < b.w ? ywork[b.x + b.row0 + c] - acc : 0.0;
+    } else {
+        // the last share to finish adds them up, in their order
+        if ((r & 15) == 0) put<true>(cpart + (int64_t)at * 64 + c, acc);
+        const int before = chain_done(shares + at - it.g);
+        if (threadIdx.x == 0) sh = before;
+        __syncthreads();
+        if (__builtin_amdgcn_readfirstlane(sh) != it.G - 1) return;
+        linv_col(b, lval, li);
+        if (threadIdx.x < 64) {
+            const int k = threadIdx.x;
+            double v = k < b.w ? ywork[b.x + b.row0 + k] : 0.0;
+            double s[kImplSplit];
+#pragma unroll
+            for (int g = 0; g < kImplSplit; ++g) s[g] = g < it.G ? get<true>(cpart + (int64_t)(at - it.g + g) * 64 + k) : 0.0;
+#pragma unroll
+            for (int g = 0; g < kImplSplit; ++g) v -= s[g];
+            sv[k] = k < b.w ? v : 0.0;
+        }
+    }
+    __syncthreads();
+    implicit_bwd_finish<true>(b, li, xwork, sp, sv);
+    chain_done(done + it.sub * kImplCounterStride);
 }
 
 // Both sweeps of one subdomain in one workgroup: its blocks in increasing
@@ -838,11 +917,11 @@ __global__ __launch_bounds__(kImplThreads) void implicit_sweeps(
                          d.row0, d.w, d.nbelow, 0};
     };
     for (int k = 0; k < S.nblocks; ++k) {
-        implicit_fwd_block<kImplBatchWide, true>(block(k), lval, rptr, rpos, xwork, ywork, ubuf, sp, sx);
+        implicit_fwd_block<kImplBatch, true>(block(k), lval, rptr, rpos, xwork, ywork, ubuf, sp, sx);
         __syncthreads();
     }
     for (int k = S.nblocks - 1; k >= 0; --k) {
-        implicit_bwd_block<kImplBatchWide, true>(block(k), rows, lval, ywork, xwork, sp, sz, sx);
+        implicit_bwd_block<kImplBatch, true>(block(k), rows, lval, ywork, xwork, sp, sz, sx);
         __syncthreads();
     }
 }
@@ -860,12 +939,12 @@ __global__ __launch_bounds__(kInitThreads) void implicit_gather(
         q[S.dual_off + pi[S.col_off + a]] = (double)sgn[S.col_off + a] * x[piv[S.col_off + a]];
 }
 
-hipError_t launch_implicit_init(const DevTables& t, const int64_t* xoff, double* xwork, const double* p,
-                                const int32_t* sub_list, int32_t count, hipStream_t stream) {
+hipError_t launch_implicit_init(const DevTables& t, const ImplicitLevels& lv, const int64_t* xoff, double* xwork,
+                                const double* p, int32_t count, hipStream_t stream) {
     if (count <= 0) return hipSuccess;
     const int C = init_split(count);
     hipLaunchKernelGGL(implicit_init, dim3((unsigned)(count * C)), dim3(kInitThreads), 0, stream, t.subs, t.piv, t.pi,
-                       t.sgn, xoff, p, xwork, sub_list, C);
+                       t.sgn, xoff, p, xwork, lv.subs, C, lv.counters, lv.counters ? lv.ncounters() : 0);
     return hipGetLastError();
 }
 
@@ -873,9 +952,11 @@ hipError_t launch_implicit_sweeps(const DevTables& t, const ImplicitLevels& lv, 
                                   int32_t count, hipStream_t stream) {
     if (count <= 0) return hipSuccess;
     // every table and workspace the sweeps dereference must be in place
-    if (!xoff || !xwork || !lv.ywork || !lv.ubuf || !lv.bpart || !lv.rptr_off || !lv.rptr || !lv.rpos) return hipErrorInvalidValue;
-    if (!lv.per_subdomain && ((lv.fw_off.size() > 1 && !lv.fw_items) || (lv.bw_off.size() > 1 && !lv.bw_items) ||
-                              lv.fw_rows.size() + 1 < lv.fw_off.size() || lv.bw_rows.size() + 1 < lv.bw_off.size()))
+    if (!xoff || !xwork || !lv.ywork || !lv.ubuf || !lv.rptr_off || !lv.rptr || !lv.rpos) return hipErrorInvalidValue;
+    if ((lv.nfw_chain > 0 || lv.nbw_chain > 0) &&
+        (!lv.counters || (lv.nfw_chain > 0 && !lv.fw_chain_items) || (lv.nbw_chain > 0 && (!lv.bw_chain_items || !lv.cpart))))
+        return hipErrorInvalidValue;
+    if (!lv.per_subdomain && ((lv.fw_off.size() > 1 && !lv.fw_items) || (lv.bw_off.size() > 1 && !lv.bw_items)))
         return hipErrorInvalidValue;
     hipError_t e = hipSuccess;
     if (lv.per_subdomain) {
@@ -883,35 +964,32 @@ hipError_t launch_implicit_sweeps(const DevTables& t, const ImplicitLevels& lv, 
                            t.rows, t.lval, lv.rptr_off, lv.rptr, lv.rpos, xoff, xwork, lv.ywork, lv.ubuf, lv.subs);
         return hipGetLastError();
     }
-    for (size_t l = 0; l + 1 < lv.fw_off.size(); ++l) {
+    int32_t* const fw_done = lv.counters + 2 * kImplCounterStride;
+    int32_t* const bw_done = fw_done + lv.nsub * kImplCounterStride;
+    for (size_t l = 0; l < lv.fw_chain && l + 1 < lv.fw_off.size(); ++l) {
         const int64_t cnt = lv.fw_off[l + 1] - lv.fw_off[l];
         if (cnt <= 0) continue;
-        const int G = impl_split(cnt, (lv.fw_rows[l] + 16 * kImplParts - 1) / (16 * kImplParts));
-        if (cnt < kImplNarrowBelow)
-            hipLaunchKernelGGL(implicit_fwd<kImplBatchNarrow>, dim3((unsigned)(cnt * G)), dim3(kImplThreads),
-                               0, stream, lv.fw_items + lv.fw_off[l], t.lval, lv.rptr, lv.rpos, xwork, lv.ywork, lv.ubuf,
-                               G);
-        else
-            hipLaunchKernelGGL(implicit_fwd<kImplBatchWide>, dim3((unsigned)cnt), dim3(kImplThreads), 0, stream,
-                               lv.fw_items + lv.fw_off[l], t.lval, lv.rptr, lv.rpos, xwork, lv.ywork, lv.ubuf, 1);
+        hipLaunchKernelGGL(implicit_fwd, dim3((unsigned)cnt), dim3(kImplThreads), 0, stream,
+                           lv.fw_items + lv.fw_off[l], t.lval, lv.rptr, lv.rpos, xwork, lv.ywork, lv.ubuf);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
-    for (size_t l = 0; l + 1 < lv.bw_off.size(); ++l) {
+    if (lv.nfw_chain > 0) {
+        hipLaunchKernelGGL(implicit_fwd_chain, dim3((unsigned)lv.nfw_chain), dim3(kImplThreads), 0, stream,
+                           lv.fw_chain_items, t.lval, lv.rptr, lv.rpos, xwork, lv.ywork, lv.ubuf, lv.counters, fw_done,
+                           (int)lv.nfw_chain);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+    }
+    if (lv.nbw_chain > 0) {
+        hipLaunchKernelGGL(implicit_bwd_chain, dim3((unsigned)lv.nbw_chain), dim3(kImplThreads), 0, stream,
+                           lv.bw_chain_items, t.rows, t.lval, lv.ywork, xwork, lv.cpart, lv.counters + kImplCounterStride,
+                           bw_done, bw_done + lv.nsub * kImplCounterStride, (int)lv.nbw_chain);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+    }
+    for (size_t l = lv.bw_chain; l + 1 < lv.bw_off.size(); ++l) {
         const int64_t cnt = lv.bw_off[l + 1] - lv.bw_off[l];
         if (cnt <= 0) continue;
-        if (cnt < kImplNarrowBelow && lv.bw_rows[l] >= kImplBwdSplitRows) {
-            const int G = impl_split(cnt, kImplSplit);
-            hipLaunchKernelGGL(implicit_bwd_part<kImplBatchNarrow>, dim3((unsigned)(cnt * G)), dim3(kImplThreads), 0,
-                               stream, lv.bw_items + lv.bw_off[l], t.rows, t.lval, xwork, lv.bpart, G);
-            if ((e = hipGetLastError()) != hipSuccess) return e;
-            hipLaunchKernelGGL(implicit_bwd_last, dim3((unsigned)cnt), dim3(kImplThreads), 0, stream,
-                               lv.bw_items + lv.bw_off[l], t.lval, lv.ywork, xwork, lv.bpart, G);
-        } else if (cnt < kImplNarrowBelow)
-            hipLaunchKernelGGL(implicit_bwd<kImplBatchNarrow>, dim3((unsigned)cnt), dim3(kImplThreads), 0, stream,
-                               lv.bw_items + lv.bw_off[l], t.rows, t.lval, lv.ywork, xwork);
-        else
-            hipLaunchKernelGGL(implicit_bwd<kImplBatchWide>, dim3((unsigned)cnt), dim3(kImplThreads), 0, stream,
-                               lv.bw_items + lv.bw_off[l], t.rows, t.lval, lv.ywork, xwork);
+        hipLaunchKernelGGL(implicit_bwd, dim3((unsigned)cnt), dim3(kImplThreads), 0, stream,
+                           lv.bw_items + lv.bw_off[l], t.rows, t.lval, lv.ywork, xwork);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     return hipSuccess;
@@ -930,7 +1008,7 @@ hipError_t launch_apply_implicit(const DevTables& t, const ImplicitLevels& lv, c
                                  const double* p, double* q, int32_t count, hipStream_t stream, hipEvent_t* ev) {
     hipError_t e = hipSuccess;
     if (ev && (e = hipEventRecord(ev[0], stream)) != hipSuccess) return e;
-    if ((e = launch_implicit_init(t, xoff, xwork, p, lv.subs, count, stream)) != hipSuccess) return e;
+    if ((e = launch_implicit_init(t, lv, xoff, xwork, p, count, stream)) != hipSuccess) return e;
     if ((e = launch_implicit_sweeps(t, lv, xoff, xwork, count, stream)) != hipSuccess) return e;
     if ((e = launch_implicit_gather(t, xoff, xwork, q, lv.subs, count, stream)) != hipSuccess) return e;
     if (ev && (e = hipEventRecord(ev[1], stream)) != hipSuccess) return e;

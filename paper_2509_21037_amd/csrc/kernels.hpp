@@ -2,6 +2,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
 #include <vector>
 
@@ -78,8 +79,6 @@ struct PcpgArgs {
 };
 
 struct ImplicitLevels;
-// 64 sums for each workgroup of a split backward level (at most 512)
-constexpr int64_t kImplPartDoubles = 512 * 64;
 // Projected CG on every subdomain, `iters` iterations: F applied explicitly
 // to the assembled subdomains, and, when lvh is given, with the factor to the
 // nimpl subdomains of lvh->subs (workspace xwork at xoff).
@@ -93,9 +92,48 @@ struct ImplBlock {
     int32_t row0, w, nbelow, pad;
 };
 
+constexpr int kImplThreads = 1024;
+constexpr int kImplParts = kImplThreads / 64;
+// Implicit sweeps, the levels next to the roots that hold fewer blocks than
+// this run as one launch per sweep (a chain); levels of more blocks, and those
+// between them and the leaves, as one launch each.  Levels of 256 / 512 / 2048
+// blocks and all in chains: 16 x 20^3 elasticity 1.43 / 1.40 / 1.32 / 1.33 ms,
+// 64 x 20^3 4.18 / 4.13 / 4.03 / 4.06, 512 x 12^3 heat 0.845 / 0.844 / 0.839 /
+// 0.871 (0.853 with every level a launch).
+constexpr int64_t kImplChainBelow = 2048;
+// Subdomains of near-chain block DAGs and fewer blocks than this on average:
+// one workgroup per subdomain runs both sweeps.  One workgroup / chains: 512
+// heat squares of 16^2 elements (5 blocks) 71 / 95 us, 24^2 (10) 161 / 164, 28^2
+// (14) 243 / 233; 64 of 24^2 71 / 84, 28^2 100 / 107, 32^2 (18) 111 / 88; one 12^3
+// heat cube (46) 304 / 286, 512 of them 1000 / 895; 16 x 20^3 elasticity in
+// uniform blocks (435) 10.1 / 4.9 ms.
+constexpr int64_t kImplChainBlocks = 16;
+// A block of a chain is split over up to kImplSplit workgroups, as many as
+// fill the chip twice.  Forward, each repeats the update sums and the diagonal
+// product and takes its share of the row tiles (at least one per wavefront).
+// Backward, from kImplBwdSplitRows rows on, each sums a share of the rows and
+// the last one to finish adds the shares and does the diagonal product.  16 x
+// 20^3 elasticity with up to 8 / 4 shares 1.43 / 1.51 ms; backward from 512 /
+// 1024 rows 1.43 / 1.47.
+constexpr int kImplSplit = 8;
+constexpr int kImplBwdSplitRows = 512;
+inline int impl_split(int64_t blocks, int tiles) {
+    return (int)std::max<int64_t>(1, std::min<int64_t>({kImplSplit, 512 / blocks, tiles}));
+}
+// ints between the counters that waiting workgroups read over and over: with
+// all subdomains' counters in one cache line the sweeps took twice as long
+constexpr int64_t kImplCounterStride = 64;
+
+// One workgroup of a chain of levels run in one launch: a block (or
+// share g of G of its row tiles) that starts when `need` workgroups (forward)
+// or blocks (backward) of its subdomain have finished before it.
+struct ImplChainItem {
+    ImplBlock b;
+    int32_t sub, need, g, G;
+};
+
 // Level schedule of the blocked triangular solves of the implicit apply:
-// blocks grouped by level (host offsets, levels run in order; fw_rows /
-// bw_rows: the most pruned rows of a block of the level); per row of a
+// blocks grouped by level (host offsets, levels run in order); per row of a
 // subdomain (rptr at rptr_off[sub], CSR) the positions in the row array where
 // it is a pruned row: its entries in the update buffer ubuf, which runs
 // parallel to the row array.
@@ -110,12 +148,21 @@ struct ImplicitLevels {
     // xwork offsets): kept apart from x so that several workgroups of one
     // forward block step read x while one of them writes y
     double* ywork = nullptr;
-    // shares of the row sums of a backward level (kImplPartDoubles)
-    double* bpart = nullptr;
     std::vector<int64_t> fw_off, bw_off;
-    std::vector<int32_t> fw_rows, bw_rows;
-    // true: one workgroup per subdomain runs both sweeps block by block (the
-    // block DAGs are near chains); false: one launch per level
+    // the chains of levels next to the roots (forward levels fw_chain and on,
+    // backward levels before bw_chain), one launch each, their workgroups in
+    // level order (shares of a block next to each other); counters: a ticket
+    // per sweep, the finished workgroups / blocks of every subdomain in each,
+    // the finished shares of each backward item; cleared by
+    // launch_implicit_init.  cpart: 64 sums for each backward item
+    const ImplChainItem* fw_chain_items = nullptr;
+    const ImplChainItem* bw_chain_items = nullptr;
+    int32_t* counters = nullptr;
+    double* cpart = nullptr;
+    int64_t nfw_chain = 0, nbw_chain = 0, nsub = 0;
+    size_t fw_chain = SIZE_MAX, bw_chain = 0;
+    int64_t ncounters() const { return kImplCounterStride * (2 + 2 * nsub) + nbw_chain; }
+    // true: one workgroup per subdomain runs both sweeps block by block
     bool per_subdomain = false;
     // the subdomains covered (device list; null = all, in index order)
     const int32_t* subs = nullptr;
@@ -128,8 +175,8 @@ struct ImplicitLevels {
 // graph of them stays valid for any p and q), q = B P^T x (gather).
 // `count` subdomains: those of `sub_list` / lv.subs, or 0 .. count - 1 when
 // the list is null.
-hipError_t launch_implicit_init(const DevTables& t, const int64_t* xoff, double* xwork, const double* p,
-                                const int32_t* sub_list, int32_t count, hipStream_t stream);
+hipError_t launch_implicit_init(const DevTables& t, const ImplicitLevels& lv, const int64_t* xoff, double* xwork,
+                                const double* p, int32_t count, hipStream_t stream);
 hipError_t launch_implicit_sweeps(const DevTables& t, const ImplicitLevels& lv, const int64_t* xoff, double* xwork,
                                   int32_t count, hipStream_t stream);
 hipError_t launch_implicit_gather(const DevTables& t, const int64_t* xoff, const double* xwork, double* q,

@@ -406,13 +406,16 @@ struct sc_plan_s {
     DevBuf<ImplBlock> d_ifw, d_ibw;
     DevBuf<int64_t> d_rptr_off;
     DevBuf<int32_t> d_rptr, d_rpos;
-    DevBuf<double> d_ubuf, d_bpart;
+    DevBuf<double> d_ubuf;
     ImplicitLevels ilv;
     // the same schedule restricted to the subdomains applied implicitly in
     // sc_apply / sc_pcpg (select_iters)
     DevBuf<ImplBlock> d_ifw_h, d_ibw_h;
     DevBuf<int32_t> d_impl_list;
     ImplicitLevels ilv_h;
+    DevBuf<ImplChainItem> d_chain_fw, d_chain_bw, d_chain_fw_h, d_chain_bw_h;
+    DevBuf<int32_t> d_chain_counters;
+    DevBuf<double> d_chain_part;
     bool mixed = false;
     bool factored = false, assembled = false;
     // temporary-memory waves (arena_cap_bytes > 0): X elements the cap holds;
@@ -538,8 +541,10 @@ struct sc_plan_s {
                          (d_lval.count + d_X.count + d_F.count) * 8 +
                          (d_lval32.count + d_X32.count + d_F32.count) * 4 +
                          (d_xwork.count + d_ywork.count + d_xoff.count) * 8 + (d_ifw.count + d_ibw.count) * sizeof(ImplBlock) +
-                         (d_rptr.count + d_rpos.count) * 4 + (d_rptr_off.count + d_ubuf.count + d_bpart.count) * 8 +
-                         (d_ifw_h.count + d_ibw_h.count) * sizeof(ImplBlock) + d_impl_list.count * 4);
+                         (d_rptr.count + d_rpos.count) * 4 + (d_rptr_off.count + d_ubuf.count) * 8 +
+                         (d_ifw_h.count + d_ibw_h.count) * sizeof(ImplBlock) + d_impl_list.count * 4 +
+                         (d_chain_fw.count + d_chain_bw.count + d_chain_fw_h.count + d_chain_bw_h.count) * sizeof(ImplChainItem) +
+                         d_chain_counters.count * 4 + d_chain_part.count * 8);
     }
     void release() {
         d_subs.release(); d_tiles.release(); d_blocks.release(); d_syrk.release();
@@ -549,8 +554,10 @@ struct sc_plan_s {
         d_lval.release(); d_X.release(); d_F.release();
         d_lval32.release(); d_X32.release(); d_F32.release();
         d_xwork.release(); d_ywork.release(); d_xoff.release();
-        d_ifw.release(); d_ibw.release(); d_rptr_off.release(); d_rptr.release(); d_rpos.release(); d_ubuf.release(); d_bpart.release();
+        d_ifw.release(); d_ibw.release(); d_rptr_off.release(); d_rptr.release(); d_rpos.release(); d_ubuf.release();
         d_ifw_h.release(); d_ibw_h.release(); d_impl_list.release();
+        d_chain_fw.release(); d_chain_bw.release(); d_chain_fw_h.release(); d_chain_bw_h.release();
+        d_chain_counters.release(); d_chain_part.release();
         if (h_lval) (void)hipHostFree(h_lval);
         h_lval = nullptr;
         if (graph_exec) (void)hipGraphExecDestroy(graph_exec);
@@ -1603,30 +1610,71 @@ static sc_status_t build_implicit(sc_plan_s* P, hipStream_t st) {
         }
         return out;
     };
-    auto level_rows = [](const std::vector<ImplBlock>& items, const std::vector<int64_t>& lo) {
-        std::vector<int32_t> out;
-        for (size_t l = 0; l + 1 < lo.size(); ++l) {
-            out.push_back(0);
-            for (int64_t k = lo[l]; k < lo[l + 1]; ++k) out.back() = std::max(out.back(), items[(size_t)k].nbelow);
+    const std::vector<ImplBlock> fwib = device_blocks(fwi), bwib = device_blocks(bwi), fwhb = device_blocks(fwh),
+                                 bwhb = device_blocks(bwh);
+    // near-chain block DAGs (fewer than 1.5 blocks per level) of a few blocks:
+    // one workgroup per subdomain; the subset by its own subdomains
+    lv.per_subdomain = 2 * nblocks_all < 3 * nlevels_all && nblocks_all < kImplChainBlocks * P->nsub;
+    lvh.per_subdomain =
+        2 * nblocks_h < 3 * nlevels_sub_h && nblocks_h < kImplChainBlocks * (int64_t)impl_list.size();
+    // the levels next to the roots as chains (one launch each way)
+    auto chain = [&](const std::vector<ImplBlock>& blocks, const std::vector<int2>& ids, const std::vector<int64_t>& lo,
+                     size_t l0, size_t l1, bool forward) {
+        std::vector<ImplChainItem> out;
+        std::vector<int32_t> done(P->nsub, 0), next(P->nsub, 0);
+        for (size_t l = l0; l < l1; ++l) {
+            const int64_t cnt = lo[l + 1] - lo[l];
+            for (int64_t k = lo[l]; k < lo[l + 1]; ++k) {
+                const ImplBlock& b = blocks[(size_t)k];
+                const int32_t i = ids[(size_t)k].x;
+                const int nrt = (b.nbelow + 15) / 16;
+                int G = 1;
+                if (forward) G = impl_split(cnt, (nrt + kImplParts - 1) / kImplParts);
+                else if (b.nbelow >= kImplBwdSplitRows) {
+                    G = impl_split(cnt, kImplSplit);
+                    const int per = (nrt + G - 1) / G;
+                    G = (nrt + per - 1) / per;
+                }
+                for (int g = 0; g < G; ++g) out.push_back(ImplChainItem{b, i, done[i], g, G});
+                next[i] += forward ? G : 1;
+            }
+            for (int64_t k = lo[l]; k < lo[l + 1]; ++k) done[ids[(size_t)k].x] = next[ids[(size_t)k].x];
         }
         return out;
     };
-    const std::vector<ImplBlock> fwib = device_blocks(fwi), bwib = device_blocks(bwi), fwhb = device_blocks(fwh),
-                                 bwhb = device_blocks(bwh);
-    lv.fw_rows = level_rows(fwib, lv.fw_off);
-    lv.bw_rows = level_rows(bwib, lv.bw_off);
-    lvh.fw_rows = level_rows(fwhb, lvh.fw_off);
-    lvh.bw_rows = level_rows(bwhb, lvh.bw_off);
-    DevBuf<double> xwork, ywork, ubuf, bpart;
+    auto narrow = [](const std::vector<int64_t>& lo, size_t l) { return lo[l + 1] - lo[l] < kImplChainBelow; };
+    auto chains = [&](ImplicitLevels& v, const std::vector<ImplBlock>& fb, const std::vector<int2>& fi,
+                      const std::vector<ImplBlock>& bb, const std::vector<int2>& bi, std::vector<ImplChainItem>& fc,
+                      std::vector<ImplChainItem>& bc) {
+        v.nsub = P->nsub;
+        const size_t nf = v.fw_off.size() - 1, nb = v.bw_off.size() - 1;
+        v.fw_chain = nf;
+        v.bw_chain = 0;
+        if (v.per_subdomain) return;
+        while (v.fw_chain > 0 && narrow(v.fw_off, v.fw_chain - 1)) --v.fw_chain;
+        while (v.bw_chain < nb && narrow(v.bw_off, v.bw_chain)) ++v.bw_chain;
+        fc = chain(fb, fi, v.fw_off, v.fw_chain, nf, true);
+        bc = chain(bb, bi, v.bw_off, 0, v.bw_chain, false);
+        v.nfw_chain = (int64_t)fc.size();
+        v.nbw_chain = (int64_t)bc.size();
+    };
+    std::vector<ImplChainItem> fwc, bwc, fwhc, bwhc;
+    chains(lv, fwib, fwi, bwib, bwi, fwc, bwc);
+    chains(lvh, fwhb, fwh, bwhb, bwh, fwhc, bwhc);
+    DevBuf<ImplChainItem> cfw, cbw, cfwh, cbwh;
+    DevBuf<int32_t> counters;
+    DevBuf<double> cpart;
+    DevBuf<double> xwork, ywork, ubuf;
     DevBuf<int64_t> xoff, rptr_off_d;
     DevBuf<ImplBlock> ifw, ibw;
     DevBuf<int32_t> rptr_d, rpos_d;
     DevBuf<ImplBlock> ifwh, ibwh;
     DevBuf<int32_t> ilist;
     auto release_all = [&]() {
-        xwork.release(); ywork.release(); ubuf.release(); bpart.release(); xoff.release(); rptr_off_d.release();
+        xwork.release(); ywork.release(); ubuf.release(); xoff.release(); rptr_off_d.release();
         ifw.release(); ibw.release(); rptr_d.release(); rpos_d.release();
         ifwh.release(); ibwh.release(); ilist.release();
+        cfw.release(); cbw.release(); cfwh.release(); cbwh.release(); counters.release(); cpart.release();
     };
     hipError_t e = xwork.alloc((size_t)off[P->nsub]);
     if (e == hipSuccess) e = ywork.alloc((size_t)off[P->nsub]);
@@ -1637,10 +1685,15 @@ static sc_status_t build_implicit(sc_plan_s* P, hipStream_t st) {
     if (e == hipSuccess) e = rptr_d.alloc(rptr.size());
     if (e == hipSuccess) e = rpos_d.alloc(std::max<size_t>(1, rpos.size()));
     if (e == hipSuccess) e = ubuf.alloc((size_t)P->nrows_total);
-    if (e == hipSuccess) e = bpart.alloc((size_t)kImplPartDoubles);
     if (e == hipSuccess) e = ifwh.alloc(fwh.size());
     if (e == hipSuccess) e = ibwh.alloc(bwh.size());
     if (e == hipSuccess) e = ilist.alloc(impl_list.size());
+    if (e == hipSuccess) e = cfw.alloc(fwc.size());
+    if (e == hipSuccess) e = cbw.alloc(bwc.size());
+    if (e == hipSuccess) e = cfwh.alloc(fwhc.size());
+    if (e == hipSuccess) e = cbwh.alloc(bwhc.size());
+    if (e == hipSuccess) e = counters.alloc((size_t)std::max(lv.ncounters(), lvh.ncounters()));
+    if (e == hipSuccess) e = cpart.alloc(64 * std::max<size_t>({1, bwc.size(), bwhc.size()}));
     auto up = [&](void* d, const void* h, size_t bytes) -> hipError_t {
         return bytes ? hipMemcpyAsync(d, h, bytes, hipMemcpyHostToDevice, st) : hipSuccess;
     };
@@ -1653,6 +1706,10 @@ static sc_status_t build_implicit(sc_plan_s* P, hipStream_t st) {
     if (e == hipSuccess) e = up(ifwh.p, fwhb.data(), fwhb.size() * sizeof(ImplBlock));
     if (e == hipSuccess) e = up(ibwh.p, bwhb.data(), bwhb.size() * sizeof(ImplBlock));
     if (e == hipSuccess) e = up(ilist.p, impl_list.data(), impl_list.size() * 4);
+    if (e == hipSuccess) e = up(cfw.p, fwc.data(), fwc.size() * sizeof(ImplChainItem));
+    if (e == hipSuccess) e = up(cbw.p, bwc.data(), bwc.size() * sizeof(ImplChainItem));
+    if (e == hipSuccess) e = up(cfwh.p, fwhc.data(), fwhc.size() * sizeof(ImplChainItem));
+    if (e == hipSuccess) e = up(cbwh.p, bwhc.data(), bwhc.size() * sizeof(ImplChainItem));
     if (e == hipSuccess) e = hipStreamSynchronize(st);    // the host tables go out of scope
     if (e != hipSuccess) {
         release_all();
@@ -1666,12 +1723,12 @@ static sc_status_t build_implicit(sc_plan_s* P, hipStream_t st) {
     lv.rpos = rpos_d.p;
     lv.ubuf = ubuf.p;
     lv.ywork = ywork.p;
-    lv.bpart = bpart.p;
-    // near-chain block DAGs (fewer than 1.5 blocks per level): a level
-    // launch would carry one block per subdomain
-    lv.per_subdomain = 2 * nblocks_all < 3 * nlevels_all;
+    lv.fw_chain_items = cfw.p;
+    lv.bw_chain_items = cbw.p;
+    lv.counters = counters.p;
+    lv.cpart = cpart.p;
     P->d_xwork = xwork; P->d_ywork = ywork; P->d_xoff = xoff; P->d_ifw = ifw; P->d_ibw = ibw;
-    P->d_rptr_off = rptr_off_d; P->d_rptr = rptr_d; P->d_rpos = rpos_d; P->d_ubuf = ubuf; P->d_bpart = bpart;
+    P->d_rptr_off = rptr_off_d; P->d_rptr = rptr_d; P->d_rpos = rpos_d; P->d_ubuf = ubuf;
     P->ilv = lv;
     lvh.fw_items = ifwh.p;
     lvh.bw_items = ibwh.p;
@@ -1680,11 +1737,13 @@ static sc_status_t build_implicit(sc_plan_s* P, hipStream_t st) {
     lvh.rpos = lv.rpos;
     lvh.ubuf = lv.ubuf;
     lvh.ywork = lv.ywork;
-    lvh.bpart = lv.bpart;
     lvh.subs = ilist.p;
-    // per-subdomain sweeps for the subset when its own block DAGs are near
-    // chains (the per-subdomain kernel reads the list)
-    lvh.per_subdomain = 2 * nblocks_h < 3 * nlevels_sub_h;
+    lvh.fw_chain_items = cfwh.p;
+    lvh.bw_chain_items = cbwh.p;
+    lvh.counters = counters.p;
+    lvh.cpart = cpart.p;
+    P->d_chain_fw = cfw; P->d_chain_bw = cbw; P->d_chain_fw_h = cfwh; P->d_chain_bw_h = cbwh;
+    P->d_chain_counters = counters; P->d_chain_part = cpart;
     P->d_ifw_h = ifwh; P->d_ibw_h = ibwh; P->d_impl_list = ilist;
     P->ilv_h = lvh;
     P->impl_ready = true;
@@ -1726,7 +1785,7 @@ sc_status_t sc_apply_implicit(sc_plan_t P, const double* p_dev, double* q_dev, v
             if (e != hipSuccess) return fail(SC_ERR_DEVICE, std::string("graph capture: ") + hipGetErrorString(e));
             P->impl_graph = ex;
         }
-        HIP_TRY(launch_implicit_init(t, P->d_xoff.p, P->d_xwork.p, p_dev, nullptr, P->nsub, st));
+        HIP_TRY(launch_implicit_init(t, P->ilv, P->d_xoff.p, P->d_xwork.p, p_dev, P->nsub, st));
         HIP_TRY(hipGraphLaunch(P->impl_graph, st));
         HIP_TRY(launch_implicit_gather(t, P->d_xoff.p, P->d_xwork.p, q_dev, nullptr, P->nsub, st));
         return SC_OK;

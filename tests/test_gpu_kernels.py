@@ -199,6 +199,36 @@ def test_implicit_apply_split_levels(count, split):
     plan.destroy()
 
 
+@pytest.mark.parametrize("count,width,split", [(1100, 16, "etree"), (900, 16, "uniform"), (3, 16, "uniform"),
+                                                (1, 16, "etree"), (40, 32, "uniform"), (3, 64, "uniform")])
+def test_implicit_apply_chains(count, width, split):
+    """Levels of thousands of blocks below a chain of smaller ones, chains alone
+    (more workgroups than run at once, one subdomain), subdomains at either
+    side of the block count up to which one workgroup does all (13 and 7 blocks):
+    against the explicit product, and the same bit for bit on every call and
+    after other work in between."""
+    import torch
+    box = scgen.box_subdomain("heat", (20, 18), 1.0 / 20, 11)
+    subs = [_columns(box, 3 + i % 5, 200 + i) for i in range(count)]
+    subs += [scgen.box_subdomain("heat", (2, 2), 0.5, 12)]
+    plan = _plan(subs, block_split=split, panel_width=width)
+    p = torch.from_numpy(np.random.default_rng(13).uniform(-1, 1, plan.dual_total)).cuda()
+    q, ref, other = torch.zeros_like(p), torch.zeros_like(p), torch.zeros_like(p)
+    plan.apply(p, ref)
+    plan.apply_implicit(p, q)
+    first = q.clone()
+    o = 0
+    for i, s in enumerate(subs):
+        a, b = q[o:o + s.m], ref[o:o + s.m]
+        assert float((a - b).norm()) <= 1e-11 * float(b.norm()), i
+        o += s.m
+    for _ in range(3):
+        plan.apply_implicit(ref, other)
+        plan.apply_implicit(p, q)
+        assert torch.equal(q, first)
+    plan.destroy()
+
+
 @pytest.mark.parametrize("width", [16, 32, 48, 64])
 def test_diagonal_inverses_at_block_widths(width):
     """Diagonal blocks of every width up to 64 (chains of 2 .. 140 nodes: the
