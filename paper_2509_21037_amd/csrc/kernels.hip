@@ -676,18 +676,21 @@ __global__ __launch_bounds__(LOADER ? 320 : 256, LOADER ? 1 : MERGE ? 2 : 3) voi
 // ---------------------------------------------------------------------------
 constexpr int kSyrkKC = 16;                  // X rows per step
 
-template <int EDGE>
+template <int EDGE, bool QUARTER = false>
 __global__ __launch_bounds__(256, EDGE == 128 ? 2 : 4) void syrk_f64(
     const SubDev* __restrict__ subs, const TileDev* __restrict__ tiles,
     const SyrkItem* __restrict__ items, const int32_t* __restrict__ ksteps, const double* __restrict__ X,
     double* __restrict__ F)
 {
     constexpr int NS = EDGE / 64;                // 64-column slabs per side
-    constexpr int MT = EDGE / 32;                // 16-column MFMA tiles per side of a wavefront's quadrant
+    constexpr int kSide = QUARTER ? EDGE / 2 : EDGE;      // of the part this workgroup computes
+    constexpr int MT = kSide / 32;               // 16-column MFMA tiles per side of a wavefront's quadrant
     constexpr int kLd = EDGE + 4;                // LDS row stride (elements)
     __shared__ __align__(16) double lds[2][2][kSyrkKC * kLd];    // [buffer][side]
-    const SyrkItem it = items[blockIdx.x];
+    const int nitem = QUARTER ? gridDim.x / 4 : gridDim.x;
+    const SyrkItem it = items[blockIdx.x % nitem];
     if (it.sub < 0) return;
+    const int part = blockIdx.x / nitem;         // QUARTER: row half 2 x, column half x & 1
     const SubDev S = subs[it.sub];
     const int lane = threadIdx.x & 63;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -752,7 +755,7 @@ __global__ __launch_bounds__(256, EDGE == 128 ? 2 : 4) void syrk_f64(
         }
     };
 
-    const int wi = wv >> 1, wj = wv & 1;
+    const int wi = (part >> 1) * kSide + (wv >> 1) * (kSide / 2), wj = (part & 1) * kSide + (wv & 1) * (kSide / 2);
     v4d acc[MT][MT];
 #pragma unroll
     for (int a = 0; a < MT; ++a)
@@ -762,8 +765,8 @@ __global__ __launch_bounds__(256, EDGE == 128 ? 2 : 4) void syrk_f64(
     // step st from LDS buffer `buf`; v: the rows of step st + 1, then st + 3
     auto step = [&](v4u (&v)[NS][4], int st, int buf) __attribute__((always_inline)) {
         const int ent = entry(st + 3);
-        const double* pa = &lds[buf][0][g * kLd + wi * (EDGE / 2) + j];
-        const double* pb = &lds[buf][diag ? 0 : 1][g * kLd + wj * (EDGE / 2) + j];
+        const double* pa = &lds[buf][0][g * kLd + wi + j];
+        const double* pb = &lds[buf][diag ? 0 : 1][g * kLd + wj + j];
 #pragma unroll
         for (int s = 0; s < kSyrkKC / 4; ++s) {
             double a[MT], b[MT];
@@ -801,8 +804,8 @@ __global__ __launch_bounds__(256, EDGE == 128 ? 2 : 4) void syrk_f64(
     if (st < nsteps) step(v1, st, 0);
     const int I2 = EDGE == 128 ? it.I : it.I >> 1, J2 = EDGE == 128 ? it.J : it.J >> 1;
     double* __restrict__ Ft = F + S.F_off + (int64_t)(I2 * (I2 + 1) / 2 + J2) * kFTileElems;
-    const int r0 = (EDGE == 128 ? 0 : 64 * (it.I & 1)) + wi * (EDGE / 2);
-    const int c0 = (EDGE == 128 ? 0 : 64 * (it.J & 1)) + wj * (EDGE / 2);
+    const int r0 = (EDGE == 128 ? 0 : 64 * (it.I & 1)) + wi;
+    const int c0 = (EDGE == 128 ? 0 : 64 * (it.J & 1)) + wj;
     const bool mirror = EDGE == 64 && I2 == J2 && !diag;
 #pragma unroll
     for (int ta = 0; ta < MT; ++ta)
@@ -1137,6 +1140,15 @@ hipError_t launch_trsm(const DevTables& t, const int32_t* order, int64_t count, 
     return hipGetLastError();
 }
 
+// FP64 launches of at most this many 64 x 64 blocks give each to four
+// workgroups, a 32 x 32 quarter each (all load both sides): a block alone on a
+// CU takes as long as the CU's matrix units need for it, while others idle.
+// Whole blocks / quarters: one 16 x 16 heat square (1 block) 14 / 7 us, one 129^2
+// triangle mesh (36) 58 / 29, 8 (288) 64 / 49, 16 (576) 92 / 76, one 12^3 heat
+// cube (105) 30 / 20, 4 (420) 38 / 35, 8 (840) 51 / 58, one uneven elasticity box
+// (861) 92 / 157.
+constexpr int64_t kSyrkQuarterItems = 512;
+
 hipError_t launch_syrk(const DevTables& t, const SyrkItem* items, int64_t ntile, int64_t nblock,
                        hipStream_t stream) {
     if (ntile > 0) {
@@ -1154,8 +1166,12 @@ hipError_t launch_syrk(const DevTables& t, const SyrkItem* items, int64_t ntile,
             hipLaunchKernelGGL(syrk_split_f32<64>, dim3((unsigned)nblock), dim3(256), 0, stream, t.subs, t.tiles,
                                items + ntile, t.ksteps, t.X32, t.F32);
         else
-            hipLaunchKernelGGL(syrk_f64<64>, dim3((unsigned)nblock), dim3(256), 0, stream, t.subs, t.tiles,
-                               items + ntile, t.ksteps, t.X, t.F);
+            if (nblock <= kSyrkQuarterItems)
+                hipLaunchKernelGGL((syrk_f64<64, true>), dim3((unsigned)(4 * nblock)), dim3(256), 0, stream, t.subs,
+                                   t.tiles, items + ntile, t.ksteps, t.X, t.F);
+            else
+                hipLaunchKernelGGL(syrk_f64<64>, dim3((unsigned)nblock), dim3(256), 0, stream, t.subs, t.tiles,
+                                   items + ntile, t.ksteps, t.X, t.F);
         return hipGetLastError();
     }
     return hipSuccess;

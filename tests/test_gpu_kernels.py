@@ -138,6 +138,20 @@ def test_syrk_at_tile_edges(kind, precision):
 
 
 @pytest.mark.parametrize("precision", ["fp64", "mixed"])
+def test_syrk_quarters_match_whole_blocks(precision):
+    """A launch of few blocks (four workgroups a block) and of many (one), at
+    every remainder of the last column tile: the same F bit for bit."""
+    subs = [_columns(scgen.box_subdomain("heat", e, 1.0 / 16, 300 + m), m, 310 + m)
+            for e, m in [((3, 2), 1), ((16, 9), 31), ((15, 13), 33), ((9, 7), 64), ((11, 18), 97), ((19, 19), 193)]]
+    few = _plan(subs, precision=precision, syrk_kind=1)
+    many = _plan(subs + [scgen.box_subdomain("heat", (3, 3), 0.3, 9)] * 600, precision=precision, syrk_kind=1)
+    for i, s in enumerate(subs):
+        assert np.array_equal(few.get_F(i), many.get_F(i)), s.m
+    few.destroy()
+    many.destroy()
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
 def test_apply_and_pcpg_at_tile_edges(precision):
     """q = F p through both explicit applies, and one projected CG step count
     of each workgroup width, at m around the stored 128 x 128 tiles: against
