@@ -115,6 +115,22 @@ def test_trsm_reads_only_rows_it_wrote(precision, split):
     ref.destroy()
 
 
+@pytest.mark.parametrize("merge", [True, False])
+def test_trsm_slab_of_4_gib(merge):
+    """A column tile whose X rows hold 4 GiB and more (64-bit row offsets in
+    the TRSM): 8.4 million rows kept down to the first pivot or not, the same
+    values where only the last few rows are kept (32-bit offsets)."""
+    n = 8_400_000
+    s = scgen.laplace_1d(n, dof=np.array([n // 2, 3 * n // 4, 7 * n // 8], dtype=np.int32), seed=4)
+    F = []
+    for staircase in (True, False):
+        plan = _plan([s], staircase=staircase, panel_width=16, pair_merge=merge)
+        F.append(plan.get_F(0))
+        plan.destroy()
+    assert np.isfinite(F[0]).all() and np.abs(F[0]).min() > 0
+    assert np.abs(F[1] - F[0]).max() <= 1e-13 * np.abs(F[0]).max()
+
+
 @pytest.mark.parametrize("precision", ["fp64", "mixed"])
 @pytest.mark.parametrize("kind", [1, 2])
 def test_syrk_at_tile_edges(kind, precision):
