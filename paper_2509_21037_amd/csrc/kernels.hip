@@ -1144,10 +1144,11 @@ hipError_t launch_trsm(const DevTables& t, const int32_t* order, int64_t count, 
 // workgroups, a 32 x 32 quarter each (all load both sides): a block alone on a
 // CU takes as long as the CU's matrix units need for it, while others idle.
 // Whole blocks / quarters: one 16 x 16 heat square (1 block) 14 / 7 us, one 129^2
-// triangle mesh (36) 58 / 29, 8 (288) 64 / 49, 16 (576) 92 / 76, one 12^3 heat
-// cube (105) 30 / 20, 4 (420) 38 / 35, 8 (840) 51 / 58, one uneven elasticity box
-// (861) 92 / 157.
-constexpr int64_t kSyrkQuarterItems = 512;
+// triangle mesh (36) 58 / 29, 8 (288) 65 / 49, one 12^3 heat cube (105) 30 / 20;
+// triangle meshes of 17^2 nodes, one block each: 256 of them 19.1 / 20.7, 320
+// 27.2 / 24.9, 352 27.3 / 27.8, 512 29 / 42; one uneven elasticity box (861) 92
+// / 157.
+constexpr int64_t kSyrkQuarterItems = 320;
 
 hipError_t launch_syrk(const DevTables& t, const SyrkItem* items, int64_t ntile, int64_t nblock,
                        hipStream_t stream) {
