@@ -1517,7 +1517,7 @@ sc_status_t sc_pcpg(sc_plan_t P, const double* const* R_host, const int32_t* k_h
 // everything goes into locals and is committed to the plan only when every
 // allocation, copy and the final synchronisation succeeded (a failed attempt
 // leaves the plan as it was and releases what it allocated).
-static sc_status_t build_implicit(sc_plan_s* P, hipStream_t st) {
+static sc_status_t build_implicit_tables(sc_plan_s* P, hipStream_t st) {
     std::vector<int64_t> off(P->nsub + 1, 0);
     for (int32_t i = 0; i < P->nsub; ++i) off[i + 1] = off[i] + P->plans[i].n;
     // levels: forward = 1 + max over the blocks whose pruned rows reach the
@@ -1748,6 +1748,14 @@ static sc_status_t build_implicit(sc_plan_s* P, hipStream_t st) {
     P->ilv_h = lvh;
     P->impl_ready = true;
     return SC_OK;
+}
+
+static sc_status_t build_implicit(sc_plan_s* P, hipStream_t st) {
+    try {
+        return build_implicit_tables(P, st);      // host tables first, then the device's
+    } catch (const std::bad_alloc&) {
+        return fail(SC_ERR_OOM, "host allocation failed in the implicit apply setup");
+    }
 }
 
 sc_status_t sc_apply_implicit(sc_plan_t P, const double* p_dev, double* q_dev, void* stream) {
