@@ -1,6 +1,7 @@
 // Device-side tables shared by the kernels and the host code that builds them.
 #pragma once
 #include <cstdint>
+#include <type_traits>
 
 namespace scasm {
 
@@ -72,6 +73,14 @@ template <class TA>
 constexpr int kPruneTiles = sizeof(TA) == 8 ? 2 : 4;
 // X slabs from this size on are out of the 32-bit offsets of a buffer resource
 constexpr int64_t kTrsmSlabBytes = 0xFFFFFF00ll;
+// Where the TRSM finds an element of a slab: the byte offset in a buffer
+// resource (an unsigned one, below kTrsmSlabBytes), or in larger slabs the
+// element index, which outgrows 32 bits from 2^25 rows on (rows go up to 2^27).
+template <class TX, bool LARGE>
+constexpr typename std::conditional<LARGE, int64_t, int32_t>::type slab_offset(int row, int col) {
+    using Off = typename std::conditional<LARGE, int64_t, int32_t>::type;
+    return LARGE ? (Off)row * kTile + col : (Off)((uint32_t)(row * kTile + col) * (uint32_t)sizeof(TX));
+}
 
 // SYRK work item: a 64 x 64 block of F (I >= J in units of 64-column X
 // tiles), its k-range a list of 16-row steps (first rows at

@@ -118,25 +118,24 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_of(const void* p, uint3
 // Access to the rows of one X slab by element offset.  LARGE = false: 32-bit
 // byte offsets of a buffer resource, kNone an offset past any slab.  LARGE =
 // true (slabs of kTrsmSlabBytes and more, which those offsets cannot span):
-// element indices and plain accesses under a branch.
+// 64-bit element indices and plain accesses under a branch.
 template <class TX, bool LARGE>
 struct SlabRows {
-    static constexpr int kNone = LARGE ? -1 : -16;
+    using Off = decltype(slab_offset<TX, LARGE>(0, 0));
+    static constexpr Off kNone = LARGE ? -1 : -16;
     TX* p;
     __amdgpu_buffer_rsrc_t r;
     __device__ __forceinline__ SlabRows(TX* x, int64_t elems)
         : p(x), r(buffer_of(x, LARGE ? 0u : (uint32_t)(elems * (int64_t)sizeof(TX)))) {}
-    __device__ __forceinline__ static int at(int row, int col) {
-        return LARGE ? row * kTile + col : (int)((uint32_t)(row * kTile + col) * (uint32_t)sizeof(TX));
-    }
+    __device__ __forceinline__ static Off at(int row, int col) { return slab_offset<TX, LARGE>(row, col); }
     // or-ed to an offset: kNone where c holds
-    __device__ __forceinline__ static int none_if(bool c) { return c ? kNone : 0; }
-    __device__ __forceinline__ TX load(int off) const {
+    __device__ __forceinline__ static Off none_if(bool c) { return c ? kNone : 0; }
+    __device__ __forceinline__ TX load(Off off) const {
         if constexpr (LARGE) return off >= 0 ? p[off] : TX(0);
         else if constexpr (sizeof(TX) == 8) return __builtin_bit_cast(TX, __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0));
         else return __builtin_bit_cast(TX, __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0));
     }
-    __device__ __forceinline__ void store(int off, TX v) const {
+    __device__ __forceinline__ void store(Off off, TX v) const {
         if constexpr (LARGE) {
             if (off >= 0) p[off] = v;
         } else if constexpr (sizeof(TX) == 8) {
@@ -396,7 +395,7 @@ __device__ __forceinline__ void trsm_tile(
     TX xin[4][4];                                // X rows of the next block, accumulator layout
     auto load_block = [&](const VisitDev& v, uint64_t held, bool act) {
         const uint64_t onl = act ? held >> g : 0;
-        const int b0 = Rows::at(v.row0 + g - kstart, col);
+        const auto b0 = Rows::at(v.row0 + g - kstart, col);
 #pragma unroll
         for (int t = 0; t < 4; ++t)
 #pragma unroll
@@ -424,13 +423,13 @@ __device__ __forceinline__ void trsm_tile(
         const bool gact = role == 1 ? nx_act : act;
 
         VX accn[PT];                             // rows of the next pruned chunk
-        int offn[PT][4];                         // where they are written
+        typename Rows::Off offn[PT][4];                         // where they are written
         auto gather = [&](int q) {               // row indices and mask from the chunk in LDS
             const int32_t* __restrict__ sidx = reinterpret_cast<const int32_t*>(smem + buf * kBufBytes + kChunkBytes);
             const int left = urows - 16 * PT * q;
             // rows never written before are zero: not read
             uint64_t fr = *reinterpret_cast<const uint64_t*>(sidx + kRowsBytes / 4) >> g;
-            int offl[PT][4];
+            typename Rows::Off offl[PT][4];
 #pragma unroll
             for (int u = 0; u < PT; ++u)
 #pragma unroll
@@ -485,7 +484,7 @@ __device__ __forceinline__ void trsm_tile(
                 __builtin_amdgcn_sched_barrier(0);
             }
             const uint64_t onl = (act ? v.on : v.on & ~v.held) >> g;
-            const int b0 = Rows::at(v.row0 + g - kstart, col);
+            const auto b0 = Rows::at(v.row0 + g - kstart, col);
 #pragma unroll
             for (int t = 0; t < 4; ++t)
 #pragma unroll
@@ -540,7 +539,7 @@ __device__ __forceinline__ void trsm_tile(
                 }
             pair_nks = nks;
         } else if (np > 0) {
-            int off[PT][4];
+            typename Rows::Off off[PT][4];
             auto take_rows = [&]() {
 #pragma unroll
                 for (int u = 0; u < PT; ++u) {
@@ -618,7 +617,7 @@ __device__ __forceinline__ void trsm_tile(
 // kTrsmSlabBytes or more.  LOADER: a fifth wavefront streams the chunks
 // (launches of at most kLoaderMaxTiles tiles).
 template <bool MERGE, bool LARGE, bool LOADER>
-__global__ __launch_bounds__(LOADER ? 320 : 256, LOADER ? 1 : MERGE ? 2 : 3) void trsm_stair_f64(
+__global__ __launch_bounds__(LOADER ? 320 : 256, LOADER ? 1 : MERGE || LARGE ? 2 : 3) void trsm_stair_f64(
     const SubDev* __restrict__ subs, const TileDev* __restrict__ tiles, const int32_t* __restrict__ rows,
     const VisitDev* __restrict__ visits, const uint64_t* __restrict__ fresh, const int32_t* __restrict__ clear,
     const double* __restrict__ lval,
@@ -631,7 +630,7 @@ __global__ __launch_bounds__(LOADER ? 320 : 256, LOADER ? 1 : MERGE ? 2 : 3) voi
 }
 
 template <bool MERGE, bool LARGE, bool LOADER>
-__global__ __launch_bounds__(LOADER ? 320 : 256, LOADER ? 1 : MERGE ? 2 : 3) void trsm_stair_mixed(
+__global__ __launch_bounds__(LOADER ? 320 : 256, LOADER ? 1 : MERGE || LARGE ? 2 : 3) void trsm_stair_mixed(
     const SubDev* __restrict__ subs, const TileDev* __restrict__ tiles, const int32_t* __restrict__ rows,
     const VisitDev* __restrict__ visits, const uint64_t* __restrict__ fresh, const int32_t* __restrict__ clear,
     const double* __restrict__ lval,
