@@ -27,7 +27,9 @@
  *     sc_last_error() returns a thread-local message for the last failure.
  *   - Asynchronous calls report launch errors at once; execution errors
  *     surface at the next synchronising call.
- *   - A plan is not thread-safe; distinct plans are independent.
+ *   - A plan is not thread-safe; distinct plans are independent.  The calls on
+ *     one plan share its workspaces: what they queue on the device must not
+ *     overlap (one stream, or streams ordered by events).
  */
 #ifndef SCASM_H
 #define SCASM_H
@@ -296,8 +298,16 @@ sc_status_t sc_apply_noalloc(sc_plan_t plan, const double* p_dev, double* q_dev,
 
 /* Solution stage, implicit apply (eq. (11)): q_i = B_i P^T L^{-T} L^{-1} P B_i^T
  * p_i with two sparse triangular solves on the device, same vector layout as
- * sc_apply.  SC_ERR_STATE before sc_factor. */
+ * sc_apply.  SC_ERR_STATE before sc_factor.  Workgroups wait for others of
+ * the same launch; a wait that does not end (calls that overlap on one plan)
+ * gives up after the plan's limit, and q_i of that subdomain is NaN, here
+ * and in sc_apply with select_iters; sc_pcpg returns SC_ERR_DEVICE then. */
 sc_status_t sc_apply_implicit(sc_plan_t plan, const double* p_dev, double* q_dev, void* stream);
+
+/* The limit of those waits, in looks of about a microsecond at a counter (>= 0;
+ * 2^24 unless set, which no sweep that runs alone comes near).  For later
+ * calls; waits for the device when a captured graph holds the old limit. */
+sc_status_t sc_set_wait_limit(sc_plan_t plan, int32_t looks);
 
 /* Solution stage: projected conjugate gradients (Sec. 2.1: the dual problem
  * (7), solved by PCPG, applying F once per iteration) on every subdomain's own

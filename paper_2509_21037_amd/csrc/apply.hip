@@ -802,25 +802,31 @@ __device__ __forceinline__ int chain_ticket(int32_t* ticket, int* sh) {
 }
 // Until `need` items have finished; what they wrote is visible afterwards.
 // Calls that overlap on one plan (they may not) share the counters: a wait
-// that they leave without an end gives up after kChainTicks (10 s at 100 MHz)
-// and releases all others of its subdomain.
-constexpr long long kChainTicks = 1000000000;
-__device__ __forceinline__ void chain_wait(int32_t* done, int need) {
-    if (threadIdx.x == 0 && need > 0) {
-        const long long t0 = wall_clock64();
-        while (__hip_atomic_load(done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < need) {
-            __builtin_amdgcn_s_sleep(8);
-            if (wall_clock64() - t0 > kChainTicks)
-                __hip_atomic_store(done, 1 << 30, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-    }
-    __syncthreads();
-}
+// that they leave without an end gives up after `looks` looks at the counter
+// and releases all others of its subdomain.  The gather then writes NaN for
+// the subdomain, whose sums may be incomplete, and the plan's fault word is
+// set.  Looks and not time: while the queue is preempted no time is up.
 struct ChainWait {
     static constexpr bool kShared = true;
     int32_t* done;
     int need;
-    __device__ __forceinline__ void operator()() const { chain_wait(done, need); }
+    int looks;
+    int32_t* fault;
+    __device__ __forceinline__ void operator()() const {
+        if (threadIdx.x == 0 && need > 0) {
+            int left = looks;
+            while (__hip_atomic_load(done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < need) {
+                if (left-- > 0) {
+                    __builtin_amdgcn_s_sleep(8);
+                } else {
+                    __hip_atomic_store(done, kImplGaveUp, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    __hip_atomic_store(fault, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    break;
+                }
+            }
+        }
+        __syncthreads();
+    }
 };
 // counts this workgroup's item, once its stores have reached memory; returns
 // the count before (thread 0)
@@ -834,7 +840,7 @@ __device__ __forceinline__ int chain_done(int32_t* done) {
 __global__ __launch_bounds__(kImplThreads, 8) void implicit_fwd_chain(
     const ImplChainItem* __restrict__ items, const double* __restrict__ lval, const int32_t* __restrict__ rptr,
     const int32_t* __restrict__ rpos, const double* __restrict__ xwork, double* __restrict__ ywork, double* ubuf,
-    int32_t* ticket, int32_t* done, int n)
+    int32_t* ticket, int32_t* done, int n, int looks, int32_t* fault)
 {
     __shared__ double sp[kImplParts][64];
     __shared__ double sx[64];
@@ -843,14 +849,14 @@ __global__ __launch_bounds__(kImplThreads, 8) void implicit_fwd_chain(
     if (at >= n) return;
     const ImplChainItem it = items[at];
     implicit_fwd_block<kImplBatch, true>(it.b, lval, rptr, rpos, xwork, ywork, ubuf, sp, sx, it.g, it.G,
-                                              ChainWait{done + it.sub * kImplCounterStride, it.need});
+                                              ChainWait{done + it.sub * kImplCounterStride, it.need, looks, fault});
     chain_done(done + it.sub * kImplCounterStride);
 }
 
 __global__ __launch_bounds__(kImplThreads, 8) void implicit_bwd_chain(
     const ImplChainItem* __restrict__ items, const int32_t* __restrict__ rows, const double* __restrict__ lval,
     const double* __restrict__ ywork, double* xwork, double* cpart, int32_t* ticket, int32_t* done, int32_t* shares,
-    int n)
+    int n, int looks, int32_t* fault)
 {
     __shared__ double sp[kImplParts][64];
     __shared__ double sz[kImplThreads];
@@ -864,7 +870,7 @@ __global__ __launch_bounds__(kImplThreads, 8) void implicit_bwd_chain(
     const int c = 4 * part + (r >> 4);
     const int nrt = (b.nbelow + 15) >> 4;
     const int per = (nrt + it.G - 1) / it.G;
-    const ChainWait wait{done + it.sub * kImplCounterStride, it.need};
+    const ChainWait wait{done + it.sub * kImplCounterStride, it.need, looks, fault};
     double li[4];
     if (it.G == 1) linv_col(b, lval, li);
     const double acc = implicit_bwd_sum<kImplBatch, true>(b, rows, lval, xwork, it.g * per,
@@ -929,14 +935,19 @@ __global__ __launch_bounds__(kImplThreads) void implicit_sweeps(
 __global__ __launch_bounds__(kInitThreads) void implicit_gather(
     const SubDev* __restrict__ subs, const int32_t* __restrict__ piv, const int32_t* __restrict__ pi,
     const int8_t* __restrict__ sgn, const int64_t* __restrict__ xoff, const double* __restrict__ xwork,
-    double* __restrict__ q, const int32_t* __restrict__ sub_list, int C)
+    double* __restrict__ q, const int32_t* __restrict__ sub_list, int C, const int32_t* __restrict__ fw_done,
+    const int32_t* __restrict__ bw_done)
 {
     const int at = (int)blockIdx.x / C, c = (int)blockIdx.x % C;
     const int sub = sub_list ? sub_list[at] : at;
     const SubDev S = subs[sub];
     const double* __restrict__ x = xwork + xoff[sub];
+    // a wait of the chains gave up (ChainWait): no value is known to be right
+    const bool bad = fw_done && (fw_done[sub * kImplCounterStride] >= kImplGaveUp ||
+                                 bw_done[sub * kImplCounterStride] >= kImplGaveUp);
     for (int a = c * kInitThreads + threadIdx.x; a < S.m; a += C * kInitThreads)
-        q[S.dual_off + pi[S.col_off + a]] = (double)sgn[S.col_off + a] * x[piv[S.col_off + a]];
+        q[S.dual_off + pi[S.col_off + a]] =
+            bad ? __builtin_nan("") : (double)sgn[S.col_off + a] * x[piv[S.col_off + a]];
 }
 
 hipError_t launch_implicit_init(const DevTables& t, const ImplicitLevels& lv, const int64_t* xoff, double* xwork,
@@ -954,7 +965,7 @@ hipError_t launch_implicit_sweeps(const DevTables& t, const ImplicitLevels& lv, 
     // every table and workspace the sweeps dereference must be in place
     if (!xoff || !xwork || !lv.ywork || !lv.ubuf || !lv.rptr_off || !lv.rptr || !lv.rpos) return hipErrorInvalidValue;
     if ((lv.nfw_chain > 0 || lv.nbw_chain > 0) &&
-        (!lv.counters || (lv.nfw_chain > 0 && !lv.fw_chain_items) || (lv.nbw_chain > 0 && (!lv.bw_chain_items || !lv.cpart))))
+        (!lv.counters || !lv.fault || (lv.nfw_chain > 0 && !lv.fw_chain_items) || (lv.nbw_chain > 0 && (!lv.bw_chain_items || !lv.cpart))))
         return hipErrorInvalidValue;
     if (!lv.per_subdomain && ((lv.fw_off.size() > 1 && !lv.fw_items) || (lv.bw_off.size() > 1 && !lv.bw_items)))
         return hipErrorInvalidValue;
@@ -964,8 +975,8 @@ hipError_t launch_implicit_sweeps(const DevTables& t, const ImplicitLevels& lv, 
                            t.rows, t.lval, lv.rptr_off, lv.rptr, lv.rpos, xoff, xwork, lv.ywork, lv.ubuf, lv.subs);
         return hipGetLastError();
     }
-    int32_t* const fw_done = lv.counters + 2 * kImplCounterStride;
-    int32_t* const bw_done = fw_done + lv.nsub * kImplCounterStride;
+    int32_t* const fw_done = lv.fw_done();
+    int32_t* const bw_done = lv.bw_done();
     for (size_t l = 0; l < lv.fw_chain && l + 1 < lv.fw_off.size(); ++l) {
         const int64_t cnt = lv.fw_off[l + 1] - lv.fw_off[l];
         if (cnt <= 0) continue;
@@ -976,13 +987,13 @@ hipError_t launch_implicit_sweeps(const DevTables& t, const ImplicitLevels& lv, 
     if (lv.nfw_chain > 0) {
         hipLaunchKernelGGL(implicit_fwd_chain, dim3((unsigned)lv.nfw_chain), dim3(kImplThreads), 0, stream,
                            lv.fw_chain_items, t.lval, lv.rptr, lv.rpos, xwork, lv.ywork, lv.ubuf, lv.counters, fw_done,
-                           (int)lv.nfw_chain);
+                           (int)lv.nfw_chain, lv.looks, lv.fault);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     if (lv.nbw_chain > 0) {
         hipLaunchKernelGGL(implicit_bwd_chain, dim3((unsigned)lv.nbw_chain), dim3(kImplThreads), 0, stream,
                            lv.bw_chain_items, t.rows, t.lval, lv.ywork, xwork, lv.cpart, lv.counters + kImplCounterStride,
-                           bw_done, bw_done + lv.nsub * kImplCounterStride, (int)lv.nbw_chain);
+                           bw_done, bw_done + lv.nsub * kImplCounterStride, (int)lv.nbw_chain, lv.looks, lv.fault);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     for (size_t l = lv.bw_chain; l + 1 < lv.bw_off.size(); ++l) {
@@ -995,12 +1006,14 @@ hipError_t launch_implicit_sweeps(const DevTables& t, const ImplicitLevels& lv, 
     return hipSuccess;
 }
 
-hipError_t launch_implicit_gather(const DevTables& t, const int64_t* xoff, const double* xwork, double* q,
-                                  const int32_t* sub_list, int32_t count, hipStream_t stream) {
+hipError_t launch_implicit_gather(const DevTables& t, const ImplicitLevels& lv, const int64_t* xoff,
+                                  const double* xwork, double* q, int32_t count, hipStream_t stream) {
     if (count <= 0) return hipSuccess;
     const int C = init_split(count);
+    const bool chains = lv.counters && !lv.per_subdomain;
     hipLaunchKernelGGL(implicit_gather, dim3((unsigned)(count * C)), dim3(kInitThreads), 0, stream, t.subs, t.piv, t.pi,
-                       t.sgn, xoff, xwork, q, sub_list, C);
+                       t.sgn, xoff, xwork, q, lv.subs, C, chains ? lv.fw_done() : nullptr,
+                       chains ? lv.bw_done() : nullptr);
     return hipGetLastError();
 }
 
@@ -1010,7 +1023,7 @@ hipError_t launch_apply_implicit(const DevTables& t, const ImplicitLevels& lv, c
     if (ev && (e = hipEventRecord(ev[0], stream)) != hipSuccess) return e;
     if ((e = launch_implicit_init(t, lv, xoff, xwork, p, count, stream)) != hipSuccess) return e;
     if ((e = launch_implicit_sweeps(t, lv, xoff, xwork, count, stream)) != hipSuccess) return e;
-    if ((e = launch_implicit_gather(t, xoff, xwork, q, lv.subs, count, stream)) != hipSuccess) return e;
+    if ((e = launch_implicit_gather(t, lv, xoff, xwork, q, count, stream)) != hipSuccess) return e;
     if (ev && (e = hipEventRecord(ev[1], stream)) != hipSuccess) return e;
     return hipSuccess;
 }

@@ -123,6 +123,10 @@ inline int impl_split(int64_t blocks, int tiles) {
 // ints between the counters that waiting workgroups read over and over: with
 // all subdomains' counters in one cache line the sweeps took twice as long
 constexpr int64_t kImplCounterStride = 64;
+// looks (of about a microsecond) at a counter before a wait gives up, and the
+// value that it leaves in the counter, above every count
+constexpr int32_t kImplLooks = 1 << 24;
+constexpr int32_t kImplGaveUp = 1 << 30;
 
 // One workgroup of a chain of levels run in one launch: a block (or
 // share g of G of its row tiles) that starts when `need` workgroups (forward)
@@ -162,6 +166,11 @@ struct ImplicitLevels {
     int64_t nfw_chain = 0, nbw_chain = 0, nsub = 0;
     size_t fw_chain = SIZE_MAX, bw_chain = 0;
     int64_t ncounters() const { return kImplCounterStride * (2 + 2 * nsub) + nbw_chain; }
+    int32_t* fw_done() const { return counters + 2 * kImplCounterStride; }
+    int32_t* bw_done() const { return fw_done() + nsub * kImplCounterStride; }
+    // set when a wait gave up (and never cleared by the sweeps)
+    int32_t* fault = nullptr;
+    int32_t looks = kImplLooks;
     // true: one workgroup per subdomain runs both sweeps block by block
     bool per_subdomain = false;
     // the subdomains covered (device list; null = all, in index order)
@@ -179,8 +188,8 @@ hipError_t launch_implicit_init(const DevTables& t, const ImplicitLevels& lv, co
                                 const double* p, int32_t count, hipStream_t stream);
 hipError_t launch_implicit_sweeps(const DevTables& t, const ImplicitLevels& lv, const int64_t* xoff, double* xwork,
                                   int32_t count, hipStream_t stream);
-hipError_t launch_implicit_gather(const DevTables& t, const int64_t* xoff, const double* xwork, double* q,
-                                  const int32_t* sub_list, int32_t count, hipStream_t stream);
+hipError_t launch_implicit_gather(const DevTables& t, const ImplicitLevels& lv, const int64_t* xoff,
+                                  const double* xwork, double* q, int32_t count, hipStream_t stream);
 hipError_t launch_apply_implicit(const DevTables& t, const ImplicitLevels& lv, const int64_t* xoff, double* xwork,
                                  const double* p, double* q, int32_t count, hipStream_t stream, hipEvent_t* ev);
 

@@ -150,6 +150,8 @@ constexpr double kSelectImplGBps = 3190.0;
 // heat 1.74 / 1.57 ms, uneven elasticity 1.96 / 2.06, 20^3 9.6 / 11.8.
 constexpr double kMergeMinShare = 0.10, kMergeMinShareMixed = 0.25;
 
+constexpr char kGaveUpMessage[] = "the implicit apply gave up waiting for a workgroup (calls that overlap on one plan?)";
+
 struct Prediction {
     double t_asm_ms = 0, t_expl_ms = 0, t_impl_ms = 0, n_star = 0;
 };
@@ -433,6 +435,7 @@ struct sc_plan_s {
     int32_t n_implicit = 0;
     hipGraphExec_t graph_exec = nullptr;        // captured assembly (use_graph)
     hipGraphExec_t impl_graph = nullptr;        // captured triangular sweeps of the implicit apply (use_graph)
+    int32_t wait_looks = kImplLooks;
     bool impl_ready = false;                    // implicit apply schedule and workspace built
     double trsm_u = 0, syrk_u = 0, trsm_d = 0, syrk_d = 0, trsm_r = 0, syrk_r = 0;
     // kernel timing: event pairs per kernel, pending until read
@@ -1500,9 +1503,14 @@ sc_status_t sc_pcpg(sc_plan_t P, const double* const* R_host, const int32_t* k_h
         a.r = dwork.p; a.w = dwork.p + nd; a.p = dwork.p + 2 * nd; a.q = dwork.p + 3 * nd;
         a.ww = dww.p; a.hist = dhist.p; a.nsub = P->nsub; a.iters = iters;
         a.dual_total = P->dual_total;
-        e = launch_pcpg(P->tables(), a, st, P->n_implicit > 0 ? &P->ilv_h : nullptr, P->d_xoff.p, P->d_xwork.p,
-                        P->n_implicit);
+        if (P->n_implicit > 0) e = hipMemsetAsync(P->ilv_h.fault, 0, sizeof(int32_t), st);
+        if (e == hipSuccess)
+            e = launch_pcpg(P->tables(), a, st, P->n_implicit > 0 ? &P->ilv_h : nullptr, P->d_xoff.p, P->d_xwork.p,
+                            P->n_implicit);
     }
+    int32_t fault = 0;
+    if (e == hipSuccess && P->n_implicit > 0)
+        e = hipMemcpyAsync(&fault, P->ilv_h.fault, sizeof(int32_t), hipMemcpyDeviceToHost, st);
     if (e == hipSuccess && wnorm_hist)
         e = hipMemcpyAsync(wnorm_hist, dhist.p, (size_t)(iters + 1) * P->nsub * 8, hipMemcpyDeviceToHost, st);
     // the workspace is released after the queued work has finished
@@ -1510,6 +1518,7 @@ sc_status_t sc_pcpg(sc_plan_t P, const double* const* R_host, const int32_t* k_h
     cleanup();
     if (e != hipSuccess) return fail(e == hipErrorOutOfMemory ? SC_ERR_OOM : SC_ERR_DEVICE,
                                      std::string("sc_pcpg: ") + hipGetErrorString(e));
+    if (fault) return fail(SC_ERR_DEVICE, std::string("sc_pcpg: ") + kGaveUpMessage);
     return SC_OK;
 }
 
@@ -1692,7 +1701,9 @@ static sc_status_t build_implicit_tables(sc_plan_s* P, hipStream_t st) {
     if (e == hipSuccess) e = cbw.alloc(bwc.size());
     if (e == hipSuccess) e = cfwh.alloc(fwhc.size());
     if (e == hipSuccess) e = cbwh.alloc(bwhc.size());
-    if (e == hipSuccess) e = counters.alloc((size_t)std::max(lv.ncounters(), lvh.ncounters()));
+    const int64_t ncounters = std::max(lv.ncounters(), lvh.ncounters());      // and the fault word
+    if (e == hipSuccess) e = counters.alloc((size_t)ncounters + 1);
+    if (e == hipSuccess) e = hipMemsetAsync(counters.p + ncounters, 0, sizeof(int32_t), st);
     if (e == hipSuccess) e = cpart.alloc(64 * std::max<size_t>({1, bwc.size(), bwhc.size()}));
     auto up = [&](void* d, const void* h, size_t bytes) -> hipError_t {
         return bytes ? hipMemcpyAsync(d, h, bytes, hipMemcpyHostToDevice, st) : hipSuccess;
@@ -1726,6 +1737,8 @@ static sc_status_t build_implicit_tables(sc_plan_s* P, hipStream_t st) {
     lv.fw_chain_items = cfw.p;
     lv.bw_chain_items = cbw.p;
     lv.counters = counters.p;
+    lv.fault = counters.p + ncounters;
+    lv.looks = P->wait_looks;
     lv.cpart = cpart.p;
     P->d_xwork = xwork; P->d_ywork = ywork; P->d_xoff = xoff; P->d_ifw = ifw; P->d_ibw = ibw;
     P->d_rptr_off = rptr_off_d; P->d_rptr = rptr_d; P->d_rpos = rpos_d; P->d_ubuf = ubuf;
@@ -1741,6 +1754,8 @@ static sc_status_t build_implicit_tables(sc_plan_s* P, hipStream_t st) {
     lvh.fw_chain_items = cfwh.p;
     lvh.bw_chain_items = cbwh.p;
     lvh.counters = counters.p;
+    lvh.fault = lv.fault;
+    lvh.looks = P->wait_looks;
     lvh.cpart = cpart.p;
     P->d_chain_fw = cfw; P->d_chain_bw = cbw; P->d_chain_fw_h = cfwh; P->d_chain_bw_h = cbwh;
     P->d_chain_counters = counters; P->d_chain_part = cpart;
@@ -1795,7 +1810,7 @@ sc_status_t sc_apply_implicit(sc_plan_t P, const double* p_dev, double* q_dev, v
         }
         HIP_TRY(launch_implicit_init(t, P->ilv, P->d_xoff.p, P->d_xwork.p, p_dev, P->nsub, st));
         HIP_TRY(hipGraphLaunch(P->impl_graph, st));
-        HIP_TRY(launch_implicit_gather(t, P->d_xoff.p, P->d_xwork.p, q_dev, nullptr, P->nsub, st));
+        HIP_TRY(launch_implicit_gather(t, P->ilv, P->d_xoff.p, P->d_xwork.p, q_dev, P->nsub, st));
         return SC_OK;
     }
     hipEvent_t ev[2];
@@ -1806,6 +1821,20 @@ sc_status_t sc_apply_implicit(sc_plan_t P, const double* p_dev, double* q_dev, v
     }
     HIP_TRY(launch_apply_implicit(t, P->ilv, P->d_xoff.p, P->d_xwork.p, p_dev, q_dev, P->nsub, st, evp));
     if (evp) P->pending.push_back({3, ev[0], ev[1]});
+    return SC_OK;
+}
+
+sc_status_t sc_set_wait_limit(sc_plan_t P, int32_t looks) {
+    g_last_error.clear();
+    if (!P) return fail(SC_ERR_INVALID_ARG, "plan is NULL");
+    if (looks < 0) return fail(SC_ERR_INVALID_ARG, "looks must be >= 0");
+    P->wait_looks = P->ilv.looks = P->ilv_h.looks = looks;
+    if (P->impl_graph) {                         // holds the old limit
+        HIP_TRY(hipSetDevice(P->device));
+        HIP_TRY(hipDeviceSynchronize());
+        (void)hipGraphExecDestroy(P->impl_graph);
+        P->impl_graph = nullptr;
+    }
     return SC_OK;
 }
 

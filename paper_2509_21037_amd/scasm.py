@@ -18,7 +18,7 @@ STATUS_NAMES = {0: "SC_OK", 1: "SC_ERR_INVALID_ARG", 2: "SC_ERR_NOT_SPD", 3: "SC
 EXPORTED = ["sc_plan_create", "sc_factor", "sc_assemble", "sc_apply", "sc_apply_implicit",
             "sc_get_F", "sc_query", "sc_plan_stats", "sc_plan_destroy", "sc_host_analyze",
             "sc_host_tile_visits", "sc_set_timing", "sc_kernel_times", "sc_pcpg", "sc_autotune", "sc_autotune_classes", "sc_apply_noalloc", "sc_preprocess", "sc_query_selection",
-            "sc_last_error"]
+            "sc_set_wait_limit", "sc_last_error"]
 
 
 class ScasmError(RuntimeError):
@@ -106,6 +106,7 @@ def load():
                                             ctypes.POINTER(vp), i32, i32, ctypes.c_char_p, vp,
                                             ctypes.POINTER(TuneClass), i32, ctypes.POINTER(i32)]
         lib.sc_query_selection.argtypes = [vp, i32, ctypes.POINTER(i32), dp, dp, dp, dp]
+        lib.sc_set_wait_limit.argtypes = [vp, i32]
         lib.sc_set_timing.argtypes = [vp, i32]
         lib.sc_kernel_times.argtypes = [vp, dp, ctypes.POINTER(ctypes.c_int64), i32]
         lib.sc_last_error.argtypes = []
@@ -471,6 +472,11 @@ class Plan:
         return {"nsub": ns.value, "dual_total": dt.value, "trsm_useful": tu.value, "syrk_useful": su.value,
                 "trsm_dense": td.value, "syrk_dense": sd.value, "trsm_reach": tr.value, "syrk_reach": sr.value,
                 "device_bytes": db.value}
+
+    def set_wait_limit(self, looks: int):
+        """Looks at a counter before a wait inside the implicit apply gives up
+        and its subdomain's result becomes NaN (sc_set_wait_limit)."""
+        _check(self._lib.sc_set_wait_limit(self._h, int(looks)))
 
     def set_timing(self, enable: bool = True):
         _check(self._lib.sc_set_timing(self._h, 1 if enable else 0))

@@ -259,6 +259,53 @@ def test_implicit_apply_chains(count, width, split):
     plan.destroy()
 
 
+@pytest.mark.parametrize("use_graph", [False, True])
+def test_implicit_wait_that_gives_up(use_graph):
+    """A wait of the chains that ends at its limit (0 looks: at once, set from
+    the host) leaves no number that could be taken for a result: NaN for its
+    subdomain, an error from the projected CG; with the limit back the same
+    plan is right again."""
+    import torch
+    subs = [scgen.box_subdomain("elasticity", e, 1.0 / 8, 400 + i) for i, e in enumerate([(8, 7, 6), (5, 6, 5), (7, 7, 7)])]
+    subs += [scgen.box_subdomain("heat", (2, 2), 0.5, 410)]
+    ref = _plan(subs, block_split="etree")
+    p = torch.from_numpy(np.random.default_rng(14).uniform(-1, 1, ref.dual_total)).cuda()
+    want, q = torch.zeros_like(p), torch.zeros_like(p)
+    ref.apply(p, want)
+    plan = _plan(subs, block_split="etree", use_graph=use_graph)
+    hybrid = _plan(subs, block_split="etree", select_iters=1)
+    assert any(hybrid.selection(i)["implicit"] for i in range(3))
+
+    def check(may_fail):
+        o, failed = 0, 0
+        for s in subs:
+            a, b = q[o:o + s.m], want[o:o + s.m]
+            o += s.m
+            if may_fail and bool(torch.isnan(a).all()):
+                failed += 1
+            else:
+                assert float((a - b).norm()) <= 1e-11 * float(b.norm())
+        assert not may_fail or failed
+
+    for pl, apply in ((plan, plan.apply_implicit), (hybrid, hybrid.apply)):
+        for limit in (1 << 24, 0, 1 << 24):
+            pl.set_wait_limit(limit)
+            for _ in range(2):
+                apply(p, q)
+                check(limit == 0)
+    lam = torch.zeros_like(p)
+    hybrid.pcpg(p, lam, 3)
+    hybrid.set_wait_limit(0)
+    with pytest.raises(P.ScasmError) as e:
+        hybrid.pcpg(p, lam, 3)
+    assert e.value.status == P.SC_ERR_DEVICE
+    hybrid.set_wait_limit(1 << 24)
+    again = torch.zeros_like(p)
+    hybrid.pcpg(p, again, 3)
+    for pl in (ref, plan, hybrid):
+        pl.destroy()
+
+
 @pytest.mark.parametrize("width", [16, 32, 48, 64])
 def test_diagonal_inverses_at_block_widths(width):
     """Diagonal blocks of every width up to 64 (chains of 2 .. 140 nodes: the
