@@ -55,8 +55,8 @@ typedef enum {
 typedef enum {
     SC_PREC_FP64 = 0,         /* every step in FP64; F stored FP64 */
     SC_PREC_MIXED = 1         /* FP64 diagonal-block solves; FP32 off-diagonal
-                                 updates, X and SYRK (FP32 MFMA, FP32 accumulate);
-                                 F stored FP32 */
+                                 updates, X and SYRK (FP32 products, formed from
+                                 bf16 ones, FP32 sums); F stored FP32 */
 } sc_precision_t;
 
 /*

@@ -821,7 +821,7 @@ __global__ __launch_bounds__(256, EDGE == 128 ? 2 : 4) void syrk_f64(
 
 // ---------------------------------------------------------------------------
 // Mixed precision (FP64 diagonal solves; FP32 X and off-diagonal updates with
-// FP32 MFMA; SYRK with FP32 sums of exact bf16 products).
+// FP32 MFMA; SYRK with FP32 products formed from bf16 ones, FP32 sums).
 // ---------------------------------------------------------------------------
 
 // FP64 factor values -> FP32 copy (round to nearest even).
@@ -835,18 +835,22 @@ __global__ __launch_bounds__(256) void convert_f64_f32(const double* __restrict_
 // blocks (EDGE = 64) or 128 x 128 tiles (EDGE = 128) of F, on the bf16 matrix
 // units.  An FP32 value is exactly the sum of three bf16 values (24 = 3 x 8
 // significant bits, each the rounded remainder of the last), so x y is a sum
-// of nine exact bf16 products; the six down to 2^-16 of x y are formed, the
-// others are below 2^-25 of it, half an FP32 rounding.  Sums stay FP32:
+// of nine exact bf16 products; all but the last, at most 2^-34 of x y, are
+// formed.  (The two before it, a middle value times a last one, are at most
+// 2^-25 each, together a whole FP32 rounding: without them an entry that is
+// one product was off by up to 0.95 ulp, now by 0.51, an FP32 product by 0.5;
+// sums of many terms do not show it.)  Sums stay FP32:
 // v_mfma_f32_32x32x16_bf16 adds the products of a whole 16-row step at once,
-// where the FP32 instruction takes four of its rows, and the five smaller
+// where the FP32 instruction takes four of its rows, and the seven smaller
 // products have their own accumulator, so that the main one is rounded once a
-// step.  The bf16 units do 16 times the FP32 rate: six products take 3/8 of
+// step.  The bf16 units do 16 times the FP32 rate: eight products take half
 // the time.  Mixed F against the FP64 F, FP32 units before / now (relative
 // Frobenius; largest element error over sqrt(F_ii F_jj)): 16 x 16 heat square
 // 8.2e-8 / 7.1e-8; 3.6e-7 / 2.6e-7, 12^3 heat 1.10e-7 / 1.08e-7; 1.0e-6 /
 // 5.6e-7, 20^3 elasticity 4.38e-7 / 4.28e-7; 5.5e-6 / 3.7e-6, 129^2 triangles
-// 1.72e-7 / 1.22e-7; 1.1e-6 / 5.2e-7 (one accumulator for all six: 8.4e-8,
-// 1.08e-7, 4.31e-7, 1.52e-7, and up to 1.3 times the old element error).
+// 1.72e-7 / 1.22e-7; 1.1e-6 / 5.2e-7 (one accumulator for the six largest
+// products: 8.4e-8, 1.08e-7, 4.31e-7, 1.52e-7, and up to 1.3 times the old
+// element error).
 // Per step a thread loads 8 rows of one column (a wavefront: 8 rows of 256
 // bytes), splits them and writes three 16-byte pieces, [plane][row half]
 // [column], the operand layout of the instruction (lane l: column l % 32, rows
@@ -855,9 +859,11 @@ __global__ __launch_bounds__(256) void convert_f64_f32(const double* __restrict_
 // two steps: no copies between them).  Wavefront (wi, wj) computes the
 // (EDGE / 2)^2 quadrant.  The two sides of a tile on the diagonal would be
 // summed in different orders: the lower one is written to both.
-// Between the matrix units (4.5 of its 9.9 ms), the split and the LDS:
-// 16 x 20^3 elasticity 15.0 ms on the FP32 units / 9.9 now, 512 x 12^3 heat
-// 1.22 / 0.84, 64 uneven elasticity boxes 2.45 / 1.54.
+// Bound by the bf16 matrix units at the clock that they leave (1.2 PFLOP/s, as
+// torch's bf16 product of 8192^2 matrices): FP32 units / six products / now,
+// 16 x 20^3 elasticity 15.0 / 10.1 / 12.0 ms, 512 x 12^3 heat 1.22 / 0.86 /
+// 0.96, 64 uneven elasticity boxes 2.45 / 1.52 / 1.76, 128 triangle meshes of
+// 129^2 nodes - / 0.132 / 0.145.
 // ---------------------------------------------------------------------------
 typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
@@ -976,14 +982,14 @@ __global__ __launch_bounds__(256, EDGE == 128 ? 2 : 4) void syrk_split_f32(
                 b[q][k] = __builtin_bit_cast(v8bf, pb[k * kPlane + 32 * q]);
             }
         // smallest products first
-        constexpr int kOrder[6][2] = {{2, 0}, {0, 2}, {1, 1}, {1, 0}, {0, 1}, {0, 0}};
+        constexpr int kOrder[8][2] = {{2, 1}, {1, 2}, {2, 0}, {0, 2}, {1, 1}, {1, 0}, {0, 1}, {0, 0}};
 #pragma unroll
-        for (int k = 0; k < 6; ++k)
+        for (int k = 0; k < 8; ++k)
 #pragma unroll
             for (int q = 0; q < NS; ++q)
 #pragma unroll
                 for (int p = 0; p < NS; ++p) {
-                    v16f& c = k == 5 ? acc[q][p] : low[q][p];
+                    v16f& c = k == 7 ? acc[q][p] : low[q][p];
                     c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[q][kOrder[k][0]], b[p][kOrder[k][1]], c, 0, 0, 0);
                 }
         store_step(v, buf ^ 1);

@@ -1,4 +1,6 @@
 """Kernels at the sizes where their tiling can go wrong, on the GPU."""
+from types import SimpleNamespace
+
 import numpy as np
 import pytest
 
@@ -151,6 +153,53 @@ def test_syrk_at_tile_edges(kind, precision):
         assert oracle.relF(F, oracle.schur(s)) <= (1e-12 if precision == "fp64" else 1e-5), i
     plan.destroy()
     other.destroy()
+
+
+def _pairs(count, seed, scale=1.0):
+    """`count` uncoupled pairs of nodes, a multiplier on every node, in the
+    order of elimination, and the X of the mixed assembly (rounded to FP32):
+    [x00, x10, x11] of every pair, X = (sign0 (x00, x10), sign1 (0, x11))."""
+    rng = np.random.default_rng(seed)
+    a, b, c = rng.uniform(1, 4, count), rng.uniform(-0.9, 0.9, count), rng.uniform(1, 4, count)
+    n = 2 * count
+    i = np.arange(n)
+    s = SimpleNamespace(n=n, rowptr=2 * np.arange(n + 1), col=np.stack([i - i % 2, i - i % 2 + 1], 1).ravel(),
+                        val=scale * np.stack([a, b, b, c], 1).ravel(), dof=i.astype(np.int32),
+                        sign=signs_from_seed(seed, n), dofs_per_node=1, perm=i.astype(np.int32))
+    order = np.empty(n, dtype=np.int64)
+    order[P.host_analyze(s, values=False)["perm"]] = i
+    first = np.where(order[0::2] < order[1::2], i[0::2], i[1::2])
+    second = first ^ 1
+    d = scale * np.where(first % 2 == 0, a, c), scale * b, scale * np.where(first % 2 == 0, c, a)
+    l00 = np.sqrt(d[0])
+    l10 = d[1] / l00
+    l11 = np.sqrt(d[2] - l10 * l10)
+    x = np.stack([1 / l00, -l10 / (l00 * l11), 1 / l11]).astype(np.float32)
+    return s, first, second, x
+
+
+@pytest.mark.parametrize("kind", [1, 2])
+def test_mixed_syrk_rounds_like_fp32_products(kind):
+    """Mixed F entries that are one product of two X entries: as accurate as
+    one FP32 product.  Half an ulp of the result from the last addition; the
+    small partial products are at most 2^-7 of it and rounded seven times in
+    FP32, each sum but the last two at most 2^-14 (2^-6 + 2^-9 ulp), and the
+    one left out is at most 2^-34 (2^-10 ulp): below 17/32 ulp.  The six
+    largest partial products alone leave up to 0.95 ulp (one entry in 50 above
+    17/32), two planes of bf16 hundreds."""
+    s, first, second, x = _pairs(400, 21)
+    plan = _plan([s], precision="mixed", syrk_kind=kind)
+    F = plan.get_F(0)
+    sg = s.sign.astype(np.float64)
+    F = sg[:, None] * F * sg[None, :]
+    x = x.astype(np.float64)
+    for got, want in ((F[second, second], x[2] * x[2]), (F[first, second], x[1] * x[2])):
+        ulp = np.spacing(np.abs(want).astype(np.float32)).astype(np.float64)
+        assert np.abs(got - want).max() > 0
+        assert (np.abs(got - want) / ulp).max() <= 17 / 32
+    want = x[0] * x[0] + x[1] * x[1]
+    assert (np.abs(F[first, first] - want) <= 2.0 ** -22 * want).all()
+    plan.destroy()
 
 
 @pytest.mark.parametrize("precision", ["fp64", "mixed"])
