@@ -105,6 +105,12 @@ struct SyrkItem {
 // 13.5 at 1.051, 13.7 / 12.5 at 1.036; mixed 0.134 / 0.258 at 2.25, 1.14 / 1.18
 // at 1.143, 1.46 / 1.44 at 1.112, 2.73 / 2.51 at 1.054.
 constexpr double kSyrkTileCost = 1.053, kSyrkTileCostMixed = 1.12;
+// The mixed SYRK splits 2^kSplitScale X into bf16 values: the last bit of the
+// smallest FP32 number is then that of the smallest bf16 number, and no value
+// of X loses bits.  X values from 2^kSplitMaxExp on, where a partial sum could
+// overflow although the sum does not (2^27 rows of 2^100), and infinities, which
+// do not split, take the FP32 units: the TRSM flags the tiles that hold some.
+constexpr int kSplitScale = 16, kSplitMaxExp = 50 - kSplitScale;
 constexpr int kStepSlabShift = 27;
 constexpr int kStepRowMask = (1 << kStepSlabShift) - 1;   // rows below 2^27 (checked at plan creation)
 

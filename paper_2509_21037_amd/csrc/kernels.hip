@@ -303,7 +303,8 @@ __device__ __forceinline__ void trsm_tile(
     const VisitDev* __restrict__ visits, const uint64_t* __restrict__ fresh, const int32_t* __restrict__ clear,
     const double* __restrict__ lval,
     const float* __restrict__ lval32, const int32_t* __restrict__ piv, const int8_t* __restrict__ sgn,
-    typename std::conditional<MIXED, float, double>::type* __restrict__ X, int ti, char* __restrict__ smem)
+    typename std::conditional<MIXED, float, double>::type* __restrict__ X, int32_t* __restrict__ xwide, int ti,
+    char* __restrict__ smem)
 {
     using TX = typename std::conditional<MIXED, float, double>::type;
     using VX = typename std::conditional<MIXED, v4f, v4d>::type;
@@ -403,6 +404,7 @@ __device__ __forceinline__ void trsm_tile(
                 xin[t][r] = xr_.load(((onl >> (16 * t + 4 * r)) & 1) ? b0 + Rows::at(16 * t + 4 * r, 0) : Rows::kNone);
     };
 
+    bool wide = false;                           // some value is beyond the bf16 split (mixed)
     VisitDev v = V[0];
     load_block(v, v.held, (v.flags >> (kVisitActShift + wv)) & 1);
     int pair_nks = 0;
@@ -485,6 +487,7 @@ __device__ __forceinline__ void trsm_tile(
             }
             const uint64_t onl = (act ? v.on : v.on & ~v.held) >> g;
             const auto b0 = Rows::at(v.row0 + g - kstart, col);
+            float most = 0.f;                    // largest |x|
 #pragma unroll
             for (int t = 0; t < 4; ++t)
 #pragma unroll
@@ -492,7 +495,9 @@ __device__ __forceinline__ void trsm_tile(
                     const TX x = (TX)tmp[t][r];
                     xr_.store(((onl >> (16 * t + 4 * r)) & 1) ? b0 + Rows::at(16 * t + 4 * r, 0) : Rows::kNone, x);
                     xb[t][r] = -x;
+                    if constexpr (MIXED) most = fmaxf(most, fabsf(x));
                 }
+            if constexpr (MIXED) wide |= __builtin_amdgcn_ballot_w64(most >= (float)(1ull << kSplitMaxExp)) != 0;
         }
         // the first block of a pair keeps its solved rows for the second
         // (zero for a wavefront that starts at the second)
@@ -610,6 +615,8 @@ __device__ __forceinline__ void trsm_tile(
         }
         v = nx;
     }
+    if constexpr (MIXED)
+        if (lane == 0) xwide[4 * (int64_t)ti + wv] = wide;
 }
 
 // MERGE: with the merged pairs (the visits' roles); without, every visit is
@@ -626,7 +633,7 @@ __global__ __launch_bounds__(LOADER ? 320 : 256, LOADER ? 1 : MERGE || LARGE ? 2
     __shared__ __align__(16) char smem[kTrsmSmem + (MERGE ? kSlotBytes<double> : 0)];
     const int ti = order[blockIdx.x];
     if (ti < 0) return;
-    trsm_tile<false, MERGE, LARGE, LOADER>(subs, tiles, rows, visits, fresh, clear, lval, nullptr, piv, sgn, X, ti, smem);
+    trsm_tile<false, MERGE, LARGE, LOADER>(subs, tiles, rows, visits, fresh, clear, lval, nullptr, piv, sgn, X, nullptr, ti, smem);
 }
 
 template <bool MERGE, bool LARGE, bool LOADER>
@@ -635,12 +642,12 @@ __global__ __launch_bounds__(LOADER ? 320 : 256, LOADER ? 1 : MERGE || LARGE ? 2
     const VisitDev* __restrict__ visits, const uint64_t* __restrict__ fresh, const int32_t* __restrict__ clear,
     const double* __restrict__ lval,
     const float* __restrict__ lval32, const int32_t* __restrict__ piv, const int8_t* __restrict__ sgn,
-    const int32_t* __restrict__ order, float* __restrict__ X)
+    const int32_t* __restrict__ order, float* __restrict__ X, int32_t* __restrict__ xwide)
 {
     __shared__ __align__(16) char smem[kTrsmSmem + (MERGE ? kSlotBytes<float> : 0)];
     const int ti = order[blockIdx.x];
     if (ti < 0) return;
-    trsm_tile<true, MERGE, LARGE, LOADER>(subs, tiles, rows, visits, fresh, clear, lval, lval32, piv, sgn, X, ti, smem);
+    trsm_tile<true, MERGE, LARGE, LOADER>(subs, tiles, rows, visits, fresh, clear, lval, lval32, piv, sgn, X, xwide, ti, smem);
 }
 
 // ---------------------------------------------------------------------------
@@ -851,6 +858,9 @@ __global__ __launch_bounds__(256) void convert_f64_f32(const double* __restrict_
 // 1.72e-7 / 1.22e-7; 1.1e-6 / 5.2e-7 (one accumulator for the six largest
 // products: 8.4e-8, 1.08e-7, 4.31e-7, 1.52e-7, and up to 1.3 times the old
 // element error).
+// Range: planes of 2^16 x hold every FP32 value exactly, F is scaled back at
+// the end; items whose tiles hold values from 2^34 on (K of about 2^-68) run on
+// the FP32 units, operands straight from memory (36 ms for 16 x 20^3 elasticity).
 // Per step a thread loads 8 rows of one column (a wavefront: 8 rows of 256
 // bytes), splits them and writes three 16-byte pieces, [plane][row half]
 // [column], the operand layout of the instruction (lane l: column l % 32, rows
@@ -861,20 +871,20 @@ __global__ __launch_bounds__(256) void convert_f64_f32(const double* __restrict_
 // summed in different orders: the lower one is written to both.
 // Bound by the bf16 matrix units at the clock that they leave (1.2 PFLOP/s, as
 // torch's bf16 product of 8192^2 matrices): FP32 units / six products / now,
-// 16 x 20^3 elasticity 15.0 / 10.1 / 12.0 ms, 512 x 12^3 heat 1.22 / 0.86 /
-// 0.96, 64 uneven elasticity boxes 2.45 / 1.52 / 1.76, 128 triangle meshes of
-// 129^2 nodes - / 0.132 / 0.145.
+// 16 x 20^3 elasticity 15.0 / 10.1 / 12.4 ms, 512 x 12^3 heat 1.22 / 0.86 /
+// 0.99, 64 uneven elasticity boxes 2.45 / 1.52 / 1.81, 128 triangle meshes of
+// 129^2 nodes 0.258 / 0.132 / 0.147.
 // ---------------------------------------------------------------------------
 typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 typedef float v2f __attribute__((ext_vector_type(2)));
 typedef float v16f __attribute__((ext_vector_type(16)));
 
-// x[0..8) as three bf16 planes, h + m + l = x
+// 2^kSplitScale x[0..8) as three bf16 planes, h + m + l
 __device__ __forceinline__ void split_bf16(const float (&x)[8], v4u& h, v4u& m, v4u& l) {
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        v2f r = {x[2 * i], x[2 * i + 1]};
+        v2f r = {x[2 * i] * (float)(1 << kSplitScale), x[2 * i + 1] * (float)(1 << kSplitScale)};
         h[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector(r, v2bf));
         r[0] -= __builtin_bit_cast(float, h[i] << 16);
         r[1] -= __builtin_bit_cast(float, h[i] & 0xFFFF0000u);
@@ -889,7 +899,7 @@ template <int EDGE>
 __global__ __launch_bounds__(256, EDGE == 128 ? 2 : 4) void syrk_split_f32(
     const SubDev* __restrict__ subs, const TileDev* __restrict__ tiles,
     const SyrkItem* __restrict__ items, const int32_t* __restrict__ ksteps, const float* __restrict__ X,
-    float* __restrict__ F)
+    const int32_t* __restrict__ xwide, float* __restrict__ F)
 {
     constexpr int NS = EDGE / 64;                // 64-column slabs per side, sub-tiles per wavefront and side
     constexpr int kPlane = EDGE * 2;             // 16-byte pieces of one plane of one side
@@ -996,24 +1006,72 @@ __global__ __launch_bounds__(256, EDGE == 128 ? 2 : 4) void syrk_split_f32(
         load_step(v, ent, st + 3 < nsteps);
         lds_barrier();
     };
-    float v0[NS][8], v1[NS][8];                  // two steps in flight
-    load_step(v0, entry(0), nsteps > 0);
-    load_step(v1, entry(1), nsteps > 1);
-    store_step(v0, 0);
-    load_step(v0, entry(2), nsteps > 2);
-    lds_barrier();
-    int st = 0;
-    for (; st + 1 < nsteps; st += 2) {
-        step(v1, st, 0);
-        step(v0, st + 1, 1);
+    bool wide = false;                           // values beyond the split, on either side
+#pragma unroll
+    for (int q = 0; q < 2 * NS; ++q) {
+        const int t64 = (q < NS ? it.I : it.J) * NS + q % NS;
+        if (t64 < S.ntiles) {
+            const int4 w = reinterpret_cast<const int4*>(xwide)[S.tile_off + t64];
+            wide |= (w.x | w.y | w.z | w.w) != 0;
+        }
     }
-    if (st < nsteps) step(v1, st, 0);
+    const double scale = wide ? 1.0 : 1.0 / (double)(1ull << 2 * kSplitScale);
+    if (!wide) {
+        float v0[NS][8], v1[NS][8];              // two steps in flight
+        load_step(v0, entry(0), nsteps > 0);
+        load_step(v1, entry(1), nsteps > 1);
+        store_step(v0, 0);
+        load_step(v0, entry(2), nsteps > 2);
+        lds_barrier();
+        int st = 0;
+        for (; st + 1 < nsteps; st += 2) {
+            step(v1, st, 0);
+            step(v0, st + 1, 1);
+        }
+        if (st < nsteps) step(v1, st, 0);
+    } else {
+        // the FP32 units, operands straight from memory: two rows at a time,
+        // lane l row l / 32, column l % 32 of this wavefront's slab
+        const float* xo[2];
+        int k0[2], on[2];
+#pragma unroll
+        for (int side = 0; side < 2; ++side) {
+            const int w = side ? wj : wi;
+            const int t64 = (side ? it.J : it.I) * NS + (EDGE == 128 ? w : 0);
+            const TileDev& T = tiles[S.tile_off + (t64 < S.ntiles ? t64 : 0)];
+            k0[side] = t64 < S.ntiles ? T.kstart : INT_MAX;
+            xo[side] = X + T.x_off + (EDGE == 128 ? 0 : 32 * w) + (lane & 31);
+            on[side] = EDGE == 128 ? 1 << (kStepSlabShift + 2 * side + w) : 0;
+        }
+        for (int st = 0; st < nsteps; ++st) {
+            const int ent = KS[st];
+            const int kb = EDGE == 128 ? ent & kStepRowMask : ent;
+#pragma unroll
+            for (int s = 0; s < kSyrkKC / 2; ++s) {
+                const int row = kb + 2 * s + (lane >> 5);
+                float x[2][NS];
+#pragma unroll
+                for (int side = 0; side < 2; ++side) {
+                    const bool have = row >= k0[side] && row < n && (EDGE == 64 || (ent & on[side]));
+#pragma unroll
+                    for (int q = 0; q < NS; ++q)
+                        x[side][q] = have ? xo[side][(int64_t)(row - k0[side]) * kTile + 32 * q] : 0.f;
+                }
+#pragma unroll
+                for (int q = 0; q < NS; ++q)
+#pragma unroll
+                    for (int p = 0; p < NS; ++p)
+                        acc[q][p] = __builtin_amdgcn_mfma_f32_32x32x2f32(x[0][q], x[1][p], acc[q][p], 0, 0, 0);
+            }
+        }
+    }
 #pragma unroll
     for (int a = 0; a < NS; ++a)
 #pragma unroll
         for (int b = 0; b < NS; ++b)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[a][b][r] += low[a][b][r];
+            for (int r = 0; r < 16; ++r)         // rounded once, subnormal results too
+                acc[a][b][r] = (float)(((double)acc[a][b][r] + (double)low[a][b][r]) * scale);
     // D: lane l, register r holds row 8 (r / 4) + 4 (l / 32) + r % 4, column l % 32
     const int I2 = EDGE == 128 ? it.I : it.I >> 1, J2 = EDGE == 128 ? it.J : it.J >> 1;
     float* __restrict__ Ft = F + S.F_off + (int64_t)(I2 * (I2 + 1) / 2 + J2) * kFTileElems;
@@ -1124,7 +1182,7 @@ static void trsm_launch(const DevTables& t, const int32_t* order, int64_t count,
     const dim3 grid((unsigned)count), block(LOADER ? 320 : 256);
     if (t.X32)
         hipLaunchKernelGGL((trsm_stair_mixed<MERGE, LARGE, LOADER>), grid, block, 0, stream, t.subs, t.tiles, t.rows,
-                           t.visits, t.fresh, t.clear, t.lval, t.lval32, t.piv, t.sgn, order, t.X32);
+                           t.visits, t.fresh, t.clear, t.lval, t.lval32, t.piv, t.sgn, order, t.X32, t.xwide);
     else
         hipLaunchKernelGGL((trsm_stair_f64<MERGE, LARGE, LOADER>), grid, block, 0, stream, t.subs, t.tiles, t.rows,
                            t.visits, t.fresh, t.clear, t.lval, t.piv, t.sgn, order, t.X);
@@ -1160,7 +1218,7 @@ hipError_t launch_syrk(const DevTables& t, const SyrkItem* items, int64_t ntile,
     if (ntile > 0) {
         if (t.X32)
             hipLaunchKernelGGL(syrk_split_f32<128>, dim3((unsigned)ntile), dim3(256), 0, stream, t.subs, t.tiles, items,
-                               t.ksteps, t.X32, t.F32);
+                               t.ksteps, t.X32, t.xwide, t.F32);
         else
             hipLaunchKernelGGL(syrk_f64<128>, dim3((unsigned)ntile), dim3(256), 0, stream, t.subs, t.tiles, items,
                                t.ksteps, t.X, t.F);
@@ -1170,7 +1228,7 @@ hipError_t launch_syrk(const DevTables& t, const SyrkItem* items, int64_t ntile,
     if (nblock > 0) {
         if (t.X32)
             hipLaunchKernelGGL(syrk_split_f32<64>, dim3((unsigned)nblock), dim3(256), 0, stream, t.subs, t.tiles,
-                               items + ntile, t.ksteps, t.X32, t.F32);
+                               items + ntile, t.ksteps, t.X32, t.xwide, t.F32);
         else
             if (nblock <= kSyrkQuarterItems)
                 hipLaunchKernelGGL((syrk_f64<64, true>), dim3((unsigned)(4 * nblock)), dim3(256), 0, stream, t.subs,

@@ -35,6 +35,8 @@ struct DevTables {
     const SyrkItem* ftiles = nullptr;      // stored F tiles (subdomain order): symmetric apply pass 1
     const int2* frows = nullptr;           // (subdomain, 128-row block): symmetric apply pass 2
     double* part = nullptr;                // 256 partial sums per stored F tile
+    int32_t* xwide = nullptr;              // mixed: per X tile and wavefront, != 0 where some value is
+                                           // beyond the bf16 split (kSplitMaxExp)
     int64_t ntiles = 0;          // TRSM workgroups (length of tile_order)
     bool trsm_merge = false;     // TRSM with the merged pairs (VisitDev::flags)
     bool trsm_large = false;     // some X slab holds kTrsmSlabBytes or more

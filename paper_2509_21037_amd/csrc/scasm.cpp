@@ -402,6 +402,7 @@ struct sc_plan_s {
     DevBuf<int8_t> d_sgn;
     DevBuf<double> d_lval, d_X, d_F;
     DevBuf<float> d_lval32, d_X32, d_F32;
+    DevBuf<int32_t> d_xwide;                    // mixed: per X tile and wavefront, values beyond the bf16 split
     DevBuf<double> d_xwork, d_ywork;          // implicit apply: n_i doubles per subdomain each
     DevBuf<int64_t> d_xoff;
     // implicit apply level schedule (built with the workspace, on first use)
@@ -542,7 +543,7 @@ struct sc_plan_s {
                          (d_rows.count + d_piv.count + d_pi.count + d_ksteps.count + d_clear.count) * 4 + d_visits.count * sizeof(VisitDev) +
                          d_fresh.count * 8 + d_sgn.count +
                          (d_lval.count + d_X.count + d_F.count) * 8 +
-                         (d_lval32.count + d_X32.count + d_F32.count) * 4 +
+                         (d_lval32.count + d_X32.count + d_F32.count + d_xwide.count) * 4 +
                          (d_xwork.count + d_ywork.count + d_xoff.count) * 8 + (d_ifw.count + d_ibw.count) * sizeof(ImplBlock) +
                          (d_rptr.count + d_rpos.count) * 4 + (d_rptr_off.count + d_ubuf.count) * 8 +
                          (d_ifw_h.count + d_ibw_h.count) * sizeof(ImplBlock) + d_impl_list.count * 4 +
@@ -555,7 +556,7 @@ struct sc_plan_s {
         d_tile_order.release(); d_tile_order_g.release(); d_syrk_g.release();
         d_rows.release(); d_piv.release(); d_pi.release(); d_ksteps.release(); d_clear.release(); d_visits.release(); d_fresh.release(); d_sgn.release();
         d_lval.release(); d_X.release(); d_F.release();
-        d_lval32.release(); d_X32.release(); d_F32.release();
+        d_lval32.release(); d_X32.release(); d_F32.release(); d_xwide.release();
         d_xwork.release(); d_ywork.release(); d_xoff.release();
         d_ifw.release(); d_ibw.release(); d_rptr_off.release(); d_rptr.release(); d_rpos.release(); d_ubuf.release();
         d_ifw_h.release(); d_ibw_h.release(); d_impl_list.release();
@@ -583,7 +584,7 @@ struct sc_plan_s {
         t.ksteps = d_ksteps.p;
         t.lval = d_lval.p; t.piv = d_piv.p; t.pi = d_pi.p; t.sgn = d_sgn.p; t.syrk = d_syrk.p;
         t.X = d_X.p; t.F = d_F.p;
-        t.lval32 = d_lval32.p; t.X32 = d_X32.p; t.F32 = d_F32.p;
+        t.lval32 = d_lval32.p; t.X32 = d_X32.p; t.F32 = d_F32.p; t.xwide = d_xwide.p;
         t.ftiles = d_ftiles.p;
         t.frows = d_frows.p;
         t.part = d_part.p;
@@ -1119,6 +1120,7 @@ sc_status_t sc_plan_create(const sc_subdomain_desc_t* sd, int32_t nsub, const sc
         ALLOC(p->d_lval32, (size_t)lv);
         ALLOC(p->d_X32, (size_t)xo);
         ALLOC(p->d_F32, (size_t)fo);
+        ALLOC(p->d_xwide, 4 * p->h_tiles.size());
     } else {
         ALLOC(p->d_X, (size_t)xo);
         ALLOC(p->d_F, (size_t)fo);
@@ -1166,6 +1168,7 @@ sc_status_t sc_plan_create(const sc_subdomain_desc_t* sd, int32_t nsub, const sc
     if (e == hipSuccess && fo > 0)
         e = p->mixed ? hipMemsetAsync(p->d_F32.p, 0, (size_t)fo * sizeof(float), st)
                      : hipMemsetAsync(p->d_F.p, 0, (size_t)fo * sizeof(double), st);
+    if (e == hipSuccess && p->d_xwide.count > 0) e = hipMemsetAsync(p->d_xwide.p, 0, p->d_xwide.count * 4, st);
     if (e == hipSuccess) e = up(p->d_piv.p, h_piv.data(), h_piv.size() * 4);
     if (e == hipSuccess) e = up(p->d_pi.p, h_pi.data(), h_pi.size() * 4);
     if (e == hipSuccess) e = up(p->d_sgn.p, h_sgn.data(), h_sgn.size());

@@ -155,26 +155,27 @@ def test_syrk_at_tile_edges(kind, precision):
     other.destroy()
 
 
-def _pairs(count, seed, scale=1.0):
-    """`count` uncoupled pairs of nodes, a multiplier on every node, in the
-    order of elimination, and the X of the mixed assembly (rounded to FP32):
-    [x00, x10, x11] of every pair, X = (sign0 (x00, x10), sign1 (0, x11))."""
+def _pairs(count, seed, scales=(0, 0, 0)):
+    """`count` uncoupled pairs of nodes with the matrices [[a, b], [b, c]] (a, b
+    and c of the sizes 2^scales), a multiplier on every node, in the order of
+    elimination, and the X of the mixed assembly (rounded to FP32): [x00, x10,
+    x11] of every pair, X = (sign0 (x00, x10), sign1 (0, x11))."""
     rng = np.random.default_rng(seed)
-    a, b, c = rng.uniform(1, 4, count), rng.uniform(-0.9, 0.9, count), rng.uniform(1, 4, count)
+    a, b, c = (np.ldexp(rng.uniform(lo, hi, count), k) for (lo, hi), k in zip([(1, 4), (-0.9, 0.9), (1, 4)], scales))
     n = 2 * count
     i = np.arange(n)
     s = SimpleNamespace(n=n, rowptr=2 * np.arange(n + 1), col=np.stack([i - i % 2, i - i % 2 + 1], 1).ravel(),
-                        val=scale * np.stack([a, b, b, c], 1).ravel(), dof=i.astype(np.int32),
+                        val=np.stack([a, b, b, c], 1).ravel(), dof=i.astype(np.int32),
                         sign=signs_from_seed(seed, n), dofs_per_node=1, perm=i.astype(np.int32))
     order = np.empty(n, dtype=np.int64)
     order[P.host_analyze(s, values=False)["perm"]] = i
     first = np.where(order[0::2] < order[1::2], i[0::2], i[1::2])
     second = first ^ 1
-    d = scale * np.where(first % 2 == 0, a, c), scale * b, scale * np.where(first % 2 == 0, c, a)
-    l00 = np.sqrt(d[0])
-    l10 = d[1] / l00
-    l11 = np.sqrt(d[2] - l10 * l10)
-    x = np.stack([1 / l00, -l10 / (l00 * l11), 1 / l11]).astype(np.float32)
+    l00 = np.sqrt(np.where(first % 2 == 0, a, c))
+    l10 = b / l00
+    l11 = np.sqrt(np.where(first % 2 == 0, c, a) - l10 * l10)
+    with np.errstate(over="ignore"):
+        x = np.stack([1 / l00, -l10 / l00 / l11, 1 / l11]).astype(np.float32)
     return s, first, second, x
 
 
@@ -200,6 +201,42 @@ def test_mixed_syrk_rounds_like_fp32_products(kind):
     want = x[0] * x[0] + x[1] * x[1]
     assert (np.abs(F[first, first] - want) <= 2.0 ** -22 * want).all()
     plan.destroy()
+
+
+@pytest.mark.parametrize("kind", [1, 2])
+@pytest.mark.parametrize("scales", [(-61, 87, 236), (-91, 72, 236), (126, 126, 126), (140, 140, 140), (-66, -66, -66),
+                                    (-70, -70, -70), (-124, -124, -124), (-160, -160, -160), (-254, -254, -254),
+                                    (-300, -300, -300)])
+def test_mixed_syrk_over_the_fp32_range(scales, kind):
+    """X values at the ends of the FP32 range, in one subdomain of a batch: of
+    10^9 or 10^13 and 10^-35 in one product, F at the smallest normal number and
+    below, X on either side of 2^34 (where the FP32 units take over), F near
+    the top, F infinite (with its sign), X infinite: as accurate as one FP32
+    product (the bound of the test above, ulps of a subnormal result included).
+    The other subdomain's F is what it is alone."""
+    s, first, second, x = _pairs(150, 22, scales)
+    other = _pairs(150, 23)[0]
+    plan, alone = (_plan(b, precision="mixed", syrk_kind=kind) for b in ([s, other], [other]))
+    sg = s.sign.astype(np.float64)
+    F = sg[:, None] * plan.get_F(0) * sg[None, :]
+    x = x.astype(np.float64)
+    pairs = [(F[second, second], x[2] * x[2])]
+    if np.isfinite(x).all():                     # (an infinity times the zeros of other columns is NaN)
+        pairs.append((F[first, second], x[1] * x[2]))
+        G = F.copy()                             # uncoupled pairs
+        for p, q in ((first, first), (second, second), (first, second), (second, first)):
+            G[p, q] = 0
+        assert np.abs(G).max() == 0
+    for got, want in pairs:
+        with np.errstate(over="ignore", invalid="ignore"):
+            w32 = want.astype(np.float32)
+            ulp = np.spacing(np.abs(w32)).astype(np.float64)
+        big = np.isinf(w32)
+        assert np.array_equal(got[big], w32[big].astype(np.float64))
+        assert (np.abs(got[~big] - want[~big]) <= 17 / 32 * ulp[~big]).all()
+    assert np.array_equal(plan.get_F(1), alone.get_F(0))
+    plan.destroy()
+    alone.destroy()
 
 
 @pytest.mark.parametrize("precision", ["fp64", "mixed"])
