@@ -333,8 +333,9 @@ sc_status_t sc_pcpg(sc_plan_t plan, const double* const* R_host, const int32_t* 
 
 /* Copy F_i (m_i x m_i, column-major, leading dimension ld >= m_i, original
  * multiplier order: the stored tiles expanded and permuted back, by a kernel
- * into device memory, on the host into host memory) to `out` (host memory when
- * on_device == 0, else device memory), converted to FP64.  Synchronises `stream`. */
+ * into memory of the plan's device, else on the host) to `out` (host memory
+ * when on_device == 0, else device memory, of any GPU), converted to FP64.
+ * Synchronises `stream`. */
 sc_status_t sc_get_F(sc_plan_t plan, int32_t sub, double* out, int32_t ld, int32_t on_device,
                      void* stream);
 

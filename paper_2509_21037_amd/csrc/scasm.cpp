@@ -1841,6 +1841,18 @@ sc_status_t sc_set_wait_limit(sc_plan_t P, int32_t looks) {
     return SC_OK;
 }
 
+// Whether a kernel on `device` may store doubles at p: the device's own memory.
+// Copies also reach other GPUs (without peer access), host memory that HIP
+// knows and pointers at any byte.
+static bool kernel_can_write(const void* p, int device) {
+    hipPointerAttribute_t a{};
+    if (hipPointerGetAttributes(&a, p) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return a.type == hipMemoryTypeDevice && a.device == device && (uintptr_t)p % sizeof(double) == 0;
+}
+
 sc_status_t sc_get_F(sc_plan_t P, int32_t sub, double* out, int32_t ld, int32_t on_device, void* stream) {
     g_last_error.clear();
     if (!P) return fail(SC_ERR_INVALID_ARG, "plan is NULL");
@@ -1855,7 +1867,7 @@ sc_status_t sc_get_F(sc_plan_t P, int32_t sub, double* out, int32_t ld, int32_t 
     HIP_TRY(hipSetDevice(P->device));
     hipStream_t st = (hipStream_t)stream;
     // packed lower tiles in sorted column order -> dense, original order
-    if (on_device) {
+    if (on_device && kernel_can_write(out, P->device)) {
         HIP_TRY(launch_expand_F(P->tables(), sub, s.m, out, ld, st));
         HIP_TRY(hipStreamSynchronize(st));
         return SC_OK;
@@ -1883,7 +1895,13 @@ sc_status_t sc_get_F(sc_plan_t P, int32_t sub, double* out, int32_t ld, int32_t 
             dense[(size_t)pi[b] * m + pi[a]] =
                 tiles[(size_t)(I * (I + 1) / 2 + J) * kFTileElems + (hi % kSyrkTile) * kSyrkTile + lo % kSyrkTile];
         }
-    for (int64_t c = 0; c < m; ++c) std::copy(dense.begin() + c * m, dense.begin() + (c + 1) * m, out + c * ld);
+    if (on_device) {
+        HIP_TRY(hipMemcpy2DAsync(out, (size_t)ld * sizeof(double), dense.data(), (size_t)m * sizeof(double),
+                                 (size_t)m * sizeof(double), (size_t)m, hipMemcpyHostToDevice, st));
+        HIP_TRY(hipStreamSynchronize(st));
+    } else {
+        for (int64_t c = 0; c < m; ++c) std::copy(dense.begin() + c * m, dense.begin() + (c + 1) * m, out + c * ld);
+    }
     return SC_OK;
 }
 

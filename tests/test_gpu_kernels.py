@@ -47,6 +47,30 @@ def test_dense_F_on_device_at_tile_edges(precision):
 
 
 @pytest.mark.parametrize("precision", ["fp64", "mixed"])
+def test_dense_F_where_no_kernel_writes(precision):
+    """sc_get_F "on the device" into memory that takes a copy and no kernel of
+    this GPU: pinned host memory, and device memory off the 8-byte grid."""
+    import ctypes
+
+    import torch
+    box = scgen.box_subdomain("heat", (20, 14), 1.0 / 20, seed=3)
+    subs = [_columns(box, m, 40 + m) for m in (1, 130)]
+    plan = _plan(subs, precision=precision)
+    for i, s in enumerate(subs):
+        ld = s.m + 3
+        for kind in ("pinned", "off"):
+            raw = torch.zeros(8 * (ld * s.m + 1), dtype=torch.uint8, **(dict(pin_memory=True) if kind == "pinned"
+                                                                       else dict(device="cuda")))
+            at = 0 if kind == "pinned" else 4
+            torch.cuda.synchronize()
+            st = P.load().sc_get_F(plan._h, i, ctypes.c_void_p(raw.data_ptr() + at), ld, 1, ctypes.c_void_p(0))
+            assert st == P.SC_OK
+            F = raw.cpu().numpy()[at:at + 8 * ld * s.m].copy().view(np.float64).reshape(s.m, ld)
+            assert np.array_equal(F[:, :s.m].T, plan.get_F(i)) and not F[:, s.m:].any(), (s.m, kind)
+    plan.destroy()
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
 @pytest.mark.parametrize("shape", ["one block", "two blocks", "pairs", "no pairs"])
 def test_trsm_small_launch_matches_large(precision, shape):
     """One subdomain alone (at most one TRSM workgroup per CU: the chunks come
