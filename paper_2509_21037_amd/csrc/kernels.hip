@@ -108,6 +108,7 @@ __device__ __forceinline__ void lds_barrier() {
 
 typedef uint32_t v2u __attribute__((ext_vector_type(2)));
 typedef uint32_t v4u __attribute__((ext_vector_type(4)));
+typedef v4u v4u_at4 __attribute__((aligned(4)));     // in memory, on any 4-byte boundary
 
 // Raw buffer resource over `bytes` bytes at p (wave-uniform): loads past them
 // return zero, stores past them are dropped.
@@ -267,7 +268,7 @@ __device__ __forceinline__ void trsm_load_wave(ChunkStream<TX, MERGE> stream, in
         const __amdgpu_buffer_rsrc_t rc = buffer_of(src, bytes);
 #pragma unroll
         for (int e = 0; e < kPieces; ++e) x.c[e] = __builtin_amdgcn_raw_buffer_load_b128(rc, lane * 16, e * 1024, 0);
-        x.ci = *reinterpret_cast<const v4u*>(lane < kRowsBytes / 16 ? reinterpret_cast<const char*>(ip) + 16 * lane
+        x.ci = *reinterpret_cast<const v4u_at4*>(lane < kRowsBytes / 16 ? reinterpret_cast<const char*>(ip) + 16 * lane
                                                                     : reinterpret_cast<const char*>(fp));
     };
     auto put = [&](const Set& x, int buf) __attribute__((always_inline)) {
@@ -366,7 +367,7 @@ __device__ __forceinline__ void trsm_tile(
         c2 = __builtin_amdgcn_raw_buffer_load_b128(rc, e, 8192, 0);
         c3 = __builtin_amdgcn_raw_buffer_load_b128(rc, e, 12288, 0);
         c4 = __builtin_amdgcn_raw_buffer_load_b128(rc, e, 16384, 0);
-        ci = *reinterpret_cast<const v4u*>(lane < kRowsBytes / 16 ? reinterpret_cast<const char*>(ip) + 16 * lane
+        ci = *reinterpret_cast<const v4u_at4*>(lane < kRowsBytes / 16 ? reinterpret_cast<const char*>(ip) + 16 * lane
                                                                    : reinterpret_cast<const char*>(fp));
     };
     auto put_chunk = [&](char* dst) {
