@@ -136,11 +136,14 @@ std::string to_plan_options(const sc_options_t& o, PlanOptions& po) {
 // Per-subdomain explicit / implicit selection (select_iters): default rates
 // measured on MI355X -- structural assembly TFLOP/s (FP64, mixed), explicit
 // apply GB/s over the stored F, implicit apply GB/s over the two sweeps' 16
-// bytes per factor entry.
-constexpr double kSelectAsmTflops64 = 45.6;
-constexpr double kSelectAsmTflopsMixed = 75.7;
+// bytes per factor entry.  64 x 20^3 elasticity on two cards: 173.7 and 181.1
+// ms (FP64), 85 and 89 (mixed), 2.87 ms, 4.03 and 3.94 ms.  Explicit or
+// implicit is then even at 148 and 167 applications (FP64), predicted 164;
+// before the kernels reached these rates it was 108.
+constexpr double kSelectAsmTflops64 = 53.5;
+constexpr double kSelectAsmTflopsMixed = 108.0;
 constexpr double kSelectExplGBps = 5800.0;
-constexpr double kSelectImplGBps = 3190.0;
+constexpr double kSelectImplGBps = 3870.0;
 
 // Share of a batch's TRSM pruned-row updates the merged pairs must save for
 // the merge-capable TRSM kernel to be launched.  That kernel holds a slot of
