@@ -648,14 +648,29 @@ extern "C" {
 
 const char* sc_last_error(void) { return g_last_error.c_str(); }
 
+static sc_status_t create_plan(const sc_subdomain_desc_t* sd, int32_t nsub, const sc_options_t* opt, void* stream,
+                               sc_plan_t* out);
+
 sc_status_t sc_plan_create(const sc_subdomain_desc_t* sd, int32_t nsub, const sc_options_t* opt,
                            void* stream, sc_plan_t* out) {
     g_last_error.clear();
+    try {
+        return create_plan(sd, nsub, opt, stream, out);
+    } catch (const std::bad_alloc&) {
+        return fail(SC_ERR_OOM, "host allocation failed");
+    }
+}
+
+static sc_status_t create_plan(const sc_subdomain_desc_t* sd, int32_t nsub, const sc_options_t* opt, void* stream,
+                               sc_plan_t* out) {
     if (!out) return fail(SC_ERR_INVALID_ARG, "out is NULL");
     *out = nullptr;
     if (nsub < 0 || (nsub > 0 && !sd)) return fail(SC_ERR_INVALID_ARG, "bad subdomain array");
-    std::unique_ptr<sc_plan_s> P(new (std::nothrow) sc_plan_s());
-    if (!P) return fail(SC_ERR_OOM, "host allocation failed");
+    auto drop = [](sc_plan_s* p) {
+        p->release();
+        delete p;
+    };
+    std::unique_ptr<sc_plan_s, decltype(drop)> P(new sc_plan_s(), drop);
     if (opt) P->opt = *opt;
     PlanOptions& po = P->popt;
     {
