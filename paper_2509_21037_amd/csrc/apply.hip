@@ -470,8 +470,9 @@ hipError_t launch_pcpg(const DevTables& t, const PcpgArgs& a, hipStream_t stream
 // then y = L^{-1} x, then z = L^{-T} y, in place.  The blocked triangular
 // solves run level by level (planner: a block's forward level is one more
 // than that of every block whose pruned rows reach it; its backward level one
-// more than that of every block its own pruned rows lie in), one launch per
-// level, one wavefront per block of all subdomains at that level:
+// more than that of every block its own pruned rows lie in), one workgroup of
+// kImplThreads threads per block step, wide levels a launch each, the levels next
+// to the roots a chain in one launch (implicit_fwd_chain):
 //   forward, block b:   y_b = L_bb^{-1} (x_b - sum of the update entries of
 //                       its rows), then u_b = L[R_b, b] y_b into the update
 //                       buffer (parallel to the pruned-row lists); a row's
@@ -481,10 +482,6 @@ hipError_t launch_pcpg(const DevTables& t, const PcpgArgs& a, hipStream_t stream
 // The diagonal inverses are the ones the TRSM uses.  Repeated DOFs (several
 // multipliers on one DOF) are summed by one thread per run of equal pivots.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ double tile_at(const double* __restrict__ At, int nks, int q, int k) {
-    return At[((int64_t)(q >> 4) * nks + (k >> 2)) * 64 + (q & 15) + 16 * (k & 3)];
-}
-
 // Linv[r][k], k <= r (or within r's diagonal 16 x 16 tile), of a block's
 // inverse diagonal: lower tiles only, tile (rt, ks) at 64 (2 rt (rt + 1) + ks)
 __device__ __forceinline__ double linv_at(const double* __restrict__ Lv, int r, int k) {

@@ -102,8 +102,11 @@ struct SyrkItem {
 // fewer products on a 2D mesh of 129^2 nodes (m = 512), 1.04 times on a 20^3
 // elasticity box.  Measured, blocks / tiles at products tiles : blocks: FP64
 // 0.39 / 0.89 ms at 2.25, 7.04 / 7.24 at 1.064, 8.19 / 8.22 at 1.054, 14.1 /
-// 13.5 at 1.051, 13.7 / 12.5 at 1.036; mixed 0.134 / 0.258 at 2.25, 1.14 / 1.18
-// at 1.143, 1.46 / 1.44 at 1.112, 2.73 / 2.51 at 1.054.
+// 13.5 at 1.051, 13.7 / 12.5 at 1.036; mixed 0.148 / 0.301 at 2.25, 1.39 / 1.41
+// at 1.143, 2.63 / 2.64 at 1.139, 1.81 / 1.76 at 1.112, 3.00 / 2.75 at 1.064,
+// 3.32 / 3.05 at 1.054.  Batches of one shape each; from one batch to the next
+// the two differ by a few percent at the same ratio, and next to the line the
+// choice is worth no more than that.
 constexpr double kSyrkTileCost = 1.053, kSyrkTileCostMixed = 1.12;
 // The mixed SYRK splits 2^kSplitScale X into bf16 values: the last bit of the
 // smallest FP32 number is then that of the smallest bf16 number, and no value

@@ -1094,7 +1094,6 @@ __global__ __launch_bounds__(256, EDGE == 128 ? 2 : 4) void syrk_split_f32(
 }
 
 // ---------------------------------------------------------------------------
-// ---------------------------------------------------------------------------
 // Inverses of the factor blocks' diagonal triangles (lower triangular, w <=
 // 64), written as the lower MFMA A tiles the TRSM and the implicit apply read.
 // One workgroup per block, four lanes per column: forward substitution on the
@@ -1102,9 +1101,13 @@ __global__ __launch_bounds__(256, EDGE == 128 ? 2 : 4) void syrk_split_f32(
 // double-double (products and their errors by fma, error-free additions, the
 // quotient corrected once), rounded to FP64 at the end: more digits than the
 // 64-bit mantissas of x87, in which the host computed the inverses before (22%
-// of its time on an 11^3 elasticity subdomain, 40% on 12^3 heat).  Bound by
-// FP64 arithmetic and LDS latency, 50 KB of LDS (packed triangles): 0.12
-// ms for the 700 blocks of 8 uneven elasticity boxes.
+// of its time on an 11^3 elasticity subdomain, 40% on 12^3 heat).  Bound by the
+// latency of a row (LDS, two reductions, two divisions), three workgroups a CU
+// (50 KB of LDS each); LDS is busy 27% of the time, a quarter to a third of
+// that with bank conflicts of the packed triangles.  0.12 ms for the 700
+// blocks of 8 uneven elasticity boxes, 0.78 for the 7616 of 16 x 20^3
+// elasticity, 1.5 for the 26112 of 512 x 12^3 heat, 3.4 for the 43008 of 128
+// triangle meshes of 129^2 nodes.
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ int tri(int i, int k) { return i * (i + 1) / 2 + k; }
 
@@ -1209,9 +1212,12 @@ hipError_t launch_trsm(const DevTables& t, const int32_t* order, int64_t count, 
 // CU takes as long as the CU's matrix units need for it, while others idle.
 // Whole blocks / quarters: one 16 x 16 heat square (1 block) 14 / 7 us, one 129^2
 // triangle mesh (36) 58 / 29, 8 (288) 65 / 49, one 12^3 heat cube (105) 30 / 20;
-// triangle meshes of 17^2 nodes, one block each: 256 of them 19.1 / 20.7, 320
-// 27.2 / 24.9, 352 27.3 / 27.8, 512 29 / 42; one uneven elasticity box (861) 92
-// / 157.
+// triangle meshes of 17^2 nodes, one block each: 64 of them 17.0 / 10.8, 128 18.2
+// / 14.0, 192 18.5 / 17.2, 256 19.1 / 20.1, 288 26.9 / 24.2, 320 26.9 / 25.7, 352
+// 27.3 / 27.8, 512 29 / 42; of 9^2 nodes 128 9.7 / 8.6, 256 10.3 / 11.2; one uneven
+// elasticity box (861) 92 / 157.  Around 256 very short blocks, one a CU, lose up
+// to 1 us; long ones gain, which the count does not tell apart.  (Not tried for
+// the mixed kernel.)
 constexpr int64_t kSyrkQuarterItems = 320;
 
 hipError_t launch_syrk(const DevTables& t, const SyrkItem* items, int64_t ntile, int64_t nblock,
